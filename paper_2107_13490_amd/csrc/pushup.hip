@@ -2,10 +2,9 @@
 // "Strategy, Resolution and Lookback") for gfx950.
 //
 // Device part: the gradient-diversity equation over a lookback window of gradient tensors held
-// as fixed-point codes.  One pass over the window: every thread owns 16 consecutive elements,
-// reads them from each tensor in turn (eight tensors' loads in flight), keeps the running
-// element-wise sum of the aligned codes in registers and the per-tensor sums of squares in
-// per-wavefront counters.  All sums are integers (exact, order-independent); a one-block
+// as fixed-point codes.  One pass over the window: every thread owns 8 consecutive elements (16 in windows of
+// int32 codes), reads them from each tensor in turn, keeps the running element-wise sum of the aligned codes in
+// registers and the per-tensor sums of squares in LDS counters.  All sums are integers (exact, order-independent); a one-block
 // follow-up kernel adds the block partials and forms the norms and the ratio in fp64.
 //
 // Host part: the scalar rules that turn the diversity into a new <WL,FL>, lookback,
@@ -33,18 +32,6 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
     return v;
 }
 
-// 16 codes of tensor k starting at element e0.  The buffer descriptor covers the tensor rounded up
-// to whole 16-byte units (the tensor is 16-byte aligned, so the last unit lies in a mapped page):
-// units past it read as 0; the codes past n inside the last unit are cleared by the caller.
-__device__ __forceinline__ void load16(const GradWindow &w, int k, uint32_t n, uint32_t e0, gd_v4u (&raw)[2])
-{
-    const uint32_t es = w.es[k];
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(w.g[k]), 0, (int)((n * es + 15u) & ~15u), 0x00020000);
-    raw[0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * es, 0, 0);
-    raw[1] = es == 2 ? __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * es + 16, 0, 0) : gd_v4u{0, 0, 0, 0};
-}
-
 __device__ __forceinline__ void unpack16(const gd_v4u (&raw)[2], int es, int (&c)[16])
 {
     if (es == 1) {
@@ -56,6 +43,114 @@ __device__ __forceinline__ void unpack16(const gd_v4u (&raw)[2], int es, int (&c
     }
 }
 
+// ---- windows of int8 / int16 codes ---------------------------------------------------------------------------
+// What bounds it: HBM for large layers, the latency of a window's loads for small ones.  A thread owns eight consecutive
+// elements of a chunk and has the loads of 16 tensors in flight (one 8- or 16-byte load each), so a window of 25 costs two
+// memory latencies; the squares of a tensor go to a lane's own LDS counter (one conflict-free addition per tensor and
+// wavefront), so that the reduction over lanes happens once per block and not once per tensor.  Measured on ResNet-18's
+// layers, windows of 25: 36,864 elements 20 -> 9 us, 0.6 M int16 elements 22.8 -> 12.2, 2.4 M int16 elements (118 MB)
+// 31.6 -> 30.4 us (was: 16 elements per thread, eight tensors in flight, a 64-bit wavefront reduction per tensor).
+constexpr int kGdChunk = kGdThreads * 8;      // elements of a block's chunk
+constexpr uint32_t kGdMaxBlocks = 1024;       // four blocks per CU; more elements than that: several chunks per block
+
+// blocks of a tensor: the same number of chunks for every block where it can be had
+static uint32_t gd_blocks(uint64_t n)
+{
+    const uint64_t chunks = std::max<uint64_t>(1, (n + kGdChunk - 1) / kGdChunk);
+    const uint64_t each = (chunks + kGdMaxBlocks - 1) / kGdMaxBlocks;
+    return (uint32_t)((chunks + each - 1) / each);
+}
+
+// The window's table as every wavefront holds it: lane k has tensor k's entry (one load for the whole table), and
+// readlane hands it out as a scalar.
+struct GdTable { uint32_t ptr_lo, ptr_hi, es, shift; };
+
+// ES: element bytes of every tensor of the window, or 0 when they differ (16 bytes are loaded for eight codes of either size)
+template <int ES>
+__device__ __forceinline__ void gd_chunks(const GdTable &tab, const int count, const uint32_t n, unsigned long long *slots,
+                                          const uint32_t blk, const uint32_t nblk)
+{
+    constexpr int U = 16;                     // tensors whose loads are in flight together
+    constexpr int NW = ES == 1 ? 2 : 4;       // 32-bit words per tensor and thread
+    typedef unsigned gd_v2u __attribute__((ext_vector_type(2)));
+    typedef short gd_v2s __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t nchunks = (n + kGdChunk - 1) / kGdChunk;
+    for (uint32_t ch = blk; ch < nchunks; ch += nblk) {
+        const uint32_t e0 = ch * kGdChunk + threadIdx.x * 8;
+        const bool tail = n - ch * kGdChunk < (uint32_t)kGdChunk;
+        int S[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) S[j] = 0;
+        for (int k0 = 0; k0 < count; k0 += U) {
+            uint32_t raw[U][NW];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                // The descriptor covers the tensor rounded up to whole 32-bit words (16-byte aligned, so mapped); words past
+                // it, and whole tensors past the window, read as 0 without memory traffic.
+                const uint32_t es = ES ? (uint32_t)ES : (uint32_t)__builtin_amdgcn_readlane((int)tab.es, k0 + u);
+                const uint64_t ptr = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)tab.ptr_hi, k0 + u) << 32 |
+                                     (uint32_t)__builtin_amdgcn_readlane((int)tab.ptr_lo, k0 + u);
+                const uint32_t bytes = k0 + u < count ? (n * es + 3u) & ~3u : 0u;
+                const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(ptr), 0, (int)bytes, 0x00020000);
+                if constexpr (NW == 2) {
+                    const gd_v2u v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, e0 * es, 0, 0);
+                    raw[u][0] = v[0]; raw[u][1] = v[1];
+                } else {
+                    const gd_v4u v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * es, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < NW; ++i) raw[u][i] = v[i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (k0 + u < count) {
+                    const int es = ES ? ES : __builtin_amdgcn_readlane((int)tab.es, k0 + u);
+                    const int sh = __builtin_amdgcn_readlane((int)tab.shift, k0 + u);
+                    if (tail) {                   // clear the codes past n
+                        const int epd = es == 1 ? 4 : 2;      // codes per word
+#pragma unroll
+                        for (int i = 0; i < NW; ++i) {
+                            const int left = (int)n - (int)(e0 + i * epd);
+                            raw[u][i] = left >= epd ? raw[u][i] : left <= 0 ? 0u : raw[u][i] & ((1u << (8 * es * left)) - 1u);
+                        }
+                    }
+                    unsigned long long *slot = slots + (k0 + u) * kWave + lane;
+                    if (es == 1) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) S[j] += (int)((unsigned)(int)(int8_t)(raw[u][j >> 2] >> (8 * (j & 3))) << sh);
+                        // at most 8 * 2^14 per chunk, a counter at most 2^28 (512 chunks per block)
+                        const int d = __builtin_amdgcn_sdot4((int)raw[u][1], (int)raw[u][1],
+                                                             __builtin_amdgcn_sdot4((int)raw[u][0], (int)raw[u][0], 0, false), false);
+                        atomicAdd(reinterpret_cast<uint32_t *>(slot), (uint32_t)d);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) S[j] += (int)((unsigned)(int)(int16_t)(raw[u][(j >> 1) % NW] >> (16 * (j & 1))) << sh);
+                        unsigned long long t = 0;
+#pragma unroll
+                        for (int i = 0; i < NW; ++i) {
+                            const gd_v2s v = __builtin_bit_cast(gd_v2s, raw[u][i]);
+                            t += (uint32_t)__builtin_amdgcn_sdot2(v, v, 0, false);      // <= 2^31
+                        }
+                        atomicAdd(slot, t);
+                    }
+                }
+            }
+        }
+        unsigned long long lo = 0, hi = 0;    // halves of the squared sums: neither can overflow
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint64_t q = (uint64_t)((long long)S[j] * (long long)S[j]);
+            lo += q & 0xffffffffull;
+            hi += q >> 32;
+        }
+        atomicAdd(slots + count * kWave + lane, lo);
+        atomicAdd(slots + (count + 1) * kWave + lane, hi);
+    }
+}
+
+__host__ __device__ inline size_t gd_lds_bytes(int count) { return (size_t)(count + 2) * kWave * sizeof(unsigned long long); }
+
 // partial[col][block]: col k < count: sum of squares of tensor k; col count / count+1: sums of the
 // low / high 32-bit halves of (aligned element sum)^2
 // BYPTR: the window description lies in device memory (written by chain_prep_kernel) instead of the
@@ -63,71 +158,23 @@ __device__ __forceinline__ void unpack16(const gd_v4u (&raw)[2], int es, int (&c
 // blk of nblk: this block's place among the blocks of the tensor (a chained step runs all layers in one launch)
 __device__ __forceinline__ void gd_partial_body(const GradWindow &w, uint32_t n, uint64_t *partial, const uint32_t blk, const uint32_t nblk)
 {
-    __shared__ uint64_t wave_part[kGdThreads / kWave][kGdMaxTensors + 2];
+    extern __shared__ unsigned long long gd_slots[];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const uint32_t e0 = (blk * kGdThreads + threadIdx.x) * kGdPerThread;
-    int S[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) S[j] = 0;
-    constexpr int U = 8;                  // tensors whose loads are in flight together
-    for (int k0 = 0; k0 < w.count; k0 += U) {
-        gd_v4u raw[U][2];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (k0 + u < w.count) load16(w, k0 + u, n, e0, raw[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (k0 + u >= w.count) break;
-            const int es = w.es[k0 + u], sh = w.shift[k0 + u];
-            if (e0 + 16 > n) {                 // last unit of the tensor: clear the codes past n
-#pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if (e0 + j >= n) {
-                        if (es == 1) raw[u][0][j >> 2] &= ~(0xffu << (8 * (j & 3)));
-                        else raw[u][j >> 3][(j >> 1) & 3] &= ~(0xffffu << (16 * (j & 1)));
-                    }
-            }
-            int c[16];
-            unpack16(raw[u], es, c);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) S[j] += (int)((unsigned)c[j] << sh);
-            // sums of squares with the packed dot-product instructions: 4 (int8) or 2 (int16) codes each
-            uint64_t sq;
-            if (es == 1) {
-                int d = 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) d = __builtin_amdgcn_sdot4((int)raw[u][0][i], (int)raw[u][0][i], d, false);
-                sq = wave_sum_u32((uint32_t)d);                    // <= 64 * 16 * 2^14
-            } else {
-                uint64_t t = 0;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    typedef short gd_v2s __attribute__((ext_vector_type(2)));
-                    const uint32_t x = raw[u][i >> 2][i & 3];
-                    const gd_v2s v = {(short)(x & 0xffff), (short)(x >> 16)};
-                    t += (uint32_t)__builtin_amdgcn_sdot2(v, v, 0, false);      // <= 2^31
-                }
-                sq = wave_sum_u64(t);
-            }
-            if (lane == 0) wave_part[wave][k0 + u] = sq;
-        }
-    }
-    uint64_t lo = 0, hi = 0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const uint64_t q = (uint64_t)((long long)S[j] * (long long)S[j]);
-        lo += q & 0xffffffffull;
-        hi += q >> 32;
-    }
-    lo = wave_sum_u64(lo);
-    hi = wave_sum_u64(hi);
-    if (lane == 0) { wave_part[wave][w.count] = lo; wave_part[wave][w.count + 1] = hi; }
+    const int count = __builtin_amdgcn_readfirstlane(w.count);
+    const uint64_t ptr = (uint64_t)w.g[lane];           // entries past the window hold nothing that is used
+    const GdTable tab = {(uint32_t)ptr, (uint32_t)(ptr >> 32), w.es[lane], w.shift[lane]};
+    for (int i = threadIdx.x; i < (count + 2) * kWave; i += kGdThreads) gd_slots[i] = 0;
+    // one element size for the whole window (a window is emptied when its layer changes format)?
+    const int es0 = __builtin_amdgcn_readfirstlane((int)tab.es);
+    const bool mixed = __ballot(lane < count && (int)tab.es != es0) != 0;
     __syncthreads();
-    for (int col = threadIdx.x; col < w.count + 2; col += kGdThreads) {
-        uint64_t v = 0;
-#pragma unroll
-        for (int i = 0; i < kGdThreads / kWave; ++i) v += wave_part[i][col];
-        partial[(size_t)col * nblk + blk] = v;
+    if (mixed) gd_chunks<0>(tab, count, n, gd_slots, blk, nblk);
+    else if (es0 == 1) gd_chunks<1>(tab, count, n, gd_slots, blk, nblk);
+    else gd_chunks<2>(tab, count, n, gd_slots, blk, nblk);
+    __syncthreads();
+    for (int col = wave; col < count + 2; col += kGdThreads / kWave) {
+        const uint64_t v = wave_sum_u64(gd_slots[col * kWave + lane]);
+        if (lane == 0) partial[(size_t)col * nblk + blk] = v;
     }
 }
 
@@ -163,9 +210,13 @@ __device__ __forceinline__ void gd_final_body(const GradWindow &w, const uint64_
         }
     }
     __syncthreads();
+    // the norms side by side (a square root and a scaling in fp64 take longer than the sums), added in window order
+    __shared__ double norm[kGdMaxTensors];
+    if ((int)threadIdx.x < w.count) norm[threadIdx.x] = ldexp(sqrt((double)col_sum[threadIdx.x]), -(int)w.fl[threadIdx.x]);
+    __syncthreads();
     if (threadIdx.x != 0) return;
     double num = 0.0;
-    for (int k = 0; k < w.count; ++k) num += ldexp(sqrt((double)col_sum[k]), -(int)w.fl[k]);
+    for (int k = 0; k < w.count; ++k) num += norm[k];
     const double sq = (double)col_sum[w.count + 1] * 4294967296.0 + (double)col_sum[w.count];
     const double den = ldexp(sqrt(sq), -w.fl_max);
     const double ds = den > 0.0 ? num / den : (num > 0.0 ? (double)INFINITY : (double)NAN);
@@ -312,13 +363,17 @@ struct ChainGeo {
 __global__ void __launch_bounds__(kGdThreads)
 gd_partial_chain_kernel(const ChainGeo geo, const GradWindow *__restrict__ win, uint64_t *partial)
 {
-    // the layer this block belongs to: every lane compares one table entry, the wavefront votes
-    const int lane = threadIdx.x & (kWave - 1);
+    // The layer this block belongs to: every lane holds one entry of the tables and compares, the wavefront votes, and
+    // readlane hands out the layer's entries.  (Indexed scalar loads of tables with different element sizes made the
+    // compiler split the addresses into parts that are not multiples of four, which scalar loads round down.)
+    const int lane = threadIdx.x & (kWave - 1), e = min(lane, geo.nlayers - 1);
     const uint32_t first = lane < geo.nlayers ? geo.first[lane] : 0xffffffffu;
     const int l = __popcll(__ballot(blockIdx.x >= first)) - 1;
-    const uint32_t blk = blockIdx.x - geo.first[l], nblk = geo.first[l + 1] - geo.first[l];
-    if (geo.wide[l]) gd_partial_wide_body(win[l], geo.n[l], partial + geo.part_off[l], blk, nblk);
-    else gd_partial_body(win[l], geo.n[l], partial + geo.part_off[l], blk, nblk);
+    auto entry = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    const uint32_t first_l = entry(geo.first[e]), nblk = entry(geo.first[e + 1]) - first_l, n = entry(geo.n[e]);
+    uint64_t *part = partial + ((uint64_t)entry((uint32_t)(geo.part_off[e] >> 32)) << 32 | entry((uint32_t)geo.part_off[e]));
+    if (entry(geo.wide[e])) gd_partial_wide_body(win[l], n, part, blockIdx.x - first_l, nblk);
+    else gd_partial_body(win[l], n, part, blockIdx.x - first_l, nblk);
 }
 
 __global__ void __launch_bounds__(kGdFinalThreads)
@@ -387,12 +442,14 @@ int gradient_diversity_chain(adapt_ctx *ctx, const ChainLayerIn *in, int nlayers
     ChainGeo geo = {};
     geo.nlayers = nlayers;
     size_t words = 0;
+    int most = 1;
     uint64_t blocks = 0;
     for (int l = 0; l < nlayers; ++l) {
         if (in[l].count < 1 || in[l].count > kGdMaxTensors || n[l] > ((size_t)1 << 30)) return ADAPT_EUNSUPPORTED;
         bool wide = false;
         for (int k = 0; k < in[l].count; ++k) wide = wide || in[l].wl[k] > 16;
-        const uint64_t grid = std::max<size_t>(1, (n[l] + per_block - 1) / per_block);
+        const uint64_t grid = wide ? std::max<size_t>(1, (n[l] + per_block - 1) / per_block) : gd_blocks(n[l]);
+        most = std::max(most, in[l].count);
         geo.first[l] = (uint32_t)blocks;
         geo.n[l] = (uint32_t)n[l];
         geo.part_off[l] = words;
@@ -405,7 +462,7 @@ int gradient_diversity_chain(adapt_ctx *ctx, const ChainLayerIn *in, int nlayers
     if (words * sizeof(uint64_t) > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
     uint64_t *partial = reinterpret_cast<uint64_t *>(scratch(ctx));
     hipLaunchKernelGGL(chain_prep_kernel, dim3(1), dim3(64), 0, ctx->stream, in, nlayers, e_g, e_stride, win, out);
-    hipLaunchKernelGGL(gd_partial_chain_kernel, dim3((unsigned)blocks), dim3(kGdThreads), 0, ctx->stream, geo, win, partial);
+    hipLaunchKernelGGL(gd_partial_chain_kernel, dim3((unsigned)blocks), dim3(kGdThreads), gd_lds_bytes(most), ctx->stream, geo, win, partial);
     hipLaunchKernelGGL(gd_final_chain_kernel, dim3(nlayers), dim3(kGdFinalThreads), 0, ctx->stream, geo, win, partial, out);
     return hip_status(ctx, hipGetLastError());
 }
@@ -414,7 +471,8 @@ size_t ws_need_gradient_diversity(uint64_t n, int count)
 {
     const size_t per_block = (size_t)kGdThreads * kGdPerThread;
     // (count + 2) words per block, or (count + 1) pairs of words for windows with int32 codes
-    return std::max<size_t>(1, (n + per_block - 1) / per_block) * (size_t)(count + 1) * 2 * sizeof(uint64_t);
+    return std::max(std::max<size_t>(1, (n + per_block - 1) / per_block) * (size_t)(count + 1) * 2,
+                    (size_t)gd_blocks(n) * (size_t)(count + 2)) * sizeof(uint64_t);
 }
 
 }  // namespace adapt
@@ -459,10 +517,11 @@ extern "C" int adapt_gradient_diversity(adapt_ctx *ctx, const adapt_grad_item *i
         return hip_status(ctx, hipGetLastError());
     }
     if (bound >= 2147483648.0) return ADAPT_EUNSUPPORTED;
-    if ((size_t)grid * (count + 2) * sizeof(uint64_t) > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
+    const int blocks = (int)gd_blocks(n);
+    if ((size_t)blocks * (count + 2) * sizeof(uint64_t) > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
     uint64_t *partial = reinterpret_cast<uint64_t *>(scratch(ctx));
-    hipLaunchKernelGGL(gd_partial_kernel<false>, dim3(grid), dim3(kGdThreads), 0, ctx->stream, w, nullptr, (uint32_t)n, partial);
-    hipLaunchKernelGGL(gd_final_kernel<false>, dim3(1), dim3(kGdFinalThreads), 0, ctx->stream, w, nullptr, partial, grid, sums, out);
+    hipLaunchKernelGGL(gd_partial_kernel<false>, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream, w, nullptr, (uint32_t)n, partial);
+    hipLaunchKernelGGL(gd_final_kernel<false>, dim3(1), dim3(kGdFinalThreads), 0, ctx->stream, w, nullptr, partial, blocks, sums, out);
     return hip_status(ctx, hipGetLastError());
 }
 
