@@ -11,6 +11,8 @@ extern "C" int adapt_conv_fwd(adapt_ctx *ctx, adapt_conv_desc d, const void *x, 
         if (!conv_ok(d)) return ADAPT_EINVAL;
         if (d.n == 0) return ADAPT_OK;
         if (!check_ptrs(x, w, y)) return ADAPT_EINVAL;
+        const int planes = wide_fwd_planes(ctx, d, x, fx, w, fw, y, ep);      // one kernel on byte planes where it applies
+        if (planes != ADAPT_EWORKSPACE && planes != ADAPT_EUNSUPPORTED) return planes;
         const int p = (d.h + 2 * d.pad - d.r) / d.stride + 1, q = (d.w + 2 * d.pad - d.s) / d.stride + 1;
         const SubContraction sub = [&](const void *pa, adapt_fmt fpa, const void *pb, adapt_fmt fpb, void *c, adapt_epilogue ex) {
             return adapt_conv_fwd(ctx, d, pa, fpa, pb, fpb, c, ex);

@@ -272,6 +272,86 @@ __device__ __forceinline__ void split_unit(const uint32_t (&r0)[4], const uint32
     }
 }
 
+// ---- addresses of the vector paths, split into what depends on the row, on the filter tap and on the reduction index ----
+
+// Row part of a K-major operand's element offset.  Returns the row's tap mask: bit t says that filter tap t reads inside
+// the tensor (convolution activations: forward x, data-gradient dy; at most 32 taps on these paths); other operands: all
+// ones, and 0 for rows beyond the operand.
+template <int OP, bool ACT>
+__device__ __forceinline__ uint32_t k_major_row(const ContractArgs &a, const int row, uint32_t &base)
+{
+    const bool valid = row < (ACT ? a.M : a.N);
+    if (OP == OP_GEMM) {
+        base = (uint32_t)row * (uint32_t)(ACT ? a.act_rs : a.wgt_rs);
+    } else if (ACT && OP == OP_FWD) {
+        const uint32_t pq = fdiv(row, a.div_q), q = row - pq * a.q;
+        const uint32_t n = fdiv(pq, a.div_p), p = pq - n * a.p;
+        const int ra = (int)p * a.stride - a.pad, rb = (int)q * a.stride - a.pad;
+        base = ((n * (uint32_t)a.h + (uint32_t)ra) * (uint32_t)a.w + (uint32_t)rb) * (uint32_t)a.c;
+        // tap (r, s) reads x[ra + r][rb + s]
+        uint32_t vs = 0, m = 0;
+        for (int ss = 0; ss < a.s; ++ss) vs |= (uint32_t)((unsigned)(rb + ss) < (unsigned)a.w) << ss;
+        for (int rr = 0; rr < a.r; ++rr)
+            if ((unsigned)(ra + rr) < (unsigned)a.h) m |= vs << (rr * a.s);
+        return valid ? m : 0u;
+    } else if (ACT && is_dgrad(OP)) {
+        const uint32_t rr = (OP == OP_DGRAD_S2 && valid) ? dgrad_real_row(a, row) : (uint32_t)row;
+        const uint32_t nh = fdiv(rr, a.div_w), w = rr - nh * a.w;
+        const uint32_t n = fdiv(nh, a.div_h), h = nh - n * a.h;
+        const int ra = (int)h + a.pad, rb = (int)w + a.pad;
+        // tap (r, s) reads dy[(ra - r) / stride][(rb - s) / stride] when both divide and lie inside; then
+        // (ra - r) / stride = floor(ra / stride) - floor(r / stride) (equal remainders cancel), so the offset
+        // splits into a row part (here) and a tap part (k_major_tap)
+        const uint32_t pa = fdiv((uint32_t)ra, a.div_stride), qa = fdiv((uint32_t)rb, a.div_stride);
+        base = (n * (uint32_t)(a.p * a.q) + pa * (uint32_t)a.q + qa) * (uint32_t)a.k;
+        uint32_t vs = 0, m = 0;
+        for (int ss = 0; ss < a.s; ++ss) {
+            const int wp = rb - ss;
+            const uint32_t qq = fdiv((uint32_t)max(wp, 0), a.div_stride);
+            vs |= (uint32_t)(wp >= 0 && (int)(qq * a.stride) == wp && (int)qq < a.q) << ss;
+        }
+        for (int r2 = 0; r2 < a.r; ++r2) {
+            const int hp = ra - r2;
+            const uint32_t pp = fdiv((uint32_t)max(hp, 0), a.div_stride);
+            if (hp >= 0 && (int)(pp * a.stride) == hp && (int)pp < a.p) m |= vs << (r2 * a.s);
+        }
+        return valid ? m : 0u;
+    } else {
+        base = (uint32_t)row * (uint32_t)a.K;      // filters: [row][k]
+    }
+    return valid ? 0xffffffffu : 0u;
+}
+
+// Tap and tap part of the element offset of a convolution's activations at reduction index k0 plus a column that is part
+// of the row's base; kq: an index that lies in the wanted tap (uniform when whole stages share a tap: scalar arithmetic).
+template <int OP, typename KQ>
+__device__ __forceinline__ void k_major_tap(const ContractArgs &a, KQ kq, int k0, uint32_t &tap, uint32_t &koff)
+{
+    tap = fdiv(kq, OP == OP_FWD ? a.div_c : a.div_k);
+    const uint32_t r = fdiv(tap, a.div_s), s = tap - r * a.s;
+    if (OP == OP_FWD) koff = (r * a.w + s) * a.c + ((uint32_t)k0 - tap * a.c);
+    else koff = (uint32_t)k0 - tap * a.k - (fdiv(r, a.div_stride) * (uint32_t)a.q + fdiv(s, a.div_stride)) * (uint32_t)a.k;
+}
+
+// Element offset of reduction index kk of an R-major operand (coff, ra, rb: row parts, see the loaders); clears ok where
+// a convolution's x has no such element
+template <int OP, bool ACT>
+__device__ __forceinline__ uint32_t r_major_offset(const ContractArgs &a, int kk, uint32_t coff, int ra, int rb, bool &ok)
+{
+    if (OP == OP_GEMM) return coff + (uint32_t)kk * (uint32_t)(ACT ? a.act_ks : a.wgt_ks);
+    if (ACT) return coff + (uint32_t)kk * (uint32_t)a.k;      // wgrad: dy[(n,p,q)][kout]
+    if (is_dgrad(OP)) {                                       // filters w[kout][r][s][c], k line = (r,s,kout)
+        const uint32_t tap = fdiv(ok ? kk : 0, a.div_k), ko = kk - tap * a.k;
+        return (ko * (uint32_t)(a.r * a.s) + tap) * (uint32_t)a.c + coff;
+    }
+    // wgrad: x[n, p*st+r-pad, q*st+s-pad, c]
+    const uint32_t np = fdiv(ok ? kk : 0, a.div_q), q = kk - np * a.q;
+    const uint32_t n = fdiv(np, a.div_p), p = np - n * a.p;
+    const int hh = (int)p * a.stride + ra, ww = (int)q * a.stride + rb;
+    ok = ok && (unsigned)hh < (unsigned)a.h && (unsigned)ww < (unsigned)a.w;
+    return ((n * (uint32_t)a.h + (uint32_t)hh) * (uint32_t)a.w + (uint32_t)ww) * (uint32_t)a.c + coff;
+}
+
 // ---- K-major operand: thread t owns rows (t/4) + 64*i and the 16-byte column (t%4) of every
 //      64-k sub-chunk of the stage.  Element offsets are 32-bit (operands below 2^32 elements,
 //      checked by the host); intermediate values may wrap, valid results do not.
@@ -300,44 +380,7 @@ struct LoaderK {
             base[i] = 0;
             tapmask[i] = valid[i] ? 0xffffffffu : 0u;
             if (MODE == LOAD_SCALAR) continue;
-            if (OP == OP_GEMM) {
-                base[i] = (uint32_t)row * (uint32_t)(ACT ? a.act_rs : a.wgt_rs);
-            } else if (ACT && OP == OP_FWD) {
-                const uint32_t pq = fdiv(row, a.div_q), q = row - pq * a.q;
-                const uint32_t n = fdiv(pq, a.div_p), p = pq - n * a.p;
-                const int ra = (int)p * a.stride - a.pad, rb = (int)q * a.stride - a.pad;
-                base[i] = ((n * (uint32_t)a.h + (uint32_t)ra) * (uint32_t)a.w + (uint32_t)rb) * (uint32_t)a.c;
-                // tap (r, s) reads x[ra + r][rb + s]
-                uint32_t vs = 0, m = 0;
-                for (int ss = 0; ss < a.s; ++ss) vs |= (uint32_t)((unsigned)(rb + ss) < (unsigned)a.w) << ss;
-                for (int rr = 0; rr < a.r; ++rr)
-                    if ((unsigned)(ra + rr) < (unsigned)a.h) m |= vs << (rr * a.s);
-                tapmask[i] = valid[i] ? m : 0u;
-            } else if (ACT && is_dgrad(OP)) {
-                const uint32_t rr = (OP == OP_DGRAD_S2 && valid[i]) ? dgrad_real_row(a, row) : (uint32_t)row;
-                const uint32_t nh = fdiv(rr, a.div_w), w = rr - nh * a.w;
-                const uint32_t n = fdiv(nh, a.div_h), h = nh - n * a.h;
-                const int ra = (int)h + a.pad, rb = (int)w + a.pad;
-                // tap (r, s) reads dy[(ra - r) / stride][(rb - s) / stride] when both divide and lie inside; then
-                // (ra - r) / stride = floor(ra / stride) - floor(r / stride) (equal remainders cancel), so the offset
-                // splits into a row part (here) and a tap part (uniform, see load_sub)
-                const uint32_t pa = fdiv((uint32_t)ra, a.div_stride), qa = fdiv((uint32_t)rb, a.div_stride);
-                base[i] = (n * (uint32_t)(a.p * a.q) + pa * (uint32_t)a.q + qa) * (uint32_t)a.k;
-                uint32_t vs = 0, m = 0;
-                for (int ss = 0; ss < a.s; ++ss) {
-                    const int wp = rb - ss;
-                    const uint32_t qq = fdiv((uint32_t)max(wp, 0), a.div_stride);
-                    vs |= (uint32_t)(wp >= 0 && (int)(qq * a.stride) == wp && (int)qq < a.q) << ss;
-                }
-                for (int r2 = 0; r2 < a.r; ++r2) {
-                    const int hp = ra - r2;
-                    const uint32_t pp = fdiv((uint32_t)max(hp, 0), a.div_stride);
-                    if (hp >= 0 && (int)(pp * a.stride) == hp && (int)pp < a.p) m |= vs << (r2 * a.s);
-                }
-                tapmask[i] = valid[i] ? m : 0u;
-            } else {
-                base[i] = (uint32_t)row * (uint32_t)a.K;      // filters: [row][k]
-            }
+            tapmask[i] = k_major_row<OP, ACT>(a, row, base[i]);
             base[i] += (threadIdx.x & 3) * 16;
         }
     }
@@ -351,20 +394,9 @@ struct LoaderK {
     {
         const __amdgpu_buffer_rsrc_t ptr = rsrc;
         const bool kin = k < a.K;
-        if (ACT && OP == OP_FWD) {
-            const uint32_t tap = fdiv(kq, a.div_c);
-            const uint32_t r = fdiv(tap, a.div_s), s = tap - r * a.s;
-            const uint32_t koff = (r * a.w + s) * a.c + ((uint32_t)k64 - tap * a.c);
-#pragma unroll
-            for (int i = 0; i < RPT; ++i) {
-                if (i < i0 || i >= i1) continue;
-                const bool ok = kin && ((tapmask[i] >> (tap & 31u)) & 1u);
-                load_unit<ES>(ptr, base[i] + koff, ok, rg.hi[sc * RPT + i], rg.lo[sc * RPT + i]);
-            }
-        } else if (ACT && is_dgrad(OP)) {
-            const uint32_t tap = fdiv(kq, a.div_k), ko = (uint32_t)k64 - tap * a.k;
-            const uint32_t r = fdiv(tap, a.div_s), s = tap - r * a.s;
-            const uint32_t koff = ko - (fdiv(r, a.div_stride) * (uint32_t)a.q + fdiv(s, a.div_stride)) * (uint32_t)a.k;
+        if (ACT && (OP == OP_FWD || is_dgrad(OP))) {
+            uint32_t tap, koff;
+            k_major_tap<OP>(a, kq, k64, tap, koff);
 #pragma unroll
             for (int i = 0; i < RPT; ++i) {
                 if (i < i0 || i >= i1) continue;
@@ -505,21 +537,7 @@ struct LoaderR {
             const int id = threadIdx.x + u * kThreads;
             const int kk = k0 + id / CPL;
             bool ok = valid[u] && kk < a.K;
-            uint32_t off;
-            if (OP == OP_GEMM) {
-                off = coff[u] + (uint32_t)kk * (uint32_t)(ACT ? a.act_ks : a.wgt_ks);
-            } else if (ACT) {                      // wgrad: dy[(n,p,q)][kout]
-                off = coff[u] + (uint32_t)kk * (uint32_t)a.k;
-            } else if (is_dgrad(OP)) {             // filters w[kout][r][s][c], k line = (r,s,kout)
-                const uint32_t tap = fdiv(ok ? kk : 0, a.div_k), ko = kk - tap * a.k;
-                off = (ko * (uint32_t)(a.r * a.s) + tap) * (uint32_t)a.c + coff[u];
-            } else {                               // wgrad: x[n, p*st+r-pad, q*st+s-pad, c]
-                const uint32_t np = fdiv(ok ? kk : 0, a.div_q), q = kk - np * a.q;
-                const uint32_t n = fdiv(np, a.div_p), p = np - n * a.p;
-                const int hh = (int)p * a.stride + ra[u], ww = (int)q * a.stride + rb[u];
-                ok = ok && (unsigned)hh < (unsigned)a.h && (unsigned)ww < (unsigned)a.w;
-                off = ((n * (uint32_t)a.h + (uint32_t)hh) * (uint32_t)a.w + (uint32_t)ww) * (uint32_t)a.c + coff[u];
-            }
+            const uint32_t off = r_major_offset<OP, ACT>(a, kk, coff[u], ra[u], rb[u], ok);
             load_unit<ES>(ptr, off, ok, rg.hi[u], rg.lo[u]);
         }
     }

@@ -173,3 +173,24 @@ def test_wide_calls_report_what_they_cannot_do():
     with pytest.raises(pkg.AdaptError):
         ctx().fxp_gemm(a, (33, 0), a, (32, 0), Epilogue.exact())
     assert pkg.acc_bits(10, pkg.Fmt(17, 0), pkg.Fmt(8, 0)) == 128
+
+
+# the forward convolution on byte planes: three planes up to 24 bits (24: offset digits), four above (32: offset digits), a narrow
+# operand beside a wide one, channels that are padded, tiles with remainders, taps that straddle a stage
+@pytest.mark.parametrize("shp,wx,ww", [((2, 9, 7, 64, 72, 3, 3, 1, 1), 24, 24), ((1, 12, 11, 20, 65, 3, 3, 2, 1), 23, 24),
+                                       ((3, 5, 5, 48, 40, 5, 5, 1, 2), 24, 12), ((2, 16, 16, 16, 129, 1, 1, 1, 0), 32, 32),
+                                       ((1, 17, 9, 80, 33, 3, 3, 1, 1), 25, 31), ((2, 7, 7, 33, 16, 3, 3, 1, 0), 8, 32),
+                                       ((130, 1, 1, 200, 70, 1, 1, 1, 0), 17, 16)])
+def test_wide_forward_on_byte_planes(shp, wx, ww):
+    n, h, w, c, k, r, s, stride, pad = shp
+    d = ConvDesc(*shp)
+    g = np.random.default_rng(sum(shp) + wx + ww)
+    x, wt = _codes(g, (n, h, w, c), wx), _codes(g, (k, r, s, c), ww)
+    fx, fw = (wx, max(wx - 4, 0)), (ww, max(ww - 2, 0))
+    cx = ctx()
+    cx.reserve_workspace(cx.workspace_bytes(pkg.CALL_CONV_FWD, conv=d, fa=fx, fb=fw))
+    y = wo.conv_fwd(x, wt, stride, pad)
+    assert np.array_equal(_i128(cx.conv_fwd(d, dev(x), fx, dev(wt), fw, Epilogue.exact())), y)
+    for wl_o, fl_o, relu, mode in ((wx, 3, True, pkg.SR), (32, 31, False, pkg.SR), (16, 0, False, pkg.RN_HALF_UP), (8, 2, True, pkg.SR)):
+        out = cx.conv_fwd(d, dev(x), fx, dev(wt), fw, Epilogue.requant(wl_o, fl_o, mode, 9, 21, relu=relu))
+        assert np.array_equal(host(out).astype(np.int64), wo.requantize(y, fx[1] + fw[1] - fl_o, wl_o, mode, 9, 21, relu)), (wl_o, fl_o)
