@@ -73,36 +73,60 @@ __host__ __device__ inline BnState bn_state(void *p, int k)
 // ---- per-channel sums -----------------------------------------------------------------------------------
 // MODE 0: (sum y, sum y^2); MODE 1: (sum dz, sum dz*y).  One group = 8 consecutive elements = 8 consecutive
 // channels of one row (channels % 8 == 0).  REG: the thread stride in groups is a multiple of channels/8, so a
-// thread meets the same eight channels every time and sums them in registers.
+// thread meets the same eight channels every time and sums them in registers, four groups' loads in flight.
+// What bounds it: the latency of the loads, then the block's flush.  The LDS sums lie as [copy][2][8][channels / 8], so
+// that the 64 lanes of an addition hit consecutive words, and thin layers keep bn_copies() of them, so that no two lanes
+// of a wavefront meet in one (in the order of the channels and with one copy, 64 channels cost eight additions in a row
+// at one address, sixteen lanes to a bank).  ResNet-18 at batch 256, mean over its layers: int16 7.6 -> 6.2 us, int8
+// 6.1 -> 5.1 us.
+__host__ __device__ inline uint32_t bn_copies(uint32_t cg) { return cg < (uint32_t)kWave && kWave % cg == 0 ? kWave / cg : 1u; }
+
 template <typename TA, typename TB, int MODE, bool REG>
 __global__ void __launch_bounds__(kBnThreads)
 bn_sums_kernel(const TA *__restrict__ a, const TB *__restrict__ b, uint64_t groups, int channels, long long *__restrict__ partial)
 {
-    extern __shared__ long long lsum[];          // [2 * channels]
-    for (int i = threadIdx.x; i < 2 * channels; i += kBnThreads) lsum[i] = 0;
+    extern __shared__ long long lsum[];          // [copies][2 * channels]
+    const uint32_t cg = (uint32_t)channels >> 3, copies = bn_copies(cg);
+    for (uint32_t i = threadIdx.x; i < copies * 2 * channels; i += kBnThreads) lsum[i] = 0;
     __syncthreads();
-    const uint32_t cg = (uint32_t)channels >> 3;
+    unsigned long long *mine = reinterpret_cast<unsigned long long *>(lsum) +
+                               (copies > 1 ? (threadIdx.x & (kWave - 1)) / cg * 2 * channels : 0u);
     const uint64_t first = (uint64_t)blockIdx.x * kBnThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kBnThreads;
     if (REG) {
         long long s1[8], s2[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) s1[e] = s2[e] = 0;
-        for (uint64_t g = first; g < groups; g += stride) {
-            int x[8], y[8];
-            load_codes8<TA>(a, g, x);
-            if (MODE == 1) load_codes8<TB>(b, g, y);
+        auto add = [&](const int (&x)[8], const int (&y)[8]) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 s1[e] += x[e];
                 s2[e] += (long long)(MODE == 1 ? x[e] * y[e] : x[e] * x[e]);
             }
+        };
+        constexpr int U = 4;
+        uint64_t g = first;
+        for (; g + (U - 1) * stride < groups; g += U * stride) {
+            int x[U][8], y[U][8];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                load_codes8<TA>(a, g + u * stride, x[u]);
+                if (MODE == 1) load_codes8<TB>(b, g + u * stride, y[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(x[u], y[u]);
+        }
+        for (; g < groups; g += stride) {
+            int x[8], y[8];
+            load_codes8<TA>(a, g, x);
+            if (MODE == 1) load_codes8<TB>(b, g, y);
+            add(x, y);
         }
         if (first < groups) {
-            const uint32_t c0 = (uint32_t)(first % cg) * 8;
+            const uint32_t c = (uint32_t)first % cg;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                atomicAdd(reinterpret_cast<unsigned long long *>(&lsum[c0 + e]), (unsigned long long)s1[e]);
-                atomicAdd(reinterpret_cast<unsigned long long *>(&lsum[channels + c0 + e]), (unsigned long long)s2[e]);
+                atomicAdd(mine + e * cg + c, (unsigned long long)s1[e]);
+                atomicAdd(mine + channels + e * cg + c, (unsigned long long)s2[e]);
             }
         }
     } else {
@@ -110,17 +134,22 @@ bn_sums_kernel(const TA *__restrict__ a, const TB *__restrict__ b, uint64_t grou
             int x[8], y[8];
             load_codes8<TA>(a, g, x);
             if (MODE == 1) load_codes8<TB>(b, g, y);
-            const uint32_t c0 = (uint32_t)(g % cg) * 8;
+            const uint32_t c = (uint32_t)(g % cg);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                atomicAdd(reinterpret_cast<unsigned long long *>(&lsum[c0 + e]), (unsigned long long)(long long)x[e]);
-                atomicAdd(reinterpret_cast<unsigned long long *>(&lsum[channels + c0 + e]),
-                          (unsigned long long)(long long)(MODE == 1 ? x[e] * y[e] : x[e] * x[e]));
+                atomicAdd(mine + e * cg + c, (unsigned long long)(long long)x[e]);
+                atomicAdd(mine + channels + e * cg + c, (unsigned long long)(long long)(MODE == 1 ? x[e] * y[e] : x[e] * x[e]));
             }
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < 2 * channels; i += kBnThreads) partial[(size_t)blockIdx.x * 2 * channels + i] = lsum[i];
+    for (int i = threadIdx.x; i < 2 * channels; i += kBnThreads) {
+        const int k = i < channels ? i : i - channels;
+        const long long *p = lsum + (i - k) + (k & 7) * cg + (k >> 3);
+        long long t = 0;
+        for (uint32_t r = 0; r < copies; ++r) t += p[(size_t)r * 2 * channels];
+        partial[(size_t)blockIdx.x * 2 * channels + i] = t;
+    }
 }
 
 // clamp(30 - E, 0, 30) for vmax = f 2^E, 1/2 <= f < 1; 30 for vmax = 0 or infinite
@@ -243,9 +272,10 @@ bn_coef_bwd_kernel(const long long *tot, int channels, void *state, double *__re
 }
 
 // Totals and coefficients in one launch.  Totals of the block partials partial[nparts][2 * channels] of a statistics
-// launch: a block takes 8 columns, 32 threads per column each add every 32nd partial (independent loads), LDS
-// combines them.  The block that finishes last (a ticket, zero before the launch and zero again after it) goes on
-// with the coefficients.
+// launch: a block takes 8 columns, 32 threads per column each add every 32nd partial, 16 loads in flight (a
+// statistics launch of two blocks per CU is one round; with the loads one behind the other the launch took 9.8 us
+// instead of 6.4), LDS combines them.  The block that finishes last (a ticket, zero before the launch and zero again
+// after it) goes on with the coefficients.
 struct BnCoefArgs {
     int channels, fl_y, fl_o;
     unsigned long long rows;
@@ -266,7 +296,13 @@ bn_total_coef_kernel(const long long *__restrict__ partial, int nparts, long lon
     const int col = blockIdx.x * 8 + col8;
     long long acc = 0;
     if (col < width)
-        for (int r = rl; r < nparts; r += 32) acc += partial[(size_t)r * width + col];
+        for (int r0 = rl; r0 < nparts; r0 += 16 * 32) {
+            long long t[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) t[u] = partial[(size_t)min(r0 + 32 * u, nparts - 1) * width + col];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) acc += r0 + 32 * u < nparts ? t[u] : 0ll;
+        }
     sm[rl][col8] = acc;
     __syncthreads();
     if (threadIdx.x < 8 && col < width) {
@@ -297,22 +333,36 @@ struct BnApplyArgs {
     uint64_t seed, stream;
 };
 
-template <typename TY, typename TR, typename TO>
+// REG here and in bn_bwd_kernel: the thread stride is a multiple of channels/8 (every layer whose channels/8 is a power of
+// two up to 256), so a thread's eight channels, and their coefficients, stay in its registers; otherwise the coefficients
+// lie in LDS and the channel index moves on by a constant (a 64-bit modulo per group and 128 bytes of LDS reads per thread
+// before).  What bounds them is the VALU (Philox and 64-bit requantization).  ResNet-18 at batch 256, mean over its layers:
+// int16 apply 14.0 -> 13.1 us, maximum pass 13.3 -> 11.8, fitting pass 16.0 -> 15.0; int8 maximum pass 9.8 -> 7.6,
+// fitting pass 11.9 -> 9.5.
+template <typename TY, typename TR, typename TO, bool REG>
 __global__ void __launch_bounds__(kBnThreads) bn_apply_kernel(const BnApplyArgs a)
 {
-    extern __shared__ long long coef[];          // B[channels] then A[channels] (int32)
+    extern __shared__ long long coef[];          // B[channels] then A[channels] (int32); not used with REG
     const BnState st = bn_state(const_cast<void *>(a.state), a.channels);
     int32_t *la = reinterpret_cast<int32_t *>(coef + a.channels);
-    for (int i = threadIdx.x; i < a.channels; i += kBnThreads) { coef[i] = st.B[i]; la[i] = st.A[i]; }
-    __syncthreads();
+    const uint32_t cg = (uint32_t)a.channels >> 3, t0 = blockIdx.x * kBnThreads + threadIdx.x, nt = gridDim.x * kBnThreads;
+    uint32_t c0 = t0 % cg * 8;
+    const uint32_t step = nt % cg * 8;
+    int32_t A[8];
+    long long B[8];
+    if (REG) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { A[e] = st.A[c0 + e]; B[e] = st.B[c0 + e]; }
+    } else {
+        for (int i = threadIdx.x; i < a.channels; i += kBnThreads) { coef[i] = st.B[i]; la[i] = st.A[i]; }
+        __syncthreads();
+    }
     const int fa = st.h->fa;
     const int rsh = st.h->fl_o + fa - a.fl_res;                  // alignment of the shortcut: left shift, or floor
-    const uint32_t cg = (uint32_t)a.channels >> 3;
     const TY *y = static_cast<const TY *>(a.y);
     const TR *res = static_cast<const TR *>(a.res);
     TO *out = static_cast<TO *>(a.out);
-    const uint64_t first = (uint64_t)blockIdx.x * kBnThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kBnThreads;
-    for (uint64_t g = first; g < a.groups; g += stride) {
+    for (uint64_t g = t0; g < a.groups; g += nt) {
         int x[8], s[8], code[8];
         load_codes8<TY>(y, g, x);
         if (a.has_res) load_codes8<TR>(res, g, s);
@@ -325,10 +375,15 @@ __global__ void __launch_bounds__(kBnThreads) bn_apply_kernel(const BnApplyArgs 
 #pragma unroll
             for (int e = 0; e < 8; ++e) r[e] = 0x8000u;
         }
-        const uint32_t c0 = (uint32_t)(g % cg) * 8;
+        if (!REG) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { A[e] = la[c0 + e]; B[e] = coef[c0 + e]; }
+            c0 += step;
+            if (c0 >= (uint32_t)a.channels) c0 -= (uint32_t)a.channels;
+        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            long long acc = (long long)la[c0 + e] * x[e] + coef[c0 + e];
+            long long acc = (long long)A[e] * x[e] + B[e];
             if (a.has_res) acc += rsh >= 0 ? (long long)((unsigned long long)(long long)s[e] << rsh) : ((long long)s[e] >> -rsh);
             code[e] = requantize_one(acc, fa, a.wl, a.relu, r[e]);
         }
@@ -351,14 +406,24 @@ struct BnBwdArgs {
     long long *e_out;
 };
 
-template <typename TD, typename TY, typename TO, bool FIT>
+template <typename TD, typename TY, typename TO, bool FIT, bool REG>
 __global__ void __launch_bounds__(kBnThreads) bn_bwd_kernel(const BnBwdArgs a)
 {
-    extern __shared__ long long coef[];          // R[channels], then P[channels], Q[channels] (int32)
+    extern __shared__ long long coef[];          // R[channels], then P[channels], Q[channels] (int32); not used with REG
     __shared__ uint64_t sm[kBnThreads / kWave];
     const BnState st = bn_state(const_cast<void *>(a.state), a.channels);
     int32_t *lp = reinterpret_cast<int32_t *>(coef + a.channels), *lq = lp + a.channels;
-    for (int i = threadIdx.x; i < a.channels; i += kBnThreads) { coef[i] = st.R[i]; lp[i] = st.P[i]; lq[i] = st.Q[i]; }
+    const uint32_t cg = (uint32_t)a.channels >> 3, t0 = blockIdx.x * kBnThreads + threadIdx.x, nt = gridDim.x * kBnThreads;
+    uint32_t c0 = t0 % cg * 8;
+    const uint32_t step = nt % cg * 8;
+    int32_t P[8], Q[8];
+    long long R[8];
+    if (REG) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { P[e] = st.P[c0 + e]; Q[e] = st.Q[c0 + e]; R[e] = st.R[c0 + e]; }
+    } else {
+        for (int i = threadIdx.x; i < a.channels; i += kBnThreads) { coef[i] = st.R[i]; lp[i] = st.P[i]; lq[i] = st.Q[i]; }
+    }
     int shift = 0;
     if (FIT) {
         uint64_t m = 0;
@@ -369,24 +434,27 @@ __global__ void __launch_bounds__(kBnThreads) bn_bwd_kernel(const BnBwdArgs a)
             if (a.shift_out) *a.shift_out = shift;
             if (a.e_out) *a.e_out = (a.e_in ? *a.e_in : 0) + st.h->fb - shift + st.h->fl_o - st.h->fl_y;
         }
-    } else {
+    } else if (!REG) {
         __syncthreads();
     }
     const int qhi = (1 << (a.wl - 1)) - 1, qlo = -(1 << (a.wl - 1));
-    const uint32_t cg = (uint32_t)a.channels >> 3;
     const TD *dz = static_cast<const TD *>(a.dz);
     const TY *y = static_cast<const TY *>(a.y);
     TO *dy = static_cast<TO *>(a.dy);
     uint64_t mx = 0;
-    const uint64_t first = (uint64_t)blockIdx.x * kBnThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kBnThreads;
-    for (uint64_t g = first; g < a.groups; g += stride) {
+    for (uint64_t g = t0; g < a.groups; g += nt) {
         int d[8], x[8];
         load_codes8<TD>(dz, g, d);
         load_codes8<TY>(y, g, x);
-        const uint32_t c0 = (uint32_t)(g % cg) * 8;
+        if (!REG) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { P[e] = lp[c0 + e]; Q[e] = lq[c0 + e]; R[e] = coef[c0 + e]; }
+            c0 += step;
+            if (c0 >= (uint32_t)a.channels) c0 -= (uint32_t)a.channels;
+        }
         long long acc[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = (long long)lp[c0 + e] * d[e] + (long long)lq[c0 + e] * x[e] + coef[c0 + e];
+        for (int e = 0; e < 8; ++e) acc[e] = (long long)P[e] * d[e] + (long long)Q[e] * x[e] + R[e];
         if (!FIT) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -805,15 +873,13 @@ static int bn_grid(const adapt_ctx *ctx, uint64_t groups)
     const uint64_t blocks = (groups + kBnThreads - 1) / kBnThreads;
     return (int)std::min<uint64_t>(std::max<uint64_t>(blocks, 1), (uint64_t)ctx->num_cu * 8);
 }
+// whether a launch of grid blocks keeps every thread on the same eight channels
+static bool same_channels(int grid, int channels) { return (uint64_t)grid * kBnThreads % ((uint64_t)channels / 8) == 0; }
 // blocks of the statistics launch: each flushes 2 * channels sums, so fewer and longer-running ones
 static int sums_grid(const adapt_ctx *ctx, uint64_t groups, int channels, bool &reg)
 {
     int grid = (int)std::min<uint64_t>(std::max<uint64_t>((groups + kBnThreads * 4 - 1) / (kBnThreads * 4), 1), (uint64_t)ctx->num_cu * 2);
-    const uint64_t cg = (uint64_t)channels / 8;
-    // register sums need a thread stride (grid * threads groups) that is a multiple of channels / 8
-    reg = false;
-    if (cg <= kBnThreads && kBnThreads % cg == 0) reg = true;
-    else if ((uint64_t)grid * kBnThreads % cg == 0) reg = true;
+    reg = same_channels(grid, channels);         // register sums
     return grid;
 }
 static bool rng_ok(adapt_rng r) { return r.mode == ADAPT_SR || r.mode == ADAPT_RN_HALF_UP; }
@@ -838,7 +904,7 @@ static int launch_sums(adapt_ctx *ctx, const void *a, int es_a, const void *b, i
 {
     bool reg;
     grid = sums_grid(ctx, groups, channels, reg);
-    const size_t lds = (size_t)2 * channels * 8;
+    const size_t lds = (size_t)2 * channels * 8 * bn_copies((uint32_t)channels / 8);
     const dim3 g(grid), t(kBnThreads);
 #define ADAPT_SUMS(TA, TB)                                                                                                          \
     do {                                                                                                                            \
@@ -893,10 +959,15 @@ extern "C" int adapt_bn_forward(adapt_ctx *ctx, const void *y, adapt_fmt fy, siz
     BnApplyArgs a;
     a.y = y; a.res = res; a.out = out; a.state = state; a.groups = groups; a.channels = channels; a.wl = fo.wl; a.relu = relu != 0;
     a.mode = rng.mode; a.has_res = res != nullptr; a.fl_res = res ? fres.fl : 0; a.seed = rng.seed; a.stream = rng.stream;
-    const size_t lds = (size_t)channels * 12;
     const dim3 g(bn_grid(ctx, groups)), t(kBnThreads);
+    const bool reg = same_channels((int)g.x, channels);
+    const size_t lds = reg ? 0 : (size_t)channels * 12;
     const int sel = (storage_bytes(fy) == 2) * 4 + ((res ? storage_bytes(fres) : 1) == 2) * 2 + (storage_bytes(fo) == 2);
-#define ADAPT_APPLY(TY, TR, TO) hipLaunchKernelGGL((bn_apply_kernel<TY, TR, TO>), g, t, lds, ctx->stream, a)
+#define ADAPT_APPLY(TY, TR, TO)                                                                                    \
+    do {                                                                                                          \
+        if (reg) hipLaunchKernelGGL((bn_apply_kernel<TY, TR, TO, true>), g, t, lds, ctx->stream, a);              \
+        else hipLaunchKernelGGL((bn_apply_kernel<TY, TR, TO, false>), g, t, lds, ctx->stream, a);                 \
+    } while (0)
     switch (sel) {
     case 0: ADAPT_APPLY(int8_t, int8_t, int8_t); break;
     case 1: ADAPT_APPLY(int8_t, int8_t, int16_t); break;
@@ -960,13 +1031,19 @@ extern "C" int adapt_bn_backward(adapt_ctx *ctx, const void *dz, int wl_dz, cons
     const int grid1 = (int)std::min<uint64_t>(std::max<uint64_t>((groups + kBnThreads - 1) / kBnThreads, 1), (uint64_t)ctx->num_cu * 4);
     a.part = reinterpret_cast<uint64_t *>(scratch(ctx) + (size_t)ctx->num_cu * 2 * 2 * (size_t)channels * 8 + (size_t)2 * channels * 8);
     a.nparts = grid1;
-    const size_t lds = (size_t)channels * 16;
     const dim3 t(kBnThreads), g2(bn_grid(ctx, groups));
+    const bool reg = same_channels(grid1, channels) && same_channels((int)g2.x, channels);
+    const size_t lds = reg ? 0 : (size_t)channels * 16;
     const int sel = (es_d == 2) * 4 + (es_y == 2) * 2 + (es_o == 2);
 #define ADAPT_BWD(TD, TY, TO)                                                                                     \
     do {                                                                                                          \
-        hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false>), dim3(grid1), t, lds, ctx->stream, a);              \
-        hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true>), g2, t, lds, ctx->stream, a);                        \
+        if (reg) {                                                                                                \
+            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false, true>), dim3(grid1), t, lds, ctx->stream, a);    \
+            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true, true>), g2, t, lds, ctx->stream, a);              \
+        } else {                                                                                                  \
+            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false, false>), dim3(grid1), t, lds, ctx->stream, a);   \
+            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true, false>), g2, t, lds, ctx->stream, a);             \
+        }                                                                                                         \
     } while (0)
     switch (sel) {
     case 0: ADAPT_BWD(int8_t, int8_t, int8_t); break;
