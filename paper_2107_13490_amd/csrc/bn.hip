@@ -426,8 +426,7 @@ __global__ void __launch_bounds__(kBnThreads) bn_bwd_kernel(const BnBwdArgs a)
     }
     int shift = 0;
     if (FIT) {
-        uint64_t m = 0;
-        for (int i = threadIdx.x; i < a.nparts; i += kBnThreads) m = a.part[i] > m ? a.part[i] : m;
+        uint64_t m = max_of_parts<kBnThreads>(a.part, a.nparts);
         m = block_max_u64(m, sm, kBnThreads / kWave);
         shift = fit_shift_of(m, a.wl);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -588,8 +587,7 @@ __global__ void __launch_bounds__(kBnThreads) bn_bwd_wide_kernel(const BnWideArg
     const BnState st = bn_state(const_cast<void *>(a.state), a.channels);
     int shift = 0;
     if (PASS == 1) {
-        uint64_t m = 0;
-        for (int i = threadIdx.x; i < a.nparts; i += kBnThreads) m = a.part[i] > m ? a.part[i] : m;
+        uint64_t m = max_of_parts<kBnThreads>(a.part, a.nparts);
         m = block_max_u64(m, sm, kBnThreads / kWave);
         shift = max(0, (int)m - (a.wl - 1));
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -766,8 +764,7 @@ __global__ void __launch_bounds__(kBnThreads) merge_kernel(const MergeArgs a)
     merge_plan(a, sa, sb, e);
     int shift = 0;
     if (FIT) {
-        uint64_t m = 0;
-        for (int i = threadIdx.x; i < a.nparts; i += kBnThreads) m = a.part[i] > m ? a.part[i] : m;
+        uint64_t m = max_of_parts<kBnThreads>(a.part, a.nparts);
         m = block_max_u64(m, sm, kBnThreads / kWave);
         shift = fit_shift_of(m, a.wl);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -841,8 +838,7 @@ __global__ void __launch_bounds__(kBnThreads) merge_wide_kernel(const MergeArgs 
     merge_plan(a, sa, sb, e);
     int shift = 0;
     if (PASS == 1) {
-        uint64_t m = 0;
-        for (int i = threadIdx.x; i < a.nparts; i += kBnThreads) m = a.part[i] > m ? a.part[i] : m;
+        uint64_t m = max_of_parts<kBnThreads>(a.part, a.nparts);
         m = block_max_u64(m, sm, kBnThreads / kWave);
         shift = max(0, (int)m - (a.wl - 1));
         if (blockIdx.x == 0 && threadIdx.x == 0) {

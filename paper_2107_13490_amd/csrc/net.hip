@@ -30,6 +30,7 @@
 namespace adapt {
 
 constexpr int kEwThreads = 256;
+constexpr int kFitSumThreads = 1024;     // of the fitting pass that also sums the squares of its codes
 
 template <typename T, int V>
 struct alignas(sizeof(T) * V) CodeVec {
@@ -162,18 +163,16 @@ absmax_kernel(const AccT *__restrict__ acc, const uint64_t n, uint64_t *__restri
 
 // codes = requantize(acc, shift) with shift = max(0, bit_length(max |acc|) - (wl-1)); every block
 // derives the shift from the partial maxima itself
-template <typename AccT, typename OutT>
-__global__ void __launch_bounds__(kEwThreads) requant_fit_kernel(const FitArgs a)
+template <typename AccT, typename OutT, int THREADS>
+__global__ void __launch_bounds__(THREADS) requant_fit_kernel(const FitArgs a)
 {
-    __shared__ uint64_t sm[kEwThreads / kWave];
-    uint64_t m = 0;
-    for (int i = threadIdx.x; i < a.nparts; i += kEwThreads) m = a.part[i] > m ? a.part[i] : m;
-    m = wave_max_u64(m);
+    __shared__ uint64_t sm[THREADS / kWave];
+    uint64_t m = wave_max_u64(max_of_parts<THREADS>(a.part, a.nparts));
     if ((threadIdx.x & (kWave - 1)) == 0) sm[threadIdx.x / kWave] = m;
     __syncthreads();
     m = sm[0];
 #pragma unroll
-    for (int i = 1; i < kEwThreads / kWave; ++i) m = sm[i] > m ? sm[i] : m;
+    for (int i = 1; i < THREADS / kWave; ++i) m = sm[i] > m ? sm[i] : m;
     const int bits = m ? 64 - __clzll((long long)m) : 0;
     const int shift = max(0, bits - (a.wl - 1));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -187,7 +186,7 @@ __global__ void __launch_bounds__(kEwThreads) requant_fit_kernel(const FitArgs a
     OutT *q = static_cast<OutT *>(a.q);
     uint64_t ss = 0;
     const uint64_t groups = a.n >> 3;
-    const uint64_t first = (uint64_t)blockIdx.x * kEwThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kEwThreads;
+    const uint64_t first = (uint64_t)blockIdx.x * THREADS + threadIdx.x, stride = (uint64_t)gridDim.x * THREADS;
     for (uint64_t grp = first; grp < groups; grp += stride) {
         long long v[8];
         load_acc8<AccT>(acc, grp, v);
@@ -221,7 +220,7 @@ __global__ void __launch_bounds__(kEwThreads) requant_fit_kernel(const FitArgs a
         __syncthreads();
         if (threadIdx.x == 0) {
 #pragma unroll
-            for (int i = 1; i < kEwThreads / kWave; ++i) ss += sm[i];
+            for (int i = 1; i < THREADS / kWave; ++i) ss += sm[i];
             if (ss) atomicAdd(a.sumsq, (unsigned long long)ss);
         }
     }
@@ -387,9 +386,11 @@ static int requantize_fit_exp(adapt_ctx *ctx, const void *acc, int acc_bits, siz
     if (n > 0 && (!acc || !q || !aligned16(acc) || !aligned16(q))) return ADAPT_EINVAL;
     const uint64_t groups = ((uint64_t)n + 7) >> 3;
     const int grid1 = (int)std::min<uint64_t>(std::max<uint64_t>((groups + kEwThreads - 1) / kEwThreads, 1), (uint64_t)ctx->num_cu * 4);
-    // Atomic additions to one address retire at about one per 10 ns on this chip, whoever issues them:
-    // with the sum of squares asked for, fewer and longer-running blocks keep that tail short.
-    const int grid2 = sumsq ? std::min(ew_grid(ctx, groups), ctx->num_cu * 2) : ew_grid(ctx, groups);
+    // Atomic additions to one address retire at about one per 10 ns on this chip, whoever issues them: with the sum of
+    // squares asked for, one block of 1024 threads per CU at most keeps that tail short.
+    const int threads = sumsq ? kFitSumThreads : kEwThreads;
+    const int grid2 = sumsq ? (int)std::min<uint64_t>(std::max<uint64_t>((groups + threads - 1) / threads, 1), (uint64_t)ctx->num_cu)
+                            : ew_grid(ctx, groups);
     if ((size_t)grid1 * 8 > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
     uint64_t *part = reinterpret_cast<uint64_t *>(scratch(ctx));
     unsigned long long *ss = reinterpret_cast<unsigned long long *>(sumsq);
@@ -406,10 +407,16 @@ static int requantize_fit_exp(adapt_ctx *ctx, const void *acc, int acc_bits, siz
         hipLaunchKernelGGL(absmax_kernel<int64_t>, dim3(grid1), block, 0, ctx->stream, (const int64_t *)acc, (uint64_t)n, part, ss);
     }
     const bool o8 = wl <= 8;
-    if (acc_bits == 32 && o8) hipLaunchKernelGGL((requant_fit_kernel<int32_t, int8_t>), dim3(grid2), block, 0, ctx->stream, a);
-    else if (acc_bits == 32) hipLaunchKernelGGL((requant_fit_kernel<int32_t, int16_t>), dim3(grid2), block, 0, ctx->stream, a);
-    else if (o8) hipLaunchKernelGGL((requant_fit_kernel<int64_t, int8_t>), dim3(grid2), block, 0, ctx->stream, a);
-    else hipLaunchKernelGGL((requant_fit_kernel<int64_t, int16_t>), dim3(grid2), block, 0, ctx->stream, a);
+#define ADAPT_FIT(ACC, OUT)                                                                                                        \
+    do {                                                                                                                           \
+        if (sumsq) hipLaunchKernelGGL((requant_fit_kernel<ACC, OUT, kFitSumThreads>), dim3(grid2), dim3(threads), 0, ctx->stream, a); \
+        else hipLaunchKernelGGL((requant_fit_kernel<ACC, OUT, kEwThreads>), dim3(grid2), block, 0, ctx->stream, a);                \
+    } while (0)
+    if (acc_bits == 32 && o8) ADAPT_FIT(int32_t, int8_t);
+    else if (acc_bits == 32) ADAPT_FIT(int32_t, int16_t);
+    else if (o8) ADAPT_FIT(int64_t, int8_t);
+    else ADAPT_FIT(int64_t, int16_t);
+#undef ADAPT_FIT
     return hip_status(ctx, hipGetLastError());
 }
 

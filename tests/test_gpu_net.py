@@ -82,6 +82,19 @@ def test_requantize_fit(n, bits, wl, mag):
         assert int(ss.item()) == wss
 
 
+# more than one group of eight per thread in the launch that sums the squares (256 blocks of 1024) and in the one that
+# does not (2048 blocks of 256), with a remainder; the largest magnitude in the last element
+@pytest.mark.parametrize("n,sums", [(2100003, True), (4200003, False), (1023 * 8 + 1, False)])
+def test_requantize_fit_several_groups_per_thread(n, sums):
+    rng = np.random.default_rng(n)
+    acc = rng.integers(-(1 << 25), 1 << 25, n)
+    acc[-1] = -(1 << 28) - 1
+    q, sh, ss = ctx().requantize_fit(dev(acc.astype(np.int32)), 8, seed=3, stream=n, want_sumsq=sums)
+    want, wsh, wss = no.requantize_fit(acc, 8, pkg.SR, 3, n)
+    assert int(sh.item()) == wsh and np.array_equal(host(q).astype(np.int64), want)
+    assert not sums or int(ss.item()) == wss
+
+
 def test_requantize_fit_degenerate_inputs():
     z = dev(np.zeros(100, np.int32))
     q, sh, ss = ctx().requantize_fit(z, 8)
