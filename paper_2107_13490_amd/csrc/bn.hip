@@ -28,6 +28,7 @@
 #include "common.hpp"
 #include "context.hpp"
 #include "fit.hpp"
+#include "ticket.hpp"
 #include "update_batch.hpp"
 #include "wide.hpp"
 
@@ -180,12 +181,8 @@ __device__ inline double block_max_f64(double v, double *sm)
     return v;
 }
 
-// The totals may have been written by other blocks of the same launch (the merged totals + coefficients kernels):
-// they are read at device scope, past this compute unit's cache.
-__device__ __forceinline__ long long total_at(const long long *tot, int i)
-{
-    return __hip_atomic_load(tot + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// The totals may have been written by other blocks of the same launch (the merged totals + coefficients kernels).
+__device__ __forceinline__ long long total_at(const long long *tot, int i) { return load_partial(tot + i); }
 
 // One block: statistics and forward coefficients from the totals.
 __device__ __forceinline__ void bn_coef_fwd_body(const long long *tot /* [2 * channels] */, int channels, unsigned long long rows, int fl_y,
@@ -290,7 +287,6 @@ __global__ void __launch_bounds__(256)
 bn_total_coef_kernel(const long long *__restrict__ partial, int nparts, long long *totals, uint32_t *ticket, const BnCoefArgs c)
 {
     __shared__ long long sm[32][8];
-    __shared__ bool last;
     const int width = 2 * c.channels;
     const int col8 = threadIdx.x & 7, rl = threadIdx.x >> 3;
     const int col = blockIdx.x * 8 + col8;
@@ -309,16 +305,9 @@ bn_total_coef_kernel(const long long *__restrict__ partial, int nparts, long lon
         long long t = 0;
 #pragma unroll
         for (int i = 0; i < 32; ++i) t += sm[i][threadIdx.x];
-        __hip_atomic_store(totals + col, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        store_partial(totals + col, t);
     }
-    __syncthreads();                               // the block's totals are issued before its ticket
-    if (threadIdx.x == 0) {
-        // release this block's totals, acquire everyone else's
-        last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-        if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next launch
-    }
-    __syncthreads();
-    if (!last) return;
+    if (!finished_last(ticket)) return;
     if (BWD) bn_coef_bwd_body(totals, c.channels, c.state, c.dgamma, c.dbeta, nullptr);
     else bn_coef_fwd_body(totals, c.channels, c.rows, c.fl_y, c.fl_o, c.gamma, c.beta, c.eps, c.state, nullptr);
 }

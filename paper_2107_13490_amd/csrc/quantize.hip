@@ -10,6 +10,7 @@
 
 #include "common.hpp"
 #include "context.hpp"
+#include "ticket.hpp"
 
 namespace adapt {
 
@@ -108,10 +109,50 @@ __device__ __forceinline__ void block_sum2(uint32_t a, uint32_t b, uint64_t &sa,
     __syncthreads();
 }
 
-template <typename OutT>
+// Small calls sum their counters in the block that finishes last instead of a second launch: a one-block launch costs
+// them as much as the conversion does (a few thousand elements 8.6 -> 5.2 us; two 256 x 256 matrices and their product
+// 15.8 -> 12.4 us).  Up to kFusedBlocks blocks and kFusedItems tensors, whose columns the four
+// wavefronts take in one round; in larger calls every block's fence would write freshly converted codes back from the
+// L2 (40 us on 8.5 M elements), and they have the second launch's time to spare.
+constexpr uint32_t kFusedBlocks = 256;
+constexpr int kFusedItems = 16;
+
+// sums of partial[cols][nblocks] by the last block of the launch, U columns and four blocks per lane in flight
+template <int U, typename Store>
+__device__ __forceinline__ void sum_columns(const uint32_t *partial, const int nblocks, const int cols, const Store &store)
+{
+    constexpr int W = kQThreads / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int c0 = threadIdx.x / kWave; c0 < cols; c0 += U * W) {
+        uint64_t sum[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum[u] = 0;
+        for (int b = lane; b < nblocks; b += 4 * kWave) {
+            uint32_t t[U][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)       // columns and blocks past the last repeat it
+                    t[u][r] = load_partial(partial + (size_t)min(c0 + u * W, cols - 1) * nblocks + min(b + r * kWave, nblocks - 1));
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum[u] += b + r * kWave < nblocks ? t[u][r] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) sum[u] += __shfl_xor((unsigned long long)sum[u], off, 64);
+            if (lane == 0 && c0 + u * W < cols) store(c0 + u * W, sum[u]);
+        }
+    }
+}
+
+template <typename OutT, bool FUSED>
 __global__ void __launch_bounds__(kQThreads)
 quantize_kernel(const float *__restrict__ x, OutT *__restrict__ q, uint64_t n, int wl, int fl, int mode,
-                uint64_t seed, uint64_t stream, uint32_t *partial /* [2][gridDim.x] or null */)
+                uint64_t seed, uint64_t stream, uint32_t *partial /* [2][gridDim.x] or null */, uint32_t *ticket, uint64_t *out0,
+                uint64_t *out1 /* FUSED: totals, either may be null */)
 {
     const QuantParams p = make_quant_params(wl, fl);
     uint32_t nnz = 0, nsat = 0;
@@ -123,8 +164,15 @@ quantize_kernel(const float *__restrict__ x, OutT *__restrict__ q, uint64_t n, i
     uint64_t bn, bs;
     block_sum2(nnz, nsat, bn, bs);
     if (threadIdx.x == 0) {
-        partial[blockIdx.x] = (uint32_t)bn;
-        partial[gridDim.x + blockIdx.x] = (uint32_t)bs;
+        store_partial(partial + blockIdx.x, (uint32_t)bn);
+        store_partial(partial + gridDim.x + blockIdx.x, (uint32_t)bs);
+    }
+    if constexpr (FUSED) {
+        if (!finished_last(ticket)) return;
+        sum_columns<1>(partial, (int)gridDim.x, 2, [&](int c, uint64_t v) {
+            uint64_t *dst = c == 0 ? out0 : out1;
+            if (dst) *dst = v;
+        });
     }
 }
 
@@ -252,9 +300,11 @@ struct QuantBatch {
 
 // nnz / saturated of every tensor: per-block partial counts in `partial[2*count][block]`, summed
 // by sum_partials_kernel (no same-address atomics, no zero-fill launch).
+template <bool FUSED>
 __global__ void __launch_bounds__(kQThreads)
 quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_t *partial /* or null */,
-                        float *range_partial /* [2*count][gridDim.x] or null */, uint64_t range_mask /* bit t: tensor t */)
+                        float *range_partial /* [2*count][gridDim.x] or null */, uint64_t range_mask /* bit t: tensor t */,
+                        uint32_t *ticket, uint64_t *out /* FUSED: totals [2*count] */)
 {
     __shared__ uint32_t wave_part[2][kQThreads / kWave];
     __shared__ float wave_range[2][kQThreads / kWave];
@@ -304,7 +354,7 @@ quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_
             if (threadIdx.x < 2 && partial != nullptr) {
                 uint32_t v = 0;
                 for (int w = 0; w < kQThreads / kWave; ++w) v += wave_part[threadIdx.x][w];
-                partial[(size_t)(2 * t + threadIdx.x) * gridDim.x + blockIdx.x] = v;
+                store_partial(partial + (size_t)(2 * t + threadIdx.x) * gridDim.x + blockIdx.x, v);
             }
             if (threadIdx.x >= kWave && threadIdx.x < kWave + 2 && want_range) {      // a second wavefront: runs beside the first
                 const int m = threadIdx.x - kWave;
@@ -316,6 +366,10 @@ quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_
         }
         if (range_partial != nullptr && !want_range && threadIdx.x < 2)      // not asked for: the neutral pair
             range_partial[(size_t)(2 * t + threadIdx.x) * gridDim.x + blockIdx.x] = threadIdx.x == 0 ? INFINITY : -INFINITY;
+    }
+    if constexpr (FUSED) {
+        if (!finished_last(ticket)) return;
+        sum_columns<8>(partial, (int)gridDim.x, 2 * batch.count, [&](int c, uint64_t v) { out[c] = v; });
     }
 }
 
@@ -349,8 +403,9 @@ using namespace adapt;
 
 // adapt_quantize with the per-block counter partials at `base` (room for `room` bytes): the context's workspace, or
 // the static array of the entry point that allocates nothing
+// (control: the ticket word, or null: no control words there)
 static int quantize_on(adapt_ctx *ctx, const float *x, size_t n, adapt_fmt fmt, adapt_rng rng, void *q, uint64_t *nnz,
-                       uint64_t *saturated, char *base, size_t room)
+                       uint64_t *saturated, char *base, size_t room, uint32_t *control)
 {
     if (!ctx || !fmt_ok_wide(fmt) || (rng.mode != ADAPT_SR && rng.mode != ADAPT_RN_HALF_UP)) return ADAPT_EINVAL;
     if (n > 0 && (!x || !q || !aligned16(x) || !aligned16(q))) return ADAPT_EINVAL;
@@ -361,16 +416,19 @@ static int quantize_on(adapt_ctx *ctx, const float *x, size_t n, adapt_fmt fmt, 
     const size_t part_bytes = ((size_t)grid * 8 + 255) & ~(size_t)255;
     if (part_bytes + 16 > room) return ADAPT_EWORKSPACE;
     uint32_t *partial = count ? reinterpret_cast<uint32_t *>(base) : nullptr;
+    const bool fused = count && control && fmt.wl <= 16 && (uint32_t)grid <= kFusedBlocks;
     if (fmt.wl > 16)
         hipLaunchKernelGGL(quantize_wide_kernel, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, (int32_t *)q, (uint64_t)n, fmt.wl,
                            fmt.fl, rng.mode, rng.seed, rng.stream, partial);
-    else if (fmt.wl <= 8)
-        hipLaunchKernelGGL(quantize_kernel<int8_t>, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, (int8_t *)q,
-                           (uint64_t)n, fmt.wl, fmt.fl, rng.mode, rng.seed, rng.stream, partial);
-    else
-        hipLaunchKernelGGL(quantize_kernel<int16_t>, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, (int16_t *)q,
-                           (uint64_t)n, fmt.wl, fmt.fl, rng.mode, rng.seed, rng.stream, partial);
-    if (count) {
+    else {
+        auto launch = [&](auto kern, auto *codes) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, codes, (uint64_t)n, fmt.wl, fmt.fl, rng.mode, rng.seed,
+                               rng.stream, partial, control, nnz, saturated);
+        };
+        if (fmt.wl <= 8) fused ? launch(quantize_kernel<int8_t, true>, (int8_t *)q) : launch(quantize_kernel<int8_t, false>, (int8_t *)q);
+        else fused ? launch(quantize_kernel<int16_t, true>, (int16_t *)q) : launch(quantize_kernel<int16_t, false>, (int16_t *)q);
+    }
+    if (count && !fused) {
         // out1 != null selects the two-destination form; a null destination is redirected to a dummy slot
         uint64_t *dummy = reinterpret_cast<uint64_t *>(base + part_bytes);
         hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(kSumThreads), 0, ctx->stream, partial, grid, 2,
@@ -383,7 +441,7 @@ extern "C" int adapt_quantize(adapt_ctx *ctx, const float *x, size_t n, adapt_fm
                               uint64_t *nnz, uint64_t *saturated)
 {
     if (!ctx) return ADAPT_EINVAL;
-    return quantize_on(ctx, x, n, fmt, rng, q, nnz, saturated, scratch(ctx), scratch_bytes(ctx));
+    return quantize_on(ctx, x, n, fmt, rng, q, nnz, saturated, scratch(ctx), scratch_bytes(ctx), ticket(ctx, 0));
 }
 
 // ---- the entry point that allocates nothing ------------------------------------------------------------------
@@ -408,7 +466,7 @@ extern "C" int adapt_quantize_noalloc(adapt_ctx *ctx, const float *x, size_t n, 
     if (!ctx->static_scratch) return ADAPT_EHIP;      // the address could not be taken when the context was created
     // at most 8 blocks per compute unit, 8 bytes each: more than kStaticScratchBytes only on a device with more
     // than 4,000 compute units, which quantize_on reports as ADAPT_EWORKSPACE
-    return quantize_on(ctx, x, n, fmt, rng, q, nnz, saturated, static_cast<char *>(ctx->static_scratch), kStaticScratchBytes);
+    return quantize_on(ctx, x, n, fmt, rng, q, nnz, saturated, static_cast<char *>(ctx->static_scratch), kStaticScratchBytes, nullptr);
 }
 
 extern "C" int adapt_quantize_batched(adapt_ctx *ctx, const adapt_quantize_item *items, int count, int mode,
@@ -450,8 +508,13 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
         if (2 * part_bytes > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
         uint32_t *partial = counters ? reinterpret_cast<uint32_t *>(scratch(ctx)) : nullptr;
         float *range_partial = ranges ? reinterpret_cast<float *>(scratch(ctx) + part_bytes) : nullptr;
-        hipLaunchKernelGGL(quantize_batched_kernel, dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
-                           seed, partial, range_partial, range_mask >> base);
+        if (counters && !ranges && grid <= kFusedBlocks && batch.count <= kFusedItems) {
+            hipLaunchKernelGGL(quantize_batched_kernel<true>, dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
+                               seed, partial, nullptr, (uint64_t)0, ticket(ctx, 0), counters + 2 * base);
+            continue;
+        }
+        hipLaunchKernelGGL(quantize_batched_kernel<false>, dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
+                           seed, partial, range_partial, range_mask >> base, nullptr, nullptr);
         // one wavefront per column: enough blocks for all the columns of the batch to run side by side
         const int sum_cols = (counters ? 2 * batch.count : 0) + (ranges ? 2 * batch.count : 0);
         const int sum_blocks = std::min(std::max((sum_cols + kSumThreads / kWave - 1) / (kSumThreads / kWave), 1), 16);

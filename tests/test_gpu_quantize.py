@@ -103,6 +103,27 @@ def test_batched_many_items():
         assert c[2 * t:2 * t + 2].tolist() == [nnz, sat]
 
 
+# around the largest call whose counters are summed by the launch itself (256 blocks of 2048 elements; 16 tensors),
+# each twice, so that a ticket left behind would show
+@pytest.mark.parametrize("n", [2048, 64 * 2048 + 1, 255 * 2048 + 9, 256 * 2048, 256 * 2048 + 1])
+@pytest.mark.parametrize("wl", [8, 12])
+def test_counters_of_single_and_two_launch_sizes(n, wl):
+    x = np.random.default_rng(n).standard_normal(n).astype(np.float32)
+    for _ in range(2):
+        _check(x, wl, wl - 2, pkg.SR, seed=3, stream=n)
+
+
+@pytest.mark.parametrize("sizes", [[3000] * 15, [3000] * 16, [3000] * 17, [100 * 2048, 156 * 2048], [100 * 2048, 156 * 2048 + 1], [0, 5]])
+def test_batched_counters_of_single_and_two_launch_calls(sizes):
+    g = np.random.default_rng(sum(sizes) + len(sizes))
+    xs = [g.standard_normal(n).astype(np.float32) for n in sizes]
+    fmts = [(8, 6) if t % 2 else (12, 10) for t in range(len(sizes))]
+    for _ in range(2):
+        _, cnt = ctx().quantize_batched([dev(x) for x in xs], fmts, list(range(len(xs))), pkg.SR, seed=5)
+        want = [c for t, x in enumerate(xs) for c in orc.quantize(x, fmts[t][0], fmts[t][1], pkg.SR, 5, t)[1:]]
+        assert u64(cnt)[:len(want)].tolist() == want
+
+
 def test_invalid_arguments_are_rejected():
     x = torch.zeros(64, dtype=torch.float32, device="cuda")
     with pytest.raises(pkg.AdaptError) as e:
