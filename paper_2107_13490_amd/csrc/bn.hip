@@ -184,32 +184,53 @@ __device__ inline double block_max_f64(double v, double *sm)
 // The totals may have been written by other blocks of the same launch (the merged totals + coefficients kernels).
 __device__ __forceinline__ long long total_at(const long long *tot, int i) { return load_partial(tot + i); }
 
+// Whatever the coefficients of channel threadIdx.x need besides the totals, read before the totals are there, and its
+// results between the two passes over the channels: the one block that forms the coefficients waits for nothing else
+// (channels beyond the block's threads read and store theirs).  ResNet-18 at batch 256, mean over its layers: forward totals
+// and coefficients 6.4 -> 6.0 us, backward 6.7 -> 6.5.
+struct BnOwnFwd { float gamma, beta; };
+__device__ __forceinline__ BnOwnFwd bn_own_fwd(int channels, const float *__restrict__ gamma, const float *__restrict__ beta)
+{
+    const int k = min((int)threadIdx.x, channels - 1);
+    return {gamma[k], beta[k]};
+}
+struct BnOwnBwd { double mean, sig, alpha, rows; };
+__device__ __forceinline__ BnOwnBwd bn_own_bwd(int channels, void *state)
+{
+    const BnState st = bn_state(state, channels);
+    const int k = min((int)threadIdx.x, channels - 1);
+    return {st.mean[k], st.sig[k], st.alpha[k], (double)st.h->rows};
+}
+
 // One block: statistics and forward coefficients from the totals.
 __device__ __forceinline__ void bn_coef_fwd_body(const long long *tot /* [2 * channels] */, int channels, unsigned long long rows, int fl_y,
                                                  int fl_o, const float *__restrict__ gamma, const float *__restrict__ beta, double eps,
-                                                 void *state, const double *__restrict__ s2d)
+                                                 void *state, const double *__restrict__ s2d, const BnOwnFwd own)
 {
     __shared__ double sm[16];
     const BnState st = bn_state(state, channels);
     const double m = (double)rows;
-    double amax = 0.0;
+    double amax = 0.0, alpha0 = 0.0, mean0 = 0.0;
     for (int k = threadIdx.x; k < channels; k += blockDim.x) {
+        const bool mine = k == (int)threadIdx.x;
         const long long s1 = total_at(tot, k);
         const double mean = (double)s1 / m;
         const double ex2 = (s2d ? s2d[k] : (double)total_at(tot, channels + k)) / m;
         const double var = fmax(ex2 - mean * mean, 0.0);
         const double sig = sqrt(var + ldexp(eps, 2 * fl_y));
-        const double alpha = ldexp((double)gamma[k], fl_o) / sig;
+        const double alpha = ldexp((double)(mine ? own.gamma : gamma[k]), fl_o) / sig;
         st.mean[k] = mean;
         st.sig[k] = sig;
         st.alpha[k] = alpha;
+        if (mine) { alpha0 = alpha; mean0 = mean; }
         amax = fmax(amax, fabs(alpha));
     }
     amax = block_max_f64(amax, sm);
     const int fa = coef_exponent(amax);
     for (int k = threadIdx.x; k < channels; k += blockDim.x) {
-        const double alpha = st.alpha[k];
-        const double off = ldexp((double)beta[k], fl_o) - st.mean[k] * alpha;
+        const bool mine = k == (int)threadIdx.x;
+        const double alpha = mine ? alpha0 : st.alpha[k];
+        const double off = ldexp((double)(mine ? own.beta : beta[k]), fl_o) - (mine ? mean0 : st.mean[k]) * alpha;
         st.A[k] = (int32_t)rint_clamped(alpha, fa, 1073741824.0);
         st.B[k] = rint_clamped(off, fa, 2305843009213693952.0);
     }
@@ -223,21 +244,23 @@ bn_coef_fwd_kernel(const long long *tot, int channels, unsigned long long rows, 
                    const float *__restrict__ beta, double eps, void *state,
                    const double *__restrict__ s2d = nullptr /* sums of squares beyond 64 bits, as their nearest doubles */)
 {
-    bn_coef_fwd_body(tot, channels, rows, fl_y, fl_o, gamma, beta, eps, state, s2d);
+    bn_coef_fwd_body(tot, channels, rows, fl_y, fl_o, gamma, beta, eps, state, s2d, bn_own_fwd(channels, gamma, beta));
 }
 
 // One block: from the totals of (sum dz, sum dz*y) the parameter gradients and the backward coefficients.
 __device__ __forceinline__ void bn_coef_bwd_body(const long long *tot /* [2 * channels] */, int channels, void *state,
-                                                 double *__restrict__ dgamma, double *__restrict__ dbeta, const double *__restrict__ d2d)
+                                                 double *__restrict__ dgamma, double *__restrict__ dbeta, const double *__restrict__ d2d,
+                                                 const BnOwnBwd own)
 {
     __shared__ double sm[16];
     const BnState st = bn_state(state, channels);
-    const double m = (double)st.h->rows;
-    double pmax = 0.0;
+    const double m = own.rows;
+    double pmax = 0.0, q0 = 0.0, r0 = 0.0;
     for (int k = threadIdx.x; k < channels; k += blockDim.x) {
         const long long d1 = total_at(tot, k);
         const double d2 = d2d ? d2d[k] : (double)total_at(tot, channels + k);
-        const double mean = st.mean[k], sig = st.sig[k], alpha = st.alpha[k];
+        const bool mine = k == (int)threadIdx.x;
+        const double mean = mine ? own.mean : st.mean[k], sig = mine ? own.sig : st.sig[k], alpha = mine ? own.alpha : st.alpha[k];
         const double dg = (d2 - mean * (double)d1) / sig;
         const double c1 = (((double)d1) / (m));
         const double c2 = dg / (m * sig);
@@ -245,16 +268,21 @@ __device__ __forceinline__ void bn_coef_bwd_body(const long long *tot /* [2 * ch
         const double r = alpha * (mean * c2 - c1);
         dgamma[k] = dg;
         dbeta[k] = (double)d1;
-        // Q and R wait in the slots of their codes until the common exponent is known
-        reinterpret_cast<double *>(st.R)[k] = r;
-        reinterpret_cast<double *>(st.B)[k] = q;       // B is not needed after the forward pass
+        // Q and R wait in registers, or in the slots of their codes, until the common exponent is known
+        if (mine) {
+            q0 = q; r0 = r;
+        } else {
+            reinterpret_cast<double *>(st.R)[k] = r;
+            reinterpret_cast<double *>(st.B)[k] = q;       // B is not needed after the forward pass
+        }
         pmax = fmax(pmax, fmax(fabs(alpha), fabs(q)));
     }
     pmax = block_max_f64(pmax, sm);
     const int fb = coef_exponent(pmax);
     for (int k = threadIdx.x; k < channels; k += blockDim.x) {
-        const double q = reinterpret_cast<const double *>(st.B)[k], r = reinterpret_cast<const double *>(st.R)[k];
-        st.P[k] = (int32_t)rint_clamped(st.alpha[k], fb, 1073741824.0);
+        const bool mine = k == (int)threadIdx.x;
+        const double q = mine ? q0 : reinterpret_cast<const double *>(st.B)[k], r = mine ? r0 : reinterpret_cast<const double *>(st.R)[k];
+        st.P[k] = (int32_t)rint_clamped(mine ? own.alpha : st.alpha[k], fb, 1073741824.0);
         st.Q[k] = (int32_t)rint_clamped(q, fb, 1073741824.0);
         st.R[k] = rint_clamped(r, fb, 2305843009213693952.0);
     }
@@ -265,7 +293,7 @@ __global__ void __launch_bounds__(1024)
 bn_coef_bwd_kernel(const long long *tot, int channels, void *state, double *__restrict__ dgamma, double *__restrict__ dbeta,
                    const double *__restrict__ d2d = nullptr /* sums of products beyond 64 bits */)
 {
-    bn_coef_bwd_body(tot, channels, state, dgamma, dbeta, d2d);
+    bn_coef_bwd_body(tot, channels, state, dgamma, dbeta, d2d, bn_own_bwd(channels, state));
 }
 
 // Totals and coefficients in one launch.  Totals of the block partials partial[nparts][2 * channels] of a statistics
@@ -288,6 +316,10 @@ bn_total_coef_kernel(const long long *__restrict__ partial, int nparts, long lon
 {
     __shared__ long long sm[32][8];
     const int width = 2 * c.channels;
+    BnOwnFwd own_f = {};
+    BnOwnBwd own_b = {};
+    if (BWD) own_b = bn_own_bwd(c.channels, c.state);
+    else own_f = bn_own_fwd(c.channels, c.gamma, c.beta);
     const int col8 = threadIdx.x & 7, rl = threadIdx.x >> 3;
     const int col = blockIdx.x * 8 + col8;
     long long acc = 0;
@@ -308,8 +340,8 @@ bn_total_coef_kernel(const long long *__restrict__ partial, int nparts, long lon
         store_partial(totals + col, t);
     }
     if (!finished_last(ticket)) return;
-    if (BWD) bn_coef_bwd_body(totals, c.channels, c.state, c.dgamma, c.dbeta, nullptr);
-    else bn_coef_fwd_body(totals, c.channels, c.rows, c.fl_y, c.fl_o, c.gamma, c.beta, c.eps, c.state, nullptr);
+    if (BWD) bn_coef_bwd_body(totals, c.channels, c.state, c.dgamma, c.dbeta, nullptr, own_b);
+    else bn_coef_fwd_body(totals, c.channels, c.rows, c.fl_y, c.fl_o, c.gamma, c.beta, c.eps, c.state, nullptr, own_f);
 }
 
 // ---- forward: out = requantize(A y + B [+ shortcut], FA) ---------------------------------------------------
