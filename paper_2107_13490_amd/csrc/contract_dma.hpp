@@ -5,8 +5,8 @@
 // tiles have no padding; bank conflicts are avoided by permuting which 16-byte chunk a lane fetches: chunk c of row r
 // lies at position c ^ swizzle(r).
 //
-// LDS fragment reads are written in assembly with explicit waits: the compiler would otherwise wait for every
-// outstanding load to LDS before each of them.
+// LDS fragment reads are written in assembly, the wait for them in the same statement: the compiler would otherwise wait
+// for every outstanding load to LDS before each of them.
 //
 // (As the main loop of the two-limb kernels, with the limb split between LDS and the matrix units, this measured within
 // 15 % of the kernels of contract_kernel.hpp either way: there a wavefront's splitting, LDS reads and products follow one
@@ -64,7 +64,32 @@ struct DmaK {
     }
 };
 
-// LDS read at addr + off (a constant), completion by the reader's own wait
-#define ADAPT_LDS_READ(instr, dst, addr, off) asm volatile(instr " %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(off))
+// LDS reads of every plane's fragments of one sub-step: one (MB = 1) or two 32-row blocks of the activations, TA bytes
+// between planes, RA between the blocks, and one block of the weights, TB bytes between planes.  The results are written at
+// different times, so none of them may share a register with an address (early clobber).
+template <int P, int MB, int TA, int RA, int TB>
+__device__ __forceinline__ void read_planes(v4i (&fa)[MB][P], v4i (&fw)[P], uint32_t xa, uint32_t xw)
+{
+    static_assert((P == 3 && MB == 2) || (P == 4 && MB == 1), "the forms that wide_planes.hip launches");
+    if constexpr (P == 3)
+        asm volatile("ds_read_b128 %0, %9 offset:%11\n\tds_read_b128 %1, %9 offset:%12\n\tds_read_b128 %2, %10 offset:%17\n\t"
+                     "ds_read_b128 %3, %9 offset:%13\n\tds_read_b128 %4, %9 offset:%14\n\tds_read_b128 %5, %10 offset:%18\n\t"
+                     "ds_read_b128 %6, %9 offset:%15\n\tds_read_b128 %7, %9 offset:%16\n\tds_read_b128 %8, %10 offset:%19\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(fa[0][0]), "=&v"(fa[MB - 1][0]), "=&v"(fw[0]), "=&v"(fa[0][1]), "=&v"(fa[MB - 1][1]), "=&v"(fw[1]),
+                       "=&v"(fa[0][2]), "=&v"(fa[MB - 1][2]), "=&v"(fw[2])
+                     : "v"(xa), "v"(xw), "n"(0), "n"(RA), "n"(TA), "n"(TA + RA), "n"(2 * TA), "n"(2 * TA + RA), "n"(0), "n"(TB), "n"(2 * TB)
+                     : "memory");
+    else
+        asm volatile("ds_read_b128 %0, %8 offset:%10\n\tds_read_b128 %1, %9 offset:%14\n\t"
+                     "ds_read_b128 %2, %8 offset:%11\n\tds_read_b128 %3, %9 offset:%15\n\t"
+                     "ds_read_b128 %4, %8 offset:%12\n\tds_read_b128 %5, %9 offset:%16\n\t"
+                     "ds_read_b128 %6, %8 offset:%13\n\tds_read_b128 %7, %9 offset:%17\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(fa[0][0]), "=&v"(fw[0]), "=&v"(fa[0][1]), "=&v"(fw[1]), "=&v"(fa[0][2]), "=&v"(fw[2]), "=&v"(fa[0][P - 1]),
+                       "=&v"(fw[P - 1])
+                     : "v"(xa), "v"(xw), "n"(0), "n"(TA), "n"(2 * TA), "n"(3 * TA), "n"(0), "n"(TB), "n"(2 * TB), "n"(3 * TB)
+                     : "memory");
+}
 
 }  // namespace adapt

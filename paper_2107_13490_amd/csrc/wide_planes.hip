@@ -12,7 +12,7 @@
 //
 // What bounds it: the matrix cores (P^2 products of 2 M N K operations; at P = 3 a sub-step of a 64 x 32 wavefront tile is
 // 18 products for 9 fragment reads), then the epilogue.  128 x 16 x 16 x 64 -> 192, 3x3, <24,21>: 327 us as four two-limb
-// contractions with 128-bit accumulation passes between them, 51 us with this kernel and its two splitting passes.
+// contractions with 128-bit accumulation passes between them, 49.2 us with this kernel and its two splitting passes.
 #include <algorithm>
 
 #include "contract_dma.hpp"
@@ -106,7 +106,8 @@ wide_fwd_kernel(const WidePlanesArgs w)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const ContractArgs &a = w.a;
     constexpr int BKT = 64, KS = BKT / 32, G = 2 * P - 1;
-    constexpr int WM = BM / 2, WN = BN / 2, MB = WM / 32, NB = WN / 32;
+    constexpr int WM = BM / 2, WN = BN / 2, MB = WM / 32;
+    static_assert(WN == 32, "a wavefront takes one 32-column block");
     typedef DmaK<OP_FWD, true, BM, 1, BKT> LA;
     typedef DmaK<OP_FWD, false, BN, 1, BKT> LB;
     constexpr int STAGE = P * (LA::TILE_BYTES + LB::TILE_BYTES);
@@ -154,22 +155,19 @@ wide_fwd_kernel(const WidePlanesArgs w)
     uint32_t ad_a[KS], ad_w[KS];
     LA::addresses(0, wm * WM, l32, g, ad_a);
     LB::addresses(P * LA::TILE_BYTES, wn * WN, nperm, g, ad_w);
-    v16i acc[G][NB][MB];
+    v16i acc[G][MB];
 #pragma unroll
     for (int s = 0; s < G; ++s)
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+        for (int j = 0; j < MB; ++j)
 #pragma unroll
-            for (int j = 0; j < MB; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[s][i][j][r] = 0;
-    int sum_m[MB][P], sum_n[NB][P];
+            for (int r = 0; r < 16; ++r) acc[s][j][r] = 0;
+    int sum_m[MB][P], sum_n[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
 #pragma unroll
         for (int j = 0; j < MB; ++j) sum_m[j][p] = 0;
-#pragma unroll
-        for (int i = 0; i < NB; ++i) sum_n[i][p] = 0;
+        sum_n[p] = 0;
     }
 
     uint32_t cur = lds0, nxt = lds0 + STAGE;
@@ -179,53 +177,25 @@ wide_fwd_kernel(const WidePlanesArgs w)
         if (kt + 1 < ksteps) fetch((kt + 1) * BKT, nxt);
         auto sub_step = [&](auto ksc) {
             constexpr int ks = decltype(ksc)::value;
-            v4i fa[MB][P], fw[NB][P];
-            const uint32_t xa = cur + ad_a[ks], xw = cur + ad_w[ks];
-            auto read = [&](auto pc) {
-                constexpr int p = decltype(pc)::value;
-                ADAPT_LDS_READ("ds_read_b128", fa[0][p], xa, p * LA::TILE_BYTES);
-                if constexpr (MB == 2) ADAPT_LDS_READ("ds_read_b128", fa[1][p], xa, p * LA::TILE_BYTES + 32 * LA::ROW_BYTES);
-                ADAPT_LDS_READ("ds_read_b128", fw[0][p], xw, p * LB::TILE_BYTES);
-                if constexpr (NB == 2) ADAPT_LDS_READ("ds_read_b128", fw[1][p], xw, p * LB::TILE_BYTES + 32 * LB::ROW_BYTES);
-            };
-            read(std::integral_constant<int, 0>{});
-            read(std::integral_constant<int, 1>{});
-            read(std::integral_constant<int, 2>{});
-            if constexpr (P == 4) read(std::integral_constant<int, P - 1>{});
-            // products in the order in which the planes arrive: plane t against all planes up to t
-            auto arrived = [&](auto tc) {
-                constexpr int t = decltype(tc)::value;
-                if constexpr (MB == 2 && NB == 2)
-                    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(fa[0][t]), "+v"(fa[1][t]), "+v"(fw[0][t]), "+v"(fw[1][t]) : "n"((P - 1 - t) * (MB + NB)));
-                else if constexpr (MB == 2)
-                    asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(fa[0][t]), "+v"(fa[1][t]), "+v"(fw[0][t]) : "n"((P - 1 - t) * (MB + NB)));
-                else
-                    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(fa[0][t]), "+v"(fw[0][t]) : "n"((P - 1 - t) * (MB + NB)));
-                auto product = [&](int pa, int pb) {
+            v4i fa[MB][P], fw[P];
+            read_planes<P, MB, LA::TILE_BYTES, 32 * LA::ROW_BYTES, LB::TILE_BYTES>(fa, fw, cur + ad_a[ks], cur + ad_w[ks]);
 #pragma unroll
-                    for (int i = 0; i < NB; ++i)
+            for (int pa = 0; pa < P; ++pa)
 #pragma unroll
-                        for (int j = 0; j < MB; ++j)
-                            acc[pa + pb][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fw[i][pb], fa[j][pa], acc[pa + pb][i][j], 0, 0, 0);
-                };
+                for (int pb = 0; pb < P; ++pb)
 #pragma unroll
-                for (int p = 0; p < t; ++p) product(p, t);
+                    for (int j = 0; j < MB; ++j)
+                        acc[pa + pb][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fw[pb], fa[j][pa], acc[pa + pb][j], 0, 0, 0);
+            if (SUMS) {
 #pragma unroll
-                for (int p = 0; p <= t; ++p) product(t, p);
-                if (SUMS) {
+                for (int p = 0; p < P; ++p)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
 #pragma unroll
-                        for (int j = 0; j < MB; ++j) sum_m[j][t] = __builtin_amdgcn_sdot4(fa[j][t][e], 0x01010101, sum_m[j][t], false);
-#pragma unroll
-                        for (int i = 0; i < NB; ++i) sum_n[i][t] = __builtin_amdgcn_sdot4(fw[i][t][e], 0x01010101, sum_n[i][t], false);
+                        for (int j = 0; j < MB; ++j) sum_m[j][p] = __builtin_amdgcn_sdot4(fa[j][p][e], 0x01010101, sum_m[j][p], false);
+                        sum_n[p] = __builtin_amdgcn_sdot4(fw[p][e], 0x01010101, sum_n[p], false);
                     }
-                }
-            };
-            arrived(std::integral_constant<int, 0>{});
-            arrived(std::integral_constant<int, 1>{});
-            arrived(std::integral_constant<int, 2>{});
-            if constexpr (P == 4) arrived(std::integral_constant<int, P - 1>{});
+            }
         };
         sub_step(std::integral_constant<int, 0>{});
         sub_step(std::integral_constant<int, 1>{});
@@ -237,7 +207,7 @@ wide_fwd_kernel(const WidePlanesArgs w)
     // ---- epilogue: a lane holds 16 consecutive outputs n of one row m per 32 x 32 block
     typedef typename WideSum<P>::type S;
     long long corr_m[MB];
-    long long *sn = reinterpret_cast<long long *>(smem);      // [4 waves][NB][32]
+    long long *sn = reinterpret_cast<long long *>(smem);      // [4 waves][32]
     if (SUMS) {
         __syncthreads();
         auto total = [&](const int (&s)[P]) {
@@ -248,81 +218,76 @@ wide_fwd_kernel(const WidePlanesArgs w)
         };
 #pragma unroll
         for (int j = 0; j < MB; ++j) corr_m[j] = total(sum_m[j]);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const long long t = total(sum_n[i]);
-            if (g == 0) sn[(wave * NB + i) * 32 + nperm] = t;
-        }
+        const long long t = total(sum_n);
+        if (g == 0) sn[wave * 32 + nperm] = t;
         __syncthreads();
     }
     const long long qhi = (1ll << (w.wl_o - 1)) - 1, qlo = a.relu ? 0 : -(1ll << (w.wl_o - 1));
     const S both = SUMS ? (S)w.off_a * (S)w.off_b * (S)((long long)ksteps * BKT) : (S)0;
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int j = 0; j < MB; ++j) {
+        const int m = m0 + wm * WM + j * 32 + l32, nb0 = n0 + wn * WN + 16 * g;
+        if (m >= a.M || nb0 >= a.N) continue;
+        const int cnt = min(16, a.N - nb0);
+        const uint64_t idx0 = (uint64_t)m * (uint64_t)a.N + (uint64_t)nb0;
+        uint32_t rw[8];
+        if (!w.raw) {
+            if (a.rmode != ADAPT_SR) {
 #pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            const int m = m0 + wm * WM + j * 32 + l32, nb0 = n0 + wn * WN + i * 32 + 16 * g;
-            if (m >= a.M || nb0 >= a.N) continue;
-            const int cnt = min(16, a.N - nb0);
-            const uint64_t idx0 = (uint64_t)m * (uint64_t)a.N + (uint64_t)nb0;
-            uint32_t rw[8];
-            if (!w.raw) {
-                if (a.rmode != ADAPT_SR) {
+                for (int e = 0; e < 8; ++e) rw[e] = 0x80008000u;
+            } else if ((a.N & 7) == 0) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) rw[e] = 0x80008000u;
-                } else if ((a.N & 7) == 0) {
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const u32x4 b = rounding_block(a.seed, a.stream, (idx0 >> 3) + h);
-                        rw[4 * h] = b.x; rw[4 * h + 1] = b.y; rw[4 * h + 2] = b.z; rw[4 * h + 3] = b.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        rw[e] = rounding_bits_of(a.seed, a.stream, idx0 + 2 * e, a.rmode) |
-                                rounding_bits_of(a.seed, a.stream, idx0 + 2 * e + 1, a.rmode) << 16;
+                for (int h = 0; h < 2; ++h) {
+                    const u32x4 b = rounding_block(a.seed, a.stream, (idx0 >> 3) + h);
+                    rw[4 * h] = b.x; rw[4 * h + 1] = b.y; rw[4 * h + 2] = b.z; rw[4 * h + 3] = b.w;
                 }
-            }
-            int q[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                S v = (S)acc[G - 1][i][j][r];
-#pragma unroll
-                for (int s = G - 2; s >= 0; --s) v = v * 256 + (S)acc[s][i][j][r];
-                if (SUMS) v += (S)w.off_b * (S)corr_m[j] + (S)w.off_a * (S)sn[(wave * NB + i) * 32 + 16 * g + r] + both;
-                if (w.raw) {
-                    if (r < cnt) {
-                        const __int128 x = (__int128)v;
-                        reinterpret_cast<longlong2 *>(a.out)[idx0 + r] = make_longlong2((long long)x, (long long)(x >> 64));
-                    }
-                } else {
-                    q[r] = requantize_sum<S>(v, a.shift, qlo, qhi, (rw[r >> 1] >> (16 * (r & 1))) & 0xffffu);
-                }
-            }
-            if (w.raw) continue;
-            const bool whole = cnt == 16 && (a.N & 15) == 0;
-            if (w.wl_o > 16) {
-                int32_t *o = static_cast<int32_t *>(a.out) + idx0;
-                if (whole) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) reinterpret_cast<int4 *>(o)[e] = make_int4(q[4 * e], q[4 * e + 1], q[4 * e + 2], q[4 * e + 3]);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        if (e < cnt) o[e] = q[e];
-                }
-            } else if (w.wl_o > 8) {
-                int16_t *o = static_cast<int16_t *>(a.out) + idx0;
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (e < cnt) o[e] = (int16_t)q[e];
             } else {
-                int8_t *o = static_cast<int8_t *>(a.out) + idx0;
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (e < cnt) o[e] = (int8_t)q[e];
+                for (int e = 0; e < 8; ++e)
+                    rw[e] = rounding_bits_of(a.seed, a.stream, idx0 + 2 * e, a.rmode) |
+                            rounding_bits_of(a.seed, a.stream, idx0 + 2 * e + 1, a.rmode) << 16;
             }
         }
+        int q[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            S v = (S)acc[G - 1][j][r];
+#pragma unroll
+            for (int s = G - 2; s >= 0; --s) v = v * 256 + (S)acc[s][j][r];
+            if (SUMS) v += (S)w.off_b * (S)corr_m[j] + (S)w.off_a * (S)sn[wave * 32 + 16 * g + r] + both;
+            if (w.raw) {
+                if (r < cnt) {
+                    const __int128 x = (__int128)v;
+                    reinterpret_cast<longlong2 *>(a.out)[idx0 + r] = make_longlong2((long long)x, (long long)(x >> 64));
+                }
+            } else {
+                q[r] = requantize_sum<S>(v, a.shift, qlo, qhi, (rw[r >> 1] >> (16 * (r & 1))) & 0xffffu);
+            }
+        }
+        if (w.raw) continue;
+        const bool whole = cnt == 16 && (a.N & 15) == 0;
+        if (w.wl_o > 16) {
+            int32_t *o = static_cast<int32_t *>(a.out) + idx0;
+            if (whole) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) reinterpret_cast<int4 *>(o)[e] = make_int4(q[4 * e], q[4 * e + 1], q[4 * e + 2], q[4 * e + 3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (e < cnt) o[e] = q[e];
+            }
+        } else if (w.wl_o > 8) {
+            int16_t *o = static_cast<int16_t *>(a.out) + idx0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (e < cnt) o[e] = (int16_t)q[e];
+        } else {
+            int8_t *o = static_cast<int8_t *>(a.out) + idx0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (e < cnt) o[e] = (int8_t)q[e];
+        }
+    }
 }
 
 template <int P, int BM, int BN>
