@@ -12,7 +12,7 @@
 //
 // What bounds it: the matrix cores (P^2 products of 2 M N K operations; at P = 3 a sub-step of a 64 x 32 wavefront tile is
 // 18 products for 9 fragment reads), then the epilogue.  128 x 16 x 16 x 64 -> 192, 3x3, <24,21>: 327 us as four two-limb
-// contractions with 128-bit accumulation passes between them, 49.2 us with this kernel and its two splitting passes.
+// contractions with 128-bit accumulation passes between them, 47.4 us with this kernel and its splitting pass.
 #include <algorithm>
 
 #include "contract_dma.hpp"
@@ -30,14 +30,26 @@ static inline size_t plane_stride(uint64_t rows, int cp) { return a256w(rows * (
 static inline int planes_for(adapt_fmt a, adapt_fmt b) { return std::max(a.wl, b.wl) <= 24 ? 3 : 4; }
 
 // codes [rows][c] -> P planes [rows][cp] (channels c..cp-1: the code 0), each followed by one chunk of the code 0
+struct PlaneSplit {
+    const void *src;
+    int8_t *dst;
+    uint64_t rows;
+    size_t stride;                  // bytes between planes
+    int c, cp, es, offset;
+};
+
+// blk of nblk: this block's place among the operand's blocks
 template <typename T, int P>
-__global__ void __launch_bounds__(256)
-split_planes_kernel(const T *__restrict__ src, int8_t *__restrict__ dst, const uint64_t rows, const int c, const int cp, const size_t stride,
-                    const int offset)
+__device__ __forceinline__ void split_planes(const PlaneSplit &o, const uint32_t blk, const uint32_t nblk)
 {
+    const T *__restrict__ src = static_cast<const T *>(o.src);
+    int8_t *__restrict__ dst = o.dst;
+    const int c = o.c, cp = o.cp, offset = o.offset;
+    const uint64_t rows = o.rows;
+    const size_t stride = o.stride;
     const int cpr = cp / kPlaneChunk;
     const uint64_t chunks = rows * (uint64_t)cpr;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i <= chunks; i += (uint64_t)gridDim.x * 256) {
+    for (uint64_t i = (uint64_t)blk * 256 + threadIdx.x; i <= chunks; i += (uint64_t)nblk * 256) {
         int v[kPlaneChunk];
         const uint64_t r = i / (uint32_t)cpr;
         const int c0 = (int)(i - r * cpr) * kPlaneChunk;
@@ -70,6 +82,19 @@ split_planes_kernel(const T *__restrict__ src, int8_t *__restrict__ dst, const u
             *reinterpret_cast<uint4 *>(dst + p * stride + i * kPlaneChunk) = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
+}
+
+// Both operands in one launch: the filter's blocks come first and are done while the activations' run (two launches: 49.2
+// instead of 47.4 us for 128 x 16 x 16 x 64 -> 192, 3x3, <24,21>, contraction included).
+template <int P>
+__global__ void __launch_bounds__(256) split_planes_kernel(const PlaneSplit act, const PlaneSplit wgt, const uint32_t wgt_blocks)
+{
+    const bool is_wgt = blockIdx.x < wgt_blocks;
+    const PlaneSplit &o = is_wgt ? wgt : act;
+    const uint32_t blk = is_wgt ? blockIdx.x : blockIdx.x - wgt_blocks, nblk = is_wgt ? wgt_blocks : gridDim.x - wgt_blocks;
+    if (o.es == 4) split_planes<int32_t, P>(o, blk, nblk);
+    else if (o.es == 2) split_planes<int16_t, P>(o, blk, nblk);
+    else split_planes<int8_t, P>(o, blk, nblk);
 }
 
 struct WidePlanesArgs {
@@ -302,14 +327,14 @@ static hipError_t launch_wide_fwd(adapt_ctx *ctx, const WidePlanesArgs &w)
 }
 
 template <int P>
-static void launch_split_planes(adapt_ctx *ctx, const void *src, adapt_fmt f, int8_t *dst, uint64_t rows, int c, size_t stride)
+static void launch_split_planes(adapt_ctx *ctx, const PlaneSplit &act, const PlaneSplit &wgt)
 {
-    const int cp = pad16(c), es = storage_bytes(f), offset = f.wl == 8 * P;
-    const uint64_t chunks = rows * (uint64_t)(cp / kPlaneChunk) + 1;
-    const dim3 g((unsigned)std::min<uint64_t>((chunks + 255) / 256, (uint64_t)ctx->num_cu * 16)), t(256);
-    if (es == 4) hipLaunchKernelGGL((split_planes_kernel<int32_t, P>), g, t, 0, ctx->stream, static_cast<const int32_t *>(src), dst, rows, c, cp, stride, offset);
-    else if (es == 2) hipLaunchKernelGGL((split_planes_kernel<int16_t, P>), g, t, 0, ctx->stream, static_cast<const int16_t *>(src), dst, rows, c, cp, stride, offset);
-    else hipLaunchKernelGGL((split_planes_kernel<int8_t, P>), g, t, 0, ctx->stream, static_cast<const int8_t *>(src), dst, rows, c, cp, stride, offset);
+    auto blocks = [&](const PlaneSplit &o) {
+        const uint64_t chunks = o.rows * (uint64_t)(o.cp / kPlaneChunk) + 1;
+        return (unsigned)std::min<uint64_t>((chunks + 255) / 256, (uint64_t)ctx->num_cu * 16);
+    };
+    const unsigned nw = blocks(wgt);
+    hipLaunchKernelGGL(split_planes_kernel<P>, dim3(nw + blocks(act)), dim3(256), 0, ctx->stream, act, wgt, nw);
 }
 
 // Whether the kernel takes this convolution: filter taps and reduction length within its bounds, planes within 32-bit offsets
@@ -360,13 +385,10 @@ int wide_fwd_planes(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, ada
     w.a.rmode = ep.rng.mode;
     w.a.seed = ep.rng.seed;
     w.a.stream = ep.rng.stream;
-    if (P == 3) {
-        launch_split_planes<3>(ctx, x, fx, xp, xrows, d.c, xs);
-        launch_split_planes<3>(ctx, wt, fw, wp, wrows, d.c, wsd);
-    } else {
-        launch_split_planes<4>(ctx, x, fx, xp, xrows, d.c, xs);
-        launch_split_planes<4>(ctx, wt, fw, wp, wrows, d.c, wsd);
-    }
+    const PlaneSplit act = {x, xp, xrows, xs, d.c, cp, storage_bytes(fx), fx.wl == 8 * P};
+    const PlaneSplit wgt = {wt, wp, wrows, wsd, d.c, cp, storage_bytes(fw), fw.wl == 8 * P};
+    if (P == 3) launch_split_planes<3>(ctx, act, wgt);
+    else launch_split_planes<4>(ctx, act, wgt);
     hipError_t e = hipGetLastError();
     // seven accumulator sets of a 64 x 32 wavefront tile do not leave room for two blocks per CU
     if (e == hipSuccess) e = P == 3 ? launch_wide_fwd<3, 128, 64>(ctx, w) : launch_wide_fwd<4, 64, 64>(ctx, w);
