@@ -53,11 +53,12 @@ __device__ __forceinline__ void unpack16(const gd_v4u (&raw)[2], int es, int (&c
 constexpr int kGdChunk = kGdThreads * 8;      // elements of a block's chunk
 constexpr uint32_t kGdMaxBlocks = 1024;       // four blocks per CU; more elements than that: several chunks per block
 
-// blocks of a tensor: the same number of chunks for every block where it can be had
-static uint32_t gd_blocks(uint64_t n)
+// blocks of a tensor: the same number of chunks for every block where it can be had, at least `each` (1, or 2 where the
+// workspace does not hold one block's sums per chunk)
+static uint32_t gd_blocks(uint64_t n, uint64_t each)
 {
     const uint64_t chunks = std::max<uint64_t>(1, (n + kGdChunk - 1) / kGdChunk);
-    const uint64_t each = (chunks + kGdMaxBlocks - 1) / kGdMaxBlocks;
+    each = std::max(each, (chunks + kGdMaxBlocks - 1) / kGdMaxBlocks);
     return (uint32_t)((chunks + each - 1) / each);
 }
 
@@ -441,21 +442,25 @@ int gradient_diversity_chain(adapt_ctx *ctx, const ChainLayerIn *in, int nlayers
     const size_t per_block = (size_t)kGdThreads * kGdPerThread;
     ChainGeo geo = {};
     geo.nlayers = nlayers;
-    size_t words = 0;
     int most = 1;
-    uint64_t blocks = 0;
     for (int l = 0; l < nlayers; ++l) {
         if (in[l].count < 1 || in[l].count > kGdMaxTensors || n[l] > ((size_t)1 << 30)) return ADAPT_EUNSUPPORTED;
-        bool wide = false;
-        for (int k = 0; k < in[l].count; ++k) wide = wide || in[l].wl[k] > 16;
-        const uint64_t grid = wide ? std::max<size_t>(1, (n[l] + per_block - 1) / per_block) : gd_blocks(n[l]);
+        for (int k = 0; k < in[l].count; ++k) geo.wide[l] = geo.wide[l] || in[l].wl[k] > 16;
         most = std::max(most, in[l].count);
-        geo.first[l] = (uint32_t)blocks;
         geo.n[l] = (uint32_t)n[l];
-        geo.part_off[l] = words;
-        geo.wide[l] = wide;
-        blocks += grid;
-        words += ws_need_gradient_diversity(n[l], in[l].count) / sizeof(uint64_t);
+    }
+    uint64_t blocks = 0;
+    size_t words = 0;
+    for (uint64_t each = 1; each <= 2; ++each) {                 // one chunk per block, or two when the workspace is too small for that
+        blocks = words = 0;
+        for (int l = 0; l < nlayers; ++l) {
+            const uint64_t grid = geo.wide[l] ? std::max<size_t>(1, (n[l] + per_block - 1) / per_block) : gd_blocks(n[l], each);
+            geo.first[l] = (uint32_t)blocks;
+            geo.part_off[l] = words;
+            blocks += grid;
+            words += grid * (size_t)(geo.wide[l] ? 2 * (in[l].count + 1) : in[l].count + 2);
+        }
+        if (words * sizeof(uint64_t) <= scratch_bytes(ctx)) break;
     }
     geo.first[nlayers] = (uint32_t)blocks;
     if (blocks >= ((uint64_t)1 << 31)) return ADAPT_EUNSUPPORTED;
@@ -472,7 +477,7 @@ size_t ws_need_gradient_diversity(uint64_t n, int count)
     const size_t per_block = (size_t)kGdThreads * kGdPerThread;
     // (count + 2) words per block, or (count + 1) pairs of words for windows with int32 codes
     return std::max(std::max<size_t>(1, (n + per_block - 1) / per_block) * (size_t)(count + 1) * 2,
-                    (size_t)gd_blocks(n) * (size_t)(count + 2)) * sizeof(uint64_t);
+                    (size_t)gd_blocks(n, 1) * (size_t)(count + 2)) * sizeof(uint64_t);
 }
 
 }  // namespace adapt
@@ -517,8 +522,9 @@ extern "C" int adapt_gradient_diversity(adapt_ctx *ctx, const adapt_grad_item *i
         return hip_status(ctx, hipGetLastError());
     }
     if (bound >= 2147483648.0) return ADAPT_EUNSUPPORTED;
-    const int blocks = (int)gd_blocks(n);
-    if ((size_t)blocks * (count + 2) * sizeof(uint64_t) > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
+    auto fits = [&](uint32_t b) { return (size_t)b * (count + 2) * sizeof(uint64_t) <= scratch_bytes(ctx); };
+    const int blocks = (int)gd_blocks(n, fits(gd_blocks(n, 1)) ? 1 : 2);
+    if (!fits((uint32_t)blocks)) return ADAPT_EWORKSPACE;
     uint64_t *partial = reinterpret_cast<uint64_t *>(scratch(ctx));
     hipLaunchKernelGGL(gd_partial_kernel<false>, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream, w, nullptr, (uint32_t)n, partial);
     hipLaunchKernelGGL(gd_final_kernel<false>, dim3(1), dim3(kGdFinalThreads), 0, ctx->stream, w, nullptr, partial, blocks, sums, out);

@@ -22,8 +22,8 @@ def _codes(rng, n, wl, scale=0.4):
     return np.clip(np.rint(rng.standard_normal(n) * lim * scale), -lim, lim - 1).astype(np.int8 if wl <= 8 else np.int16)
 
 
-def _check(codes, fmts):
-    out, sums = ctx().gradient_diversity([dev(c) for c in codes], fmts)
+def _check(codes, fmts, cx=None):
+    out, sums = (cx or ctx()).gradient_diversity([dev(c) for c in codes], fmts)
     ref = pu.gradient_diversity_np([c.astype(np.int64) for c in codes], [f[1] for f in fmts])
     got = host(sums).view(np.uint64)
     k = len(codes)
@@ -54,6 +54,26 @@ def test_mixed_formats_and_storage_types():
     fmts = [(8, 5), (12, 9), (4, 1), (16, 13), (6, 3), (9, 6), (8, 7)]
     codes = [_codes(rng, 50001, wl) for wl, _ in fmts]
     _check(codes, fmts)
+
+
+# a context that holds one row of sums per 4096 elements and nothing more: twice the chunks per block (one chunk is 2048
+# elements); less than that is reported
+@pytest.mark.parametrize("n,count,wl", [(300001, 5, 8), (300001, 5, 12), (4096, 1, 8), (1 << 20, 25, 12), (20000, 64, 8)])
+def test_workspace_of_one_row_per_4096_elements(n, count, wl):
+    rng = np.random.default_rng(n + count)
+    codes = [_codes(rng, n, wl) for _ in range(count)]
+    need = -(-n // 4096) * (count + 2) * 8
+    cx = pkg.Context(workspace_bytes=need)
+    try:
+        _check(codes, [(wl, 4)] * count, cx)
+    finally:
+        cx.close()
+    cx = pkg.Context(workspace_bytes=need - 8)
+    try:
+        with pytest.raises(pkg.AdaptError):
+            cx.gradient_diversity([dev(c) for c in codes], [(wl, 4)] * count)
+    finally:
+        cx.close()
 
 
 def test_closed_forms():
