@@ -109,41 +109,44 @@ __device__ __forceinline__ void block_sum2(uint32_t a, uint32_t b, uint64_t &sa,
     __syncthreads();
 }
 
-// Small calls sum their counters in the block that finishes last instead of a second launch: a one-block launch costs
-// them as much as the conversion does (a few thousand elements 8.6 -> 5.2 us; two 256 x 256 matrices and their product
-// 15.8 -> 12.4 us).  Up to kFusedBlocks blocks and kFusedItems tensors, whose columns the four
-// wavefronts take in one round; in larger calls every block's fence would write freshly converted codes back from the
-// L2 (40 us on 8.5 M elements), and they have the second launch's time to spare.
-constexpr uint32_t kFusedBlocks = 256;
-constexpr int kFusedItems = 16;
+// Small calls sum their counters in the block that finishes last instead of a second launch.  In a stream the launch costs
+// more than the sum (us, second launch -> this): 1,000 elements 6.8 -> 4.4, 200,000 6.6 -> 4.5, 350,000 6.6 -> 5.1, two
+// tensors of 50,000 7.9 -> 5.7, four of 50,000 8.9 -> 7.4.  What bounds it is the ticket: every block's fence and its
+// addition to one word cost about 20 ns one behind the other, so the grid stays at kFusedGrid blocks, of up to three chunks
+// of 2048 elements (with a block per chunk 350,000 elements took 6.7).  The lines are where a captured graph, in which a
+// second launch costs 1.5 us, loses more than a tenth: 200,000 elements 4.7 -> 4.7, 350,000 5.0 -> 5.4, 524,288 5.3 -> 6.2;
+// two tensors of 50,000 5.5 -> 5.7, of 100,000 5.7 -> 6.2, of 150,000 5.9 -> 7.8; and more than four tensors gain in neither
+// (eight of 12,500: 11.0 -> 10.9 and 10.4 -> 10.8; sixteen of 6,250: 15.7 -> 17.3 and 14.4 -> 16.4).
+constexpr int kFusedGrid = 64;
+constexpr uint32_t kFusedBlocks = 192;          // chunks of a single call
+constexpr uint32_t kFusedBatchBlocks = 128;     // of a batched call, of at most
+constexpr int kFusedItems = 4;                  // tensors: one round of sum_columns<2>
 
-// sums of partial[cols][nblocks] by the last block of the launch, U columns and four blocks per lane in flight
+// a block's count: read by another block of the same launch (FUSED), or by the next launch
+template <bool FUSED>
+__device__ __forceinline__ void keep_partial(uint32_t *p, uint32_t v)
+{
+    if constexpr (FUSED) store_partial(p, v);
+    else *p = v;
+}
+
+// sums of partial[cols][nblocks] by the last block of the launch: a wavefront takes U columns, a lane a block of each (the
+// counts of so few chunks fit 32 bits)
 template <int U, typename Store>
 __device__ __forceinline__ void sum_columns(const uint32_t *partial, const int nblocks, const int cols, const Store &store)
 {
+    static_assert(kFusedGrid <= kWave, "a lane per block");
     constexpr int W = kQThreads / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     for (int c0 = threadIdx.x / kWave; c0 < cols; c0 += U * W) {
-        uint64_t sum[U];
+        uint32_t t[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) sum[u] = 0;
-        for (int b = lane; b < nblocks; b += 4 * kWave) {
-            uint32_t t[U][4];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)       // columns and blocks past the last repeat it
-                    t[u][r] = load_partial(partial + (size_t)min(c0 + u * W, cols - 1) * nblocks + min(b + r * kWave, nblocks - 1));
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sum[u] += b + r * kWave < nblocks ? t[u][r] : 0u;
-        }
+        for (int u = 0; u < U; ++u)               // columns and blocks past the last repeat it
+            t[u] = load_partial(partial + (size_t)min(c0 + u * W, cols - 1) * nblocks + min(lane, nblocks - 1));
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) sum[u] += __shfl_xor((unsigned long long)sum[u], off, 64);
-            if (lane == 0 && c0 + u * W < cols) store(c0 + u * W, sum[u]);
+            const uint32_t sum = wave_sum_u32(lane < nblocks ? t[u] : 0u);
+            if (lane == 0 && c0 + u * W < cols) store(c0 + u * W, (uint64_t)sum);
         }
     }
 }
@@ -164,8 +167,8 @@ quantize_kernel(const float *__restrict__ x, OutT *__restrict__ q, uint64_t n, i
     uint64_t bn, bs;
     block_sum2(nnz, nsat, bn, bs);
     if (threadIdx.x == 0) {
-        store_partial(partial + blockIdx.x, (uint32_t)bn);
-        store_partial(partial + gridDim.x + blockIdx.x, (uint32_t)bs);
+        keep_partial<FUSED>(partial + blockIdx.x, (uint32_t)bn);
+        keep_partial<FUSED>(partial + gridDim.x + blockIdx.x, (uint32_t)bs);
     }
     if constexpr (FUSED) {
         if (!finished_last(ticket)) return;
@@ -354,7 +357,7 @@ quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_
             if (threadIdx.x < 2 && partial != nullptr) {
                 uint32_t v = 0;
                 for (int w = 0; w < kQThreads / kWave; ++w) v += wave_part[threadIdx.x][w];
-                store_partial(partial + (size_t)(2 * t + threadIdx.x) * gridDim.x + blockIdx.x, v);
+                keep_partial<FUSED>(partial + (size_t)(2 * t + threadIdx.x) * gridDim.x + blockIdx.x, v);
             }
             if (threadIdx.x >= kWave && threadIdx.x < kWave + 2 && want_range) {      // a second wavefront: runs beside the first
                 const int m = threadIdx.x - kWave;
@@ -369,7 +372,7 @@ quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_
     }
     if constexpr (FUSED) {
         if (!finished_last(ticket)) return;
-        sum_columns<8>(partial, (int)gridDim.x, 2 * batch.count, [&](int c, uint64_t v) { out[c] = v; });
+        sum_columns<2>(partial, (int)gridDim.x, 2 * batch.count, [&](int c, uint64_t v) { out[c] = v; });
     }
 }
 
@@ -411,12 +414,13 @@ static int quantize_on(adapt_ctx *ctx, const float *x, size_t n, adapt_fmt fmt, 
     if (n > 0 && (!x || !q || !aligned16(x) || !aligned16(q))) return ADAPT_EINVAL;
     if (n > ((uint64_t)1 << 40)) return ADAPT_EINVAL;
     if ((nnz && ((uintptr_t)nnz & 7)) || (saturated && ((uintptr_t)saturated & 7))) return ADAPT_EINVAL;
-    const int grid = grid_for(ctx, n);
+    int grid = grid_for(ctx, n);
     const bool count = nnz || saturated;
     const size_t part_bytes = ((size_t)grid * 8 + 255) & ~(size_t)255;
     if (part_bytes + 16 > room) return ADAPT_EWORKSPACE;
     uint32_t *partial = count ? reinterpret_cast<uint32_t *>(base) : nullptr;
     const bool fused = count && control && fmt.wl <= 16 && (uint32_t)grid <= kFusedBlocks;
+    if (fused) grid = std::min(grid, kFusedGrid);
     if (fmt.wl > 16)
         hipLaunchKernelGGL(quantize_wide_kernel, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, (int32_t *)q, (uint64_t)n, fmt.wl,
                            fmt.fl, rng.mode, rng.seed, rng.stream, partial);
@@ -508,7 +512,8 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
         if (2 * part_bytes > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
         uint32_t *partial = counters ? reinterpret_cast<uint32_t *>(scratch(ctx)) : nullptr;
         float *range_partial = ranges ? reinterpret_cast<float *>(scratch(ctx) + part_bytes) : nullptr;
-        if (counters && !ranges && grid <= kFusedBlocks && batch.count <= kFusedItems) {
+        if (counters && !ranges && grid <= kFusedBatchBlocks && batch.count <= kFusedItems) {
+            grid = std::min<uint64_t>(grid, kFusedGrid);
             hipLaunchKernelGGL(quantize_batched_kernel<true>, dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
                                seed, partial, nullptr, (uint64_t)0, ticket(ctx, 0), counters + 2 * base);
             continue;

@@ -103,9 +103,9 @@ def test_batched_many_items():
         assert c[2 * t:2 * t + 2].tolist() == [nnz, sat]
 
 
-# around the largest call whose counters are summed by the launch itself (256 blocks of 2048 elements; 16 tensors),
-# each twice, so that a ticket left behind would show
-@pytest.mark.parametrize("n", [2048, 64 * 2048 + 1, 255 * 2048 + 9, 256 * 2048, 256 * 2048 + 1])
+# around the largest call whose counters are summed by the launch itself (192 chunks of 2048 elements on at most 64
+# blocks; 4 tensors of together 128 chunks), each twice, so that a ticket left behind would show
+@pytest.mark.parametrize("n", [2048, 64 * 2048 + 1, 128 * 2048 + 8, 192 * 2048, 192 * 2048 + 1, 255 * 2048 + 9, 256 * 2048, 256 * 2048 + 1])
 @pytest.mark.parametrize("wl", [8, 12])
 def test_counters_of_single_and_two_launch_sizes(n, wl):
     x = np.random.default_rng(n).standard_normal(n).astype(np.float32)
@@ -113,7 +113,8 @@ def test_counters_of_single_and_two_launch_sizes(n, wl):
         _check(x, wl, wl - 2, pkg.SR, seed=3, stream=n)
 
 
-@pytest.mark.parametrize("sizes", [[3000] * 15, [3000] * 16, [3000] * 17, [100 * 2048, 156 * 2048], [100 * 2048, 156 * 2048 + 1], [0, 5]])
+@pytest.mark.parametrize("sizes", [[3000] * 15, [3000] * 16, [3000] * 17, [100 * 2048, 156 * 2048], [100 * 2048, 156 * 2048 + 1], [0, 5],
+                                   [3000] * 4, [3000] * 5, [70 * 2048 + 3, 0, 9, 56 * 2048], [64 * 2048, 64 * 2048], [64 * 2048 + 1, 64 * 2048]])
 def test_batched_counters_of_single_and_two_launch_calls(sizes):
     g = np.random.default_rng(sum(sizes) + len(sizes))
     xs = [g.standard_normal(n).astype(np.float32) for n in sizes]
