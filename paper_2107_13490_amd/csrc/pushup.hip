@@ -49,15 +49,27 @@ __device__ __forceinline__ void unpack16(const gd_v4u (&raw)[2], int es, int (&c
 // memory latencies; the squares of a tensor go to a lane's own LDS counter (one conflict-free addition per tensor and
 // wavefront), so that the reduction over lanes happens once per block and not once per tensor.  Measured on ResNet-18's
 // layers, windows of 25: 36,864 elements 20 -> 9 us, 0.6 M int16 elements 22.8 -> 12.2, 2.4 M int16 elements (118 MB)
-// 31.6 -> 30.4 us (was: 16 elements per thread, eight tensors in flight, a 64-bit wavefront reduction per tensor).
+// 31.6 -> 30.4 us (was: 16 elements per thread, eight tensors in flight, a 64-bit wavefront reduction per tensor; that form
+// is still up to 0.4 us faster for one tensor below 0.6 M elements, and 0.9 us for five at 2.4 M).
 constexpr int kGdChunk = kGdThreads * 8;      // elements of a block's chunk
 constexpr uint32_t kGdMaxBlocks = 1024;       // four blocks per CU; more elements than that: several chunks per block
 
-// blocks of a tensor: the same number of chunks for every block where it can be had, at least `each` (1, or 2 where the
-// workspace does not hold one block's sums per chunk)
-static uint32_t gd_blocks(uint64_t n, uint64_t each)
+
+// Short windows of large tensors have too few loads in flight with one chunk at a time, so a block has four chunks' (and takes
+// at least four): 8.4 M int8 elements, one tensor 13.8 -> 8.9 us, four 17.2 -> 12.0; 50 M 52 -> 22 and 68 -> 39.  Below
+// 1024 chunks that would leave CUs without a block; more than four tensors or six bytes per element fill the queue by
+// themselves, and the registers of four chunks (two wavefronts per SIMD instead of four) cost more than they give (8.4 M,
+// five int8 tensors 19.3 -> 22.9; 16.8 M, three int16 tensors 26.4 -> 25.5, four 29.3 -> 32.3).
+constexpr int kGdShort = 4;
+constexpr int kGdShortChunks = 4;
+static bool gd_short(uint64_t n, int count, int element_bytes) { return count <= kGdShort && element_bytes <= 6 && n > (uint64_t)1023 * kGdChunk; }
+
+// Blocks of a tensor: the same number of chunks for every block where it can be had, at least `each` (1, or 2 where the
+// workspace does not hold one block's sums per chunk).
+static uint32_t gd_blocks(uint64_t n, bool brief, uint64_t each)
 {
     const uint64_t chunks = std::max<uint64_t>(1, (n + kGdChunk - 1) / kGdChunk);
+    if (brief) each = kGdShortChunks;
     each = std::max(each, (chunks + kGdMaxBlocks - 1) / kGdMaxBlocks);
     return (uint32_t)((chunks + each - 1) / each);
 }
@@ -66,25 +78,27 @@ static uint32_t gd_blocks(uint64_t n, uint64_t each)
 // readlane hands it out as a scalar.
 struct GdTable { uint32_t ptr_lo, ptr_hi, es, shift; };
 
-// ES: element bytes of every tensor of the window, or 0 when they differ (16 bytes are loaded for eight codes of either size)
-template <int ES>
+// ES: element bytes of every tensor of the window, or 0 when they differ (16 bytes are loaded for eight codes of either size);
+// U: tensors, and V: chunks whose loads are in flight together
+template <int ES, int U, int V>
 __device__ __forceinline__ void gd_chunks(const GdTable &tab, const int count, const uint32_t n, unsigned long long *slots,
                                           const uint32_t blk, const uint32_t nblk)
 {
-    constexpr int U = 16;                     // tensors whose loads are in flight together
     constexpr int NW = ES == 1 ? 2 : 4;       // 32-bit words per tensor and thread
     typedef unsigned gd_v2u __attribute__((ext_vector_type(2)));
     typedef short gd_v2s __attribute__((ext_vector_type(2)));
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t nchunks = (n + kGdChunk - 1) / kGdChunk;
-    for (uint32_t ch = blk; ch < nchunks; ch += nblk) {
-        const uint32_t e0 = ch * kGdChunk + threadIdx.x * 8;
-        const bool tail = n - ch * kGdChunk < (uint32_t)kGdChunk;
-        int S[8];
+    for (uint32_t ch = blk; ch < nchunks; ch += V * nblk) {
+        // chunk v of the round starts at element c0(v); past the last chunk (below 2^30 + 2^23) every load reads as 0
+        auto c0 = [&](int v) { return (ch + (uint32_t)v * nblk) * kGdChunk; };
+        int S[V][8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) S[j] = 0;
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) S[v][j] = 0;
         for (int k0 = 0; k0 < count; k0 += U) {
-            uint32_t raw[U][NW];
+            uint32_t raw[U][V][NW];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 // The descriptor covers the tensor rounded up to whole 32-bit words (16-byte aligned, so mapped); words past
@@ -94,13 +108,17 @@ __device__ __forceinline__ void gd_chunks(const GdTable &tab, const int count, c
                                      (uint32_t)__builtin_amdgcn_readlane((int)tab.ptr_lo, k0 + u);
                 const uint32_t bytes = k0 + u < count ? (n * es + 3u) & ~3u : 0u;
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(ptr), 0, (int)bytes, 0x00020000);
-                if constexpr (NW == 2) {
-                    const gd_v2u v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, e0 * es, 0, 0);
-                    raw[u][0] = v[0]; raw[u][1] = v[1];
-                } else {
-                    const gd_v4u v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * es, 0, 0);
 #pragma unroll
-                    for (int i = 0; i < NW; ++i) raw[u][i] = v[i];
+                for (int v = 0; v < V; ++v) {
+                    const uint32_t off = (c0(v) + threadIdx.x * 8) * es;
+                    if constexpr (NW == 2) {
+                        const gd_v2u x = __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, 0);
+                        raw[u][v][0] = x[0]; raw[u][v][1] = x[1];
+                    } else {
+                        const gd_v4u x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+#pragma unroll
+                        for (int i = 0; i < NW; ++i) raw[u][v][i] = x[i];
+                    }
                 }
             }
 #pragma unroll
@@ -108,30 +126,39 @@ __device__ __forceinline__ void gd_chunks(const GdTable &tab, const int count, c
                 if (k0 + u < count) {
                     const int es = ES ? ES : __builtin_amdgcn_readlane((int)tab.es, k0 + u);
                     const int sh = __builtin_amdgcn_readlane((int)tab.shift, k0 + u);
-                    if (tail) {                   // clear the codes past n
-                        const int epd = es == 1 ? 4 : 2;      // codes per word
 #pragma unroll
-                        for (int i = 0; i < NW; ++i) {
-                            const int left = (int)n - (int)(e0 + i * epd);
-                            raw[u][i] = left >= epd ? raw[u][i] : left <= 0 ? 0u : raw[u][i] & ((1u << (8 * es * left)) - 1u);
+                    for (int v = 0; v < V; ++v) {
+                        if (n - c0(v) < (uint32_t)kGdChunk) {         // the last chunk: clear the codes past n
+                            const int epd = es == 1 ? 4 : 2;      // codes per word
+#pragma unroll
+                            for (int i = 0; i < NW; ++i) {
+                                const int left = (int)n - (int)(c0(v) + threadIdx.x * 8 + i * epd);
+                                raw[u][v][i] = left >= epd ? raw[u][v][i] : left <= 0 ? 0u : raw[u][v][i] & ((1u << (8 * es * left)) - 1u);
+                            }
                         }
                     }
                     unsigned long long *slot = slots + (k0 + u) * kWave + lane;
                     if (es == 1) {
+                        int d = 0;                // at most 8 * 2^14 per chunk, a counter at most 2^28 (512 chunks per block)
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) S[j] += (int)((unsigned)(int)(int8_t)(raw[u][j >> 2] >> (8 * (j & 3))) << sh);
-                        // at most 8 * 2^14 per chunk, a counter at most 2^28 (512 chunks per block)
-                        const int d = __builtin_amdgcn_sdot4((int)raw[u][1], (int)raw[u][1],
-                                                             __builtin_amdgcn_sdot4((int)raw[u][0], (int)raw[u][0], 0, false), false);
+                        for (int v = 0; v < V; ++v) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) S[v][j] += (int)((unsigned)(int)(int8_t)(raw[u][v][j >> 2] >> (8 * (j & 3))) << sh);
+                            d = __builtin_amdgcn_sdot4((int)raw[u][v][0], (int)raw[u][v][0], d, false);
+                            d = __builtin_amdgcn_sdot4((int)raw[u][v][1], (int)raw[u][v][1], d, false);
+                        }
                         atomicAdd(reinterpret_cast<uint32_t *>(slot), (uint32_t)d);
                     } else {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) S[j] += (int)((unsigned)(int)(int16_t)(raw[u][(j >> 1) % NW] >> (16 * (j & 1))) << sh);
                         unsigned long long t = 0;
 #pragma unroll
-                        for (int i = 0; i < NW; ++i) {
-                            const gd_v2s v = __builtin_bit_cast(gd_v2s, raw[u][i]);
-                            t += (uint32_t)__builtin_amdgcn_sdot2(v, v, 0, false);      // <= 2^31
+                        for (int v = 0; v < V; ++v) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) S[v][j] += (int)((unsigned)(int)(int16_t)(raw[u][v][(j >> 1) % NW] >> (16 * (j & 1))) << sh);
+#pragma unroll
+                            for (int i = 0; i < NW; ++i) {
+                                const gd_v2s x = __builtin_bit_cast(gd_v2s, raw[u][v][i]);
+                                t += (uint32_t)__builtin_amdgcn_sdot2(x, x, 0, false);      // <= 2^31
+                            }
                         }
                         atomicAdd(slot, t);
                     }
@@ -140,11 +167,13 @@ __device__ __forceinline__ void gd_chunks(const GdTable &tab, const int count, c
         }
         unsigned long long lo = 0, hi = 0;    // halves of the squared sums: neither can overflow
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint64_t q = (uint64_t)((long long)S[j] * (long long)S[j]);
-            lo += q & 0xffffffffull;
-            hi += q >> 32;
-        }
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint64_t q = (uint64_t)((long long)S[v][j] * (long long)S[v][j]);
+                lo += q & 0xffffffffull;
+                hi += q >> 32;
+            }
         atomicAdd(slots + count * kWave + lane, lo);
         atomicAdd(slots + (count + 1) * kWave + lane, hi);
     }
@@ -154,9 +183,10 @@ __host__ __device__ inline size_t gd_lds_bytes(int count) { return (size_t)(coun
 
 // partial[col][block]: col k < count: sum of squares of tensor k; col count / count+1: sums of the
 // low / high 32-bit halves of (aligned element sum)^2
-// BYPTR: the window description lies in device memory (written by chain_prep_kernel) instead of the
-// kernel arguments
 // blk of nblk: this block's place among the blocks of the tensor (a chained step runs all layers in one launch)
+// FORM: GD_LONG / GD_SHORT, or by the window and the tensor (a chained step's layers differ)
+enum { GD_LONG, GD_SHORT, GD_EITHER };
+template <int FORM>
 __device__ __forceinline__ void gd_partial_body(const GradWindow &w, uint32_t n, uint64_t *partial, const uint32_t blk, const uint32_t nblk)
 {
     extern __shared__ unsigned long long gd_slots[];
@@ -169,9 +199,17 @@ __device__ __forceinline__ void gd_partial_body(const GradWindow &w, uint32_t n,
     const int es0 = __builtin_amdgcn_readfirstlane((int)tab.es);
     const bool mixed = __ballot(lane < count && (int)tab.es != es0) != 0;
     __syncthreads();
-    if (mixed) gd_chunks<0>(tab, count, n, gd_slots, blk, nblk);
-    else if (es0 == 1) gd_chunks<1>(tab, count, n, gd_slots, blk, nblk);
-    else gd_chunks<2>(tab, count, n, gd_slots, blk, nblk);
+    const bool brief = FORM == GD_SHORT || (FORM == GD_EITHER && count <= kGdShort && n > nblk * (uint32_t)kGdChunk);
+    if (FORM != GD_LONG && brief) {
+        constexpr int V = kGdShortChunks;
+        if (mixed) gd_chunks<0, kGdShort, V>(tab, count, n, gd_slots, blk, nblk);
+        else if (es0 == 1) gd_chunks<1, kGdShort, V>(tab, count, n, gd_slots, blk, nblk);
+        else gd_chunks<2, kGdShort, V>(tab, count, n, gd_slots, blk, nblk);
+    } else if (FORM != GD_SHORT) {
+        if (mixed) gd_chunks<0, 16, 1>(tab, count, n, gd_slots, blk, nblk);
+        else if (es0 == 1) gd_chunks<1, 16, 1>(tab, count, n, gd_slots, blk, nblk);
+        else gd_chunks<2, 16, 1>(tab, count, n, gd_slots, blk, nblk);
+    }
     __syncthreads();
     for (int col = wave; col < count + 2; col += kGdThreads / kWave) {
         const uint64_t v = wave_sum_u64(gd_slots[col * kWave + lane]);
@@ -179,11 +217,11 @@ __device__ __forceinline__ void gd_partial_body(const GradWindow &w, uint32_t n,
     }
 }
 
-template <bool BYPTR>
+template <bool SHORT>
 __global__ void __launch_bounds__(kGdThreads)
-gd_partial_kernel(const GradWindow wv, const GradWindow *__restrict__ wp, uint32_t n, uint64_t *partial)
+gd_partial_kernel(const GradWindow w, uint32_t n, uint64_t *partial)
 {
-    gd_partial_body(BYPTR ? *wp : wv, n, partial, blockIdx.x, gridDim.x);
+    gd_partial_body<SHORT ? GD_SHORT : GD_LONG>(w, n, partial, blockIdx.x, gridDim.x);
 }
 
 // One block: column sums (one wavefront per column at a time), then the norms and the ratio.
@@ -195,15 +233,17 @@ __device__ __forceinline__ void gd_final_body(const GradWindow &w, const uint64_
     for (int col = wave; col < w.count + 2; col += kGdFinalThreads / kWave) {
         const uint64_t *p = partial + (size_t)col * nblocks;
         uint64_t v = 0;
-        int b = lane;
-        for (; b + 7 * kWave < nblocks; b += 8 * kWave) {
+        int b0 = 0;
+        // Eight rows per lane in flight, the last one repeated past the end (one behind the other beyond whole rounds of 512 rows:
+        // 589,824 elements, 25 tensors, 15.3 instead of 13.5 us); up to three rounds of one are as fast.
+        for (; b0 + 3 * kWave < nblocks; b0 += 8 * kWave) {
             uint64_t t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = p[b + u * kWave];
+            for (int u = 0; u < 8; ++u) t[u] = p[min(b0 + u * kWave + lane, nblocks - 1)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v += t[u];
+            for (int u = 0; u < 8; ++u) v += b0 + u * kWave + lane < nblocks ? t[u] : 0ull;
         }
-        for (; b < nblocks; b += kWave) v += p[b];
+        for (; b0 + lane < nblocks; b0 += kWave) v += p[b0 + lane];
         v = wave_sum_u64(v);
         if (lane == 0) {
             col_sum[col] = v;
@@ -374,7 +414,7 @@ gd_partial_chain_kernel(const ChainGeo geo, const GradWindow *__restrict__ win, 
     const uint32_t first_l = entry(geo.first[e]), nblk = entry(geo.first[e + 1]) - first_l, n = entry(geo.n[e]);
     uint64_t *part = partial + ((uint64_t)entry((uint32_t)(geo.part_off[e] >> 32)) << 32 | entry((uint32_t)geo.part_off[e]));
     if (entry(geo.wide[e])) gd_partial_wide_body(win[l], n, part, blockIdx.x - first_l, nblk);
-    else gd_partial_body(win[l], n, part, blockIdx.x - first_l, nblk);
+    else gd_partial_body<GD_EITHER>(win[l], n, part, blockIdx.x - first_l, nblk);
 }
 
 __global__ void __launch_bounds__(kGdFinalThreads)
@@ -443,9 +483,15 @@ int gradient_diversity_chain(adapt_ctx *ctx, const ChainLayerIn *in, int nlayers
     ChainGeo geo = {};
     geo.nlayers = nlayers;
     int most = 1;
+    bool brief[kGdMaxLayers];
     for (int l = 0; l < nlayers; ++l) {
         if (in[l].count < 1 || in[l].count > kGdMaxTensors || n[l] > ((size_t)1 << 30)) return ADAPT_EUNSUPPORTED;
-        for (int k = 0; k < in[l].count; ++k) geo.wide[l] = geo.wide[l] || in[l].wl[k] > 16;
+        int bytes = 0;
+        for (int k = 0; k < in[l].count; ++k) {
+            geo.wide[l] = geo.wide[l] || in[l].wl[k] > 16;
+            bytes += in[l].wl[k] <= 8 ? 1 : 2;
+        }
+        brief[l] = gd_short(n[l], in[l].count, bytes);
         most = std::max(most, in[l].count);
         geo.n[l] = (uint32_t)n[l];
     }
@@ -454,7 +500,7 @@ int gradient_diversity_chain(adapt_ctx *ctx, const ChainLayerIn *in, int nlayers
     for (uint64_t each = 1; each <= 2; ++each) {                 // one chunk per block, or two when the workspace is too small for that
         blocks = words = 0;
         for (int l = 0; l < nlayers; ++l) {
-            const uint64_t grid = geo.wide[l] ? std::max<size_t>(1, (n[l] + per_block - 1) / per_block) : gd_blocks(n[l], each);
+            const uint64_t grid = geo.wide[l] ? std::max<size_t>(1, (n[l] + per_block - 1) / per_block) : gd_blocks(n[l], brief[l], each);
             geo.first[l] = (uint32_t)blocks;
             geo.part_off[l] = words;
             blocks += grid;
@@ -477,7 +523,7 @@ size_t ws_need_gradient_diversity(uint64_t n, int count)
     const size_t per_block = (size_t)kGdThreads * kGdPerThread;
     // (count + 2) words per block, or (count + 1) pairs of words for windows with int32 codes
     return std::max(std::max<size_t>(1, (n + per_block - 1) / per_block) * (size_t)(count + 1) * 2,
-                    (size_t)gd_blocks(n, 1) * (size_t)(count + 2)) * sizeof(uint64_t);
+                    (size_t)gd_blocks(n, false, 1) * (size_t)(count + 2)) * sizeof(uint64_t);
 }
 
 }  // namespace adapt
@@ -522,11 +568,15 @@ extern "C" int adapt_gradient_diversity(adapt_ctx *ctx, const adapt_grad_item *i
         return hip_status(ctx, hipGetLastError());
     }
     if (bound >= 2147483648.0) return ADAPT_EUNSUPPORTED;
+    int bytes = 0;
+    for (int k = 0; k < count; ++k) bytes += w.es[k];
+    const bool brief = gd_short(n, count, bytes);
     auto fits = [&](uint32_t b) { return (size_t)b * (count + 2) * sizeof(uint64_t) <= scratch_bytes(ctx); };
-    const int blocks = (int)gd_blocks(n, fits(gd_blocks(n, 1)) ? 1 : 2);
+    const int blocks = (int)gd_blocks(n, brief, fits(gd_blocks(n, brief, 1)) ? 1 : 2);
     if (!fits((uint32_t)blocks)) return ADAPT_EWORKSPACE;
     uint64_t *partial = reinterpret_cast<uint64_t *>(scratch(ctx));
-    hipLaunchKernelGGL(gd_partial_kernel<false>, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream, w, nullptr, (uint32_t)n, partial);
+    auto kern = brief ? gd_partial_kernel<true> : gd_partial_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream, w, (uint32_t)n, partial);
     hipLaunchKernelGGL(gd_final_kernel<false>, dim3(1), dim3(kGdFinalThreads), 0, ctx->stream, w, nullptr, partial, blocks, sums, out);
     return hip_status(ctx, hipGetLastError());
 }

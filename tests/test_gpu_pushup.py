@@ -49,6 +49,34 @@ def test_sizes_and_window_lengths(n, count):
     assert ds >= 1.0 - 1e-12
 
 
+# around the sizes from which a block takes more than one chunk of 2048 elements (1024 chunks; 1023 for windows of up to four
+# tensors, which then take four at a time), unequal shares of the last blocks, one and two load rounds of tensors (16)
+@pytest.mark.parametrize("n,count", [(n, c) for n in (1023 * 2048, 1023 * 2048 + 1, 2097152, 2097153, 4200003) for c in (1, 2, 4, 5)] +
+                         [(2097153, 17), (4200003, 17)])
+@pytest.mark.parametrize("wls", [(8,), (12,), (8, 16, 5)])
+def test_several_chunks_per_block(n, count, wls):
+    rng = np.random.default_rng(n + 100 * count + len(wls))
+    base = [_codes(rng, n, wl) for wl in wls]
+    wl = [wls[k % len(wls)] for k in range(count)]
+    codes = [np.roll(base[k % len(wls)], 977 * k) for k in range(count)]       # other elements in every tensor, drawn once
+    _check(codes, [(w, 3 + k % 2) for k, w in enumerate(wl)])
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 9, 2047, 2048, 2049, 131071, 131073, 150001])
+@pytest.mark.parametrize("wls", [(16,), (12, 8)])
+def test_odd_tails_of_int16_and_mixed_windows(n, wls):
+    rng = np.random.default_rng(n)
+    for count in (1, 3, 18):
+        _check([_codes(rng, n, wls[k % len(wls)]) for k in range(count)], [(wls[k % len(wls)], 4) for k in range(count)])
+
+
+@pytest.mark.parametrize("count", [3, 6])
+def test_counters_of_the_most_negative_codes_over_several_chunks(count):
+    n = 4300001
+    _check([np.full(n, -128, dtype=np.int8)] * count, [(8, 0)] * count)
+    _check([np.full(n, -32768, dtype=np.int16)] * count, [(16, 0)] * count)
+
+
 def test_mixed_formats_and_storage_types():
     rng = np.random.default_rng(5)
     fmts = [(8, 5), (12, 9), (4, 1), (16, 13), (6, 3), (9, 6), (8, 7)]
