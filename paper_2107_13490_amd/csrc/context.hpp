@@ -53,8 +53,12 @@ typedef std::function<int(const void *, adapt_fmt, const void *, adapt_fmt, void
 int wide_contraction(adapt_ctx *ctx, const void *a, adapt_fmt fa, uint64_t elems_a, const void *b, adapt_fmt fb, uint64_t elems_b,
                      uint64_t outputs, int64_t k_total, void *out, adapt_epilogue ep, const SubContraction &sub);
 size_t ws_need_wide(uint64_t elems_a, bool wide_a, uint64_t elems_b, bool wide_b, uint64_t outputs, bool raw);
+// the same for the composition's faster form, one buffer per pair of parts (plus at least 1 MiB for its part contractions)
+size_t ws_need_wide_all_pairs(adapt_fmt fa, uint64_t elems_a, adapt_fmt fb, uint64_t elems_b, uint64_t outputs);
 // The forward convolution in one kernel on byte planes (wide_planes.hip): ADAPT_EWORKSPACE or ADAPT_EUNSUPPORTED, with
-// nothing launched, where the composition has to take the call; bytes of scratch it takes (0: it never applies)
+// nothing launched, where the composition takes the call; bytes of scratch it takes (0: it never applies); whether the
+// composition is the faster of the two
+bool wide_fwd_composed_faster(int num_cu, const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw);
 int wide_fwd_planes(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, adapt_fmt fx, const void *w, adapt_fmt fw, void *y, adapt_epilogue ep);
 size_t ws_need_wide_fwd(const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw);
 // formats of the parts an operand is split into (lowest first), their weight step in bits; returns their number

@@ -122,6 +122,20 @@ size_t ws_need_wide(uint64_t elems_a, bool wide_a, uint64_t elems_b, bool wide_b
     return (wide_a ? 3 * a256(elems_a * 2) : 0) + (wide_b ? 3 * a256(elems_b * 2) : 0) + a256(outputs * 8) + (raw ? 0 : a256(outputs * 16));
 }
 
+// Bytes of scratch with which a composition keeps one buffer per pair of parts, besides what its part contractions take
+// (at least 1 MiB): the room it asks for before it does so is twice its minimal tail
+static size_t tail_all_pairs(adapt_fmt fa, uint64_t elems_a, adapt_fmt fb, uint64_t elems_b, uint64_t outputs)
+{
+    adapt_fmt pf[3];
+    int step;
+    const int npairs = wide_parts(fa, pf, &step) * wide_parts(fb, pf, &step);
+    return (fa.wl > 16 ? 3 * a256(elems_a * 2) : 0) + (fb.wl > 16 ? 3 * a256(elems_b * 2) : 0) + (size_t)npairs * a256(outputs * 8);
+}
+size_t ws_need_wide_all_pairs(adapt_fmt fa, uint64_t elems_a, adapt_fmt fb, uint64_t elems_b, uint64_t outputs)
+{
+    return tail_all_pairs(fa, elems_a, fb, elems_b, outputs) + ws_need_wide(elems_a, fa.wl > 16, elems_b, fb.wl > 16, outputs, false);
+}
+
 // The parts an operand of format f is split into: their formats (lowest first) and the weight step in bits; returns
 // the number of parts (1: the operand as it is)
 int wide_parts(adapt_fmt f, adapt_fmt fmt[3], int *step)
@@ -151,13 +165,10 @@ int wide_contraction(adapt_ctx *ctx, const void *a, adapt_fmt fa, uint64_t elems
     const bool wide_a = fa.wl > 16, wide_b = fb.wl > 16;
     // buffers of this call at the end of the workspace; the contractions of the parts see the rest
     const size_t keep = (size_t)1 << 20;
-    adapt_fmt pf[3];
-    int step;
-    const int npairs = wide_parts(fa, pf, &step) * wide_parts(fb, pf, &step);
     // one output buffer per pair and a single combining pass, when the workspace has room for that beside what a
     // part contraction of this size may itself need (taken as twice the minimal tail); else one buffer and a pass per pair
     const size_t tail_min = ws_need_wide(elems_a, wide_a, elems_b, wide_b, outputs, ep.raw != 0);
-    const size_t tail_all = (wide_a ? 3 * a256(elems_a * 2) : 0) + (wide_b ? 3 * a256(elems_b * 2) : 0) + (size_t)npairs * a256(outputs * 8);
+    const size_t tail_all = tail_all_pairs(fa, elems_a, fb, elems_b, outputs);
     const bool all_pairs = tail_all + tail_min + keep <= scratch_bytes(ctx);
     const size_t tail = all_pairs ? tail_all : tail_min;
     if (tail + keep > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;

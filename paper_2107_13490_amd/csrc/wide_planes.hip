@@ -14,6 +14,7 @@
 // 18 products for 9 fragment reads), then the epilogue.  128 x 16 x 16 x 64 -> 192, 3x3, <24,21>: 327 us as four two-limb
 // contractions with 128-bit accumulation passes between them, 47.4 us with this kernel and its splitting pass.
 #include <algorithm>
+#include <cmath>
 
 #include "contract_dma.hpp"
 #include "wide.hpp"
@@ -353,8 +354,58 @@ size_t ws_need_wide_fwd(const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw)
     return (size_t)P * (plane_stride((uint64_t)d.n * d.h * d.w, cp) + plane_stride((uint64_t)d.k * d.r * d.s, cp));
 }
 
-// The forward convolution by planes, or ADAPT_EWORKSPACE / ADAPT_EUNSUPPORTED when the composed path has to take it
-// (nothing has been launched then)
+// The planes take P^2 products for every pair of operands, on one block per 128 x 64 (64 x 64) outputs that walks the whole
+// reduction; the composition multiplies a narrow operand as it is and splits a long reduction over blocks, but launches
+// several kernels and takes its exact partial results through memory.  So neither is the faster one everywhere (us,
+// composition / planes): 128 x 16 x 16 x 64 -> 192 3x3 <24,24> bits 217 / 55, <8,24> 93 / 48; 128 x 4096 -> 4096 <24,24>
+// 148 / 103, <8,24> 78 / 103; 128 x 4096 -> 10 <24,24> 53 / 93, <8,24> 26 / 93; 32 x 4 x 4 x 512 -> 512 3x3 <24,24> 113 / 101,
+// <24,8> 54 / 102.  The line is drawn by two sums over what each does, fitted to 667 calls of 1 to 256 images of 1 x 1 to
+// 32 x 32, 3 to 4096 channels, 8 to 32 bits a side on 256 CUs: with it a call takes 0.3 % more than the faster form on
+// average, at most 22 % (always the planes: 19 %, up to 5.4 times; always the composition: 2.1 times), and 300 calls that
+// it was not fitted to 0.4 % (at most 27 %).
+static double planes_us(int num_cu, const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw, double m, double n)
+{
+    const int P = planes_for(fx, fw), cp = pad16(d.c), bm = P == 3 ? 128 : 64;
+    const double stages = (d.r * d.s * cp + 63) / 64, tiles = std::ceil(m / bm) * std::ceil(n / 64);
+    const double rounds = std::max(1.0, tiles / num_cu), xr = (double)d.n * d.h * d.w, wr = (double)d.k * d.r * d.s;
+    const double stage = fx.wl == 8 * P || fw.wl == 8 * P ? 1.17 : 0.93;                 // with / without the sums of offset digits
+    const double bytes = (xr * storage_bytes(fx) + wr * storage_bytes(fw)) * d.c + (xr + wr) * cp * P;      // of the splitting pass
+    return 11.0 + (d.k % 8 ? 4.5 * rounds : 0.0) + stage * stages * rounds + 1.7e-6 * m * n + 0.15e-6 * bytes;
+}
+
+static double composed_us(int num_cu, const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw, double m, double n)
+{
+    adapt_fmt pa[3], pb[3];
+    int step;
+    const int na = wide_parts(fx, pa, &step), nb = wide_parts(fw, pb, &step);
+    const double k = (double)d.r * d.s * pad16(d.c), tiles = std::ceil(m / 64) * std::ceil(n / 64);
+    double launches = 1, chain = 0, bytes = 0;
+    for (int i = 0; i < na; ++i)
+        for (int j = 0; j < nb; ++j) {
+            const int la = pa[i].wl > 8 ? 2 : 1, lb = pb[j].wl > 8 ? 2 : 1, bkt = la * lb == 1 ? 128 : 64;
+            double splits = 1;                                   // as plan_contraction splits
+            if (tiles < num_cu && k >= 8 * bkt) splits = std::max(1.0, std::min(std::ceil(2 * num_cu / tiles), std::floor(k / (4 * bkt))));
+            const double acc = adapt_acc_bits((int64_t)d.r * d.s * d.c, pa[i], pb[j]) == 32 ? 4 : 8;
+            launches += (splits > 1 ? 2 : 1) + (d.c < kPadC ? 2 : 0);
+            chain += k / 64 / splits * std::max(1.0, tiles * splits / (2 * num_cu)) * la * lb;
+            bytes += 2 * m * n * acc * (1 + (splits > 1 ? splits : 0));      // partial results and slabs, written and read
+        }
+    const double gather = d.c > kPadC && d.c % 16 ? 8.0 : 1.0;               // element by element
+    double split = 0;
+    if (fx.wl > 16) { launches += 1; split += (double)d.n * d.h * d.w * d.c * (4 + 2 * na); }
+    if (fw.wl > 16) { launches += 1; split += (double)d.k * d.r * d.s * d.c * (4 + 2 * nb); }
+    return 3.6 * launches + 0.19 * gather * chain + 0.35e-6 * bytes + 0.14e-6 * split;
+}
+
+bool wide_fwd_composed_faster(int num_cu, const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw)
+{
+    const double m = (double)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1), n = d.k;
+    return planes_us(num_cu, d, fx, fw, m, n) >= 1.05 * composed_us(num_cu, d, fx, fw, m, n);
+}
+
+// The forward convolution by planes, or ADAPT_EWORKSPACE / ADAPT_EUNSUPPORTED when the composed path takes it (nothing
+// has been launched then): where the planes do not apply, or where the composition is faster and the workspace holds its
+// faster form
 int wide_fwd_planes(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, adapt_fmt fx, const void *wt, adapt_fmt fw, void *y, adapt_epilogue ep)
 {
     if (!fmt_ok_wide(fx) || !fmt_ok_wide(fw)) return ADAPT_EINVAL;
@@ -365,6 +416,10 @@ int wide_fwd_planes(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, ada
     if (need == 0) return ADAPT_EUNSUPPORTED;
     if (need > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
     const uint64_t xrows = (uint64_t)d.n * d.h * d.w, wrows = (uint64_t)d.k * d.r * d.s;
+    const uint64_t outputs = (uint64_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1) * d.k;
+    if (wide_fwd_composed_faster(ctx->num_cu, d, fx, fw) &&
+        ws_need_wide_all_pairs(fx, xrows * d.c, fw, wrows * d.c, outputs) + ((size_t)1 << 20) <= scratch_bytes(ctx))
+        return ADAPT_EUNSUPPORTED;
     const size_t xs = plane_stride(xrows, cp), wsd = plane_stride(wrows, cp);
     int8_t *xp = reinterpret_cast<int8_t *>(scratch(ctx)), *wp = xp + (size_t)P * xs;
     WidePlanesArgs w = {};

@@ -144,9 +144,11 @@ extern "C" size_t adapt_workspace_bytes(const adapt_ctx *ctx, const adapt_worksp
                 const uint64_t nx = (uint64_t)d.n * d.h * d.w * d.c, nw = (uint64_t)d.k * d.r * d.s * d.c, ny = (uint64_t)d.n * p * qq * d.k;
                 const uint64_t ea = q->call == ADAPT_CALL_CONV_FWD ? nx : ny, eb = q->call == ADAPT_CALL_CONV_WGRAD ? nx : nw;
                 const uint64_t outs = q->call == ADAPT_CALL_CONV_FWD ? ny : q->call == ADAPT_CALL_CONV_DGRAD ? nx : nw;
-                const size_t composed = std::max<size_t>(inner, (size_t)1 << 20) + ws_need_wide(ea, q->fa.wl > 16, eb, q->fb.wl > 16, outs, false);
                 const size_t planes = q->call == ADAPT_CALL_CONV_FWD ? ws_need_wide_fwd(d, q->fa, q->fb) : 0;
-                return std::max(composed, planes) + slack;
+                const size_t composed = planes && wide_fwd_composed_faster(num_cu, d, q->fa, q->fb)
+                                            ? ws_need_wide_all_pairs(q->fa, ea, q->fb, eb, outs)
+                                            : ws_need_wide(ea, q->fa.wl > 16, eb, q->fb.wl > 16, outs, false);
+                return std::max(std::max<size_t>(inner, (size_t)1 << 20) + composed, planes) + slack;
             }
             if (q->call == ADAPT_CALL_CONV_BACKWARD && fmt_ok_wide(q->fa) && fmt_ok_wide(q->fb) && fmt_ok_wide(q->fc) &&
                 (q->fa.wl > 16 || q->fb.wl > 16 || q->fc.wl > 16) && conv_ok(q->conv)) {

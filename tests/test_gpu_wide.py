@@ -194,3 +194,88 @@ def test_wide_forward_on_byte_planes(shp, wx, ww):
     for wl_o, fl_o, relu, mode in ((wx, 3, True, pkg.SR), (32, 31, False, pkg.SR), (16, 0, False, pkg.RN_HALF_UP), (8, 2, True, pkg.SR)):
         out = cx.conv_fwd(d, dev(x), fx, dev(wt), fw, Epilogue.requant(wl_o, fl_o, mode, 9, 21, relu=relu))
         assert np.array_equal(host(out).astype(np.int64), wo.requantize(y, fx[1] + fw[1] - fl_o, wl_o, mode, 9, 21, relu)), (wl_o, fl_o)
+
+
+def _planes_bytes(shp, wx, ww):
+    """Scratch of the plane form: 3 (up to 24 bits) or 4 byte planes of x and w, channels padded to 16, a chunk of 16 after each."""
+    n, h, w, c, k, r, s, _, _ = shp
+    cp, p = -(-c // 16) * 16, 3 if max(wx, ww) <= 24 else 4
+    stride = lambda rows: -(-(rows * cp + 16) // 256) * 256
+    return p * (stride(n * h * w) + stride(k * r * s))
+
+
+def _fwd_in(nbytes, shp, x, fx, wt, fw, ep):
+    cx = pkg.Context(workspace_bytes=nbytes)
+    try:
+        return cx.conv_fwd(ConvDesc(*shp), dev(x), fx, dev(wt), fw, ep)
+    finally:
+        torch.cuda.synchronize()
+        cx.close()
+
+
+# A workspace for the planes alone (the composition takes more than 1 MiB): that the call succeeds shows that the plane kernel
+# ran, also where the composition is the faster form.  The longest reduction (32,704 padded indices) with every digit at
+# -128 comes within 0.3 % of the int32 accumulators' bound.
+@pytest.mark.parametrize("shp,wx,ww,extreme", [((2, 9, 7, 64, 72, 3, 3, 1, 1), 24, 24, False), ((3, 5, 5, 48, 40, 5, 5, 1, 2), 24, 12, False),
+                                               ((130, 1, 1, 200, 70, 1, 1, 1, 0), 17, 16, False), ((16, 1, 1, 4096, 10, 1, 1, 1, 0), 8, 24, False),
+                                               ((16, 1, 1, 4096, 10, 1, 1, 1, 0), 32, 28, False), ((5, 4, 4, 512, 36, 3, 3, 1, 1), 24, 8, False),
+                                               ((3, 1, 1, 32704, 5, 1, 1, 1, 0), 32, 32, True), ((3, 1, 1, 32704, 5, 1, 1, 1, 0), 24, 24, True),
+                                               ((2, 3, 8, 1001, 3, 4, 8, 1, 2), 28, 32, True)])
+def test_wide_forward_in_a_workspace_for_the_planes_alone(shp, wx, ww, extreme):
+    n, h, w, c, k, r, s, stride, pad = shp
+    g = np.random.default_rng(sum(shp) + wx)
+    x, wt = _codes(g, (n, h, w, c), wx), _codes(g, (k, r, s, c), ww)
+    if extreme:
+        x[...], wt[...] = -(1 << (wx - 1)), -(1 << (ww - 1))
+    fx, fw = (wx, wx // 2), (ww, ww // 2)
+    y = wo.conv_fwd(x, wt, stride, pad)
+    need = _planes_bytes(shp, wx, ww)
+    assert np.array_equal(_i128(_fwd_in(need, shp, x, fx, wt, fw, Epilogue.exact())), y)
+    out = _fwd_in(need, shp, x, fx, wt, fw, Epilogue.requant(20, 3, pkg.SR, 9, 21))
+    assert np.array_equal(host(out).astype(np.int64), wo.requantize(y, fx[1] + fw[1] - 3, 20, pkg.SR, 9, 21, False))
+    with pytest.raises(pkg.AdaptError):
+        _fwd_in(need - 256, shp, x, fx, wt, fw, Epilogue.exact())
+
+
+# what the planes do not take: more than 32 taps, more than 32,704 padded indices, a workspace for the composition alone
+@pytest.mark.parametrize("shp,wx,ww,only_composed", [((2, 9, 8, 16, 12, 7, 7, 1, 3), 24, 20, None), ((3, 1, 1, 32705, 5, 1, 1, 1, 0), 32, 24, None),
+                                                     ((2, 6, 5, 8, 7, 3, 11, 2, 5), 32, 8, None), ((8, 100, 100, 1, 1, 3, 3, 1, 1), 28, 28, 9 << 19)])
+def test_wide_forward_by_the_composition_alone(shp, wx, ww, only_composed):
+    n, h, w, c, k, r, s, stride, pad = shp
+    g = np.random.default_rng(sum(shp) + wx)
+    x, wt = _codes(g, (n, h, w, c), wx), _codes(g, (k, r, s, c), ww)
+    fx, fw = (wx, wx - 4), (ww, ww - 2)
+    y = wo.conv_fwd(x, wt, stride, pad)
+    if only_composed is None:
+        with pytest.raises(pkg.AdaptError):                # the planes' bytes do not help: the composition asks for more
+            _fwd_in(_planes_bytes(shp, wx, ww), shp, x, fx, wt, fw, Epilogue.exact())
+    else:
+        assert only_composed < _planes_bytes(shp, wx, ww)
+    nbytes = only_composed or ctx().workspace_bytes(pkg.CALL_CONV_FWD, conv=ConvDesc(*shp), fa=fx, fb=fw)
+    assert np.array_equal(_i128(_fwd_in(nbytes, shp, x, fx, wt, fw, Epilogue.exact())), y)
+    out = _fwd_in(nbytes, shp, x, fx, wt, fw, Epilogue.requant(wx, 3, pkg.SR, 9, 21, relu=True))
+    assert np.array_equal(host(out).astype(np.int64), wo.requantize(y, fx[1] + fw[1] - 3, wx, pkg.SR, 9, 21, True))
+
+
+# both sides of the dispatch: the query counts the composition's buffers (a partial result per pair of parts) exactly where it
+# is the faster form; every form gives the same bits
+@pytest.mark.parametrize("shp,wx,ww,composed", [((128, 1, 1, 4096, 10, 1, 1, 1, 0), 24, 24, True), ((128, 1, 1, 4096, 10, 1, 1, 1, 0), 8, 24, True),
+                                                ((8, 4, 4, 512, 16, 3, 3, 1, 1), 24, 8, True), ((256, 1, 1, 512, 100, 1, 1, 1, 0), 24, 24, False),
+                                                ((2, 9, 9, 32, 40, 3, 3, 1, 1), 24, 24, False), ((2, 8, 8, 16, 16, 3, 3, 1, 1), 8, 32, False)])
+def test_wide_forward_takes_the_faster_form(shp, wx, ww, composed):
+    n, h, w, c, k, r, s, stride, pad = shp
+    d = ConvDesc(*shp)
+    g = np.random.default_rng(sum(shp) + wx)
+    x, wt = _codes(g, (n, h, w, c), wx), _codes(g, (k, r, s, c), ww)
+    fx, fw = (wx, wx // 2), (ww, ww // 2)
+    outs, parts = n * d.p * d.q * k, lambda f: 1 if f <= 16 else 2 if f < 32 else 3
+    up = lambda b: -(-b // 256) * 256
+    split = sum(3 * up(2 * t.size) for t, f in ((x, wx), (wt, ww)) if f > 16)
+    all_pairs = 2 * split + up(8 * outs) + up(16 * outs) + parts(wx) * parts(ww) * up(8 * outs) + (1 << 20)
+    need = ctx().workspace_bytes(pkg.CALL_CONV_FWD, conv=d, fa=fx, fb=fw)
+    assert (need >= all_pairs) == composed
+    y = wo.conv_fwd(x, wt, stride, pad)
+    want = wo.requantize(y, fx[1] + fw[1] - 3, 20, pkg.SR, 9, 21, False)
+    for nbytes in (need, 4 * all_pairs, _planes_bytes(shp, wx, ww)):
+        out = _fwd_in(nbytes, shp, x, fx, wt, fw, Epilogue.requant(20, 3, pkg.SR, 9, 21))
+        assert np.array_equal(host(out).astype(np.int64), want), nbytes
