@@ -74,12 +74,15 @@ __host__ __device__ inline BnState bn_state(void *p, int k)
 // ---- per-channel sums -----------------------------------------------------------------------------------
 // MODE 0: (sum y, sum y^2); MODE 1: (sum dz, sum dz*y).  One group = 8 consecutive elements = 8 consecutive
 // channels of one row (channels % 8 == 0).  REG: the thread stride in groups is a multiple of channels/8, so a
-// thread meets the same eight channels every time and sums them in registers, four groups' loads in flight.
+// thread meets the same eight channels every time and sums them in registers, four groups' loads in flight (three in the
+// backward mode with an int16 operand: four of two operands cost 124 registers and, 256 x 32 x 32 x 64, 14.2 us for two
+// int16 operands and 11.7 for an int8 gradient, three 12.8 and 9.8, one 13.6 and 10.5).
 // What bounds it: the latency of the loads, then the block's flush.  The LDS sums lie as [copy][2][8][channels / 8], so
 // that the 64 lanes of an addition hit consecutive words, and thin layers keep bn_copies() of them, so that no two lanes
 // of a wavefront meet in one (in the order of the channels and with one copy, 64 channels cost eight additions in a row
-// at one address, sixteen lanes to a bank).  ResNet-18 at batch 256, mean over its layers: int16 7.6 -> 6.2 us, int8
-// 6.1 -> 5.1 us.
+// at one address, sixteen lanes to a bank).  ResNet-18 at batch 256, mean over its layers, forward mode: int16 7.6 -> 6.2
+// us, int8 6.1 -> 5.1; backward mode, 256 x 32 x 32 x 64 and 256 x 16 x 16 x 128: int16 13.4 -> 12.8 and 7.8 -> 7.5, int8 10.2 -> 9.1
+// and 7.0 -> 6.1.
 __host__ __device__ inline uint32_t bn_copies(uint32_t cg) { return cg < (uint32_t)kWave && kWave % cg == 0 ? kWave / cg : 1u; }
 
 template <typename TA, typename TB, int MODE, bool REG>
@@ -104,7 +107,7 @@ bn_sums_kernel(const TA *__restrict__ a, const TB *__restrict__ b, uint64_t grou
                 s2[e] += (long long)(MODE == 1 ? x[e] * y[e] : x[e] * x[e]);
             }
         };
-        constexpr int U = 4;
+        constexpr int U = MODE == 1 && sizeof(TA) + sizeof(TB) > 2 ? 3 : 4;
         uint64_t g = first;
         for (; g + (U - 1) * stride < groups; g += U * stride) {
             int x[U][8], y[U][8];
