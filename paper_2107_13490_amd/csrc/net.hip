@@ -30,7 +30,7 @@
 namespace adapt {
 
 constexpr int kEwThreads = 256;
-constexpr int kFitSumThreads = 1024;     // of the fitting pass that also sums the squares of its codes
+constexpr int kFitSumThreads = 1024;     // of the fitting pass that also sums the squares of the codes of a large tensor
 
 template <typename T, int V>
 struct alignas(sizeof(T) * V) CodeVec {
@@ -387,8 +387,11 @@ static int requantize_fit_exp(adapt_ctx *ctx, const void *acc, int acc_bits, siz
     const uint64_t groups = ((uint64_t)n + 7) >> 3;
     const int grid1 = (int)std::min<uint64_t>(std::max<uint64_t>((groups + kEwThreads - 1) / kEwThreads, 1), (uint64_t)ctx->num_cu * 4);
     // Atomic additions to one address retire at about one per 10 ns on this chip, whoever issues them: with the sum of
-    // squares asked for, one block of 1024 threads per CU at most keeps that tail short.
-    const int threads = sumsq ? kFitSumThreads : kEwThreads;
+    // squares asked for, one block per CU at most keeps that tail short, of 1024 threads where 256 are too few.  Smaller tensors
+    // stay with 256: a large block starts and reduces later (36,864 elements 6.1 us, with 1024 threads 7.5; 147,456 6.7 and 7.8; 300,000
+    // 7.8 either way; 524,288 9.3 and 8.3).
+    const bool large = sumsq && groups > (uint64_t)ctx->num_cu * 160;
+    const int threads = large ? kFitSumThreads : kEwThreads;
     const int grid2 = sumsq ? (int)std::min<uint64_t>(std::max<uint64_t>((groups + threads - 1) / threads, 1), (uint64_t)ctx->num_cu)
                             : ew_grid(ctx, groups);
     if ((size_t)grid1 * 8 > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
@@ -409,7 +412,7 @@ static int requantize_fit_exp(adapt_ctx *ctx, const void *acc, int acc_bits, siz
     const bool o8 = wl <= 8;
 #define ADAPT_FIT(ACC, OUT)                                                                                                        \
     do {                                                                                                                           \
-        if (sumsq) hipLaunchKernelGGL((requant_fit_kernel<ACC, OUT, kFitSumThreads>), dim3(grid2), dim3(threads), 0, ctx->stream, a); \
+        if (large) hipLaunchKernelGGL((requant_fit_kernel<ACC, OUT, kFitSumThreads>), dim3(grid2), dim3(threads), 0, ctx->stream, a); \
         else hipLaunchKernelGGL((requant_fit_kernel<ACC, OUT, kEwThreads>), dim3(grid2), block, 0, ctx->stream, a);                \
     } while (0)
     if (acc_bits == 32 && o8) ADAPT_FIT(int32_t, int8_t);

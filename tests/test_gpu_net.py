@@ -83,8 +83,9 @@ def test_requantize_fit(n, bits, wl, mag):
 
 
 # more than one group of eight per thread in the launch that sums the squares (256 blocks of 1024) and in the one that
-# does not (2048 blocks of 256), with a remainder; the largest magnitude in the last element
-@pytest.mark.parametrize("n,sums", [(2100003, True), (4200003, False), (1023 * 8 + 1, False)])
+# does not (2048 blocks of 256), with a remainder; around the size from which the first has 1024 threads (256 x 160 groups);
+# the largest magnitude in the last element
+@pytest.mark.parametrize("n,sums", [(2100003, True), (4200003, False), (1023 * 8 + 1, False), (327680, True), (327681, True), (327691, True)])
 def test_requantize_fit_several_groups_per_thread(n, sums):
     rng = np.random.default_rng(n)
     acc = rng.integers(-(1 << 25), 1 << 25, n)
