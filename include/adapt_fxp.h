@@ -20,8 +20,8 @@
  *   - Return value: ADAPT_OK (0) or a negative adapt_status.  Nothing is printed, no
  *     exceptions cross the boundary.  On error no kernel of that call has been launched.
  *   - Storage of a tensor in format <wl,fl>: int8_t for wl <= 8 (sign-extended codes),
- *     int16_t for 9 <= wl <= 16, int32_t for 17 <= wl <= 32 (adapt_quantize and the four
- *     contractions take those; every other entry point stops at 16).  The represented value
+ *     int16_t for 9 <= wl <= 16, int32_t for 17 <= wl <= 32 (only the entry points that say so
+ *     take those).  The represented value
  *     of code q is q * 2^-fl.
  *   - Layouts: activations NHWC, filters KRSC (Cout, R, S, Cin), row-major, dense.
  */
@@ -201,17 +201,29 @@ int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantize_item *ite
  * results, output shapes and rounding bits are those of the unpadded operands.  When one operand
  * has wl <= 8 and the other 9..16, the int8 operand is multiplied as a single limb. */
 
-/* Word lengths 17..32 (adapt_fxp_gemm, adapt_conv_fwd, adapt_conv_dgrad, adapt_conv_wgrad; operands
- * and / or the requantized output): an operand above 16 bits is int32_t codes; the call splits it
- * into parts the narrow kernels take (17..23 bits: the signed low byte and the rest, a = a1 2^8 +
- * a0; 24..31 bits: the signed low half-word and the rest, a = a1 2^16 + a0; 32 bits: three 11-bit
- * parts a = a2 2^22 + a1 2^11 + a0 with a0, a1 in [0, 2047], a2 = a >> 22), runs the exact
- * contraction of every pair of parts (four for two operands of up to 31 bits, nine for two of 32,
- * two or three with one narrow operand) on the int8 matrix cores, adds the partial results at their
- * power-of-two weights in 128-bit integers and applies the epilogue's rule once; the result is the
- * exact contraction of the full codes, requantized as for any other.  The parts, one partial result (8 bytes per output) and the 128-bit sums (16 bytes
- * per output) live in the workspace (adapt_workspace_bytes counts them).  adapt_fxp_gemm needs
- * ldc == N and K > 0 on this path; adapt_conv_backward and the chain stop at 16 bits. */
+/* Word lengths 17..32 (adapt_fxp_gemm, adapt_conv_fwd, adapt_conv_dgrad, adapt_conv_wgrad,
+ * adapt_conv_backward; operands and / or the requantized output): an operand above 16 bits is
+ * int32_t codes; the result is the exact contraction of the full codes, requantized as for any
+ * other.  Two forms compute it, with the same bits:
+ *   composition  every call: an operand above 16 bits is split into parts the narrow kernels take
+ *                (17..23 bits: the signed low byte and the rest, a = a1 2^8 + a0; 24..31 bits: the
+ *                signed low half-word and the rest, a = a1 2^16 + a0; 32 bits: three 11-bit parts
+ *                a = a2 2^22 + a1 2^11 + a0 with a0, a1 in [0, 2047], a2 = a >> 22), the exact
+ *                contraction of every pair of parts runs on the int8 matrix cores (four for two
+ *                operands of up to 31 bits, nine for two of 32, two or three with one narrow operand),
+ *                and the partial results are added at their power-of-two weights in 128-bit integers.
+ *                The parts, one partial result (8 bytes per output) and the 128-bit sums (16 bytes per
+ *                output) live in the workspace; with room for one partial result per pair of parts
+ *                they are combined in one pass.
+ *   byte planes  adapt_conv_fwd with at most 32 filter taps, at most 32,704 indices of the reduction
+ *                (channels rounded up to 16) and an operand above 16 bits: both operands are rewritten
+ *                as 3 (up to 24 bits) or 4 planes of signed bytes in the workspace, and one kernel
+ *                multiplies them and applies the epilogue.  Taken when the workspace holds the planes,
+ *                unless the composition is the faster form (few output tiles with a long reduction, a
+ *                narrow operand beside a wide one) and the workspace holds its one-pass buffers.
+ * adapt_workspace_bytes counts the composition with one partial result, and for adapt_conv_fwd the
+ * planes and, where it is the faster form, the composition's one-pass buffers.  adapt_fxp_gemm needs
+ * ldc == N and K > 0 on this path. */
 
 /* 32 if K * 2^(wl_a-1) * 2^(wl_b-1) <= 2^31 - 1 (every possible sum fits int32), else 64; 128 when
  * an operand has more than 16 bits. */

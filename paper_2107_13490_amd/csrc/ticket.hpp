@@ -6,13 +6,15 @@
 namespace adapt {
 
 // True in every thread of the block that finishes last.  The word is zero before the launch and zero again after it; the
-// partial results are stored and read at device scope (store_partial, load_partial).
+// partial results are stored and read at device scope (store_partial, load_partial), and stored by threads of the block's
+// first wavefront only: the release below is that wavefront's, and the barrier before it does not wait for global stores of
+// the others to arrive.
 __device__ __forceinline__ bool finished_last(uint32_t *ticket)
 {
     __shared__ bool last;
-    __syncthreads();                               // the block's partial results are issued before its ticket
+    __syncthreads();
     if (threadIdx.x == 0) {
-        // release this block's partial results, acquire everyone else's
+        // release this wavefront's partial results, acquire everyone else's
         last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
         if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next launch
     }

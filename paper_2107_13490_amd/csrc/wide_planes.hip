@@ -10,9 +10,11 @@
 //     multiplied index, sum a b = sum A B + O_b sum A + O_a sum B + O_a O_b K.  Padding must then be the code 0 and not the
 //     byte 0: every plane ends in 16 bytes of its digit of 0, and invalid chunks are fetched from there.
 //
-// What bounds it: the matrix cores (P^2 products of 2 M N K operations; at P = 3 a sub-step of a 64 x 32 wavefront tile is
-// 18 products for 9 fragment reads), then the epilogue.  128 x 16 x 16 x 64 -> 192, 3x3, <24,21>: 327 us as four two-limb
-// contractions with 128-bit accumulation passes between them, 47.4 us with this kernel and its splitting pass.
+// What bounds it: P^2 products of 2 M N K operations at about a third of what the matrix cores reach alone (at P = 3 a sub-step
+// of a 64 x 32 wavefront tile is 18 products behind 9 fragment reads), then the 64- or 128-bit epilogue and the splitting pass.
+// 128 x 16 x 16 x 64 -> 192, 3x3, <24,21>: 327 us as four two-limb contractions with 128-bit accumulation passes between them,
+// 47.4 us with this kernel and its splitting pass.  Grids of few tiles with a long reduction, and narrow operands beside wide
+// ones, stay with the composition (wide_fwd_composed_faster below).
 #include <algorithm>
 #include <cmath>
 
@@ -134,8 +136,8 @@ wide_fwd_kernel(const WidePlanesArgs w)
     constexpr int BKT = 64, KS = BKT / 32, G = 2 * P - 1;
     constexpr int WM = BM / 2, WN = BN / 2, MB = WM / 32;
     static_assert(WN == 32, "a wavefront takes one 32-column block");
-    typedef DmaK<OP_FWD, true, BM, 1, BKT> LA;
-    typedef DmaK<OP_FWD, false, BN, 1, BKT> LB;
+    typedef DmaK<true, BM> LA;
+    typedef DmaK<false, BN> LB;
     constexpr int STAGE = P * (LA::TILE_BYTES + LB::TILE_BYTES);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, g = lane >> 5;
