@@ -358,11 +358,12 @@ struct BnApplyArgs {
 };
 
 // REG here and in bn_bwd_kernel: the thread stride is a multiple of channels/8 (every layer whose channels/8 is a power of
-// two up to 256), so a thread's eight channels, and their coefficients, stay in its registers; otherwise the coefficients
-// lie in LDS and the channel index moves on by a constant (a 64-bit modulo per group and 128 bytes of LDS reads per thread
-// before).  What bounds them is the VALU (Philox and 64-bit requantization).  ResNet-18 at batch 256, mean over its layers:
-// int16 apply 14.0 -> 13.1 us, maximum pass 13.3 -> 11.8, fitting pass 16.0 -> 15.0; int8 maximum pass 9.8 -> 7.6,
-// fitting pass 11.9 -> 9.5.
+// two up to 256), so a thread's eight channels, and their coefficients, stay in its registers; otherwise, and in the backward
+// passes of thin layers (adapt_bn_backward), the coefficients lie in LDS and the channel index moves on by a constant (a
+// 64-bit modulo per group before).  LDS values are read where they are used: held in arrays first they took 20 registers more
+// and two wavefronts per SIMD (32 x 13 x 13 x 520: apply 9.1 instead of 7.7 us).  What bounds the kernels is the VALU (Philox and
+// 64-bit requantization), the maximum pass the loads.  Registers against the modulo form, us, int16: 256 x 16 x 16 x 128 apply
+// 12.4 -> 11.2, maximum pass 14.8 -> 10.6, fitting pass 18.1 -> 13.7; 256 x 4 x 4 x 512 6.1 -> 4.9, 7.0 -> 5.6, 8.6 -> 6.5.
 template <typename TY, typename TR, typename TO, bool REG>
 __global__ void __launch_bounds__(kBnThreads) bn_apply_kernel(const BnApplyArgs a)
 {
@@ -399,19 +400,17 @@ __global__ void __launch_bounds__(kBnThreads) bn_apply_kernel(const BnApplyArgs 
 #pragma unroll
             for (int e = 0; e < 8; ++e) r[e] = 0x8000u;
         }
-        if (!REG) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { A[e] = la[c0 + e]; B[e] = coef[c0 + e]; }
-            c0 += step;
-            if (c0 >= (uint32_t)a.channels) c0 -= (uint32_t)a.channels;
-        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            long long acc = (long long)A[e] * x[e] + B[e];
+            long long acc = (long long)(REG ? A[e] : la[c0 + e]) * x[e] + (REG ? B[e] : coef[c0 + e]);
             if (a.has_res) acc += rsh >= 0 ? (long long)((unsigned long long)(long long)s[e] << rsh) : ((long long)s[e] >> -rsh);
             code[e] = requantize_one(acc, fa, a.wl, a.relu, r[e]);
         }
         store_codes8<TO>(out, g, code);
+        if (!REG) {
+            c0 += step;
+            if (c0 >= (uint32_t)a.channels) c0 -= (uint32_t)a.channels;
+        }
     }
 }
 
@@ -469,15 +468,14 @@ __global__ void __launch_bounds__(kBnThreads) bn_bwd_kernel(const BnBwdArgs a)
         int d[8], x[8];
         load_codes8<TD>(dz, g, d);
         load_codes8<TY>(y, g, x);
-        if (!REG) {
+        long long acc[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { P[e] = lp[c0 + e]; Q[e] = lq[c0 + e]; R[e] = coef[c0 + e]; }
+        for (int e = 0; e < 8; ++e)
+            acc[e] = (long long)(REG ? P[e] : lp[c0 + e]) * d[e] + (long long)(REG ? Q[e] : lq[c0 + e]) * x[e] + (REG ? R[e] : coef[c0 + e]);
+        if (!REG) {
             c0 += step;
             if (c0 >= (uint32_t)a.channels) c0 -= (uint32_t)a.channels;
         }
-        long long acc[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = (long long)P[e] * d[e] + (long long)Q[e] * x[e] + R[e];
         if (!FIT) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -1052,18 +1050,21 @@ extern "C" int adapt_bn_backward(adapt_ctx *ctx, const void *dz, int wl_dz, cons
     a.part = reinterpret_cast<uint64_t *>(scratch(ctx) + (size_t)ctx->num_cu * 2 * 2 * (size_t)channels * 8 + (size_t)2 * channels * 8);
     a.nparts = grid1;
     const dim3 t(kBnThreads), g2(bn_grid(ctx, groups));
-    const bool reg = same_channels(grid1, channels) && same_channels((int)g2.x, channels);
-    const size_t lds = reg ? 0 : (size_t)channels * 16;
+    // Coefficients in registers from 128 channels on.  Thinner layers read few LDS words, each for several lanes at once, and
+    // their maximum pass, which does little else, is faster that way (us, registers / LDS: 256 x 32 x 32 x 64 int16 17.7 / 15.9,
+    // 1024 x 32 x 32 x 16 17.4 / 12.2; 256 x 8 x 8 x 256 6.9 / 10.3); so is the fitting pass (20.9 / 19.8, 20.0 / 18.7; 10.0 / 13.6)
+    // but for 64 channels of int8 codes and more than one group per thread (17.8 / 19.5).
+    const bool reg_max = same_channels(grid1, channels) && channels >= 128;
+    const bool reg_fit = same_channels((int)g2.x, channels) &&
+                         (channels >= 128 || (channels >= 64 && es_d + es_y == 2 && groups > (uint64_t)g2.x * kBnThreads));
+    const size_t lds_max = reg_max ? 0 : (size_t)channels * 16, lds_fit = reg_fit ? 0 : (size_t)channels * 16;
     const int sel = (es_d == 2) * 4 + (es_y == 2) * 2 + (es_o == 2);
-#define ADAPT_BWD(TD, TY, TO)                                                                                     \
-    do {                                                                                                          \
-        if (reg) {                                                                                                \
-            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false, true>), dim3(grid1), t, lds, ctx->stream, a);    \
-            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true, true>), g2, t, lds, ctx->stream, a);              \
-        } else {                                                                                                  \
-            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false, false>), dim3(grid1), t, lds, ctx->stream, a);   \
-            hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true, false>), g2, t, lds, ctx->stream, a);             \
-        }                                                                                                         \
+#define ADAPT_BWD(TD, TY, TO)                                                                                          \
+    do {                                                                                                               \
+        if (reg_max) hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false, true>), dim3(grid1), t, lds_max, ctx->stream, a); \
+        else hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, false, false>), dim3(grid1), t, lds_max, ctx->stream, a);   \
+        if (reg_fit) hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true, true>), g2, t, lds_fit, ctx->stream, a);      \
+        else hipLaunchKernelGGL((bn_bwd_kernel<TD, TY, TO, true, false>), g2, t, lds_fit, ctx->stream, a);             \
     } while (0)
     switch (sel) {
     case 0: ADAPT_BWD(int8_t, int8_t, int8_t); break;

@@ -85,13 +85,15 @@ def test_batch_norm_forward_and_backward(shape, fy, fo, fres, relu):
 # channel counts around what the statistics kernel copies its LDS sums by and what keeps coefficients in registers
 # (channels / 8 of 1, 2, 32, 64; 6 and 65 divide nothing), and tensors of which every thread meets more than one group
 # (more than 2048 * 256 of them), with (128) and without (24) coefficients in registers; the statistics' load rounds of three
-# and four groups per thread with their remainders (512 * 256 threads at most) for every pair of storage widths
+# and four groups per thread with their remainders (512 * 256 threads at most) for every pair of storage widths; 64 channels
+# with more than one group per thread, whose passes take their coefficients from different places in int8 and int16
 @pytest.mark.parametrize("shape,fy,fo,fres", [((3, 7, 9, 8), (8, 5), (12, 8), None), ((9, 16, 16, 16), (16, 12), (8, 4), (8, 4)),
                                               ((2, 9, 9, 48), (10, 7), (8, 5), None), ((2, 7, 7, 256), (8, 6), (16, 10), (12, 8)),
                                               ((1, 5, 5, 512), (12, 8), (12, 8), None), ((1, 3, 11, 520), (8, 5), (8, 5), (16, 12)),
                                               ((175, 32, 32, 24), (12, 9), (8, 5), None), ((129, 16, 16, 128), (8, 5), (12, 9), (8, 4)),
                                               ((129, 16, 16, 128), (12, 9), (8, 5), None), ((200, 16, 16, 128), (12, 9), (12, 8), None),
-                                              ((90, 16, 16, 128), (8, 5), (8, 5), None)])
+                                              ((90, 16, 16, 128), (8, 5), (8, 5), None), ((65, 32, 32, 64), (8, 5), (8, 5), None),
+                                              ((65, 32, 32, 64), (12, 9), (8, 5), None)])
 def test_batch_norm_channel_counts_and_several_groups_per_thread(shape, fy, fo, fres):
     test_batch_norm_forward_and_backward(shape, fy, fo, fres, True)
 
