@@ -412,6 +412,17 @@ def test_gradient_scales_too_far_apart_drop_the_oldest_window_entries():
     assert any(u == 1 for u in per_step[2]) and any(u > 1 for row in per_step for u in row), per_step
 
 
+@pytest.mark.parametrize("fmts", [[(8, 5), (12, 8)], [(10, 6), (8, 4)]])
+def test_precision_switching_of_a_layer_whose_short_window_takes_several_chunks(fmts):
+    # 2,113,536 weights: more than 1024 chunks of 2048, windows of one to three gradients (four chunks at a time) beside a
+    # layer with one chunk per block
+    layers = [no.Layer(1, 1, 2064, 1024, 1, 1, 1, 0, relu=True, pool=False), no.Layer(1, 1, 1024, 16, 1, 1, 1, 0, relu=False, pool=False)]
+    kw = dict(lb_lwr=1, lb_upr=3, lb_init=3, r_lwr=50, r_upr=60, r_init=55, gamma=0.5, eps=1e-2, buff=2, wl_lo=6, wl_hi=10)
+    used = []
+    _train_with_switch(layers, fmts, n=4, steps=4, seed=35, sp_kw=kw, used_seen=used)
+    assert max(used) >= 2, used
+
+
 def test_a_precision_switch_that_fails_changes_nothing():
     # scratch that is enough for the contractions and the diversities but not for the KL search of a 64K-weight layer
     # at 4000 bins: the first call fails after the diversities were made, the repeated call must match the oracle,
