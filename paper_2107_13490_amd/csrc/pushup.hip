@@ -15,6 +15,7 @@
 #include "common.hpp"
 #include "context.hpp"
 #include "grad_window.hpp"
+#include "ticket.hpp"
 #include "wide.hpp"
 
 namespace adapt {
@@ -63,6 +64,12 @@ constexpr uint32_t kGdMaxBlocks = 1024;       // four blocks per CU; more elemen
 constexpr int kGdShort = 4;
 constexpr int kGdShortChunks = 4;
 static bool gd_short(uint64_t n, int count, int element_bytes) { return count <= kGdShort && element_bytes <= 6 && n > (uint64_t)1023 * kGdChunk; }
+
+// Few blocks: the last one to finish adds the sums, no second launch.  Its ticket costs every block about 20 ns behind the
+// others', a second launch and its reduction 0.8 us plus 40 ns per tensor (device time; and 2.5 us of the host's).  Two launches
+// -> one, in a captured graph: 25 tensors of 36,864 elements 11.3 -> 9.1 us, of 147,456 (72 blocks) 11.7 -> 9.8; 8 of 73,728
+// 7.4 -> 7.1; one of 1,728 5.1 -> 5.4, of 147,456 6.3 -> 7.0 (not taken).
+static bool gd_one_launch(int blocks, int count) { return blocks <= 32 + 2 * count; }
 
 // Blocks of a tensor: the same number of chunks for every block where it can be had, at least `each` (1, or 2 where the
 // workspace does not hold one block's sums per chunk).
@@ -181,12 +188,12 @@ __device__ __forceinline__ void gd_chunks(const GdTable &tab, const int count, c
 
 __host__ __device__ inline size_t gd_lds_bytes(int count) { return (size_t)(count + 2) * kWave * sizeof(unsigned long long); }
 
-// partial[col][block]: col k < count: sum of squares of tensor k; col count / count+1: sums of the
+// partial[col][block] (SHARED: [block][col]): col k < count: sum of squares of tensor k; col count / count+1: sums of the
 // low / high 32-bit halves of (aligned element sum)^2
 // blk of nblk: this block's place among the blocks of the tensor (a chained step runs all layers in one launch)
 // FORM: GD_LONG / GD_SHORT, or by the window and the tensor (a chained step's layers differ)
 enum { GD_LONG, GD_SHORT, GD_EITHER };
-template <int FORM>
+template <int FORM, bool SHARED = false>
 __device__ __forceinline__ void gd_partial_body(const GradWindow &w, uint32_t n, uint64_t *partial, const uint32_t blk, const uint32_t nblk)
 {
     extern __shared__ unsigned long long gd_slots[];
@@ -211,20 +218,47 @@ __device__ __forceinline__ void gd_partial_body(const GradWindow &w, uint32_t n,
         else gd_chunks<2, 16, 1>(tab, count, n, gd_slots, blk, nblk);
     }
     __syncthreads();
-    for (int col = wave; col < count + 2; col += kGdThreads / kWave) {
-        const uint64_t v = wave_sum_u64(gd_slots[col * kWave + lane]);
-        if (lane == 0) partial[(size_t)col * nblk + blk] = v;
+    // The 64 lane counters of a column are added by eight threads (eight words each, rotated so that neighbouring columns meet
+    // different banks), so that all columns of a window of up to 30 are one round of three lane exchanges.
+    const int part = threadIdx.x & 7;
+    for (int col = threadIdx.x >> 3; col < (count + 2 + 7) / 8 * 8; col += kGdThreads / 8) {
+        uint64_t v = 0;
+        if (col < count + 2) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v += gd_slots[col * kWave + 8 * ((i + col) & 7) + part];
+        }
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) v += __shfl_xor((unsigned long long)v, off, 64);
+        // the first word of a column's counters, which only the column's own eight threads (one wavefront) have read
+        if (part == 0 && col < count + 2) gd_slots[col * kWave] = v;
     }
+    __syncthreads();
+    if (threadIdx.x < kWave)
+        for (int col = lane; col < count + 2; col += kWave) {
+            const uint64_t v = gd_slots[col * kWave];
+            if (SHARED) store_partial(partial + (size_t)blk * (count + 2) + col, v);
+            else partial[(size_t)col * nblk + blk] = v;
+        }
 }
 
-template <bool SHORT>
-__global__ void __launch_bounds__(kGdThreads)
-gd_partial_kernel(const GradWindow w, uint32_t n, uint64_t *partial)
+// The norms and the ratio from the column sums; every thread of the block calls it.
+__device__ __forceinline__ void gd_ratio(const GradWindow &w, const uint64_t *col_sum, double *out)
 {
-    gd_partial_body<SHORT ? GD_SHORT : GD_LONG>(w, n, partial, blockIdx.x, gridDim.x);
+    // the norms side by side (a square root and a scaling in fp64 take longer than the sums), added in window order
+    __shared__ double norm[kGdMaxTensors];
+    if ((int)threadIdx.x < w.count) norm[threadIdx.x] = ldexp(sqrt((double)col_sum[threadIdx.x]), -(int)w.fl[threadIdx.x]);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double num = 0.0;
+    for (int k = 0; k < w.count; ++k) num += norm[k];
+    const double sq = (double)col_sum[w.count + 1] * 4294967296.0 + (double)col_sum[w.count];
+    const double den = ldexp(sqrt(sq), -w.fl_max);
+    const double ds = den > 0.0 ? num / den : (num > 0.0 ? (double)INFINITY : (double)NAN);
+    out[0] = ds;
+    out[1] = (ds > 0.0 && ds < (double)INFINITY) ? log(ds) : 1.0;
 }
 
-// One block: column sums (one wavefront per column at a time), then the norms and the ratio.
+// One block: column sums of [col][block] (one wavefront per column at a time), then the norms and the ratio.
 __device__ __forceinline__ void gd_final_body(const GradWindow &w, const uint64_t *__restrict__ partial, int nblocks, uint64_t *sums_out,
                                               double *out)
 {
@@ -251,26 +285,67 @@ __device__ __forceinline__ void gd_final_body(const GradWindow &w, const uint64_
         }
     }
     __syncthreads();
-    // the norms side by side (a square root and a scaling in fp64 take longer than the sums), added in window order
-    __shared__ double norm[kGdMaxTensors];
-    if ((int)threadIdx.x < w.count) norm[threadIdx.x] = ldexp(sqrt((double)col_sum[threadIdx.x]), -(int)w.fl[threadIdx.x]);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    double num = 0.0;
-    for (int k = 0; k < w.count; ++k) num += norm[k];
-    const double sq = (double)col_sum[w.count + 1] * 4294967296.0 + (double)col_sum[w.count];
-    const double den = ldexp(sqrt(sq), -w.fl_max);
-    const double ds = den > 0.0 ? num / den : (num > 0.0 ? (double)INFINITY : (double)NAN);
-    out[0] = ds;
-    out[1] = (ds > 0.0 && ds < (double)INFINITY) ? log(ds) : 1.0;
+    gd_ratio(w, col_sum, out);
 }
 
-template <bool BYPTR>
-__global__ void __launch_bounds__(kGdFinalThreads)
-gd_final_kernel(const GradWindow wv, const GradWindow *__restrict__ wp, const uint64_t *__restrict__ partial, int nblocks,
-                uint64_t *sums_out, double *out)
+// The same in the block that finishes last, from rows [block][count + 2] written in this launch: a thread adds one column of
+// every (kGdThreads / columns)-th row with all its loads in flight, neighbouring threads read neighbouring words.
+constexpr int kGdRows = 10;
+__device__ __forceinline__ void gd_last_block(const GradWindow &w, const uint64_t *partial, int nblocks, uint64_t *sums_out, double *out)
 {
-    gd_final_body(BYPTR ? *wp : wv, partial, nblocks, sums_out, out);
+    __shared__ uint64_t wave_part[kGdThreads / kWave][kGdMaxTensors + 2];
+    __shared__ uint64_t col_sum[kGdMaxTensors + 2];
+    const int cols = w.count + 2, lp = 32 - __builtin_clz(cols - 1);      // cols <= 2^lp; cols >= 3
+    const int col = threadIdx.x & ((1 << lp) - 1), groups = kGdThreads >> lp;
+    uint64_t v = 0;
+    if (col < cols)
+        for (int b = threadIdx.x >> lp; b < nblocks; b += kGdRows * groups) {
+            uint64_t t[kGdRows];
+#pragma unroll
+            for (int u = 0; u < kGdRows; ++u) {      // the last row repeated past the end
+                const uint64_t *p = partial + (size_t)min(b + u * groups, nblocks - 1) * cols + col;
+                t[u] = load_partial(p);
+            }
+#pragma unroll
+            for (int u = 0; u < kGdRows; ++u) v += b + u * groups < nblocks ? t[u] : 0ull;
+        }
+    // the threads of a wavefront that hold the same column, then the wavefronts that do (all, up to 64 columns; else each second)
+    for (int off = 1 << lp; off < kWave; off <<= 1) v += __shfl_xor((unsigned long long)v, off, 64);
+    const int wave = threadIdx.x / kWave;
+    if ((lp >= 6 || (int)(threadIdx.x & (kWave - 1)) < (1 << lp)) && col < cols) wave_part[wave][col] = v;
+    __syncthreads();
+    if ((int)threadIdx.x < cols) {
+        const int first = (int)threadIdx.x >= kWave ? 1 : 0, step = lp > 6 ? 2 : 1;
+        v = 0;
+#pragma unroll
+        for (int i = 0; i < kGdThreads / kWave; ++i)
+            if (first + i * step < kGdThreads / kWave) v += wave_part[first + i * step][threadIdx.x];
+        col_sum[threadIdx.x] = v;
+        if (sums_out) sums_out[threadIdx.x] = v;
+    }
+    __syncthreads();
+    gd_ratio(w, col_sum, out);
+}
+
+template <int FORM>
+__global__ void __launch_bounds__(kGdThreads)
+gd_partial_kernel(const GradWindow w, uint32_t n, uint64_t *partial)
+{
+    gd_partial_body<FORM>(w, n, partial, blockIdx.x, gridDim.x);
+}
+
+__global__ void __launch_bounds__(kGdFinalThreads)
+gd_final_kernel(const GradWindow w, const uint64_t *__restrict__ partial, int nblocks, uint64_t *sums_out, double *out)
+{
+    gd_final_body(w, partial, nblocks, sums_out, out);
+}
+
+// both phases in one launch: the block that finishes last adds the rows
+__global__ void __launch_bounds__(kGdThreads)
+gd_small_kernel(const GradWindow w, uint32_t n, uint64_t *partial, uint32_t *ticket, uint64_t *sums_out, double *out)
+{
+    gd_partial_body<GD_LONG, true>(w, n, partial, blockIdx.x, gridDim.x);
+    if (finished_last(ticket)) gd_last_block(w, partial, (int)gridDim.x, sums_out, out);
 }
 
 // ---- windows that hold int32 codes (word lengths 17..32) --------------------------------------------------------
@@ -575,9 +650,13 @@ extern "C" int adapt_gradient_diversity(adapt_ctx *ctx, const adapt_grad_item *i
     const int blocks = (int)gd_blocks(n, brief, fits(gd_blocks(n, brief, 1)) ? 1 : 2);
     if (!fits((uint32_t)blocks)) return ADAPT_EWORKSPACE;
     uint64_t *partial = reinterpret_cast<uint64_t *>(scratch(ctx));
-    auto kern = brief ? gd_partial_kernel<true> : gd_partial_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream, w, (uint32_t)n, partial);
-    hipLaunchKernelGGL(gd_final_kernel<false>, dim3(1), dim3(kGdFinalThreads), 0, ctx->stream, w, nullptr, partial, blocks, sums, out);
+    if (gd_one_launch(blocks, count)) {
+        hipLaunchKernelGGL(gd_small_kernel, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream, w, (uint32_t)n, partial, ticket(ctx, 0), sums, out);
+        return hip_status(ctx, hipGetLastError());
+    }
+    hipLaunchKernelGGL(brief ? gd_partial_kernel<GD_SHORT> : gd_partial_kernel<GD_LONG>, dim3(blocks), dim3(kGdThreads), gd_lds_bytes(count), ctx->stream,
+                       w, (uint32_t)n, partial);
+    hipLaunchKernelGGL(gd_final_kernel, dim3(1), dim3(kGdFinalThreads), 0, ctx->stream, w, partial, blocks, sums, out);
     return hip_status(ctx, hipGetLastError());
 }
 
