@@ -250,3 +250,13 @@ def test_workspace_query_covers_batched_searches():
                 assert sel[t].tolist() == [ref["wl_sel"], ref["fl_sel"]], (case, t)
         finally:
             cx.close()
+
+
+# counters in one, two and four copies (by the bins and the elements a block counts), with and without zeros
+@pytest.mark.parametrize("n,bins", [(65536, 64), (65536, 300), (300001, 100), (300001, 1500), (1 << 20, 150), (2100003, 64), (2100003, 700)])
+def test_copies_of_the_counters(n, bins):
+    rng = np.random.default_rng(n + bins)
+    w = (rng.standard_normal(n) * 0.05).astype(np.float32)
+    w[rng.random(n) < 0.4] = 0.0
+    w[[3, n - 1]] = np.inf, np.nan
+    _compare(w, 3, 16, 2, bins, 1e-2, seed=3, stream=4)

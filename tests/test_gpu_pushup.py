@@ -160,3 +160,16 @@ def test_invalid_arguments():
         ctx().gradient_diversity([dev(np.zeros(64, dtype=np.int16)), g], [(16, 0), (8, 16)])
     with pytest.raises(pkg.AdaptError):
         ctx().gradient_diversity([], [])
+
+
+# up to 32 + 2 * count blocks of 2048 elements finish in one launch (and leave its ticket as they found it); column sums of a
+# block by groups of eight threads: 30 columns more than a round, the last of 66
+@pytest.mark.parametrize("n,count", [(b * 2048 + e, c) for c in (1, 25) for b, e in ((32 + 2 * c, 0), (32 + 2 * c, 1))] +
+                         [(70001, c) for c in (2, 29, 30, 31, 61, 62, 63, 64)])
+@pytest.mark.parametrize("wls", [(8,), (16, 6)])
+def test_one_launch_and_its_limits(n, count, wls):
+    rng = np.random.default_rng(n + count)
+    codes = [_codes(rng, n, wls[k % len(wls)], 0.2) for k in range(count)]
+    fmts = [(wls[k % len(wls)], 4 + k % 2) for k in range(count)]
+    for _ in range(2):
+        _check(codes, fmts)
