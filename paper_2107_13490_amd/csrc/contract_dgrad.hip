@@ -25,29 +25,10 @@ extern "C" int adapt_conv_dgrad(adapt_ctx *ctx, adapt_conv_desc d, const void *d
     if (d.n == 0) return ADAPT_OK;
     if (!check_ptrs(dy, w, dx)) return ADAPT_EINVAL;
     if (!epilogue_ok(ep)) return ADAPT_EINVAL;
-    ContractArgs a = {};
-    if (d.c < kPadC) {           // few input channels: the filters get zero channels appended (vector loads of their rows)
-        size_t off = 0;
-        const void *wp;
-        if (pad_channels(ctx, w, storage_bytes(fw), (size_t)d.k * d.r * d.s, d.c, off, &wp) == ADAPT_OK &&
-            fill_dgrad_padded(a, d, dy, fdy, wp, fw, dx) == ADAPT_OK) {
-            const int s = run_contraction<OP_DGRAD>(ctx, a, fdy, fw, ep, off);
-            if (s != ADAPT_EWORKSPACE) return s;
-        }
-        a = ContractArgs{};
-    }
-    if (wants_cout_pad(d) && d.r * d.s <= 32) {      // output channels not a multiple of 16: dy with zero channels appended
-        size_t off = 0;
-        const void *dyp;
-        if (pad_cout(ctx, dy, storage_bytes(fdy), (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1),
-                     d.k, off, &dyp) == ADAPT_OK &&
-            fill_dgrad_kpad(a, d, dyp, fdy, w, fw, dx) == ADAPT_OK) {
-            const int s = run_contraction<OP_DGRAD>(ctx, a, fdy, fw, ep, off);
-            if (s != ADAPT_EWORKSPACE) return s;
-        }
-        a = ContractArgs{};
-    }
-    if (int s = fill_dgrad(a, d, dy, fdy, w, fw, dx)) return s;
-    return run_contraction<OP_DGRAD>(ctx, a, fdy, fw, ep, 0);
+    PadJobs pads;
+    ContractPlan pd, pw;
+    if (int s = plan_gradients(ctx, GRAD_DX, d, dy, fdy, w, fw, nullptr, fdy, dx, ep, nullptr, ep, scratch_bytes(ctx), pads, pd, pw)) return s;
+    hipError_t e = launch_pads(ctx, pads);
+    if (e == hipSuccess) e = launch_and_finish(ctx, pd, launch_planned<OP_DGRAD>);
+    return hip_status(ctx, e);
 }
-

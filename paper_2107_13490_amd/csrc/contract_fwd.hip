@@ -24,18 +24,10 @@ extern "C" int adapt_conv_fwd(adapt_ctx *ctx, adapt_conv_desc d, const void *x, 
     if (d.n == 0) return ADAPT_OK;
     if (!check_ptrs(x, w, y)) return ADAPT_EINVAL;
     if (!epilogue_ok(ep)) return ADAPT_EINVAL;
-    ContractArgs a = {};
-    if (d.c < kPadC) {           // few input channels: run on zero-padded copies when the workspace holds them
-        size_t off = 0;
-        const void *xp, *wp;
-        if (pad_channels(ctx, x, storage_bytes(fx), (size_t)d.n * d.h * d.w, d.c, off, &xp) == ADAPT_OK &&
-            pad_channels(ctx, w, storage_bytes(fw), (size_t)d.k * d.r * d.s, d.c, off, &wp) == ADAPT_OK &&
-            fill_fwd_padded(a, d, xp, fx, wp, fw, y) == ADAPT_OK) {
-            const int s = run_contraction<OP_FWD>(ctx, a, fx, fw, ep, off);
-            if (s != ADAPT_EWORKSPACE) return s;
-        }
-        a = ContractArgs{};
-    }
-    if (int s = fill_fwd(a, d, x, fx, w, fw, y)) return s;
-    return run_contraction<OP_FWD>(ctx, a, fx, fw, ep, 0);
+    PadJobs pads;
+    ContractPlan p;
+    if (int s = plan_fwd(ctx, d, x, fx, w, fw, y, ep, scratch_bytes(ctx), pads, p)) return s;
+    hipError_t e = launch_pads(ctx, pads);
+    if (e == hipSuccess) e = launch_and_finish(ctx, p, launch_planned<OP_FWD>);
+    return hip_status(ctx, e);
 }

@@ -1493,9 +1493,8 @@ struct ContractPlan {
 template <int OP>
 static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_fmt fb, adapt_epilogue ep,
                             size_t ws_offset /* bytes of scratch already in use */, ContractPlan &p,
-                            size_t ws_limit = (size_t)-1 /* bytes of scratch there are; default: the context's */)
+                            size_t ws_limit /* bytes of scratch there are */)
 {
-    if (ws_limit == (size_t)-1) ws_limit = scratch_bytes(ctx);
     const int limbs = (fa.wl > 8 || fb.wl > 8) ? 2 : 1;
     const int bits = adapt_acc_bits(a.k_bound ? a.k_bound : a.K, fa, fb);
     int final_mode;
@@ -1664,110 +1663,52 @@ static hipError_t finish_planned(adapt_ctx *ctx, const ContractPlan &p)
     return hipGetLastError();
 }
 
-template <int OP>
-static int run_contraction(adapt_ctx *ctx, const ContractArgs &a, adapt_fmt fa, adapt_fmt fb, adapt_epilogue ep, size_t ws_offset)
-{
-    ContractPlan p;
-    if (int s = plan_contraction<OP>(ctx, a, fa, fb, ep, ws_offset, p)) return s;
-    hipError_t e = launch_planned<OP>(ctx, p);
-    if (e == hipSuccess) e = finish_planned(ctx, p);
-    return hip_status(ctx, e);
-}
-
-// ---- layers with few input channels ------------------------------------------------------------
-// The first layer of an image network has 3 input channels: too few for 16-byte operand loads, so
-// the contraction would gather element by element.  Such layers run on copies of x and w with
-// zero channels appended up to 16 (in the context's workspace): the zeros add nothing to any sum, the
-// outputs keep their logical shape and index (and with it their rounding bits), and the vector
-// paths apply.  Measured on 256 x 32 x 32 x 3 -> 64, <12,9>: fwd 90 -> 60 us, dgrad 277 -> 95, wgrad 104 -> 51.
-constexpr int kPadC = 16;
-
-template <typename T>
-__global__ void __launch_bounds__(256) pad_channels_kernel(const T *__restrict__ src, T *__restrict__ dst, const uint32_t rows, const int c)
-{
-    for (uint32_t r = blockIdx.x * 256 + threadIdx.x; r < rows; r += gridDim.x * 256) {
-        constexpr int PER = 4 / (int)sizeof(T);                      // codes per 32-bit word
-        uint32_t wds[kPadC / PER];
-#pragma unroll
-        for (int q = 0; q < kPadC / PER; ++q) wds[q] = 0;
-#pragma unroll
-        for (int e = 0; e < kPadC; ++e) {
-            const uint32_t v = e < c ? (uint32_t)src[(size_t)r * c + e] & (sizeof(T) == 1 ? 0xffu : 0xffffu) : 0u;
-            wds[e / PER] |= v << (8 * (int)sizeof(T) * (e % PER));
-        }
-        uint4 *o = reinterpret_cast<uint4 *>(dst + (size_t)r * kPadC);
-#pragma unroll
-        for (int q = 0; q < kPadC / PER / 4; ++q) o[q] = make_uint4(wds[4 * q], wds[4 * q + 1], wds[4 * q + 2], wds[4 * q + 3]);
-    }
-}
-
-// Appends zero channels to a [rows][c] tensor of es-byte codes; the copy lives at scratch + off, which is advanced.
-static int pad_channels(adapt_ctx *ctx, const void *src, int es, size_t rows, int c, size_t &off, const void **out)
-{
-    const size_t bytes = rows * kPadC * (size_t)es;
-    off = (off + 255) & ~(size_t)255;
-    if (rows >= ((size_t)1 << 31) || off + bytes > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
-    char *dst = scratch(ctx) + off;
-    const unsigned grid = (unsigned)std::min<size_t>(std::max<size_t>((rows + 255) / 256, 1), (size_t)ctx->num_cu * 8);
-    if (es == 1)
-        hipLaunchKernelGGL(pad_channels_kernel<int8_t>, dim3(grid), dim3(256), 0, ctx->stream, static_cast<const int8_t *>(src),
-                           reinterpret_cast<int8_t *>(dst), (uint32_t)rows, c);
-    else
-        hipLaunchKernelGGL(pad_channels_kernel<int16_t>, dim3(grid), dim3(256), 0, ctx->stream, static_cast<const int16_t *>(src),
-                           reinterpret_cast<int16_t *>(dst), (uint32_t)rows, c);
-    if (hipGetLastError() != hipSuccess) return ADAPT_EHIP;
-    *out = dst;
-    off += bytes;
-    return ADAPT_OK;
-}
-
-// A classifier has 10 or 100 output channels: the rows of dy are then not a multiple of 16 codes, and both gradient
-// contractions would gather dy element by element.  They run on a copy of dy with zero channels appended up to the
-// next multiple of 16 instead (in the context's workspace): zeros add nothing to the data gradient (the filter rows
-// that would meet them lie beyond the filter tensor and read as zero as well), and the weight gradient keeps its
-// d.k real rows.  Measured on 256 x 512 -> 100, one limb: dgrad 25 -> 9 us, wgrad 30 -> 12 us.
-template <typename T>
-__global__ void __launch_bounds__(256)
-pad_rows_kernel(const T *__restrict__ src, T *__restrict__ dst, const uint64_t chunks, const int c, const int c_to)
-{
-    constexpr int PER = 16 / (int)sizeof(T);                       // codes per 16-byte chunk
-    const int cpr = c_to / PER;                                      // chunks per row
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < chunks; i += (uint64_t)gridDim.x * 256) {
-        const uint64_t r = i / (uint64_t)cpr;
-        const int e0 = (int)(i - r * cpr) * PER;
-        T v[PER];
-#pragma unroll
-        for (int e = 0; e < PER; ++e) v[e] = e0 + e < c ? src[r * (uint64_t)c + e0 + e] : (T)0;
-        reinterpret_cast<uint4 *>(dst)[i] = *reinterpret_cast<const uint4 *>(v);
-    }
-}
+// ---- operands whose rows are not whole 16-byte groups --------------------------------------------
+// The vector paths load 16 codes at a time along the contiguous direction of an operand.  Where that extent (input channels
+// of x and w, output channels of dy, a GEMM operand's leading dimension) is not a multiple of 16, the contraction runs on
+// copies with zero codes appended to every row (in the context's workspace): zeros add nothing to any sum, and the outputs
+// keep their logical shape and index, and with it their rounding bits.  The alternative, gathering element by element, costs
+// far more than the copies: 256 x 32 x 32 x 3 -> 64 3x3 <12,9> forward 90 -> 60 us.
+struct PadJob {
+    const void *src;
+    void *dst;
+    uint64_t stride;              // bytes from one source row to the next
+    uint32_t row_bytes, cpr;      // bytes of a source row that are copied, 16-byte chunks of a copied row
+    uint32_t chunks, first;       // chunks of the copy, first block of the launch that works on it
+    FastDiv div_cpr;
+};
+struct PadJobs {
+    PadJob job[3];
+    int count;
+    uint32_t blocks;
+};
+constexpr uint32_t kPadChunksPerBlock = 256;       // one per thread
 
 static inline int round_up16(int k) { return (k + 15) & ~15; }
 
-// Copy of dy [rows][k] with rows of round_up16(k) codes at scratch + off, which is advanced.
-static int pad_cout(adapt_ctx *ctx, const void *dy, int es, size_t rows, int k, size_t &off, const void **out)
+// Plans the copy of a [rows][c] tensor of es-byte codes (rows ld codes apart) with rows of round_up16(c) codes at byte `off` of
+// the scratch; `off` advances to its end.
+static int add_pad(adapt_ctx *ctx, PadJobs &jobs, const void *src, int es, size_t rows, int c, int ld, size_t ws_limit, size_t &off, const void **out)
 {
-    const int k_to = round_up16(k);
-    const size_t bytes = rows * (size_t)k_to * (size_t)es;
+    const size_t bytes = rows * (size_t)round_up16(c) * (size_t)es;
     off = (off + 255) & ~(size_t)255;
-    if (bytes >= ((size_t)1 << 32) || off + bytes > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
-    char *dst = scratch(ctx) + off;
-    const uint64_t chunks = bytes / 16;
-    const unsigned grid = (unsigned)std::min<uint64_t>(std::max<uint64_t>((chunks + 255) / 256, 1), (uint64_t)ctx->num_cu * 8);
-    if (es == 1)
-        hipLaunchKernelGGL(pad_rows_kernel<int8_t>, dim3(grid), dim3(256), 0, ctx->stream, static_cast<const int8_t *>(dy),
-                           reinterpret_cast<int8_t *>(dst), chunks, k, k_to);
-    else
-        hipLaunchKernelGGL(pad_rows_kernel<int16_t>, dim3(grid), dim3(256), 0, ctx->stream, static_cast<const int16_t *>(dy),
-                           reinterpret_cast<int16_t *>(dst), chunks, k, k_to);
-    if (hipGetLastError() != hipSuccess) return ADAPT_EHIP;
-    *out = dst;
+    if (bytes >= ((size_t)1 << 32) || off + bytes > ws_limit) return ADAPT_EWORKSPACE;
+    PadJob &j = jobs.job[jobs.count++];
+    j.src = src;
+    j.dst = ctx->ws ? scratch(ctx) + off : nullptr;      // no workspace: a sizing query, nothing is launched
+    j.stride = (uint64_t)ld * es;
+    j.row_bytes = (uint32_t)(c * es);
+    j.cpr = (uint32_t)(round_up16(c) * es / 16);
+    j.chunks = (uint32_t)(bytes / 16);
+    j.first = jobs.blocks;
+    j.div_cpr = make_fastdiv(j.cpr);
+    jobs.blocks += (j.chunks + kPadChunksPerBlock - 1) / kPadChunksPerBlock;
+    *out = j.dst;
     off += bytes;
     return ADAPT_OK;
 }
 
-// true when the gradient contractions of this layer take the padded copy of dy
-static inline bool wants_cout_pad(const adapt_conv_desc &d) { return d.n > 0 && d.k % 16 != 0 && d.c >= 16 && d.c % 16 == 0; }
+hipError_t launch_pads(adapt_ctx *ctx, const PadJobs &jobs);      // contract_gemm.hip
 
 static bool epilogue_ok(const adapt_epilogue &ep)
 {
@@ -1848,62 +1789,100 @@ static int fill_fwd(ContractArgs &a, const adapt_conv_desc &d, const void *x, ad
     return ADAPT_OK;
 }
 
-// The same contractions on operands with zero channels appended (see pad_channels): `wp` / `xp` hold kPadC channels.
-static int fill_fwd_padded(ContractArgs &a, const adapt_conv_desc &d, const void *xp, adapt_fmt fx, const void *wp, adapt_fmt fw, void *y)
+// A convolution's contractions as the library runs them: on padded copies where the channels ask for it and the workspace
+// holds them (fewer copies, then none, where it does not), else on the operands as they are.  `pads` are launched before the
+// plans.
+enum { PAD_C = 1, PAD_K = 2 };      // input channels (x, w), output channels (dy)
+static inline int conv_pads_wanted(const adapt_conv_desc &d, bool gradients)
 {
-    adapt_conv_desc d2 = d;
-    d2.c = kPadC;
-    if (int s = fill_fwd(a, d2, xp, fx, wp, fw, y)) return s;
-    a.k_bound = d.r * d.s * d.c;       // the caller's accumulator type follows the logical reduction length
-    return ADAPT_OK;
+    if (d.n <= 0) return 0;
+    return (d.c % 16 ? PAD_C : 0) | (gradients && d.k % 16 ? PAD_K : 0);
 }
 
-static int fill_dgrad_padded(ContractArgs &a, const adapt_conv_desc &d, const void *dy, adapt_fmt fdy, const void *wp, adapt_fmt fw, void *dx)
+static int plan_fwd(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, adapt_fmt fx, const void *w, adapt_fmt fw, void *y, adapt_epilogue ep,
+                    size_t ws_limit, PadJobs &pads, ContractPlan &p)
 {
-    if (int s = fill_dgrad(a, d, dy, fdy, wp, fw, dx)) return s;
-    a.c = kPadC;                       // stride of the filter rows; the output keeps d.c columns
-    a.wgt_bytes = (uint32_t)((long long)d.k * d.r * d.s * kPadC * a.wgt_es);
-    a.wgt_load = LOAD_ROWS;
-    return ADAPT_OK;
+    if (conv_pads_wanted(d, false) && d.r * d.s <= 32) {
+        pads = PadJobs{};
+        ContractArgs a = {};
+        size_t off = 0;
+        const void *xp, *wp;
+        adapt_conv_desc d2 = d;
+        d2.c = round_up16(d.c);
+        if (add_pad(ctx, pads, x, storage_bytes(fx), (size_t)d.n * d.h * d.w, d.c, d.c, ws_limit, off, &xp) == ADAPT_OK &&
+            add_pad(ctx, pads, w, storage_bytes(fw), (size_t)d.k * d.r * d.s, d.c, d.c, ws_limit, off, &wp) == ADAPT_OK &&
+            fill_fwd(a, d2, xp, fx, wp, fw, y) == ADAPT_OK) {
+            a.k_bound = d.r * d.s * d.c;       // the caller's accumulator type follows the logical reduction length
+            if (plan_contraction<OP_FWD>(ctx, a, fx, fw, ep, off, p, ws_limit) == ADAPT_OK) return ADAPT_OK;
+        }
+    }
+    pads = PadJobs{};
+    ContractArgs a = {};
+    if (int s = fill_fwd(a, d, x, fx, w, fw, y)) return s;
+    return plan_contraction<OP_FWD>(ctx, a, fx, fw, ep, 0, p, ws_limit);
 }
 
-// Weight gradient on a padded x: the kernel fills slabs of r*s*kPadC columns, finish_kernel picks the d.c real ones.
-static int fill_wgrad_padded(ContractArgs &a, const adapt_conv_desc &d, const void *dy, adapt_fmt fdy, const void *xp, adapt_fmt fx, void *dw)
+// which of the two gradients a call computes
+enum { GRAD_DX = 1, GRAD_DW = 2 };
+static int plan_gradients(adapt_ctx *ctx, int which, const adapt_conv_desc &d, const void *dy, adapt_fmt fdy, const void *w, adapt_fmt fw,
+                          const void *x, adapt_fmt fx, void *dx, adapt_epilogue ep_dx, void *dw, adapt_epilogue ep_dw, size_t ws_limit,
+                          PadJobs &pads, ContractPlan &pd, ContractPlan &pw)
 {
-    adapt_conv_desc d2 = d;
-    d2.c = kPadC;
-    if (int s = fill_wgrad(a, d2, dy, fdy, xp, fx, dw)) return s;
-    a.force_finish = 1;
-    return ADAPT_OK;
-}
-
-static void unpad_wgrad_finish(ContractPlan &p, const adapt_conv_desc &d)
-{
-    if (p.empty) return;
-    p.fin.N = d.r * d.s * d.c;
-    p.fin.ldc = p.fin.N;
-    p.fin.pad_c = d.c;
-    p.fin.pad_to = kPadC;
-}
-
-// The gradient contractions on dy with zero channels appended (see pad_cout): dyp has rows of round_up16(d.k) codes.
-static int fill_dgrad_kpad(ContractArgs &a, const adapt_conv_desc &d, const void *dyp, adapt_fmt fdy, const void *w, adapt_fmt fw, void *dx)
-{
-    adapt_conv_desc d2 = d;
-    d2.k = round_up16(d.k);
-    if (int s = fill_dgrad(a, d2, dyp, fdy, w, fw, dx)) return s;
-    a.wgt_bytes = (uint32_t)((long long)d.k * d.r * d.s * d.c * a.wgt_es);      // the filter rows of the appended channels read as zero
-    a.k_bound = d.r * d.s * d.k;       // the caller's accumulator type follows the logical reduction length
-    return ADAPT_OK;
-}
-
-static int fill_wgrad_kpad(ContractArgs &a, const adapt_conv_desc &d, const void *dyp, adapt_fmt fdy, const void *x, adapt_fmt fx, void *dw)
-{
-    adapt_conv_desc d2 = d;
-    d2.k = round_up16(d.k);
-    if (int s = fill_wgrad(a, d2, dyp, fdy, x, fx, dw)) return s;
-    a.M = d.k;                         // dw keeps its real rows; the appended ones are never written
-    return ADAPT_OK;
+    const int wanted = conv_pads_wanted(d, true);
+    const size_t dy_rows = (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1);
+    const int attempts[4] = {wanted, wanted & PAD_C, wanted & PAD_K, 0};
+    int last = -1;
+    for (int t = 0; t < 4; ++t) {
+        const int use = attempts[t];
+        if (use == last) continue;
+        last = use;
+        // the vector path of dy keeps one validity bit per filter tap and row: a data gradient beyond that has no use for copies
+        const bool dx_pads = d.r * d.s <= 32;
+        if (use && !dx_pads && !(which & GRAD_DW)) continue;
+        pads = PadJobs{};
+        size_t off = 0;
+        const void *dyp = dy, *xp = x, *wp = w;
+        adapt_conv_desc dk = d;                       // dy's rows as they lie in memory
+        bool ok = true;
+        if (use & PAD_K) {
+            dk.k = round_up16(d.k);
+            ok = add_pad(ctx, pads, dy, storage_bytes(fdy), dy_rows, d.k, d.k, ws_limit, off, &dyp) == ADAPT_OK;
+        }
+        if (ok && (use & PAD_C) && (which & GRAD_DW)) ok = add_pad(ctx, pads, x, storage_bytes(fx), (size_t)d.n * d.h * d.w, d.c, d.c, ws_limit, off, &xp) == ADAPT_OK;
+        if (ok && (use & PAD_C) && (which & GRAD_DX) && dx_pads) ok = add_pad(ctx, pads, w, storage_bytes(fw), (size_t)d.k * d.r * d.s, d.c, d.c, ws_limit, off, &wp) == ADAPT_OK;
+        int s = ok ? ADAPT_OK : ADAPT_EWORKSPACE;
+        if (s == ADAPT_OK && (which & GRAD_DX)) {
+            ContractArgs a = {};
+            s = dx_pads ? fill_dgrad(a, dk, dyp, fdy, wp, fw, dx) : fill_dgrad(a, d, dy, fdy, w, fw, dx);
+            if ((use & PAD_C) && dx_pads) {                        // stride of the filter rows; the output keeps d.c columns
+                a.c = round_up16(d.c);
+                a.wgt_load = LOAD_ROWS;
+            }
+            if (use && dx_pads) {
+                // the filter rows of appended output channels lie beyond the tensor and read as zero
+                a.wgt_bytes = (uint32_t)((long long)d.k * d.r * d.s * a.c * a.wgt_es);
+                a.k_bound = d.r * d.s * d.k;
+            }
+            if (s == ADAPT_OK) s = plan_contraction<OP_DGRAD>(ctx, a, fdy, fw, ep_dx, off, pd, ws_limit);
+        }
+        if (s == ADAPT_OK && (which & GRAD_DW)) {
+            ContractArgs a = {};
+            adapt_conv_desc dw2 = dk;
+            if (use & PAD_C) dw2.c = round_up16(d.c);
+            s = fill_wgrad(a, dw2, dyp, fdy, xp, fx, dw);
+            a.M = d.k;                                // dw keeps its real rows; the appended ones are never written
+            if (use & PAD_C) a.force_finish = 1;      // the kernel fills slabs with the appended columns, finish_kernel picks the real ones
+            if (s == ADAPT_OK) s = plan_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep_dw, off, pw, ws_limit);
+            if (s == ADAPT_OK && (use & PAD_C) && !pw.empty) {
+                pw.fin.N = d.r * d.s * d.c;
+                pw.fin.ldc = pw.fin.N;
+                pw.fin.pad_c = d.c;
+                pw.fin.pad_to = dw2.c;
+            }
+        }
+        if (s == ADAPT_OK || use == 0) return s;
+    }
+    return ADAPT_EUNSUPPORTED;                        // not reached: the last attempt uses no copies
 }
 
 static void fill_gemm(ContractArgs &a, int transA, int transB, int M, int N, int K, const void *A, adapt_fmt fa, int lda,
@@ -1923,6 +1902,42 @@ static void fill_gemm(ContractArgs &a, int transA, int transB, int M, int N, int
     a.wgt_load = transB ? ((K % 16 == 0 && ldb % 16 == 0) ? LOAD_VEC : LOAD_SCALAR)
                         : ((N % 16 == 0 && ldb % 16 == 0) ? LOAD_ROWS : LOAD_SCALAR);
     a.ldc = ldc;
+}
+
+static int plan_gemm(adapt_ctx *ctx, int transA, int transB, int M, int N, int K, const void *A, adapt_fmt fa, int lda, const void *B,
+                     adapt_fmt fb, int ldb, void *C, int ldc, adapt_epilogue ep, size_t ws_limit, PadJobs &pads, ContractPlan &p)
+{
+    ContractArgs a = {};
+    fill_gemm(a, transA, transB, M, N, K, A, fa, lda, B, fb, ldb, C, ldc);
+    pads = PadJobs{};
+    const bool pa = a.act_load == LOAD_SCALAR, pb = a.wgt_load == LOAD_SCALAR;
+    if ((pa || pb) && M > 0 && N > 0 && K > 0) {
+        const int wa = transA ? M : K, wb = transB ? K : N;      // codes of a row
+        size_t off = 0;
+        const void *Ap = A, *Bp = B;
+        if ((!pa || add_pad(ctx, pads, A, a.act_es, transA ? K : M, wa, lda, ws_limit, off, &Ap) == ADAPT_OK) &&
+            (!pb || add_pad(ctx, pads, B, a.wgt_es, transB ? N : K, wb, ldb, ws_limit, off, &Bp) == ADAPT_OK)) {
+            ContractArgs v = {};
+            fill_gemm(v, transA, transB, M, N, K, Ap, fa, pa ? round_up16(wa) : lda, Bp, fb, pb ? round_up16(wb) : ldb, C, ldc);
+            // an operand with its rows along k ends at a multiple of 16 now; the other's lines beyond K lie outside it and read as zero
+            v.act_load = transA ? LOAD_ROWS : LOAD_VEC;
+            v.wgt_load = transB ? LOAD_VEC : LOAD_ROWS;
+            if (!transA || transB) v.K = round_up16(K);
+            if (pa) v.act_bytes = (uint32_t)((long long)(transA ? K : M) * round_up16(wa) * v.act_es);
+            if (pb) v.wgt_bytes = (uint32_t)((long long)(transB ? N : K) * round_up16(wb) * v.wgt_es);
+            v.k_bound = K;
+            if (plan_contraction<OP_GEMM>(ctx, v, fa, fb, ep, off, p, ws_limit) == ADAPT_OK) return ADAPT_OK;
+        }
+        pads = PadJobs{};
+    }
+    return plan_contraction<OP_GEMM>(ctx, a, fa, fb, ep, 0, p, ws_limit);
+}
+
+// The launches of a planned call
+static hipError_t launch_and_finish(adapt_ctx *ctx, const ContractPlan &p, hipError_t (*launch)(adapt_ctx *, const ContractPlan &))
+{
+    hipError_t e = launch(ctx, p);
+    return e == hipSuccess ? finish_planned(ctx, p) : e;
 }
 
 static bool check_ptrs(const void *x, const void *y, const void *z) { return x && y && z && aligned16(x) && aligned16(y) && aligned16(z); }

@@ -26,35 +26,10 @@ extern "C" int adapt_conv_wgrad(adapt_ctx *ctx, adapt_conv_desc d, const void *d
     if (!dw || !aligned16(dw)) return ADAPT_EINVAL;
     if (d.n > 0 && !check_ptrs(dy, x, dw)) return ADAPT_EINVAL;
     if (!epilogue_ok(ep)) return ADAPT_EINVAL;
-    ContractArgs a = {};
-    if (d.c < kPadC && d.n > 0) {      // few input channels: x gets zero channels appended, the finish kernel drops them again
-        size_t off = 0;
-        const void *xp;
-        ContractPlan p;
-        if (pad_channels(ctx, x, storage_bytes(fx), (size_t)d.n * d.h * d.w, d.c, off, &xp) == ADAPT_OK &&
-            fill_wgrad_padded(a, d, dy, fdy, xp, fx, dw) == ADAPT_OK) {
-            const int s = plan_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep, off, p);
-            if (s == ADAPT_OK) {
-                unpad_wgrad_finish(p, d);
-                hipError_t e = launch_planned<OP_WGRAD>(ctx, p);
-                if (e == hipSuccess) e = finish_planned(ctx, p);
-                return hip_status(ctx, e);
-            }
-            if (s != ADAPT_EWORKSPACE) return s;
-        }
-        a = ContractArgs{};
-    }
-    if (wants_cout_pad(d)) {           // output channels not a multiple of 16: dy with zero channels appended
-        size_t off = 0;
-        const void *dyp;
-        if (pad_cout(ctx, dy, storage_bytes(fdy), (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1),
-                     d.k, off, &dyp) == ADAPT_OK &&
-            fill_wgrad_kpad(a, d, dyp, fdy, x, fx, dw) == ADAPT_OK) {
-            const int s = run_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep, off);
-            if (s != ADAPT_EWORKSPACE) return s;
-        }
-        a = ContractArgs{};
-    }
-    if (int s = fill_wgrad(a, d, dy, fdy, x, fx, dw)) return s;
-    return run_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep, 0);
+    PadJobs pads;
+    ContractPlan pd, pw;
+    if (int s = plan_gradients(ctx, GRAD_DW, d, dy, fdy, nullptr, fdy, x, fx, nullptr, ep, dw, ep, scratch_bytes(ctx), pads, pd, pw)) return s;
+    hipError_t e = launch_pads(ctx, pads);
+    if (e == hipSuccess) e = launch_and_finish(ctx, pw, launch_planned<OP_WGRAD>);
+    return hip_status(ctx, e);
 }

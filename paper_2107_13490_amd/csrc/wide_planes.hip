@@ -388,15 +388,14 @@ static double composed_us(int num_cu, const adapt_conv_desc &d, adapt_fmt fx, ad
             double splits = 1;                                   // as plan_contraction splits
             if (tiles < num_cu && k >= 8 * bkt) splits = std::max(1.0, std::min(std::ceil(2 * num_cu / tiles), std::floor(k / (4 * bkt))));
             const double acc = adapt_acc_bits((int64_t)d.r * d.s * d.c, pa[i], pb[j]) == 32 ? 4 : 8;
-            launches += (splits > 1 ? 2 : 1) + (d.c < kPadC ? 2 : 0);
+            launches += (splits > 1 ? 2 : 1) + (d.c % 16 ? 1 : 0);      // the slab sum, the padded copies
             chain += k / 64 / splits * std::max(1.0, tiles * splits / (2 * num_cu)) * la * lb;
             bytes += 2 * m * n * acc * (1 + (splits > 1 ? splits : 0));      // partial results and slabs, written and read
         }
-    const double gather = d.c > kPadC && d.c % 16 ? 8.0 : 1.0;               // element by element
     double split = 0;
     if (fx.wl > 16) { launches += 1; split += (double)d.n * d.h * d.w * d.c * (4 + 2 * na); }
     if (fw.wl > 16) { launches += 1; split += (double)d.k * d.r * d.s * d.c * (4 + 2 * nb); }
-    return 3.6 * launches + 0.19 * gather * chain + 0.35e-6 * bytes + 0.14e-6 * split;
+    return 3.6 * launches + 0.19 * chain + 0.35e-6 * bytes + 0.14e-6 * split;
 }
 
 bool wide_fwd_composed_faster(int num_cu, const adapt_conv_desc &d, adapt_fmt fx, adapt_fmt fw)
@@ -419,8 +418,9 @@ int wide_fwd_planes(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, ada
     if (need > scratch_bytes(ctx)) return ADAPT_EWORKSPACE;
     const uint64_t xrows = (uint64_t)d.n * d.h * d.w, wrows = (uint64_t)d.k * d.r * d.s;
     const uint64_t outputs = (uint64_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1) * d.k;
+    const size_t inner = d.c % 16 ? (size_t)(xrows + wrows) * cp * 2 + 1024 : 0;      // the part contractions' padded copies
     if (wide_fwd_composed_faster(ctx->num_cu, d, fx, fw) &&
-        ws_need_wide_all_pairs(fx, xrows * d.c, fw, wrows * d.c, outputs) + ((size_t)1 << 20) <= scratch_bytes(ctx))
+        ws_need_wide_all_pairs(fx, xrows * d.c, fw, wrows * d.c, outputs) + std::max((size_t)1 << 20, inner) <= scratch_bytes(ctx))
         return ADAPT_EUNSUPPORTED;
     const size_t xs = plane_stride(xrows, cp), wsd = plane_stride(wrows, cp);
     int8_t *xp = reinterpret_cast<int8_t *>(scratch(ctx)), *wp = xp + (size_t)P * xs;

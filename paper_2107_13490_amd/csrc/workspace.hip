@@ -8,60 +8,19 @@ namespace {
 
 constexpr size_t kInvalid = 0;
 
-size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
-
-// zero-padded copies of a narrow layer's operands (see pad_channels)
-size_t pad_bytes(size_t off, size_t rows, int es) { return a256(off) + rows * kPadC * (size_t)es; }
-
 size_t conv_need(adapt_ctx *dry, int call, const adapt_conv_desc &d, adapt_fmt fa, adapt_fmt fb, adapt_fmt fc)
 {
     const adapt_epilogue ep = {1, {8, 0}, {ADAPT_RN_HALF_UP, 0, 0}, 0};      // exact output: the widest slabs
     const size_t big = (size_t)1 << 62;
-    const bool narrow = d.c < kPadC && d.n > 0;
-    const size_t x_rows = (size_t)d.n * d.h * d.w, w_rows = (size_t)d.k * d.r * d.s;
-    const size_t dy_rows = (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1);
-    ContractArgs a = {};
-    ContractPlan p;
-    size_t need = 0;
-    if (call == ADAPT_CALL_CONV_FWD) {                       // operands x (fa), w (fb)
-        size_t off = 0;
-        if (narrow) {
-            off = pad_bytes(pad_bytes(0, x_rows, storage_bytes(fa)), w_rows, storage_bytes(fb));
-            if (fill_fwd_padded(a, d, nullptr, fa, nullptr, fb, nullptr) != ADAPT_OK) return kInvalid;
-        } else if (fill_fwd(a, d, nullptr, fa, nullptr, fb, nullptr) != ADAPT_OK) return kInvalid;
-        if (plan_contraction<OP_FWD>(dry, a, fa, fb, ep, off, p, big) != ADAPT_OK) return kInvalid;
-        need = p.ws_end;
-    }
-    if (call == ADAPT_CALL_CONV_DGRAD || call == ADAPT_CALL_CONV_BACKWARD) {      // operands dy (fa), w (fb)
-        size_t off = 0;
-        a = ContractArgs{};
-        if (narrow) {
-            if (call == ADAPT_CALL_CONV_BACKWARD) off = pad_bytes(0, x_rows, storage_bytes(fc));
-            off = pad_bytes(off, w_rows, storage_bytes(fb));
-            if (fill_dgrad_padded(a, d, nullptr, fa, nullptr, fb, nullptr) != ADAPT_OK) return kInvalid;
-        } else if (wants_cout_pad(d) && d.r * d.s <= 32) {   // the copy of dy with zero channels appended, then the plan on it
-            off = a256(0) + dy_rows * (size_t)round_up16(d.k) * storage_bytes(fa);
-            if (fill_dgrad_kpad(a, d, nullptr, fa, nullptr, fb, nullptr) != ADAPT_OK) return kInvalid;
-        } else if (fill_dgrad(a, d, nullptr, fa, nullptr, fb, nullptr) != ADAPT_OK) return kInvalid;
-        if (plan_contraction<OP_DGRAD>(dry, a, fa, fb, ep, off, p, big) != ADAPT_OK) return kInvalid;
-        need = std::max(need, p.ws_end);
-    }
-    if (call == ADAPT_CALL_CONV_WGRAD || call == ADAPT_CALL_CONV_BACKWARD) {      // operands dy (fa), x (fb; fc in a backward call)
-        const adapt_fmt fx = call == ADAPT_CALL_CONV_BACKWARD ? fc : fb;
-        size_t off = 0;
-        a = ContractArgs{};
-        if (narrow) {
-            off = pad_bytes(0, x_rows, storage_bytes(fx));
-            if (call == ADAPT_CALL_CONV_BACKWARD) off = pad_bytes(off, w_rows, storage_bytes(fb));
-            if (fill_wgrad_padded(a, d, nullptr, fa, nullptr, fx, nullptr) != ADAPT_OK) return kInvalid;
-        } else if (wants_cout_pad(d) && (call == ADAPT_CALL_CONV_WGRAD || d.r * d.s <= 32)) {
-            off = a256(0) + dy_rows * (size_t)round_up16(d.k) * storage_bytes(fa);
-            if (fill_wgrad_kpad(a, d, nullptr, fa, nullptr, fx, nullptr) != ADAPT_OK) return kInvalid;
-        } else if (fill_wgrad(a, d, nullptr, fa, nullptr, fx, nullptr) != ADAPT_OK) return kInvalid;
-        if (plan_contraction<OP_WGRAD>(dry, a, fa, fx, ep, off, p, big) != ADAPT_OK) return kInvalid;
-        need = std::max(need, p.ws_end);
-    }
-    return need;
+    PadJobs pads;
+    ContractPlan p = {}, pw = {};
+    if (call == ADAPT_CALL_CONV_FWD)                          // operands x (fa), w (fb)
+        return plan_fwd(dry, d, nullptr, fa, nullptr, fb, nullptr, ep, big, pads, p) == ADAPT_OK ? p.ws_end : kInvalid;
+    // operands dy (fa), w (fb) and x (fc; fb in a weight-gradient call)
+    const int which = call == ADAPT_CALL_CONV_DGRAD ? GRAD_DX : call == ADAPT_CALL_CONV_WGRAD ? GRAD_DW : GRAD_DX | GRAD_DW;
+    const adapt_fmt fx = call == ADAPT_CALL_CONV_BACKWARD ? fc : fb;
+    if (plan_gradients(dry, which, d, nullptr, fa, nullptr, fb, nullptr, fx, nullptr, ep, nullptr, ep, big, pads, p, pw) != ADAPT_OK) return kInvalid;
+    return std::max(p.ws_end, pw.ws_end);
 }
 
 }  // namespace
@@ -124,11 +83,12 @@ extern "C" size_t adapt_workspace_bytes(const adapt_ctx *ctx, const adapt_worksp
                                     q->fb.wl > 16, (uint64_t)q->M * q->N, false) + slack;
             }
             const int lda = q->lda ? q->lda : (q->transA ? q->M : q->K), ldb = q->ldb ? q->ldb : (q->transB ? q->K : q->N);
-            ContractArgs a = {};
-            fill_gemm(a, q->transA, q->transB, q->M, q->N, q->K, nullptr, q->fa, lda, nullptr, q->fb, ldb, nullptr, q->N);
+            PadJobs pads;
             ContractPlan p;
             const adapt_epilogue ep = {1, {8, 0}, {ADAPT_RN_HALF_UP, 0, 0}, 0};
-            if (plan_contraction<OP_GEMM>(&dry, a, q->fa, q->fb, ep, 0, p, (size_t)1 << 62) != ADAPT_OK) return kInvalid;
+            if (plan_gemm(&dry, q->transA, q->transB, q->M, q->N, q->K, nullptr, q->fa, lda, nullptr, q->fb, ldb, nullptr, q->N, ep, (size_t)1 << 62,
+                          pads, p) != ADAPT_OK)
+                return kInvalid;
             return p.ws_end + slack;
         }
         case ADAPT_CALL_CONV_FWD:

@@ -642,3 +642,44 @@ def test_config4_full_batch_launch_configurations():
 
 def test_config5_full_batch_launch_configurations():
     _full_batch_consistency(wk.resnet18_cifar_layers())
+
+
+# ---- operands whose rows are not whole 16-byte groups run on padded copies ---------------------------------------------
+@pytest.mark.parametrize("case", [
+    # n, h, w, c, k, r, s, stride, pad
+    (3, 9, 7, 17, 10, 3, 3, 1, 1),        # both channel numbers ragged
+    (2, 8, 8, 83, 48, 5, 5, 2, 2),
+    (5, 6, 5, 31, 122, 1, 1, 1, 0),
+    (2, 16, 15, 3, 10, 7, 7, 2, 3),       # 49 taps: only the weight gradient has a use for the copies
+    (4, 7, 7, 250, 16, 3, 3, 1, 1),
+])
+@pytest.mark.parametrize("wls", [(8, 8, 8), (12, 16, 9), (7, 13, 16)])
+def test_ragged_channels(case, wls):
+    _conv_all(case, *wls, extreme=True)
+    n, h, w, c, k, r, s, st, pad = case
+    d = ConvDesc(*case)
+    fx, fw, fdy = ((wl, wl - 3) for wl in wls)
+    x, wt, dy = (to_dev(codes(shape, wl, 7 + i, True)) for i, (shape, wl) in
+                 enumerate((((n, h, w, c), wls[0]), ((k, r, s, c), wls[1]), ((n, d.p, d.q, k), wls[2]))))
+    ex = Epilogue.exact()
+    dx, dw = ctx().conv_backward(d, dy, fdy, wt, fw, x, fx, ex, ex)
+    # a workspace that holds no copy, and one that holds some of them: the same results
+    for kib in (8, 24, 64):
+        small = pkg.Context(workspace_bytes=kib << 10)
+        assert torch.equal(small.conv_fwd(d, x, fx, wt, fw, ex), ctx().conv_fwd(d, x, fx, wt, fw, ex)), kib
+        dx2, dw2 = small.conv_backward(d, dy, fdy, wt, fw, x, fx, ex, ex)
+        assert torch.equal(dx, dx2) and torch.equal(dw, dw2), kib
+        torch.cuda.synchronize()
+        small.close()
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("m,n,k", [(37, 29, 19), (64, 33, 80), (130, 48, 97)])
+@pytest.mark.parametrize("gap", [0, 5])
+def test_gemm_ragged_rows(ta, tb, m, n, k, gap):
+    a, b = codes((k, m + gap) if ta else (m, k + gap), 12, 1, True), codes((n, k + gap) if tb else (k, n + gap), 8, 2, True)
+    ad, bd = to_dev(a)[:, :a.shape[1] - gap], to_dev(b)[:, :b.shape[1] - gap]      # leading dimension beyond the rows' codes
+    want = (a[:, :a.shape[1] - gap].T if ta else a[:, :a.shape[1] - gap]).astype(np.int64) @ \
+        (b[:, :b.shape[1] - gap].T if tb else b[:, :b.shape[1] - gap]).astype(np.int64)
+    got = ctx().fxp_gemm(ad, (12, 9), bd, (8, 5), Epilogue.exact(), bool(ta), bool(tb))
+    assert np.array_equal(host(got).astype(np.int64), want)
