@@ -744,6 +744,113 @@ __device__ __forceinline__ void emit_run(const ContractArgs &a, void *out, int m
 }
 
 // ---------------------------------------------------------------------------------------------
+// A wavefront's accumulators to the output: MB x NB blocks of 32 x 32, NW wavefronts per block; rows[j] is the output row of
+// the lane in block row j, ncol0 the first column of the wavefront's tile, kpad the reduction length with its padding, lin the
+// block's number in its contraction.  `smem` is free for the wavefronts of the block once they have all arrived.
+// ---------------------------------------------------------------------------------------------
+template <int LIMBS, int LAL, int LBL, bool OFFS, bool W_R, int MB, int NB, int NW, bool AMAX>
+__device__ __forceinline__ void contract_epilogue(const ContractArgs &a, const v16i (&acc_hh)[NB][MB], const v16i (&acc_x)[NB][MB],
+                                                  const v16i (&acc_ll)[NB][MB], const int (&sum_m)[MB], const int (&sum_n)[NB], char *const smem,
+                                                  const int (&rows)[MB], const int ncol0, const long long kpad, void *out, const unsigned lin)
+{
+    constexpr bool BOTH2 = LAL == 2 && LBL == 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, g = lane >> 5;
+    const int wrow = W_R ? l32 : 16 * ((l32 >> 2) & 1) + 4 * (l32 >> 3) + (l32 & 3);
+    // lane holds, for block (i,j): m = rows[j] and 16 values of n (see contract_body)
+    long long corr_m[MB];
+    int *sn = reinterpret_cast<int *>(smem);          // [NW][NB][32] n-side sums
+    if (OFFS) {
+        __syncthreads();                              // the tiles are no longer read
+#pragma unroll
+        for (int j = 0; j < MB; ++j) corr_m[j] = (long long)(sum_m[j] + __shfl_xor(sum_m[j], 32, 64));
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int t = sum_n[i] + __shfl_xor(sum_n[i], 32, 64);
+            if (g == 0) sn[(wave * NB + i) * 32 + wrow] = t;
+        }
+        __syncthreads();
+    }
+    unsigned long long vmax = 0;                      // largest magnitude of this lane's outputs (exact modes, when asked for)
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            long long v[16];
+            // a.fast: the host has checked the bound that lets a two-limb sum take one of the 32-bit forms
+            const bool pair_form = BOTH2 && !OFFS && a.fast, i32_form = LIMBS == 2 && !BOTH2 && !OFFS && a.fast;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (LIMBS == 1) {
+                    v[r] = acc_hh[i][j][r];
+                } else if (pair_form) {
+                    const int u = (acc_hh[i][j][r] << 8) + acc_x[i][j][r] + (acc_ll[i][j][r] >> 8);
+                    v[r] = ((long long)u << 32) | (uint32_t)(acc_ll[i][j][r] & 255);
+                } else if (i32_form) {
+                    v[r] = (long long)((acc_hh[i][j][r] << 8) + acc_x[i][j][r]);
+                } else {
+                    if (BOTH2) v[r] = ((long long)acc_hh[i][j][r] << 16) + ((long long)acc_x[i][j][r] << 8) + (long long)acc_ll[i][j][r];
+                    else v[r] = ((long long)acc_hh[i][j][r] << 8) + (long long)acc_x[i][j][r];
+                    if (OFFS) {
+                        const int nl = W_R ? 8 * (r >> 2) + 4 * g + (r & 3) : 16 * g + r;
+                        const long long s_n = sn[(wave * NB + i) * 32 + nl];
+                        // one side with one limb: the other side's sums are zero and never enter
+                        v[r] += BOTH2 ? 128 * (corr_m[j] + s_n) + 16384 * kpad : 128 * (LBL == 2 ? corr_m[j] : s_n);
+                    }
+                }
+            }
+            long long w[16];
+            if constexpr (W_R) {
+                // lanes l and l^32 hold interleaved runs of 4 of the same output row: swap halves
+                // so that each ends up with 16 consecutive n (lane/32 = 0: n 0..15, 1: n 16..31)
+                long long recv[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const long long low = v[t], high = v[8 + t];      // (loads in the arms of a conditional would keep v in memory)
+                    const long long send = g == 0 ? high : low;
+                    const int lo = __shfl_xor((int)(uint32_t)send, 32, 64);
+                    const int hi = LIMBS == 1 ? (lo >> 31) : __shfl_xor((int)(send >> 32), 32, 64);
+                    recv[t] = ((long long)hi << 32) | (uint32_t)lo;
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const long long v0 = v[t], v4 = v[4 + t], v8 = v[8 + t], v12 = v[12 + t], r0 = recv[t], r4 = recv[4 + t];
+                    w[t] = g == 0 ? v0 : r0;
+                    w[4 + t] = g == 0 ? r0 : v8;
+                    w[8 + t] = g == 0 ? v4 : r4;
+                    w[12 + t] = g == 0 ? r4 : v12;
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 16; ++t) w[t] = v[t];
+            }
+            const int m = rows[j], nn = ncol0 + i * 32 + 16 * g;
+            if (LIMBS == 1) emit_run<16, FORM_I32, AMAX>(a, out, m, nn, w, vmax);
+            else if (pair_form) emit_run<16, FORM_PAIR, AMAX>(a, out, m, nn, w, vmax);
+            else if (i32_form) emit_run<16, FORM_I32, AMAX>(a, out, m, nn, w, vmax);
+            else emit_run<16, FORM_I64, AMAX>(a, out, m, nn, w, vmax);
+        }
+    if constexpr (AMAX) {
+        unsigned long long *sm = reinterpret_cast<unsigned long long *>(smem);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const unsigned long long o = __shfl_xor(vmax, off, 64);
+            vmax = o > vmax ? o : vmax;
+        }
+        __syncthreads();                              // every wavefront has left the main loop: the tiles are free
+        if (lane == 0) sm[wave] = vmax;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long m = sm[0];
+#pragma unroll
+            for (int i = 1; i < NW; ++i) m = sm[i] > m ? sm[i] : m;
+            if (a.amax_part != nullptr && lin < a.amax_cap) a.amax_part[lin] = m;
+            if (lin == 0 && a.amax_zero != nullptr) *a.amax_zero = 0;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // the kernel: block tile BM x BN, 4 wavefronts in a WGM x WGN grid, wave tile (BM/WGM) x (BN/WGN)
 // built from 32x32 MFMA blocks; BKT reduction indices per stage.  One LDS stage: the global
 // loads of the next stage are in flight (in registers) while the MFMAs of the current one
@@ -1053,103 +1160,12 @@ __device__ __forceinline__ void contract_body(const ContractArgs &a, const unsig
     }
 
     // ---- epilogue -----------------------------------------------------------------------------
-    // lane holds, for block (i,j): m = m0 + wm*WM + j*32 + l32 and 16 values of n (see above)
-    long long corr_m[MB];
-    int *sn = reinterpret_cast<int *>(smem);          // [4 waves][NB][32] n-side sums
-    if (OFFS) {
-        __syncthreads();                              // the tiles are no longer read
+    int rows[MB];
 #pragma unroll
-        for (int j = 0; j < MB; ++j) corr_m[j] = (long long)(sum_m[j] + __shfl_xor(sum_m[j], 32, 64));
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int t = sum_n[i] + __shfl_xor(sum_n[i], 32, 64);
-            if (g == 0) sn[(wave * NB + i) * 32 + wrow] = t;
-        }
-        __syncthreads();
-    }
-    const long long kpad = (long long)ksteps * BKT;
-    void *out = static_cast<char *>(a.out) + (long long)split * a.slab_bytes;
-    unsigned long long vmax = 0;                      // largest magnitude of this lane's outputs (exact modes, when asked for)
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            int m_of = 0, nb_of = 0;
-            long long v[16];
-            // a.fast: the host has checked the bound that lets a two-limb sum take one of the 32-bit forms
-            const bool pair_form = BOTH2 && !OFFS && a.fast, i32_form = LIMBS == 2 && !BOTH2 && !OFFS && a.fast;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (LIMBS == 1) {
-                    v[r] = acc_hh[i][j][r];
-                } else if (pair_form) {
-                    const int u = (acc_hh[i][j][r] << 8) + acc_x[i][j][r] + (acc_ll[i][j][r] >> 8);
-                    v[r] = ((long long)u << 32) | (uint32_t)(acc_ll[i][j][r] & 255);
-                } else if (i32_form) {
-                    v[r] = (long long)((acc_hh[i][j][r] << 8) + acc_x[i][j][r]);
-                } else {
-                    if (BOTH2) v[r] = ((long long)acc_hh[i][j][r] << 16) + ((long long)acc_x[i][j][r] << 8) + (long long)acc_ll[i][j][r];
-                    else v[r] = ((long long)acc_hh[i][j][r] << 8) + (long long)acc_x[i][j][r];
-                    if (OFFS) {
-                        const int nl = W_R ? 8 * (r >> 2) + 4 * g + (r & 3) : 16 * g + r;
-                        const long long s_n = sn[(wave * NB + i) * 32 + nl];
-                        // one side with one limb: the other side's sums are zero and never enter
-                        v[r] += BOTH2 ? 128 * (corr_m[j] + s_n) + 16384 * kpad : 128 * (LBL == 2 ? corr_m[j] : s_n);
-                    }
-                }
-            }
-            auto emit = [&](const long long (&vals)[16]) {
-                if (LIMBS == 1) emit_run<16, FORM_I32, AMAX>(a, out, m_of, nb_of + 16 * g, vals, vmax);
-                else if (pair_form) emit_run<16, FORM_PAIR, AMAX>(a, out, m_of, nb_of + 16 * g, vals, vmax);
-                else if (i32_form) emit_run<16, FORM_I32, AMAX>(a, out, m_of, nb_of + 16 * g, vals, vmax);
-                else emit_run<16, FORM_I64, AMAX>(a, out, m_of, nb_of + 16 * g, vals, vmax);
-            };
-            int m = m0 + wm * WM + j * 32 + l32;
-            const int nb0 = n0 + wn * WN + i * 32;
-            if (dg) m = dg_row[dg ? j : 0];                                  // class order -> row of dx
-            m_of = m; nb_of = nb0;
-            if constexpr (W_R) {
-                // lanes l and l^32 hold interleaved runs of 4 of the same output row: swap halves
-                // so that each ends up with 16 consecutive n (lane/32 = 0: n 0..15, 1: n 16..31)
-                long long recv[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const long long send = g == 0 ? v[8 + t] : v[t];
-                    const int lo = __shfl_xor((int)(uint32_t)send, 32, 64);
-                    const int hi = LIMBS == 1 ? (lo >> 31) : __shfl_xor((int)(send >> 32), 32, 64);
-                    recv[t] = ((long long)hi << 32) | (uint32_t)lo;
-                }
-                long long w[16];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    w[t] = g == 0 ? v[t] : recv[t];
-                    w[4 + t] = g == 0 ? recv[t] : v[8 + t];
-                    w[8 + t] = g == 0 ? v[4 + t] : recv[4 + t];
-                    w[12 + t] = g == 0 ? recv[4 + t] : v[12 + t];
-                }
-                emit(w);
-            } else {
-                emit(v);
-            }
-        }
-    if constexpr (AMAX) {
-        unsigned long long *sm = reinterpret_cast<unsigned long long *>(smem);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const unsigned long long o = __shfl_xor(vmax, off, 64);
-            vmax = o > vmax ? o : vmax;
-        }
-        __syncthreads();                              // every wavefront has left the main loop: the tiles are free
-        if (lane == 0) sm[wave] = vmax;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long m = sm[0];
-#pragma unroll
-            for (int i = 1; i < 4; ++i) m = sm[i] > m ? sm[i] : m;
-            if (a.amax_part != nullptr && lin < a.amax_cap) a.amax_part[lin] = m;
-            if (lin == 0 && a.amax_zero != nullptr) *a.amax_zero = 0;
-        }
-    }
+    for (int j = 0; j < MB; ++j) rows[j] = dg ? dg_row[dg ? j : 0] : m0 + wm * WM + j * 32 + l32;      // class order -> row of dx
+    contract_epilogue<LIMBS, LAL, LBL, OFFS, W_R, MB, NB, WGM * WGN, AMAX>(
+        a, acc_hh, acc_x, acc_ll, sum_m, sum_n, smem, rows, n0 + wn * WN, (long long)ksteps * BKT,
+        static_cast<char *>(a.out) + (long long)split * a.slab_bytes, lin);
 }
 
 // Two-limb 64x64 tiles: three accumulator sets and the staging registers land a few registers above what three
@@ -1319,17 +1335,18 @@ static hipError_t launch_bn(adapt_ctx *ctx, const ContractArgs &a, int splits, T
 template <int OP, int AMODE, int WMODE, int LM>
 static hipError_t launch_pipe2(adapt_ctx *ctx, const ContractArgs &a, int splits, TileShape t)
 {
-    if (t.pipe == 2) {
-        if (t.bm == 128) return launch_es<OP, 2, AMODE, WMODE, LM, LM, 128, 64, 2, 2, 64, 2>(ctx, a, splits);
-        return launch_es<OP, 2, AMODE, WMODE, LM, LM, 64, 128, 2, 2, 64, 2>(ctx, a, splits);
-    }
+    if constexpr (OP != OP_WGRAD)
+        if (t.pipe == 2) {
+            if (t.bm == 128) return launch_es<OP, 2, AMODE, WMODE, LM, LM, 128, 64, 2, 2, 64, 2>(ctx, a, splits);
+            return launch_es<OP, 2, AMODE, WMODE, LM, LM, 64, 128, 2, 2, 64, 2>(ctx, a, splits);
+        }
     return launch_es<OP, 2, AMODE, WMODE, LM, LM, 128, 128, 2, 2, 64, 1>(ctx, a, splits);
 }
 
 template <int OP, int LIMBS, int AMODE, int WMODE>
 static hipError_t launch_tile(adapt_ctx *ctx, const ContractArgs &a, int splits, TileShape t)
 {
-    if constexpr (LIMBS == 2 && AMODE != LOAD_SCALAR && WMODE != LOAD_SCALAR && OP != OP_GEMM && OP != OP_WGRAD)
+    if constexpr (LIMBS == 2 && AMODE != LOAD_SCALAR && WMODE != LOAD_SCALAR && OP != OP_GEMM)
         if (t.pipe) return a.balanced ? launch_pipe2<OP, AMODE, WMODE, 3>(ctx, a, splits, t) : launch_pipe2<OP, AMODE, WMODE, 2>(ctx, a, splits, t);
     if constexpr (AMODE == LOAD_SCALAR) {
         return launch_variant<OP, LIMBS, AMODE, WMODE, 128, 64, 2, 2, 64>(ctx, a, splits);
@@ -1474,13 +1491,85 @@ static int pick_split_tile(const ContractArgs &a, int limbs, int acc_bits, int n
         const double cost = operand * rounds / 10.7e12 + slab / 3.1e12 + (sp > 1 ? 5e-6 : 0.0) + epilogue;
         if (cost < best) { best = cost; best_splits = (int)sp; t.bm = bm; t.bn = bn; }
     }
+    // two int16 operands, large tiles: the double-buffered pipeline (128 -> 128 3x3 at 16 x 16, batch 256, <12,9>: both gradients
+    // 117.2 -> 106.5 us)
+    t.pipe = limbs == 2 && t.bm == 128 && t.bn == 128 && a.act_es == 2 && a.wgt_es == 2 ? 1 : 0;
     return best_splits;
+}
+
+// ---- the kernel on input patches (contract_halo.hpp) ----------------------------------------------
+enum { HALO_NONE = 0, HALO_256x128, HALO_128x64, HALO_TILES };
+constexpr int kHaloShape[HALO_TILES][3] = {{0, 0, 0}, {256, 128, 512}, {128, 64, 256}};      // rows, columns, threads
+constexpr int kHaloK = 64;       // channels of a chunk
+
+constexpr int halo_row_bytes(int limbs) { return kHaloK * limbs + 16; }
+// one stage of filters: forward [columns][64 codes per limb + 16], data gradient [limb][64 lines][columns + 16]
+constexpr int halo_b_bytes(int op, int limbs, int bn) { return op == OP_FWD ? bn * halo_row_bytes(limbs) : limbs * kHaloK * (bn + 16); }
+
+// most pixels a patch of bm output rows has: whole rows of the output image, halo rows for every image they touch
+static int halo_pixels(int bm, int oh, int ow, int r, int s)
+{
+    const bool whole = bm % ow == 0;
+    const int rows = whole ? bm / ow : (bm - 2) / ow + 2;
+    const int images = whole && rows % oh == 0 ? rows / oh : whole && oh % rows == 0 ? 1 : (rows + oh - 2) / oh + 1;
+    return (rows + images * (r - 1)) * (ow + s - 1);
+}
+template <int OP>
+static size_t halo_lds(const ContractArgs &a, int tile)
+{
+    const int la = a.act_es, lb = a.wgt_es;      // limbs: int8 one, int16 two
+    const int pix = OP == OP_FWD ? halo_pixels(kHaloShape[tile][0], a.p, a.q, a.r, a.s) : halo_pixels(kHaloShape[tile][0], a.h, a.w, a.r, a.s);
+    return 2 * ((size_t)pix * halo_row_bytes(la) + halo_b_bytes(OP, lb, kHaloShape[tile][1]));
+}
+// The tile for a contraction, or HALO_NONE where the kernels above are at least as fast.  Times in us, forward at <12,9> unless
+// said otherwise, kernels above -> 256 x 128 / 128 x 64 tiles:
+//   256 x 16 x 16 x 128 -> 128  53.6 -> 38.7 / 47.1    8 x 12 bits  35.9 -> 26.4 / 30.5     data gradient  57.8 -> 40.4 / 48.8
+//   256 x 32 x 32 x 64 -> 64    55.9 -> 78.6 / 49.5    8 x 12 bits  38.4 -> 66.6 / 33.9
+//   256 x 8 x 8 x 256 -> 256    43.1 -> 53.1 / 40.4    8 x 12 bits  34.5 -> 38.4 / 28.3
+//   128 x 16 x 16 x 64 -> 192   24.9 -> 23.4 / 23.4    8 x 12 bits  18.4 -> 19.0 / 14.9
+//   128 x 8 x 8 x 256 -> 256    29.3 -> 53.0 / 28.9    8 x 12 bits  20.9 -> 38.0 / 22.5   (128 x 64 tiles: one block per CU)
+//   256 x 4 x 4 x 512 -> 512    55.1 ->    - / 61.5    (2.25 patch pixels per output)
+// One limb gains 5 % at most (19.9 -> 19.0) and two operands of 16 bits, whose offset sums do not fit the large tile's
+// registers, 6 % (71.0 -> 66.9) where there are tiles enough.
+template <int OP>
+static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
+{
+    const int taps = a.r * a.s, ch = OP == OP_FWD ? a.c : a.k;
+    if (limbs != 2 || a.stride != 1 || taps < 4 || taps > 32 || ch % kHaloK != 0 || a.act_load != LOAD_VEC) return HALO_NONE;
+    if (a.wgt_load != (OP == OP_FWD ? LOAD_VEC : LOAD_ROWS)) return HALO_NONE;
+    if (OP == OP_DGRAD && (a.pad > a.r - 1 || a.pad > a.s - 1)) return HALO_NONE;
+    auto tiles = [&](int t) {
+        return (long long)((a.M + kHaloShape[t][0] - 1) / kHaloShape[t][0]) * ((a.N + kHaloShape[t][1] - 1) / kHaloShape[t][1]);
+    };
+    auto fits = [&](int t, int lds_limit) {
+        const int bm = kHaloShape[t][0];
+        const int pix = OP == OP_FWD ? halo_pixels(bm, a.p, a.q, a.r, a.s) : halo_pixels(bm, a.h, a.w, a.r, a.s);
+        // a chunk's patch is written in one share of the block's threads per tap but the last
+        return halo_lds<OP>(a, t) <= (size_t)lds_limit && pix * (kHaloK / 16) <= (taps - 1) * kHaloShape[t][2] && 4 * pix <= 7 * bm;
+    };
+    const bool offset16 = a.act_es == 2 && a.wgt_es == 2 && !a.balanced;
+    // rounds of resident blocks (256 x 128 tiles: one block per CU, 128 x 64: two); a last, partly filled round takes at least a
+    // third of a whole one
+    auto rounds = [&](int t, int per_cu) {
+        const double r = (double)tiles(t) / (per_cu * num_cu), whole = std::floor(r);
+        return r > whole ? whole + 0.35 + 0.65 * (r - whole) : whole;
+    };
+    // relative times: a whole round of the large tiles 2.0, of the small ones 1.2
+    const double large = rounds(HALO_256x128, 1), small = rounds(HALO_128x64, 2), ideal = (double)tiles(HALO_128x64) / (2 * num_cu);
+    if (!offset16 && 2.0 * large <= 1.2 * small && large >= 0.93 && fits(HALO_256x128, 160 * 1024)) return HALO_256x128;
+    // one chunk of int16 activations against int8 filters: the patch's way into LDS is the longer part (256 x 12 x 11 x 64 -> 192,
+    // 16 x 8 bits 24.5 -> 26.2)
+    if (OP == OP_FWD && a.act_es == 2 && a.wgt_es == 1 && ch == kHaloK) return HALO_NONE;
+    // (a nearly empty last round: 528 tiles, data gradient of 128 x 12 x 11 x 256 -> 64, 8 x 16 bits 20.4 -> 23.8)
+    if (ideal >= (offset16 ? 1.5 : 1.0) && ideal >= 0.85 * small && fits(HALO_128x64, 80 * 1024)) return HALO_128x64;
+    return HALO_NONE;
 }
 
 // A contraction planned on the host: what the kernel gets, and what finish_kernel gets when K is
 // split across blocks (exact partial sums in workspace slabs) because a single block could overflow
 // its int32 accumulators or because the output has too few tiles to fill the GPU.
 struct ContractPlan {
+    int halo;               // tile of the kernel on input patches (contract_halo.hpp), or HALO_NONE
     ContractArgs kern;      // arguments of the contraction kernel (final output, or slabs)
     ContractArgs fin;       // arguments of finish_kernel (splits > 1)
     TileShape tile;
@@ -1521,6 +1610,7 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
         if (fa.wl > 8 && fb.wl > 8) a.fast = a.shift >= 1 && a.shift <= 16 && kbits + mag <= 38;      // (u, low byte) form
         else a.fast = a.shift >= 1 && kbits + mag <= 30;                                                // fits 32 bits
     }
+    p.halo = HALO_NONE;
     p.limbs = limbs;
     p.bits = bits;
     p.empty = a.M == 0 || a.N == 0;
@@ -1587,6 +1677,7 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
         a.out_mode = final_mode;
         arm(a);
         p.kern = a;
+        if constexpr (OP == OP_FWD || OP == OP_DGRAD) p.halo = halo_tile<OP>(a, limbs, ctx->num_cu);
         return ADAPT_OK;
     }
     // a partial sum is bounded like the total, so the slabs use the total's accumulator type
@@ -1636,10 +1727,17 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
 // the stride-2 data gradient in class order: its kernel instances are compiled in a file of their own (contract_dgrad_s2.hip)
 hipError_t launch_planned_dgrad_s2(adapt_ctx *ctx, const ContractPlan &p);
 
+hipError_t launch_halo_fwd(adapt_ctx *ctx, const ContractPlan &p);
+hipError_t launch_halo_dgrad(adapt_ctx *ctx, const ContractPlan &p);
+
 template <int OP>
 static hipError_t launch_planned(adapt_ctx *ctx, const ContractPlan &p)
 {
     if (p.empty) return hipSuccess;
+    if constexpr (OP == OP_FWD)
+        if (p.halo) return launch_halo_fwd(ctx, p);
+    if constexpr (OP == OP_DGRAD)
+        if (p.halo) return launch_halo_dgrad(ctx, p);
     if constexpr (OP == OP_DGRAD)
         if (p.kern.dg_classes) return launch_planned_dgrad_s2(ctx, p);
     return p.limbs == 1 ? launch_modes<OP, 1>(ctx, p.kern, p.splits, p.tile) : launch_modes<OP, 2>(ctx, p.kern, p.splits, p.tile);

@@ -643,6 +643,46 @@ def test_config4_full_batch_launch_configurations():
 def test_config5_full_batch_launch_configurations():
     _full_batch_consistency(wk.resnet18_cifar_layers())
 
+# ---- stride-1 convolutions on input patches in LDS: large tiles (256 x 128) and small ones (128 x 64) ------------------
+PATCH_CASES = [
+    # n, h, w, c, k, r, s, pad, wl_x, wl_w        tile; what is at its edge
+    (256, 16, 16, 64, 128, 3, 3, 1, 12, 12),      # large; one chunk of channels, tiles are whole samples
+    (256, 16, 16, 128, 128, 3, 3, 1, 8, 13),      # large; two chunks
+    (256, 16, 16, 128, 128, 3, 3, 1, 16, 8),
+    (240, 16, 17, 64, 112, 3, 3, 1, 15, 9),       # large; rows and samples that tiles cut anywhere, columns beyond N, a last tile of 0 rows
+    (171, 19, 20, 64, 128, 3, 3, 0, 9, 16),       # large; no padding: the output is smaller than the input
+    (64, 32, 32, 64, 128, 5, 5, 2, 12, 12),       # large; 25 taps, the largest patch
+    (256, 16, 16, 64, 128, 3, 3, 2, 12, 6),       # (padding beyond the filter's reach in the data gradient is not taken there)
+    (64, 32, 32, 64, 64, 3, 3, 1, 12, 12),        # small; rows of one sample
+    (256, 8, 8, 192, 256, 3, 3, 1, 12, 12),       # small; two samples per tile, three chunks
+    (96, 32, 32, 64, 64, 3, 3, 1, 16, 16),        # small; offset split of both operands
+    (96, 32, 32, 128, 48, 3, 3, 1, 16, 7),
+    (96, 32, 32, 64, 64, 3, 3, 1, 5, 16),
+]
+
+
+@pytest.mark.parametrize("case", PATCH_CASES)
+def test_convolutions_on_patches(case):
+    n, h, w, c, k, r, s, pad, wlx, wlw = case
+    d = ConvDesc(n, h, w, c, k, r, s, 1, pad)
+    fx, fw = (wlx, wlx - 3), (wlw, wlw - 3)
+    x, wt, dy = codes((n, h, w, c), wlx, 1, True), codes((k, r, s, c), wlw, 2, True), codes((n, d.p, d.q, k), wlx, 3, True)
+    sh = wlx - 3 + wlw - 3 - (wlx - 4)
+    eps = [Epilogue.requant(wlx, wlx - 4, pkg.SR, 3, 40, relu=True), Epilogue.requant(wlx, wlx - 4, pkg.SR, 3, 41)]
+    xd, wd, dyd, ex = to_dev(x), to_dev(wt), to_dev(dy), Epilogue.exact()
+    y, yq = (host(ctx().conv_fwd(d, xd, fx, wd, fw, e)).astype(np.int64) for e in (ex, eps[0]))
+    # the data gradient of the layer with its channel numbers exchanged, so that both directions see the case's sizes
+    d2 = ConvDesc(n, h, w, k, c, r, s, 1, pad)
+    wt2, dy2 = codes((c, r, s, k), wlw, 4, True), codes((n, d2.p, d2.q, c), wlx, 5, True)
+    dx, dxq = (host(ctx().conv_dgrad(d2, to_dev(dy2), fx, to_dev(wt2), fw, e)).astype(np.int64) for e in (ex, eps[1]))
+    for i in _spread_samples(n, d.p * d.q):
+        want = co.conv_fwd(x[i:i + 1], wt, 1, pad)
+        assert np.array_equal(y[i:i + 1], want), i
+        assert np.array_equal(yq[i:i + 1], orc.requantize(want, sh, wlx, orc.SR, 3, 40, True, start=i * d.p * d.q * k)), i
+        want = co.conv_dgrad(dy2[i:i + 1], wt2, h, w, 1, pad)
+        assert np.array_equal(dx[i:i + 1], want), i
+        assert np.array_equal(dxq[i:i + 1], orc.requantize(want, sh, wlx, orc.SR, 3, 41, False, start=i * h * w * k)), i
+
 
 # ---- operands whose rows are not whole 16-byte groups run on padded copies ---------------------------------------------
 @pytest.mark.parametrize("case", [
