@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 RN_HALF_UP = 0
 SR = 1
@@ -53,7 +54,7 @@ class Epilogue(C.Structure):
 
     @staticmethod
     def requant(wl, fl, mode=SR, seed=0, stream=0, relu=False):
-        return Epilogue(0, Fmt(wl, fl), Rng(mode, seed, stream), int(relu))
+        return Epilogue(0, _fmt((wl, fl)), Rng(mode, seed, stream), int(relu))
 
 
 class QuantizeItem(C.Structure):
@@ -156,15 +157,15 @@ def load_library():
     lib.adapt_reserve_workspace.argtypes = [vp, sz]
     lib.adapt_quantize.argtypes = [vp, vp, sz, Fmt, Rng, vp, vp, vp]
     lib.adapt_quantize_noalloc.argtypes = [vp, vp, sz, Fmt, Rng, vp, vp, vp]
-    lib.adapt_quantize_batched.argtypes = [vp, C.POINTER(QuantizeItem), i, i, u64, vp]
-    lib.adapt_quantize_batched_ranges.argtypes = [vp, C.POINTER(QuantizeItem), i, i, u64, vp, vp, u64]
+    lib.adapt_quantize_batched.argtypes = [vp, vp, i, i, u64, vp]
+    lib.adapt_quantize_batched_ranges.argtypes = [vp, vp, i, i, u64, vp, vp, u64]
     lib.adapt_fxp_gemm.argtypes = [vp, i, i, i, i, i, vp, Fmt, i, vp, Fmt, i, vp, i, Epilogue]
     for f in (lib.adapt_conv_fwd, lib.adapt_conv_dgrad, lib.adapt_conv_wgrad):
         f.argtypes = [vp, ConvDesc, vp, Fmt, vp, Fmt, vp, Epilogue]
     lib.adapt_conv_backward.argtypes = [vp, ConvDesc, vp, Fmt, vp, Fmt, vp, Fmt, vp, Epilogue, vp, Epilogue]
     lib.adapt_kld_precision_search.argtypes = [vp, vp, sz, i, i, i, i, dbl, dbl, Rng, vp, vp, vp, vp]
-    lib.adapt_kld_precision_search_batched.argtypes = [vp, C.POINTER(KldItem), i, i, i, dbl, dbl, i, u64, vp, vp]
-    lib.adapt_kld_precision_search_batched_ranged.argtypes = [vp, C.POINTER(KldItem), C.POINTER(C.c_void_p), i, i, i, dbl, dbl, i, u64,
+    lib.adapt_kld_precision_search_batched.argtypes = [vp, vp, i, i, i, dbl, dbl, i, u64, vp, vp]
+    lib.adapt_kld_precision_search_batched_ranged.argtypes = [vp, vp, C.POINTER(C.c_void_p), i, i, i, dbl, dbl, i, u64,
                                                               vp, vp]
     lib.adapt_kld_precision_search_ranged.argtypes = [vp, vp, sz, vp, i, i, i, i, dbl, dbl, Rng, vp, vp, vp, vp]
     lib.adapt_sgd_update_quantize.argtypes = [vp, vp, sz, vp, Fmt, vp, SgdParams, Fmt, Rng, vp, vp, vp]
@@ -212,7 +213,7 @@ def load_library():
     lib.adapt_net_forward.argtypes = [vp, vp, Rng]
     lib.adapt_net_backward.argtypes = [vp, vp, i, Rng]
     lib.adapt_net_update.argtypes = [vp, SgdParams, Rng]
-    lib.adapt_gradient_diversity.argtypes = [vp, C.POINTER(GradItem), i, sz, vp, vp]
+    lib.adapt_gradient_diversity.argtypes = [vp, vp, i, sz, vp, vp]
     lib.adapt_pushup_suggest.argtypes = [dbl, i, i, i, i, i, C.POINTER(PushupResult)]
     lib.adapt_strategy_next.argtypes = [i, dbl, dbl]
     lib.adapt_lookback_next.argtypes = [i, dbl, i, i, dbl]
@@ -277,7 +278,28 @@ def perf_step_memory(rows):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # the argument types are c_void_p
+
+
+_fmts = {}
+_U64 = (1 << 64) - 1
+
+
+def _fmt(f):
+    """The Fmt of a (wl, fl) pair.  Formats are few and passed by value, so one object per pair is kept."""
+    key = (int(f[0]), int(f[1]))
+    r = _fmts.get(key)
+    if r is None:
+        if len(_fmts) >= 4096:
+            _fmts.clear()
+        r = _fmts[key] = Fmt(*key)
+    return r
+
+
+# Descriptor arrays of the batched calls: the values of all items in order, packed at once.  Building one ctypes structure per item
+# costs more host time than the call (a window of 25 gradients 17 us, packed 7).
+def _pack(layout: str, count: int, values) -> bytes:
+    return struct.pack("=" + layout * count, *values) if count else bytes(struct.calcsize("=" + layout))
 
 
 def _check(status: int, where: str):
@@ -373,15 +395,15 @@ class Context:
             out = torch.empty(x.shape, dtype=self.storage_dtype(wl), device=x.device)
         if counters is None:
             counters = torch.empty(2, dtype=torch.int64, device=x.device)
-        _check(self._lib.adapt_quantize(self._h, _ptr(x), x.numel(), Fmt(wl, fl), Rng(mode, seed, stream), _ptr(out),
-                                        C.c_void_p(counters.data_ptr()), C.c_void_p(counters.data_ptr() + 8)),
+        _check(self._lib.adapt_quantize(self._h, _ptr(x), x.numel(), _fmt((wl, fl)), Rng(mode, seed, stream), _ptr(out),
+                                        counters.data_ptr(), counters.data_ptr() + 8),
                "adapt_quantize")
         return out, counters
 
     def quantize_noalloc(self, x, wl, fl, mode, seed, stream, out, counters):
         """adapt_quantize_noalloc: every buffer is the caller's (nothing is allocated here either)."""
-        _check(self._lib.adapt_quantize_noalloc(self._h, _ptr(x), x.numel(), Fmt(wl, fl), Rng(mode, seed, stream), _ptr(out),
-                                                C.c_void_p(counters.data_ptr()), C.c_void_p(counters.data_ptr() + 8)),
+        _check(self._lib.adapt_quantize_noalloc(self._h, _ptr(x), x.numel(), _fmt((wl, fl)), Rng(mode, seed, stream), _ptr(out),
+                                                counters.data_ptr(), counters.data_ptr() + 8),
                "adapt_quantize_noalloc")
         return out, counters
 
@@ -396,10 +418,10 @@ class Context:
             outs = [torch.empty(x.shape, dtype=self.storage_dtype(f[0]), device=x.device) for x, f in zip(xs, fmts)]
         if counters is None:
             counters = torch.empty(2 * max(n, 1), dtype=torch.int64, device=xs[0].device if n else "cuda")
-        items = (QuantizeItem * max(n, 1))()
-        for t in range(n):
-            items[t] = QuantizeItem(xs[t].data_ptr(), outs[t].data_ptr(), xs[t].numel(), fmts[t][0], fmts[t][1],
-                                    streams[t])
+        values = []
+        for x, q, f, st in zip(xs, outs, fmts, streams):
+            values += (x.data_ptr(), q.data_ptr(), x.numel(), f[0], f[1], st & _U64)
+        items = _pack("QQQiiQ", n, values)
         if ranges is None:
             _check(self._lib.adapt_quantize_batched(self._h, items, n, mode, seed, _ptr(counters)),
                    "adapt_quantize_batched")
@@ -428,7 +450,7 @@ class Context:
         m, k = (a.shape[1], a.shape[0]) if trans_a else a.shape
         k2, n = (b.shape[1], b.shape[0]) if trans_b else b.shape
         assert k == k2
-        fa, fb = Fmt(*fa), Fmt(*fb)
+        fa, fb = _fmt(fa), _fmt(fb)
         if out is None:
             out = self._out_tensor((m, n), k, fa, fb, ep, a.device)
         lda = a.stride(0) if a.numel() else max(a.shape[1], 1)      # empty tensors report stride 0
@@ -440,7 +462,7 @@ class Context:
 
     def conv_fwd(self, d: ConvDesc, x, fx, w, fw, ep, out=None):
         torch = self._torch
-        fx, fw = Fmt(*fx), Fmt(*fw)
+        fx, fw = _fmt(fx), _fmt(fw)
         if out is None:
             out = self._out_tensor((d.n, d.p, d.q, d.k), d.r * d.s * d.c, fx, fw, ep, x.device)
         _check(self._lib.adapt_conv_fwd(self._h, d, _ptr(x), fx, _ptr(w), fw, _ptr(out), ep), "adapt_conv_fwd")
@@ -448,7 +470,7 @@ class Context:
 
     def conv_dgrad(self, d: ConvDesc, dy, fdy, w, fw, ep, out=None):
         torch = self._torch
-        fdy, fw = Fmt(*fdy), Fmt(*fw)
+        fdy, fw = _fmt(fdy), _fmt(fw)
         if out is None:
             out = self._out_tensor((d.n, d.h, d.w, d.c), d.r * d.s * d.k, fdy, fw, ep, dy.device)
         _check(self._lib.adapt_conv_dgrad(self._h, d, _ptr(dy), fdy, _ptr(w), fw, _ptr(out), ep), "adapt_conv_dgrad")
@@ -456,7 +478,7 @@ class Context:
 
     def conv_wgrad(self, d: ConvDesc, dy, fdy, x, fx, ep, out=None):
         torch = self._torch
-        fdy, fx = Fmt(*fdy), Fmt(*fx)
+        fdy, fx = _fmt(fdy), _fmt(fx)
         if out is None:
             out = self._out_tensor((d.k, d.r, d.s, d.c), d.n * d.p * d.q, fdy, fx, ep, dy.device)
         _check(self._lib.adapt_conv_wgrad(self._h, d, _ptr(dy), fdy, _ptr(x), fx, _ptr(out), ep), "adapt_conv_wgrad")
@@ -465,7 +487,7 @@ class Context:
     def conv_backward(self, d: ConvDesc, dy, fdy, w, fw, x, fx, ep_dx, ep_dw, out_dx=None, out_dw=None):
         """Both gradients of a layer in one call; returns (dx, dw)."""
         torch = self._torch
-        fdy, fw, fx = Fmt(*fdy), Fmt(*fw), Fmt(*fx)
+        fdy, fw, fx = _fmt(fdy), _fmt(fw), _fmt(fx)
         if out_dx is None:
             out_dx = self._out_tensor((d.n, d.h, d.w, d.c), d.r * d.s * d.k, fdy, fw, ep_dx, dy.device)
         if out_dw is None:
@@ -520,9 +542,10 @@ class Context:
             kld = torch.empty((max(n, 1), ncand), dtype=torch.float64, device=dev)
         if sel is None:
             sel = torch.empty((max(n, 1), 2), dtype=torch.int32, device=dev)
-        items = (KldItem * max(n, 1))()
-        for t in range(n):
-            items[t] = KldItem(ws[t].data_ptr(), ws[t].numel(), ils[t], bins[t], streams[t])
+        values = []
+        for w, il, nb, st in zip(ws, ils, bins, streams):
+            values += (w.data_ptr(), w.numel(), il, nb, st & _U64)
+        items = _pack("QQiiQ", n, values)
         if ranges is None:
             _check(self._lib.adapt_kld_precision_search_batched(self._h, items, n, wl_lo, wl_hi, eps, alpha, mode, seed,
                                                                 _ptr(kld), _ptr(sel)), "adapt_kld_precision_search_batched")
@@ -550,11 +573,12 @@ class Context:
         if sums is None and want_sums:
             wide = any(f[0] > 16 for f in fmts)
             sums = torch.empty(2 * (count + 1) if wide else count + 2, dtype=torch.int64, device=dev)
-        items = (GradItem * max(count, 1))()
-        for k in range(count):
-            if gs[k].numel() != n:
+        values = []
+        for g, f in zip(gs, fmts):
+            if g.numel() != n:
                 raise ValueError("all gradients of a window have the same number of elements")
-            items[k] = GradItem(gs[k].data_ptr(), fmts[k][0], fmts[k][1])
+            values += (g.data_ptr(), f[0], f[1])
+        items = _pack("Qii", count, values)
         _check(self._lib.adapt_gradient_diversity(self._h, items, count, n, _ptr(sums), _ptr(out)),
                "adapt_gradient_diversity")
         return out, sums
@@ -573,7 +597,7 @@ class Context:
         if rng_range is None:
             rng_range = torch.empty(2, dtype=torch.float32, device=w.device)
         _check(self._lib.adapt_sgd_update_quantize(self._h, _ptr(w), w.numel(), _ptr(g), Fmt(*fg), _ptr(g_sumsq),
-                                                   SgdParams(lr, l1, l2), Fmt(wl, fl), Rng(mode, seed, stream), _ptr(out),
+                                                   SgdParams(lr, l1, l2), _fmt((wl, fl)), Rng(mode, seed, stream), _ptr(out),
                                                    _ptr(counters), _ptr(rng_range)), "adapt_sgd_update_quantize")
         return out, counters, rng_range
 
