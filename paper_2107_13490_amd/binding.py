@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import struct
+from operator import index
 
 RN_HALF_UP = 0
 SR = 1
@@ -287,7 +288,8 @@ _U64 = (1 << 64) - 1
 
 def _fmt(f):
     """The Fmt of a (wl, fl) pair.  Formats are few and passed by value, so one object per pair is kept."""
-    key = (int(f[0]), int(f[1]))
+    wl, fl = f
+    key = (index(wl), index(fl))
     r = _fmts.get(key)
     if r is None:
         if len(_fmts) >= 4096:

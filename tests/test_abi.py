@@ -122,3 +122,12 @@ def test_host_side_sizing_needs_no_gpu():
     g16 = lib.adapt_graph_workspace_bytes(nodes, 3, 0)
     assert 0 < g16 < lib.adapt_graph_workspace_bytes_wide(nodes, 3, 0, 32)
     assert lib.adapt_bn_state_bytes(64) >= 64 + 64 * 52 and lib.adapt_bn_state_bytes(0) == 0 and lib.adapt_bn_state_bytes(5000) == 0
+
+
+@pytest.mark.parametrize("bad", [(8.0, 6), (8, None), ("8", 6), (8, 6, 1)])
+def test_kept_formats_refuse_what_the_structure_refuses(bad):
+    from paper_2107_13490_amd import binding
+    with pytest.raises((TypeError, ValueError)):
+        binding._fmt(bad)
+    f = binding._fmt((8, 6))
+    assert (f.wl, f.fl) == (8, 6)
