@@ -2,14 +2,14 @@
 // distribution of a tensor and of its <WL_c, FL_c> quantizations, for all candidate word
 // lengths in one pass over the tensor.
 //
-// Four launches per search (per batch of searches in the batched form), all on the context's stream, no host round trip (kernel boundaries
+// Four launches per search (three for a tensor of up to 131,072 elements; per batch of searches in the batched form), all on the context's stream, no host round trip (kernel boundaries
 // order the phases; only the small final kernel uses a device-wide fence):
 //   range    per-block min / max of the finite elements.
 //   hist     every block first reduces the range partials and derives the bin grid (power-of-two
 //            width) and the per-candidate integer bin parameters (the "plan"; block 0 also stores
 //            it for the later kernels), then reads its share of the tensor once: reference bin +
 //            one bin per candidate for every element, counted in LDS histograms, and written to the block's own slab with plain stores.
-//   sum      blocks of (256 bins, row): add the slabs of one row.
+//   sum      blocks of (256 bins, row): add the slabs of one row (tensors with few slabs: done by the final launch).
 //   final    blocks of (256 bins, candidate): partial KL sums in fp64; the last block to finish adds
 //            the partial sums in a fixed order and picks the lowest WL with KL < eps.
 // All counts are integers, so the result does not depend on the order of accumulation.
