@@ -288,9 +288,10 @@ __device__ __forceinline__ uint32_t k_major_row(const ContractArgs &a, const int
         const uint32_t n = fdiv(pq, a.div_p), p = pq - n * a.p;
         const int ra = (int)p * a.stride - a.pad, rb = (int)q * a.stride - a.pad;
         base = ((n * (uint32_t)a.h + (uint32_t)ra) * (uint32_t)a.w + (uint32_t)rb) * (uint32_t)a.c;
-        // tap (r, s) reads x[ra + r][rb + s]: columns [-rb, w - rb) of the filter (at most 32 taps: shifts below 32, or 64-bit)
-        const int lo = min(max(-rb, 0), a.s), hi = max(min(a.w - rb, a.s), lo);
-        const uint32_t vs = (uint32_t)((1ull << hi) - (1ull << lo));
+        // tap (r, s) reads x[ra + r][rb + s].  (The columns' mask as a difference of two 64-bit shifts: 128 x 16 x 16 x 64 -> 192 3x3,
+        // 8 bits 10.6 -> 10.7 us; 37 x 15 x 11 x 48 -> 100 stride 2, 8 x 12 bits 7.45 -> 7.42)
+        uint32_t vs = 0;
+        for (int ss = 0; ss < a.s; ++ss) vs |= (uint32_t)((unsigned)(rb + ss) < (unsigned)a.w) << ss;
         uint32_t m = 0;
         for (int rr = 0; rr < a.r; ++rr)
             if ((unsigned)(ra + rr) < (unsigned)a.h) m |= vs << (rr * a.s);
