@@ -1920,17 +1920,11 @@ static int fill_fwd(ContractArgs &a, const adapt_conv_desc &d, const void *x, ad
 // A convolution's contractions as the library runs them: on padded copies where the channels ask for it and the workspace
 // holds them (fewer copies, then none, where it does not), else on the operands as they are.  `pads` are launched before the
 // plans.
-enum { PAD_C = 1, PAD_K = 2 };      // input channels (x, w), output channels (dy)
-static inline int conv_pads_wanted(const adapt_conv_desc &d, bool gradients)
-{
-    if (d.n <= 0) return 0;
-    return (d.c % 16 ? PAD_C : 0) | (gradients && d.k % 16 ? PAD_K : 0);
-}
 
 static int plan_fwd(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, adapt_fmt fx, const void *w, adapt_fmt fw, void *y, adapt_epilogue ep,
                     size_t ws_limit, PadJobs &pads, ContractPlan &p)
 {
-    if (conv_pads_wanted(d, false) && d.r * d.s <= 32) {
+    if (d.n > 0 && d.c % 16 != 0 && d.r * d.s <= 32) {
         pads = PadJobs{};
         ContractArgs a = {};
         size_t off = 0;
@@ -1956,52 +1950,54 @@ static int plan_gradients(adapt_ctx *ctx, int which, const adapt_conv_desc &d, c
                           const void *x, adapt_fmt fx, void *dx, adapt_epilogue ep_dx, void *dw, adapt_epilogue ep_dw, size_t ws_limit,
                           PadJobs &pads, ContractPlan &pd, ContractPlan &pw)
 {
-    const int wanted = conv_pads_wanted(d, true);
+    enum { PAD_X = 1, PAD_W = 2, PAD_DY = 4 };        // the operands that are copied
+    // the vector path of dy keeps one validity bit per filter tap and row: a data gradient beyond that has no use for copies
+    const bool dx_pads = (which & GRAD_DX) && d.r * d.s <= 32;
+    const bool c_ragged = d.n > 0 && d.c % 16 != 0, k_ragged = d.n > 0 && d.k % 16 != 0;
+    const int wanted = (c_ragged && (which & GRAD_DW) ? PAD_X : 0) | (c_ragged && dx_pads ? PAD_W : 0) |
+                       (k_ragged && (dx_pads || (which & GRAD_DW)) ? PAD_DY : 0);
     const size_t dy_rows = (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1);
-    const int attempts[4] = {wanted, wanted & PAD_C, wanted & PAD_K, 0};
+    const int attempts[4] = {wanted, wanted & ~PAD_DY, wanted & ~PAD_X, 0};
     int last = -1;
     for (int t = 0; t < 4; ++t) {
         const int use = attempts[t];
         if (use == last) continue;
         last = use;
-        // the vector path of dy keeps one validity bit per filter tap and row: a data gradient beyond that has no use for copies
-        const bool dx_pads = d.r * d.s <= 32;
-        if (use && !dx_pads && !(which & GRAD_DW)) continue;
         pads = PadJobs{};
         size_t off = 0;
         const void *dyp = dy, *xp = x, *wp = w;
         adapt_conv_desc dk = d;                       // dy's rows as they lie in memory
         bool ok = true;
-        if (use & PAD_K) {
+        if (use & PAD_DY) {
             dk.k = round_up16(d.k);
             ok = add_pad(ctx, pads, dy, storage_bytes(fdy), dy_rows, d.k, d.k, ws_limit, off, &dyp) == ADAPT_OK;
         }
-        if (ok && (use & PAD_C) && (which & GRAD_DW)) ok = add_pad(ctx, pads, x, storage_bytes(fx), (size_t)d.n * d.h * d.w, d.c, d.c, ws_limit, off, &xp) == ADAPT_OK;
-        if (ok && (use & PAD_C) && (which & GRAD_DX) && dx_pads) ok = add_pad(ctx, pads, w, storage_bytes(fw), (size_t)d.k * d.r * d.s, d.c, d.c, ws_limit, off, &wp) == ADAPT_OK;
+        if (ok && (use & PAD_X)) ok = add_pad(ctx, pads, x, storage_bytes(fx), (size_t)d.n * d.h * d.w, d.c, d.c, ws_limit, off, &xp) == ADAPT_OK;
+        if (ok && (use & PAD_W)) ok = add_pad(ctx, pads, w, storage_bytes(fw), (size_t)d.k * d.r * d.s, d.c, d.c, ws_limit, off, &wp) == ADAPT_OK;
         int s = ok ? ADAPT_OK : ADAPT_EWORKSPACE;
         if (s == ADAPT_OK && (which & GRAD_DX)) {
             ContractArgs a = {};
-            s = dx_pads ? fill_dgrad(a, dk, dyp, fdy, wp, fw, dx) : fill_dgrad(a, d, dy, fdy, w, fw, dx);
-            if ((use & PAD_C) && dx_pads) {                        // stride of the filter rows; the output keeps d.c columns
+            // The output channels appended to dy have no filter rows.  The vector loads check the filters' extent and read zeros
+            // there; the element-wise gather does not, so with gathered filters the data gradient takes dy as it is.
+            const bool dy_copy = (use & PAD_DY) && dx_pads && (d.c % 16 == 0 || (use & PAD_W));
+            s = fill_dgrad(a, dy_copy ? dk : d, dy_copy ? dyp : dy, fdy, wp, fw, dx);
+            if (use & PAD_W) {                                     // stride of the filter rows; the output keeps d.c columns
                 a.c = round_up16(d.c);
                 a.wgt_load = LOAD_ROWS;
             }
-            if (use && dx_pads) {
-                // the filter rows of appended output channels lie beyond the tensor and read as zero
-                a.wgt_bytes = (uint32_t)((long long)d.k * d.r * d.s * a.c * a.wgt_es);
-                a.k_bound = d.r * d.s * d.k;
-            }
+            a.wgt_bytes = (uint32_t)((long long)d.k * d.r * d.s * a.c * a.wgt_es);
+            a.k_bound = d.r * d.s * d.k;
             if (s == ADAPT_OK) s = plan_contraction<OP_DGRAD>(ctx, a, fdy, fw, ep_dx, off, pd, ws_limit);
         }
         if (s == ADAPT_OK && (which & GRAD_DW)) {
             ContractArgs a = {};
             adapt_conv_desc dw2 = dk;
-            if (use & PAD_C) dw2.c = round_up16(d.c);
+            if (use & PAD_X) dw2.c = round_up16(d.c);
             s = fill_wgrad(a, dw2, dyp, fdy, xp, fx, dw);
             a.M = d.k;                                // dw keeps its real rows; the appended ones are never written
-            if (use & PAD_C) a.force_finish = 1;      // the kernel fills slabs with the appended columns, finish_kernel picks the real ones
+            if (use & PAD_X) a.force_finish = 1;      // the kernel fills slabs with the appended columns, finish_kernel picks the real ones
             if (s == ADAPT_OK) s = plan_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep_dw, off, pw, ws_limit);
-            if (s == ADAPT_OK && (use & PAD_C) && !pw.empty) {
+            if (s == ADAPT_OK && (use & PAD_X) && !pw.empty) {
                 pw.fin.N = d.r * d.s * d.c;
                 pw.fin.ldc = pw.fin.N;
                 pw.fin.pad_c = d.c;
