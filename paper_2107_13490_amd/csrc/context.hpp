@@ -82,7 +82,8 @@ inline int hip_status(adapt_ctx *c, hipError_t e)
 }
 
 // A kernel that wants more than 64 KiB of dynamic LDS needs the limit raised once before its first launch;
-// the context remembers which kernels it has done that for (no process-wide state).
+// the context remembers which kernels it has done that for (no process-wide state).  lds_bytes is the most that any
+// launch of the kernel takes, the same in every call: the limit is the process's, and a context asks once.
 inline hipError_t allow_big_lds(adapt_ctx *c, const void *kernel, size_t lds_bytes)
 {
     if (lds_bytes <= 64 * 1024) return hipSuccess;

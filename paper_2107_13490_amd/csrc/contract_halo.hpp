@@ -278,7 +278,8 @@ static hipError_t launch_halo_as(adapt_ctx *ctx, const HaloArgs &h)
     static_assert(kHaloShape[TILE][2] == 64 * WGM * WGN, "threads of the tile");
     void (*kern)(const HaloArgs) = halo_kernel<OP, AES == 1 && WES == 1 ? 1 : 2, AES, WES, BM, BN, WGM, WGN, AMAX>;
     const size_t lds = halo_lds<OP>(h.a, TILE);
-    if (hipError_t e = allow_big_lds(ctx, reinterpret_cast<const void *>(kern), lds); e != hipSuccess) return e;
+    // a launch's LDS depends on the layer: the most that any layer takes is requested
+    if (hipError_t e = allow_big_lds(ctx, reinterpret_cast<const void *>(kern), kHaloMaxLds[TILE]); e != hipSuccess) return e;
     const unsigned tiles = (unsigned)((h.a.M + BM - 1) / BM) * (unsigned)((h.a.N + BN - 1) / BN);
     hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * WGM * WGN), lds, ctx->stream, h);
     note_amax_blocks(ctx, h.a, tiles);

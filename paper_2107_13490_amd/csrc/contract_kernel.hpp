@@ -1530,6 +1530,8 @@ static int pick_split_tile(const ContractArgs &a, int limbs, int acc_bits, int n
 // ---- the kernel on input patches (contract_halo.hpp) ----------------------------------------------
 enum { HALO_NONE = 0, HALO_256x128, HALO_128x64, HALO_TILES };
 constexpr int kHaloShape[HALO_TILES][3] = {{0, 0, 0}, {256, 128, 512}, {128, 64, 256}};      // rows, columns, threads
+// LDS that a block may take, by its patch: one block per CU, or two
+constexpr int kHaloMaxLds[HALO_TILES] = {0, 160 * 1024, 80 * 1024};
 constexpr int kHaloK = 64;       // channels of a chunk
 
 constexpr int halo_row_bytes(int limbs) { return kHaloK * limbs + 16; }
@@ -1571,11 +1573,11 @@ static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
     auto tiles = [&](int t) {
         return (long long)((a.M + kHaloShape[t][0] - 1) / kHaloShape[t][0]) * ((a.N + kHaloShape[t][1] - 1) / kHaloShape[t][1]);
     };
-    auto fits = [&](int t, int lds_limit) {
+    auto fits = [&](int t) {
         const int bm = kHaloShape[t][0];
         const int pix = OP == OP_FWD ? halo_pixels(bm, a.p, a.q, a.r, a.s) : halo_pixels(bm, a.h, a.w, a.r, a.s);
         // a chunk's patch is written in one share of the block's threads per tap but the last
-        return halo_lds<OP>(a, t) <= (size_t)lds_limit && pix * (kHaloK / 16) <= (taps - 1) * kHaloShape[t][2] && 4 * pix <= 7 * bm;
+        return halo_lds<OP>(a, t) <= (size_t)kHaloMaxLds[t] && pix * (kHaloK / 16) <= (taps - 1) * kHaloShape[t][2] && 4 * pix <= 7 * bm;
     };
     const bool offset16 = a.act_es == 2 && a.wgt_es == 2 && !a.balanced;
     // rounds of resident blocks (256 x 128 tiles: one block per CU, 128 x 64: two); a last, partly filled round takes at least a
@@ -1586,12 +1588,12 @@ static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
     };
     // relative times: a whole round of the large tiles 2.0, of the small ones 1.2
     const double large = rounds(HALO_256x128, 1), small = rounds(HALO_128x64, 2), ideal = (double)tiles(HALO_128x64) / (2 * num_cu);
-    if (!offset16 && 2.0 * large <= 1.2 * small && large >= 0.93 && fits(HALO_256x128, 160 * 1024)) return HALO_256x128;
+    if (!offset16 && 2.0 * large <= 1.2 * small && large >= 0.93 && fits(HALO_256x128)) return HALO_256x128;
     // one chunk of int16 activations against int8 filters: the patch's way into LDS is the longer part (256 x 12 x 11 x 64 -> 192,
     // 16 x 8 bits 24.5 -> 26.2)
     if (OP == OP_FWD && a.act_es == 2 && a.wgt_es == 1 && ch == kHaloK) return HALO_NONE;
     // (a nearly empty last round: 528 tiles, data gradient of 128 x 12 x 11 x 256 -> 64, 8 x 16 bits 20.4 -> 23.8)
-    if (ideal >= (offset16 ? 1.5 : 1.0) && ideal >= 0.85 * small && fits(HALO_128x64, 80 * 1024)) return HALO_128x64;
+    if (ideal >= (offset16 ? 1.5 : 1.0) && ideal >= 0.85 * small && fits(HALO_128x64)) return HALO_128x64;
     return HALO_NONE;
 }
 
