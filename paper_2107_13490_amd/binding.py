@@ -283,13 +283,11 @@ def _ptr(t):
 
 
 _fmts = {}
-_U64 = (1 << 64) - 1
 
 
 def _fmt(f):
     """The Fmt of a (wl, fl) pair.  Formats are few and passed by value, so one object per pair is kept."""
-    wl, fl = f
-    key = (index(wl), index(fl))
+    key = (*map(index, f),)
     r = _fmts.get(key)
     if r is None:
         if len(_fmts) >= 4096:
@@ -299,9 +297,16 @@ def _fmt(f):
 
 
 # Descriptor arrays of the batched calls: the values of all items in order, packed at once.  Building one ctypes structure per item
-# costs more host time than the call (a window of 25 gradients 17 us, packed 7).
-def _pack(layout: str, count: int, values) -> bytes:
-    return struct.pack("=" + layout * count, *values) if count else bytes(struct.calcsize("=" + layout))
+# costs more host time than the call (a window of 25 gradients 17 us, packed 7).  What does not pack (a negative stream, a word
+# length that is no integer or longer than its field) goes into the structures, which wrap or refuse it.
+def _items(cls, layout: str, count: int, values):
+    if not count:
+        return bytes(C.sizeof(cls))
+    try:
+        return struct.pack("=" + layout * count, *values)
+    except struct.error:
+        width = len(layout)
+        return (cls * count)(*(cls(*values[t * width:(t + 1) * width]) for t in range(count)))
 
 
 def _check(status: int, where: str):
@@ -421,9 +426,10 @@ class Context:
         if counters is None:
             counters = torch.empty(2 * max(n, 1), dtype=torch.int64, device=xs[0].device if n else "cuda")
         values = []
-        for x, q, f, st in zip(xs, outs, fmts, streams):
-            values += (x.data_ptr(), q.data_ptr(), x.numel(), f[0], f[1], st & _U64)
-        items = _pack("QQQiiQ", n, values)
+        for t in range(n):
+            f = fmts[t]
+            values += (xs[t].data_ptr(), outs[t].data_ptr(), xs[t].numel(), f[0], f[1], streams[t])
+        items = _items(QuantizeItem, "QQQiiQ", n, values)
         if ranges is None:
             _check(self._lib.adapt_quantize_batched(self._h, items, n, mode, seed, _ptr(counters)),
                    "adapt_quantize_batched")
@@ -545,9 +551,9 @@ class Context:
         if sel is None:
             sel = torch.empty((max(n, 1), 2), dtype=torch.int32, device=dev)
         values = []
-        for w, il, nb, st in zip(ws, ils, bins, streams):
-            values += (w.data_ptr(), w.numel(), il, nb, st & _U64)
-        items = _pack("QQiiQ", n, values)
+        for t in range(n):
+            values += (ws[t].data_ptr(), ws[t].numel(), ils[t], bins[t], streams[t])
+        items = _items(KldItem, "QQiiQ", n, values)
         if ranges is None:
             _check(self._lib.adapt_kld_precision_search_batched(self._h, items, n, wl_lo, wl_hi, eps, alpha, mode, seed,
                                                                 _ptr(kld), _ptr(sel)), "adapt_kld_precision_search_batched")
@@ -576,11 +582,12 @@ class Context:
             wide = any(f[0] > 16 for f in fmts)
             sums = torch.empty(2 * (count + 1) if wide else count + 2, dtype=torch.int64, device=dev)
         values = []
-        for g, f in zip(gs, fmts):
+        for k in range(count):
+            g, f = gs[k], fmts[k]
             if g.numel() != n:
                 raise ValueError("all gradients of a window have the same number of elements")
             values += (g.data_ptr(), f[0], f[1])
-        items = _pack("Qii", count, values)
+        items = _items(GradItem, "Qii", count, values)
         _check(self._lib.adapt_gradient_diversity(self._h, items, count, n, _ptr(sums), _ptr(out)),
                "adapt_gradient_diversity")
         return out, sums

@@ -131,3 +131,48 @@ def test_kept_formats_refuse_what_the_structure_refuses(bad):
         binding._fmt(bad)
     f = binding._fmt((8, 6))
     assert (f.wl, f.fl) == (8, 6)
+
+
+def test_batched_descriptors_are_those_of_the_structures():
+    import numpy as np
+    import torch
+    from paper_2107_13490_amd import binding as b
+
+    class Recorder:
+        def __getattr__(self, name):
+            return lambda h, items, *rest: (setattr(self, "items", bytes(items)), 0)[1]
+
+    cx = b.Context.__new__(b.Context)
+    cx._lib, cx._torch, cx._h = Recorder(), torch, None
+    ts = [torch.zeros(4 + t) for t in range(3)]
+    kw = dict(outs=ts, counters=torch.zeros(6, dtype=torch.int64))
+
+    def check(cls, rows):
+        got = (cls * len(rows)).from_buffer_copy(cx._lib.items)
+        for g, row in zip(got, rows):
+            want = cls(*row)
+            assert [getattr(g, f) for f, _ in cls._fields_] == [getattr(want, f) for f, _ in cls._fields_]
+    # what the fields take: plain and numpy integers, negative and oversized ones (they wrap)
+    for streams in ([1, 2, 3], np.arange(3), list(np.arange(3, dtype=np.uint64)), [-1, 1 << 64, 5], torch.arange(3)):
+        for wl in (8, np.int32(8), (1 << 32) + 8):
+            cx.quantize_batched(ts, [(wl, 5)] * 3, streams, **kw)
+            check(b.QuantizeItem, [(t.data_ptr(), t.data_ptr(), t.numel(), wl, 5, s) for t, s in zip(ts, streams)])
+        kld, sel = torch.zeros(3, 15, dtype=torch.float64), torch.zeros(3, 2, dtype=torch.int32)
+        cx.kld_precision_search_batched(ts, [2, 2, 2], [64, np.int64(65), 66], streams, 2, 16, 0.1, kld=kld, sel=sel)
+        check(b.KldItem, [(t.data_ptr(), t.numel(), 2, 64 + i, s) for i, (t, s) in enumerate(zip(ts, streams))])
+    same = [ts[0]] * 2
+    cx.gradient_diversity(same, [(8, 5), (np.int64(9), -1)], sums=ts[0], out=ts[0])
+    check(b.GradItem, [(ts[0].data_ptr(), 8, 5), (ts[0].data_ptr(), 9, -1)])
+    cx.quantize_batched([], [], [], counters=ts[0])
+    assert cx._lib.items == bytes(40)
+    # and what they refuse
+    for bad in ((8.5, 5), (8, "5"), (None, 5)):
+        with pytest.raises(TypeError):
+            cx.quantize_batched(ts, [bad] * 3, [1, 2, 3], **kw)
+        with pytest.raises(TypeError):
+            cx.gradient_diversity(same, [bad] * 2, sums=ts[0], out=ts[0])
+    for call in (lambda: cx.quantize_batched(ts, [(8, 5)] * 3, [1, 2], **kw), lambda: cx.quantize_batched(ts, [(8, 5)] * 2, [1, 2, 3], **kw),
+                 lambda: cx.gradient_diversity(same, [(8, 5)], sums=ts[0], out=ts[0])):
+        with pytest.raises(IndexError):
+            call()
+    assert (b._fmt((8,)).wl, b._fmt((8,)).fl) == (8, 0) and b._fmt(np.array([9, 4])).fl == 4
