@@ -292,7 +292,8 @@ __global__ void zero_words_kernel(uint32_t *p, size_t n)
 // slabs[block][row][bins] with plain stores: device-wide atomics on shared counters are far
 // slower than that on this GPU.  USE_LDS = false (bins too large for LDS) counts with atomics
 // straight into the block's slab, which the host has cleared.
-template <bool USE_LDS, bool WIDE = false>
+// FEW: see kld_hist_kernel
+template <bool USE_LDS, bool WIDE = false, bool FEW = false>
 __device__ __forceinline__ void kld_hist_body(const float *__restrict__ w, uint64_t n, const float *__restrict__ range_partial,
                                               int range_blocks, int wl_lo, int wl_hi, int il, int bins, KldPlan *plan_out,
                                               uint32_t *tickets, uint32_t *slabs, int total_rows, int rows_per_group, int copies_log2, int mode,
@@ -450,50 +451,33 @@ __device__ __forceinline__ void kld_hist_body(const float *__restrict__ w, uint6
     // Two groups per pass fit 64 registers, so that two blocks of 1024 threads share a CU: the kernel waits (atomics of a
     // wavefront one behind the other, memory, the barriers of the plan) more than it computes.  Four groups per pass and one block
     // per CU: 8.4 M elements, 150 bins 97.6 -> 86.4 us, 0.9 M 42.8 -> 39.6, the 21 weight tensors of ResNet-18 117 -> 100.
-    constexpr int kPass = WIDE ? 4 : 2;
+    constexpr int kPass = FEW ? 1 : WIDE ? 4 : 2;
     const uint64_t full_groups = n >> 3;
     const uint64_t first = (uint64_t)geo.bx * nthreads + threadIdx.x;
     const uint64_t stride = (uint64_t)geo.gx * nthreads;
     uint64_t g = first;
-    for (; g + (kPass - 1) * stride < full_groups; g += kPass * stride) {
-        float v[kPass][8];
-        int r[kPass][8], cnt[kPass];
+    auto pass = [&](auto groups) {
+        constexpr int G = decltype(groups)::value;
+        float v[G][8];
+        int r[G][8], cnt[G];
 #pragma unroll
-        for (int u = 0; u < kPass; ++u) {
+        for (int u = 0; u < G; ++u) {
             const float4 a = reinterpret_cast<const float4 *>(w)[2 * (g + u * stride)];
             const float4 b = reinterpret_cast<const float4 *>(w)[2 * (g + u * stride) + 1];
             v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w; v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
             cnt[u] = 8;
         }
 #pragma unroll
-        for (int u = 0; u < kPass; ++u) rounding_of(g + u * stride, r[u]);
-        count_groups(std::integral_constant<int, kPass>{}, v, r, cnt);
-    }
-    // the last groups of the thread (fewer than kPass): a pass of two, then single groups
-    if (g + stride < full_groups) {
-        float v[2][8];
-        int r[2][8];
-        const int cnt[2] = {8, 8};
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float4 a = reinterpret_cast<const float4 *>(w)[2 * (g + u * stride)];
-            const float4 b = reinterpret_cast<const float4 *>(w)[2 * (g + u * stride) + 1];
-            v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w; v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) rounding_of(g + u * stride, r[u]);
-        count_groups(std::integral_constant<int, 2>{}, v, r, cnt);
-        g += 2 * stride;
-    }
-    for (; g < full_groups; g += stride) {
-        const float4 a = reinterpret_cast<const float4 *>(w)[2 * g];
-        const float4 b = reinterpret_cast<const float4 *>(w)[2 * g + 1];
-        const float v[1][8] = {{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
-        int r[1][8];
-        const int cnt[1] = {8};
-        rounding_of(g, r[0]);
-        count_groups(std::integral_constant<int, 1>{}, v, r, cnt);
-    }
+        for (int u = 0; u < G; ++u) rounding_of(g + u * stride, r[u]);
+        count_groups(groups, v, r, cnt);
+        g += G * stride;
+    };
+    if constexpr (kPass > 1)
+        while (g + (kPass - 1) * stride < full_groups) pass(std::integral_constant<int, kPass>{});
+    // the last groups of the thread (fewer than kPass): of four, a pass of two, then single groups
+    if constexpr (kPass > 2)
+        if (g + stride < full_groups) pass(std::integral_constant<int, 2>{});
+    while (g < full_groups) pass(std::integral_constant<int, 1>{});
     if ((n & 7) && first == 0) {
         float v[1][8];
         int r[1][8];
@@ -555,13 +539,18 @@ __device__ __forceinline__ void kld_hist_body(const float *__restrict__ w, uint6
     }
 }
 
-template <bool USE_LDS, bool WIDE = false>
-__global__ void __launch_bounds__(kHistMaxThreads, WIDE ? 4 : 8)
+// FEW: blocks of at most 512 threads, one group of elements per thread, and no more blocks than are resident at 128 registers (two
+// per CU).  The 64 registers that let four share a CU, and copies of the counters, only cost there.  With them and without, us per
+// search: 70,000 elements, 150 bins 18.4 and 17.4; 200,000 22.6 and 21.7; 520,000 29.6 and 28.3 (more blocks than that: 700,000
+// elements 36.1, with 128 registers 37.6).
+constexpr int kHistFewThreads = 512;
+template <bool USE_LDS, bool WIDE = false, bool FEW = false>
+__global__ void __launch_bounds__(FEW ? kHistFewThreads : kHistMaxThreads, WIDE || FEW ? 4 : 8)
 kld_hist_kernel(const float *__restrict__ w, uint64_t n, const float *__restrict__ range_partial, int range_blocks,
                 int wl_lo, int wl_hi, int il, int bins, KldPlan *plan_out, uint32_t *tickets, uint32_t *slabs, int total_rows,
                 int rows_per_group, int copies_log2, int mode, uint64_t seed, uint64_t stream)
 {
-    kld_hist_body<USE_LDS, WIDE>(w, n, range_partial, range_blocks, wl_lo, wl_hi, il, bins, plan_out, tickets, slabs, total_rows,
+    kld_hist_body<USE_LDS, WIDE, FEW>(w, n, range_partial, range_blocks, wl_lo, wl_hi, il, bins, plan_out, tickets, slabs, total_rows,
                            rows_per_group, copies_log2, mode, seed, stream, BlockGeo{blockIdx.x, blockIdx.y, gridDim.x, gridDim.y});
 }
 
@@ -783,13 +772,14 @@ kld_range_batched_kernel(const KldBatch b)
     kld_range_body(it.w, it.n, reinterpret_cast<float *>(b.ws + it.off_range), BlockGeo{l, 0, (unsigned)it.range_blocks, 1});
 }
 
-template <bool WIDE>
-__global__ void __launch_bounds__(kHistMaxThreads, WIDE ? 4 : 8)
+// FEW: as kld_hist_kernel
+template <bool WIDE, bool FEW = false>
+__global__ void __launch_bounds__(FEW ? kHistFewThreads : kHistMaxThreads, WIDE || FEW ? 4 : 8)
 kld_hist_batched_kernel(const KldBatch b)
 {
     ADAPT_KLD_FIND(first_hist);
     const int rows = b.wl_hi - b.wl_lo + 2;
-    kld_hist_body<true, WIDE>(it.w, it.n, it.range ? it.range : reinterpret_cast<const float *>(b.ws + it.off_range),
+    kld_hist_body<true, WIDE, FEW>(it.w, it.n, it.range ? it.range : reinterpret_cast<const float *>(b.ws + it.off_range),
                         it.range ? 1 : it.range_blocks, b.wl_lo, b.wl_hi,
                         it.il, it.bins, reinterpret_cast<KldPlan *>(b.ws + it.off_plan),
                         reinterpret_cast<uint32_t *>(b.ws + it.off_klpart), reinterpret_cast<uint32_t *>(b.ws + it.off_slabs), rows,
@@ -821,12 +811,13 @@ kld_final_batched_kernel(const KldBatch b)
 static size_t hist_lds_bytes(int rows, int bins, int copies_log2) { return (size_t)rows * (((size_t)bins << copies_log2) + kPrivWords) * 4 + 16; }
 
 // Copies of every counter: four (16 save nothing more) where two blocks still share a CU's LDS, and no more counters in a row
-// than a quarter of the elements that the block counts into it (clearing and adding up the copies has to stay small beside
-// them).  One copy -> four: 8.4 M elements, 64 bins 101.2 -> 88.2 us, 150 bins 89.6 -> 86.4; no change from 400 bins on.
+// than a sixteenth of the elements that the block counts into it: clearing and adding up the copies has to stay small beside
+// them.  Four copies against one, us: 8.4 M elements, 64 bins 94.1 and 118.6, 150 bins 92.2 and 100.2, 300 bins 91.3 and 93.6;
+// 1.2 M, 64 bins 42.4 and 46.3, 150 bins 42.6 and 41.8, 300 bins 43.5 and 42.1.
 static int copies_of(int rows, int bins, uint64_t block_elements)
 {
     int cl = 0;
-    while (cl < 2 && hist_lds_bytes(rows, bins, cl + 1) <= kLdsBudget / 2 && ((uint64_t)bins << (cl + 1)) * 4 <= block_elements) ++cl;
+    while (cl < 2 && hist_lds_bytes(rows, bins, cl + 1) <= kLdsBudget / 2 && ((uint64_t)bins << (cl + 1)) * 16 <= block_elements) ++cl;
     return cl;
 }
 
@@ -871,16 +862,17 @@ static int search_one(adapt_ctx *ctx, const float *w, uint64_t n, int wl_lo, int
         const int want_groups = std::max(1, (2 * ctx->num_cu + hist_grid - 1) / hist_grid);
         rows_per_group = std::max(1, std::min(rows_per_group, (rows + want_groups - 1) / want_groups));
         const int groups = (rows + rows_per_group - 1) / rows_per_group;
-        const int cl = copies_of(rows_per_group, bins, n / (uint64_t)hist_grid);
+        const bool few = threads <= kHistFewThreads && hist_grid * groups <= 2 * ctx->num_cu;      // fewer than 2^20 elements: one group each
+        const int cl = few ? 0 : copies_of(rows_per_group, bins, n / (uint64_t)hist_grid);
         const size_t lds = hist_lds_bytes(rows_per_group, bins, cl);
         if (wl_hi > 16)
             hipLaunchKernelGGL((kld_hist_kernel<true, true>), dim3(hist_grid, groups), dim3(threads), lds, ctx->stream, w, n, range_src,
                                range_count, wl_lo, wl_hi, il, bins, plan, reinterpret_cast<uint32_t *>(klpart), slabs, rows, rows_per_group,
                                cl, mode, seed, stream);
         else
-            hipLaunchKernelGGL((kld_hist_kernel<true, false>), dim3(hist_grid, groups), dim3(threads), lds, ctx->stream, w, n, range_src,
-                               range_count, wl_lo, wl_hi, il, bins, plan, reinterpret_cast<uint32_t *>(klpart), slabs, rows, rows_per_group,
-                               cl, mode, seed, stream);
+            hipLaunchKernelGGL((few ? kld_hist_kernel<true, false, true> : kld_hist_kernel<true, false, false>), dim3(hist_grid, groups), dim3(threads),
+                               lds, ctx->stream, w, n, range_src, range_count, wl_lo, wl_hi, il, bins, plan, reinterpret_cast<uint32_t *>(klpart),
+                               slabs, rows, rows_per_group, cl, mode, seed, stream);
     } else {
         const size_t zw = (size_t)hist_grid * hist_words;
         hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min<size_t>((zw + 255) / 256, (size_t)ctx->num_cu * 8)),
@@ -918,8 +910,10 @@ static int check_search_args(int wl_lo, int wl_hi, int il, int bins, double eps,
 static hipError_t allow_hist_lds(adapt_ctx *ctx)
 {
     hipError_t e = allow_big_lds(ctx, reinterpret_cast<const void *>(&kld_hist_kernel<true, false>), kLdsBudget);
+    if (e == hipSuccess) e = allow_big_lds(ctx, reinterpret_cast<const void *>(&kld_hist_kernel<true, false, true>), kLdsBudget);
     if (e == hipSuccess) e = allow_big_lds(ctx, reinterpret_cast<const void *>(&kld_hist_kernel<true, true>), kLdsBudget);
     if (e == hipSuccess) e = allow_big_lds(ctx, reinterpret_cast<const void *>(&kld_hist_batched_kernel<false>), kLdsBudget);
+    if (e == hipSuccess) e = allow_big_lds(ctx, reinterpret_cast<const void *>(&kld_hist_batched_kernel<false, true>), kLdsBudget);
     if (e == hipSuccess) e = allow_big_lds(ctx, reinterpret_cast<const void *>(&kld_hist_batched_kernel<true>), kLdsBudget);
     return e;
 }
@@ -1011,10 +1005,21 @@ static int search_batch(adapt_ctx *ctx, const adapt_kld_item *items, const float
             lds_max = std::max(lds_max, hist_lds_bytes(rpg, src.bins, it.copies_log2));
             b.item[b.count++] = it;
         }
+        // three tensors of 36,864 elements, 64 bins: with 64 registers and copies 19.0 us, with 128 and one copy 17.8
+        const bool few = threads <= kHistFewThreads && load <= per_block && nh <= 2u * (unsigned)ctx->num_cu;
+        if (few) {
+            lds_max = 0;
+            for (int i = 0; i < b.count; ++i) {
+                b.item[i].copies_log2 = 0;
+                lds_max = std::max(lds_max, hist_lds_bytes(b.item[i].rows_per_group, b.item[i].bins, 0));
+            }
+        }
         for (int i = b.count; i < kKldBatchMax; ++i) { b.first_range[i] = b.first_hist[i] = b.first_sum[i] = b.first_final[i] = 0xffffffffu; }
         if (nr) hipLaunchKernelGGL(kld_range_batched_kernel, dim3(nr), dim3(kRangeThreads), 0, ctx->stream, b);
         if (wl_hi > 16) hipLaunchKernelGGL(kld_hist_batched_kernel<true>, dim3(nh), dim3(threads), lds_max, ctx->stream, b);
-        else hipLaunchKernelGGL(kld_hist_batched_kernel<false>, dim3(nh), dim3(threads), lds_max, ctx->stream, b);
+        else
+            hipLaunchKernelGGL((few ? kld_hist_batched_kernel<false, true> : kld_hist_batched_kernel<false, false>), dim3(nh), dim3(threads), lds_max,
+                               ctx->stream, b);
         hipLaunchKernelGGL(kld_sum_batched_kernel, dim3(nsum), dim3(kChunk), 0, ctx->stream, b);
         hipLaunchKernelGGL(kld_final_batched_kernel, dim3(nf), dim3(kChunk), 0, ctx->stream, b);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return hip_status(ctx, e);

@@ -260,3 +260,25 @@ def test_copies_of_the_counters(n, bins):
     w[rng.random(n) < 0.4] = 0.0
     w[[3, n - 1]] = np.inf, np.nan
     _compare(w, 3, 16, 2, bins, 1e-2, seed=3, stream=4)
+
+
+# histogram blocks with 128 registers, up to two per CU (of 512 threads, one group of elements each), and beyond that with 64;
+# single searches and batches on either side, batches against the single search of each tensor
+@pytest.mark.parametrize("n,bins", [(5, 64), (65535, 64), (65536, 150), (266240, 64), (333000, 64), (393217, 200), (524288, 150), (528385, 150)])
+def test_few_blocks_and_many(n, bins):
+    rng = np.random.default_rng(n + bins)
+    w = (rng.standard_normal(n) * 0.05).astype(np.float32)
+    w[rng.random(n) < 0.3] = 0.0
+    _compare(w, 3, 16, 2, bins, 1e-2, seed=5, stream=6)
+
+
+@pytest.mark.parametrize("sizes", [(7,), (36864,) * 3, (65536,) * 8, (65536,) * 9, (36864,) * 21, (1048575, 9), (1 << 20, 100)])
+def test_batches_of_few_blocks_and_many(sizes):
+    rng = np.random.default_rng(len(sizes))
+    ws = [dev((rng.standard_normal(n) * 0.05).astype(np.float32)) for n in sizes]
+    c = ctx()
+    for bins in (60, 300):
+        kld, sel = c.kld_precision_search_batched(ws, [2] * len(ws), [bins] * len(ws), list(range(len(ws))), 4, 16, 1e-2, seed=7)
+        for t, w in enumerate(ws):
+            one = c.kld_precision_search(w, 4, 16, 2, bins, 1e-2, seed=7, stream=t)
+            assert np.allclose(host(kld)[t], host(one["kld"]), rtol=1e-12, atol=0) and host(sel)[t].tolist() == host(one["sel"]).tolist(), (t, bins)
