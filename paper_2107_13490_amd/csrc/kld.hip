@@ -2,7 +2,7 @@
 // distribution of a tensor and of its <WL_c, FL_c> quantizations, for all candidate word
 // lengths in one pass over the tensor.
 //
-// Four launches per search (three for a tensor of up to 131,072 elements; per batch of searches in the batched form), all on the context's stream, no host round trip (kernel boundaries
+// Four launches per search (three for a tensor of up to 131,072 elements without very many bins; per batch of searches in the batched form), all on the context's stream, no host round trip (kernel boundaries
 // order the phases; only the small final kernel uses a device-wide fence):
 //   range    per-block min / max of the finite elements.
 //   hist     every block first reduces the range partials and derives the bin grid (power-of-two
@@ -885,8 +885,10 @@ static int search_one(adapt_ctx *ctx, const float *w, uint64_t n, int wl_lo, int
                                wl_lo, wl_hi, il, bins, plan, reinterpret_cast<uint32_t *>(klpart), slabs, rows, rows, 0, mode, seed, stream);
     }
     // few slabs (up to 131,072 elements): their sums and the KL terms in one launch.  3,000 elements 16.7 -> 15.6 us, 65,536 (400 bins)
-    // 17.8 -> 16.5, 130,000 19.1 -> 18.8; beyond that the slabs are read one round behind the other (520,000: 28.6 -> 30.0)
-    if (hist_grid <= 32) {
+    // 17.8 -> 16.5, 130,000 19.1 -> 18.8; beyond that the slabs are read one round behind the other (520,000: 28.6 -> 30.0).  Every
+    // candidate adds up the reference row again, so the counters have to be few as well: 60,000 elements, 4,096 bins 26.2 -> 25.7,
+    // 8,192 35.9 -> 35.8, 12,288 40.7 -> 43.5; 20,000 elements, 12,288 bins 34.3 -> 34.1, 16,384 44.2 -> 45.7.
+    if (hist_grid <= 32 && (uint64_t)hist_grid * bins <= (1u << 17)) {
         hipLaunchKernelGGL(kld_final_kernel<true>, dim3(nchunks, ncand), dim3(kChunk), 0, ctx->stream, plan, rows, bins, alpha, klpart, slabs,
                            hist_grid, hist, wl_lo, il, eps, kld, sel, reinterpret_cast<long long *>(grid));
     } else {
