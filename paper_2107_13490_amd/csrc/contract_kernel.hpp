@@ -809,16 +809,22 @@ __device__ __forceinline__ void contract_epilogue(const ContractArgs &a, const v
             long long v[16];
             // a.fast: the host has checked the bound that lets a two-limb sum take one of the 32-bit forms
             const bool pair_form = BOTH2 && !OFFS && a.fast, i32_form = LIMBS == 2 && !BOTH2 && !OFFS && a.fast;
+            // (one branch for all 16, since inside the loop it stays 16: 60 x 6 x 6 x 144 -> 224 1x1, 14 bits 5.4 -> 5.2 us)
+            if (LIMBS == 1) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (LIMBS == 1) {
-                    v[r] = acc_hh[i][j][r];
-                } else if (pair_form) {
+                for (int r = 0; r < 16; ++r) v[r] = acc_hh[i][j][r];
+            } else if (pair_form) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
                     const int u = (acc_hh[i][j][r] << 8) + acc_x[i][j][r] + (acc_ll[i][j][r] >> 8);
                     v[r] = ((long long)u << 32) | (uint32_t)(acc_ll[i][j][r] & 255);
-                } else if (i32_form) {
-                    v[r] = (long long)((acc_hh[i][j][r] << 8) + acc_x[i][j][r]);
-                } else {
+                }
+            } else if (i32_form) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = (long long)((acc_hh[i][j][r] << 8) + acc_x[i][j][r]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
                     if (BOTH2) v[r] = ((long long)acc_hh[i][j][r] << 16) + ((long long)acc_x[i][j][r] << 8) + (long long)acc_ll[i][j][r];
                     else v[r] = ((long long)acc_hh[i][j][r] << 8) + (long long)acc_x[i][j][r];
                     if (OFFS) {
