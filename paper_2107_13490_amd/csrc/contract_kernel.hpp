@@ -1932,7 +1932,11 @@ static int fill_fwd(ContractArgs &a, const adapt_conv_desc &d, const void *x, ad
 static int plan_fwd(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, adapt_fmt fx, const void *w, adapt_fmt fw, void *y, adapt_epilogue ep,
                     size_t ws_limit, PadJobs &pads, ContractPlan &p)
 {
-    if (d.n > 0 && d.c % 16 != 0 && d.r * d.s <= 32) {
+    // One stage of gathered operands in one row of tiles is less than the copies' launch: 8 x 1 x 1 x 24 -> 64, 8 bits 7.9 us against
+    // 8.6 with copies (32 x 4 x 4 x 24 -> 64: 11.3 against 8.2)
+    const long long rows = (long long)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1);
+    const bool tiny = rows <= 64 && (long long)d.r * d.s * d.c <= 64;
+    if (d.n > 0 && d.c % 16 != 0 && d.r * d.s <= 32 && !tiny) {
         pads = PadJobs{};
         ContractArgs a = {};
         size_t off = 0;
@@ -1961,10 +1965,13 @@ static int plan_gradients(adapt_ctx *ctx, int which, const adapt_conv_desc &d, c
     enum { PAD_X = 1, PAD_W = 2, PAD_DY = 4 };        // the operands that are copied
     // the vector path of dy keeps one validity bit per filter tap and row: a data gradient beyond that has no use for copies
     const bool dx_pads = (which & GRAD_DX) && d.r * d.s <= 32;
-    const bool c_ragged = d.n > 0 && d.c % 16 != 0, k_ragged = d.n > 0 && d.k % 16 != 0;
+    const size_t dy_rows = (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1);
+    // as in plan_fwd, one limb: both gradients of 8 x 1 x 1 x 24 -> 64 13.4 us against 17.3 with copies, of 32 rows 15.0 and 16.6 (of 128
+    // 21.4 and 17.4, at 12 bits 20.0 and 14.3)
+    const bool tiny = dy_rows <= 32 && (long long)d.r * d.s * d.k <= 64 && d.k % 16 == 0 && fdy.wl <= 8 && fw.wl <= 8 && fx.wl <= 8;
+    const bool c_ragged = d.n > 0 && d.c % 16 != 0 && !tiny, k_ragged = d.n > 0 && d.k % 16 != 0;
     const int wanted = (c_ragged && (which & GRAD_DW) ? PAD_X : 0) | (c_ragged && dx_pads ? PAD_W : 0) |
                        (k_ragged && (dx_pads || (which & GRAD_DW)) ? PAD_DY : 0);
-    const size_t dy_rows = (size_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1);
     const int attempts[4] = {wanted, wanted & ~PAD_DY, wanted & ~PAD_X, 0};
     int last = -1;
     for (int t = 0; t < 4; ++t) {
@@ -2043,7 +2050,11 @@ static int plan_gemm(adapt_ctx *ctx, int transA, int transB, int M, int N, int K
     fill_gemm(a, transA, transB, M, N, K, A, fa, lda, B, fb, ldb, C, ldc);
     pads = PadJobs{};
     const bool pa = a.act_load == LOAD_SCALAR, pb = a.wgt_load == LOAD_SCALAR;
-    if ((pa || pb) && M > 0 && N > 0 && K > 0) {
+    // The gather's time goes by its stages of 64 codes, and with one of them and few tiles it is less than the copies' launch (8 bits,
+    // us, gathered and copied: 64 x 64 x 10 7.1 and 9.3, 250 x 64 x 60 8.5 and 9.2; 64 x 64 x 100 11.4 and 9.4, 2000 x 1000 x 20 8.8 and
+    // 7.7).  Rows that are not whole groups of 8 outputs have the slower epilogue under it (130 x 250 x 20 10.4 and 9.6).
+    const bool one_stage = K <= 64 && N % 8 == 0 && (long long)M * N <= 65536;
+    if ((pa || pb) && M > 0 && N > 0 && K > 0 && !one_stage) {
         const int wa = transA ? M : K, wb = transB ? K : N;      // codes of a row
         size_t off = 0;
         const void *Ap = A, *Bp = B;

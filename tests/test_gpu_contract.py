@@ -723,3 +723,23 @@ def test_gemm_ragged_rows(ta, tb, m, n, k, gap):
         (b[:, :b.shape[1] - gap].T if tb else b[:, :b.shape[1] - gap]).astype(np.int64)
     got = ctx().fxp_gemm(ad, (12, 9), bd, (8, 5), Epilogue.exact(), bool(ta), bool(tb))
     assert np.array_equal(host(got).astype(np.int64), want)
+
+
+# ragged operands that are gathered all the same, and their neighbours that are copied
+@pytest.mark.parametrize("case", [(8, 1, 1, 24, 64, 1, 1, 1, 0), (32, 1, 1, 24, 64, 1, 1, 1, 0), (33, 1, 1, 24, 64, 1, 1, 1, 0), (16, 2, 2, 61, 32, 1, 1, 1, 0),
+                                  (13, 5, 1, 61, 32, 1, 1, 1, 0), (2, 4, 4, 7, 16, 2, 2, 1, 0), (2, 4, 4, 7, 10, 3, 3, 1, 1)])
+@pytest.mark.parametrize("wls", [(8, 8, 8), (7, 12, 8)])
+def test_few_ragged_rows(case, wls):
+    _conv_all(case, *wls, extreme=True)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("m,n,k", [(37, 8, 19), (64, 64, 63), (64, 64, 65), (130, 40, 33), (9, 36, 50)])
+@pytest.mark.parametrize("wl", [8, 12])
+def test_gemm_one_gathered_stage(ta, tb, m, n, k, wl):
+    a, b = codes((k, m) if ta else (m, k), wl, 1, True), codes((n, k) if tb else (k, n), 8, 2, True)
+    want = (a.T if ta else a).astype(np.int64) @ (b.T if tb else b).astype(np.int64)
+    got = ctx().fxp_gemm(to_dev(a), (wl, wl - 3), to_dev(b), (8, 5), Epilogue.exact(), bool(ta), bool(tb))
+    assert np.array_equal(host(got).astype(np.int64), want)
+    got = ctx().fxp_gemm(to_dev(a), (wl, wl - 3), to_dev(b), (8, 5), Epilogue.requant(8, 4, pkg.SR, 3, 9), bool(ta), bool(tb))
+    assert np.array_equal(host(got), orc.requantize(want, wl - 2, 8, orc.SR, 3, 9, False).astype(np.int8))
