@@ -42,8 +42,8 @@ halo_kernel(const HaloArgs h)
     constexpr int PS = halo_row_bytes(LAL), BB = halo_b_bytes(OP, LBL, BN);
     constexpr int BRS = W_R ? BN + 16 : halo_row_bytes(LBL);      // bytes of a filter row (forward) or line (data gradient)
     constexpr int B_LO = W_R ? kHaloK * BRS : kHaloK;             // from a filter's high limb to its low limb
-    constexpr int BT = BN * (kHaloK / 16), BU = (BT + NT - 1) / NT;      // 16-code filter units of a stage, and of a thread
-    constexpr bool BPART = BT % NT != 0;                          // the last threads have none
+    constexpr int BT = BN * (kHaloK / 16), BU = BT / NT;          // 16-code filter units of a stage, and of a thread
+    static_assert(BT % NT == 0, "every thread has the same number of filter units");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, g = lane >> 5;
     const int wm = wave / WGN, wn = wave % WGN;
     const int nperm = 16 * ((l32 >> 2) & 1) + 4 * (l32 >> 3) + (l32 & 3);
@@ -107,12 +107,12 @@ halo_kernel(const HaloArgs h)
         if (W_R) {
             const int line = id / (BN / 16), col = id % (BN / 16) * 16;
             boff[i] = (uint32_t)line * (uint32_t)(taps * a.c) + (uint32_t)(n0 + col);
-            bok[i] = n0 + col < a.N && (!BPART || id < BT);
+            bok[i] = n0 + col < a.N;
             bdst[i] = line * BRS + col;
         } else {
             const int row = id >> 2, col = (id & 3) * 16;
             boff[i] = (uint32_t)(n0 + row) * (uint32_t)a.K + (uint32_t)col;
-            bok[i] = n0 + row < a.N && (!BPART || id < BT);
+            bok[i] = n0 + row < a.N;
             bdst[i] = row * BRS + col;
         }
     }
@@ -121,7 +121,6 @@ halo_kernel(const HaloArgs h)
         load_unit<EB>(rb, boff[i] + at, bok[i] && on, r0, r1);
     };
     auto b_store = [&](int i, char *dst, const uint32_t (&r0)[4], const uint32_t (&r1)[4]) {
-        if (BPART && (int)threadIdx.x + i * NT >= BT) return;      // whole wavefronts
         uint32_t hi[4], lo[4];
         split_unit<EB, bal_of(WES)>(r0, r1, hi, lo);
         *reinterpret_cast<uint4 *>(dst + bdst[i]) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
