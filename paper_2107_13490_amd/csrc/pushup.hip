@@ -68,7 +68,8 @@ static bool gd_short(uint64_t n, int count, int element_bytes) { return count <=
 // Few blocks: the last one to finish adds the sums, no second launch.  Its ticket costs every block about 20 ns behind the
 // others', a second launch and its reduction 0.8 us plus 40 ns per tensor (device time; and 2.5 us of the host's).  Two launches
 // -> one, in a captured graph: 25 tensors of 36,864 elements 11.3 -> 9.1 us, of 147,456 (72 blocks) 11.7 -> 9.8; 8 of 73,728
-// 7.4 -> 7.1; one of 1,728 5.1 -> 5.4, of 147,456 6.3 -> 7.0 (not taken).
+// 7.4 -> 7.1; one of 147,456 6.3 -> 7.0 (not taken: 72 blocks).  One tensor of 1,728 elements is taken for the host's sake: its
+// graph takes 5.1 -> 5.4 us, calls one behind the other 9.9 -> 5.8.
 static bool gd_one_launch(int blocks, int count) { return blocks <= 32 + 2 * count; }
 
 // Blocks of a tensor, each with at least `each` chunks (1, or 2 where the workspace does not hold one block's sums per chunk).  As
