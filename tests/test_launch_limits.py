@@ -33,6 +33,9 @@ print(fake.fake_launches(), fake.fake_big_launches(), fake.fake_over_limit())
 
 
 def test_launches_stay_within_the_lds_requested_for_their_kernels(tmp_path):
+    from paper_2107_13490_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
     lib = str(tmp_path / "libfake_hip.so")
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
                     os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", lib], check=True)

@@ -7,6 +7,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def test_planned_reads_stay_inside_the_operands(tmp_path):
     from paper_2107_13490_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
     lib = os.path.dirname(build.LIB)
     exe = str(tmp_path / "plan_extents")
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17",
