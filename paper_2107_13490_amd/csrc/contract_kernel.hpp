@@ -99,6 +99,7 @@ struct ContractArgs {
     int k_bound;                 // reduction length that decides the accumulator type (0: K); smaller than K when
                                  // zero channels were appended
     int force_finish;            // always go through slabs and finish_kernel
+    int slab_rows;               // layout of the slabs: 0 as the output, 1 [32 rows][column][row of the 32] (contract_rows.hpp)
     int pad_c, pad_to;           // finish_kernel: the slabs hold pad_to channels per filter tap, the output pad_c (0: same)
     long long slab_bytes;        // split-K: split y writes its exact partial sums to out + y*slab_bytes
     long long ldc;               // output row stride in elements
@@ -775,13 +776,14 @@ __device__ __forceinline__ void emit_run(const ContractArgs &a, void *out, int m
 
 // ---------------------------------------------------------------------------------------------
 // A wavefront's accumulators to the output: MB x NB blocks of 32 x 32, NW wavefronts per block; rows[j] is the output row of
-// the lane in block row j, ncol0 the first column of the wavefront's tile, kpad the reduction length with its padding, lin the
+// the lane in block row j, ncol0 the first column of the wavefront's tile, ncol_step from one of its column blocks to the next, kpad the reduction length with its padding, lin the
 // block's number in its contraction.  `smem` is free for the wavefronts of the block once they have all arrived.
 // ---------------------------------------------------------------------------------------------
 template <int LIMBS, int LAL, int LBL, bool OFFS, bool W_R, int MB, int NB, int NW, bool AMAX>
 __device__ __forceinline__ void contract_epilogue(const ContractArgs &a, const v16i (&acc_hh)[NB][MB], const v16i (&acc_x)[NB][MB],
                                                   const v16i (&acc_ll)[NB][MB], const int (&sum_m)[MB], const int (&sum_n)[NB], char *const smem,
-                                                  const int (&rows)[MB], const int ncol0, const long long kpad, void *out, const unsigned lin)
+                                                  const int (&rows)[MB], const int ncol0, const long long kpad, void *out, const unsigned lin,
+                                                  const int ncol_step = 32)
 {
     constexpr bool BOTH2 = LAL == 2 && LBL == 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -860,7 +862,7 @@ __device__ __forceinline__ void contract_epilogue(const ContractArgs &a, const v
 #pragma unroll
                 for (int t = 0; t < 16; ++t) w[t] = v[t];
             }
-            const int m = rows[j], nn = ncol0 + i * 32 + 16 * g;
+            const int m = rows[j], nn = ncol0 + i * ncol_step + 16 * g;
             if (LIMBS == 1) emit_run<16, FORM_I32, AMAX>(a, out, m, nn, w, vmax);
             else if (pair_form) emit_run<16, FORM_PAIR, AMAX>(a, out, m, nn, w, vmax);
             else if (i32_form) emit_run<16, FORM_I32, AMAX>(a, out, m, nn, w, vmax);
@@ -1248,31 +1250,65 @@ contract_pair_kernel(const ContractArgs a, const ContractArgs b, const unsigned 
 }
 
 // ---- helper: split-K finish ---------------------------------------------------------------------------
-// split-K: sums the `splits` slabs of exact partial sums (dense M x N each) and converts
-template <typename AccT>
+// split-K: sums the `splits` slabs of exact partial sums and converts.  G threads share an output's slabs (where the outputs are few,
+// the chain of loads per output is what takes the time) and add up in LDS.
+template <typename AccT, int G>
 __global__ void __launch_bounds__(256)
 finish_kernel(const AccT *__restrict__ ws, int splits, ContractArgs a)
 {
-    const size_t total = (size_t)a.M * a.N;
-    const size_t slab = (size_t)a.slab_bytes / sizeof(AccT);        // elements per slab (more than total with appended channels)
+    constexpr int E = 256 / G;                                      // outputs of a block at a time
+    __shared__ long long part[G == 1 ? 1 : 256];
+    const size_t slab = (size_t)a.slab_bytes / sizeof(AccT);        // elements per slab
+    // positions to visit: outputs, or slab elements where rows or columns of them may have no output
+    const size_t total = a.slab_rows ? slab : (size_t)a.M * a.N;
+    const int slab_n = a.pad_c ? a.N / a.pad_c * a.pad_to : a.N;    // columns of a slab
+    const int own = threadIdx.x % E, group = threadIdx.x / E;
     unsigned long long vmax = 0;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const size_t m = i / a.N, n = i % a.N;
-        size_t j = i;                                               // position inside a slab
-        if (a.pad_c) {
-            const size_t tap = n / a.pad_c, c = n - tap * a.pad_c;
-            j = m * ((size_t)a.N / a.pad_c * a.pad_to) + tap * a.pad_to + c;
+    for (size_t base = (size_t)blockIdx.x * E; base < total; base += (size_t)gridDim.x * E) {
+        const size_t i = base + own;
+        size_t m, n, j = i;                                         // j: position inside a slab
+        bool out = i < total;
+        if (a.slab_rows) {
+            const size_t q = i / 32;
+            n = q % slab_n;
+            m = q / slab_n * 32 + i % 32;
+            if (a.pad_c) {
+                const size_t tap = n / a.pad_to, c = n - tap * a.pad_to;
+                out = out && c < (size_t)a.pad_c;
+                n = tap * a.pad_c + c;
+            }
+            out = out && m < (size_t)a.M;
+        } else {
+            m = i / a.N;
+            n = i % a.N;
+            if (a.pad_c) {
+                const size_t tap = n / a.pad_c, c = n - tap * a.pad_c;
+                j = m * slab_n + tap * a.pad_to + c;
+            }
         }
         long long v = 0;
-        int y = 0;
-        for (; y + 8 <= splits; y += 8) {      // eight independent loads in flight
-            AccT t[8];
+        if (out) {
+            int y = group;
+            for (; y + 7 * G < splits; y += 8 * G) {                // eight independent loads in flight
+                AccT t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = ws[(size_t)(y + u) * slab + j];
+                for (int u = 0; u < 8; ++u) t[u] = ws[(size_t)(y + u * G) * slab + j];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v += (long long)t[u];
+                for (int u = 0; u < 8; ++u) v += (long long)t[u];
+            }
+            for (; y < splits; y += G) v += (long long)ws[(size_t)y * slab + j];
         }
-        for (; y < splits; ++y) v += (long long)ws[(size_t)y * slab + j];
+        if (G > 1) {
+            part[threadIdx.x] = v;
+            __syncthreads();
+            if (group == 0) {
+#pragma unroll
+                for (int u = 1; u < G; ++u) v += part[u * E + own];
+            }
+            __syncthreads();
+            if (group != 0) continue;                               // (the loop's bounds are the block's)
+        }
+        if (!out) continue;
         const size_t o = m * (size_t)a.ldc + n;
         if (a.out_mode == OUT_RAW32 || a.out_mode == OUT_RAW64) {
             const unsigned long long mag = v < 0 ? 0ull - (unsigned long long)v : (unsigned long long)v;
@@ -1282,7 +1318,7 @@ finish_kernel(const AccT *__restrict__ ws, int splits, ContractArgs a)
             case OUT_RAW32: static_cast<int32_t *>(a.out)[o] = (int32_t)v; break;
             case OUT_RAW64: static_cast<long long *>(a.out)[o] = v; break;
             default: {
-                const int q = requantize_one(v, a.shift, a.wl_o, a.relu, rounding_bits_of(a.seed, a.stream, i, a.rmode));
+                const int q = requantize_one(v, a.shift, a.wl_o, a.relu, rounding_bits_of(a.seed, a.stream, (uint64_t)m * a.N + n, a.rmode));
                 if (a.out_mode == OUT_Q8) static_cast<int8_t *>(a.out)[o] = (int8_t)q;
                 else static_cast<int16_t *>(a.out)[o] = (int16_t)q;
             }
@@ -1603,11 +1639,69 @@ static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
     return HALO_NONE;
 }
 
+// ---- weight gradients on image rows in LDS (contract_rows.hpp) -------------------------------------
+constexpr int kRowsTaps = 3;
+constexpr int kRowsChannels = 64;      // of a block, input and output
+constexpr int kRowsSlots = 128;        // reduction indices of a stage
+constexpr int kRowsLines = 192;        // most input pixels of a stage (output rows of four pixels)
+struct RowsGeometry {
+    int rps, slots;      // output rows and pixels of a stage
+    int pw, lines;       // columns of a staged input row, staged input pixels
+    int stages;          // of the whole reduction
+};
+static RowsGeometry rows_geometry(const ContractArgs &a)
+{
+    RowsGeometry g;
+    g.rps = kRowsSlots / a.q;
+    g.slots = g.rps * a.q;
+    g.pw = a.q + kRowsTaps - 1;
+    g.lines = g.rps * g.pw;
+    g.stages = g.rps == 0 ? 0 : (a.n * a.p + g.rps - 1) / g.rps;
+    return g;
+}
+static long long rows_tiles(const ContractArgs &a)
+{
+    return (long long)((a.M + kRowsChannels - 1) / kRowsChannels) * ((a.c + kRowsChannels - 1) / kRowsChannels) * a.r;
+}
+constexpr size_t rows_lds(int la, int lb)
+{
+    const size_t per_round = 512 * 16 / (kRowsChannels * lb), lines = (kRowsLines + per_round - 1) / per_round * per_round;
+    const size_t stage = (size_t)(kRowsChannels + 32) * ((size_t)la * kRowsSlots + (size_t)lb * lines);
+    // the two groups' sums on their way to one
+    const size_t sums = (size_t)512 * 4 * (kRowsTaps * 8 * (la == 2 && lb == 2 ? 3 : la == 2 || lb == 2 ? 2 : 1) + kRowsTaps + 1);
+    return 2 * stage > sums ? 2 * stage : sums;
+}
+// Splits of a weight gradient on image rows, 0 where the kernels above take it.  One block per CU; the kernel pays where the blocks
+// fill at least half of the CUs' products with real channels and slots, and where each walks at least 12 stages (its start, the
+// groups' exchange and the slabs are 8 us).  260 drawn layers at 4..16 bits, both kernels with the slab sum: of those that the rule takes none
+// is slower by more than 0.3 us, the median takes 0.83 of the time; of the others a fifth would gain (most by 5 %) and the rest lose (up
+// to 2.1 times).  us, kernels above -> here:
+//   256 x 16 x 16 x 128 -> 128  <12,9> 65.2 -> 54.7   8 x 12 bits 51.3 -> 37.2   12 x 8 bits 53.9 -> 34.5   16 bits 72.6 -> 64.3
+//   256 x 32 x 32 x 64 -> 64           68.0 -> 49.5               53.3 -> 37.1               50.2 -> 34.9           84.5 -> 62.2
+//   128 x 8 x 8 x 384 -> 256           60.0 -> 44.4               51.0 -> 35.7               47.6 -> 34.9           75.6 -> 58.8
+//   256 x 11 x 11 x 48 -> 112 at 37 images (7 stages) 18.2 -> 18.8, 12.6 -> 14.9, 12.8 -> 14.6: left to the kernels above
+static int rows_splits(const ContractArgs &a, int limbs, int num_cu)
+{
+    if (limbs != 2 || a.stride != 1 || a.s != kRowsTaps || a.K == 0 || a.act_load != LOAD_ROWS || a.wgt_load != LOAD_ROWS) return 0;
+    const RowsGeometry g = rows_geometry(a);
+    if (g.stages == 0 || g.lines > kRowsLines) return 0;
+    // the chunks' offsets run on for two stages beyond the reduction and must not come round to the operands' starts
+    const uint64_t beyond = 4ull * kRowsSlots * (uint64_t)std::max(a.k * a.act_es, 2 * a.c * a.wgt_es) + (1ull << 20);
+    if (a.act_bytes + beyond >= 1ull << 32 || a.wgt_bytes + beyond >= 1ull << 32) return 0;
+    const long long tiles = rows_tiles(a);
+    const int cap = 32768 / kRowsSlots;                  // stages that int32 accumulators hold
+    const int want = std::max((int)std::max(1ll, std::min<long long>(num_cu / tiles, g.stages)), (g.stages + cap - 1) / cap);
+    const int per = (g.stages + want - 1) / want, splits = (g.stages + per - 1) / per;
+    const double real = (double)a.M * a.c * a.r / ((double)tiles * kRowsChannels * kRowsChannels) * g.slots / kRowsSlots;
+    const double rounds = (double)tiles * splits / num_cu;
+    return per >= 12 && real * rounds >= 0.5 * std::ceil(rounds) ? splits : 0;
+}
+
 // A contraction planned on the host: what the kernel gets, and what finish_kernel gets when K is
 // split across blocks (exact partial sums in workspace slabs) because a single block could overflow
 // its int32 accumulators or because the output has too few tiles to fill the GPU.
 struct ContractPlan {
-    int halo;               // tile of the kernel on input patches (contract_halo.hpp), or HALO_NONE
+    int halo;               // tile of the kernel on input patches (contract_halo.hpp) or, weight gradients, 1 for the kernel on image rows (contract_rows.hpp); or 0
     ContractArgs kern;      // arguments of the contraction kernel (final output, or slabs)
     ContractArgs fin;       // arguments of finish_kernel (splits > 1)
     TileShape tile;
@@ -1657,6 +1751,56 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
     p.ws_end = ws_offset;
     if (p.empty) return ADAPT_OK;
 
+    // exact output with a sink armed: the launch that writes the final output also stores its blocks' largest magnitudes
+    const adapt_amax_sink &sink = ctx->amax[OP == OP_WGRAD ? 1 : 0];
+    auto arm = [&](ContractArgs &dst) {
+        if (!(OP == OP_DGRAD || OP == OP_WGRAD) || !ep.raw || sink.part == nullptr) return;
+        dst.amax_part = sink.part;
+        dst.amax_zero = sink.zero;
+        dst.amax_cap = (unsigned)sink.capacity;
+    };
+    // K split: the kernel fills slabs behind ws_offset (a partial sum is bounded like the total, so they use the total's accumulator
+    // type), finish_kernel adds them
+    const size_t slab = (size_t)a.M * a.N * (bits == 32 ? 4 : 8);
+    const size_t off = (ws_offset + 255) & ~(size_t)255;
+    const size_t room = ws_limit > off ? ws_limit - off : 0;
+    auto to_slabs = [&](int splits, size_t slab) {
+        p.splits = splits;
+        p.ws_end = off + slab * (size_t)splits;
+        char *acc = ctx->ws ? scratch(ctx) + off : nullptr;      // no workspace: a sizing query, nothing is launched
+        p.acc = acc;
+        p.kern = a;
+        p.kern.out = acc;
+        p.kern.ldc = a.N;
+        p.kern.slab_bytes = (long long)slab;
+        p.kern.out_mode = bits == 32 ? OUT_RAW32 : OUT_RAW64;
+        p.kern.fast = 0;                                  // exact partial sums go to the slabs
+        p.fin = a;
+        p.fin.out_mode = final_mode;
+        p.fin.slab_bytes = (long long)slab;
+        arm(p.fin);
+    };
+    if constexpr (OP == OP_WGRAD) {
+        if (const int want = rows_splits(a, limbs, ctx->num_cu)) {
+            const int stages = rows_geometry(a).stages, per = (stages + want - 1) / want, splits = (stages + per - 1) / per;
+            const bool direct = splits == 1 && !a.force_finish;
+            const size_t rows_slab = (size_t)((a.M + 31) / 32 * 32) * a.N * (bits == 32 ? 4 : 8);
+            if (direct || rows_slab * (size_t)splits <= room) {
+                a.k_per_split = per;             // in stages
+                a.slab_bytes = 0;
+                p.halo = 1;
+                if (!direct) {
+                    a.slab_rows = 1;
+                    to_slabs(splits, rows_slab);
+                } else {
+                    a.out_mode = final_mode;
+                    arm(a);
+                    p.kern = a;
+                }
+                return ADAPT_OK;
+            }
+        }
+    }
     TileShape t = pick_tile<OP>(a, limbs, ctx->num_cu);
     int model_splits = 0;
     if (OP == OP_WGRAD && a.act_load != LOAD_SCALAR && a.wgt_load != LOAD_SCALAR) model_splits = pick_split_tile(a, limbs, bits, ctx->num_cu, t);
@@ -1703,14 +1847,6 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
     p.tile = t;
     p.splits = splits;
     p.ws_end = ws_offset;
-    // exact output with a sink armed: the launch that writes the final output also stores its blocks' largest magnitudes
-    const adapt_amax_sink &sink = ctx->amax[OP == OP_WGRAD ? 1 : 0];
-    auto arm = [&](ContractArgs &dst) {
-        if (!(OP == OP_DGRAD || OP == OP_WGRAD) || !ep.raw || sink.part == nullptr) return;
-        dst.amax_part = sink.part;
-        dst.amax_zero = sink.zero;
-        dst.amax_cap = (unsigned)sink.capacity;
-    };
     if (splits == 1 && !a.force_finish) {
         a.out_mode = final_mode;
         arm(a);
@@ -1718,11 +1854,6 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
         if constexpr (OP == OP_FWD || OP == OP_DGRAD) p.halo = halo_tile<OP>(a, limbs, ctx->num_cu);
         return ADAPT_OK;
     }
-    // a partial sum is bounded like the total, so the slabs use the total's accumulator type
-    const size_t acc_bytes = bits == 32 ? 4 : 8;
-    const size_t slab = (size_t)a.M * a.N * acc_bytes;
-    const size_t off = (ws_offset + 255) & ~(size_t)255;
-    const size_t room = ws_limit > off ? ws_limit - off : 0;
     if (slab * (size_t)splits > room) {
         // Not enough workspace for the preferred number of splits: take as many as fit.  Splits that only
         // serve parallelism may go down to none (the result is the same, only slower); the splits that
@@ -1746,19 +1877,7 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
             return ADAPT_OK;
         }
     }
-    p.ws_end = off + slab * (size_t)splits;
-    char *acc = ctx->ws ? scratch(ctx) + off : nullptr;      // no workspace: a sizing query, nothing is launched
-    p.acc = acc;
-    p.kern = a;
-    p.kern.out = acc;
-    p.kern.ldc = a.N;
-    p.kern.slab_bytes = (long long)slab;
-    p.kern.out_mode = bits == 32 ? OUT_RAW32 : OUT_RAW64;
-    p.kern.fast = 0;                                  // exact partial sums go to the slabs
-    p.fin = a;
-    p.fin.out_mode = final_mode;
-    p.fin.slab_bytes = (long long)slab;
-    arm(p.fin);
+    to_slabs(splits, slab);
     return ADAPT_OK;
 }
 
@@ -1767,6 +1886,7 @@ hipError_t launch_planned_dgrad_s2(adapt_ctx *ctx, const ContractPlan &p);
 
 hipError_t launch_halo_fwd(adapt_ctx *ctx, const ContractPlan &p);
 hipError_t launch_halo_dgrad(adapt_ctx *ctx, const ContractPlan &p);
+hipError_t launch_rows(adapt_ctx *ctx, const ContractPlan &p);
 
 template <int OP>
 static hipError_t launch_planned(adapt_ctx *ctx, const ContractPlan &p)
@@ -1776,6 +1896,8 @@ static hipError_t launch_planned(adapt_ctx *ctx, const ContractPlan &p)
         if (p.halo) return launch_halo_fwd(ctx, p);
     if constexpr (OP == OP_DGRAD)
         if (p.halo) return launch_halo_dgrad(ctx, p);
+    if constexpr (OP == OP_WGRAD)
+        if (p.halo) return launch_rows(ctx, p);
     if constexpr (OP == OP_DGRAD)
         if (p.kern.dg_classes) return launch_planned_dgrad_s2(ctx, p);
     return p.limbs == 1 ? launch_modes<OP, 1>(ctx, p.kern, p.splits, p.tile) : launch_modes<OP, 2>(ctx, p.kern, p.splits, p.tile);
@@ -1790,11 +1912,24 @@ hipError_t launch_planned_wgrad(adapt_ctx *ctx, const ContractPlan &p);
 static hipError_t finish_planned(adapt_ctx *ctx, const ContractPlan &p)
 {
     if (p.empty || p.acc == nullptr) return hipSuccess;
-    const unsigned fgrid = (unsigned)std::min<size_t>(((size_t)p.fin.M * p.fin.N + 255) / 256, (size_t)ctx->num_cu * 8);
-    if (p.bits == 32)
-        hipLaunchKernelGGL(finish_kernel<int32_t>, dim3(fgrid), dim3(256), 0, ctx->stream, reinterpret_cast<const int32_t *>(p.acc), p.splits, p.fin);
-    else
-        hipLaunchKernelGGL(finish_kernel<long long>, dim3(fgrid), dim3(256), 0, ctx->stream, reinterpret_cast<const long long *>(p.acc), p.splits, p.fin);
+    const size_t total = p.fin.slab_rows ? (size_t)p.fin.slab_bytes / (p.bits == 32 ? 4 : 8) : (size_t)p.fin.M * p.fin.N;
+    // Threads that share an output: 256 x 28 x 28 x 32 -> 48 at 169 images, 85 slabs, both launches 27.1 us with one, 24.7 with four; 92 x
+    // 16 -> 32 at 115, 81 slabs 26.5, 24.9, 24.6 with 16; with more outputs there are threads enough (147,456 outputs, 21 slabs 55.2, 54.7,
+    // 57.9; 589,824, 5 slabs 51.4, 55.4, 77.4)
+    const int share = p.splits < 32 || total > 24000 ? 1 : total > 9216 ? 4 : 16;
+    const unsigned per = 256 / share, fgrid = (unsigned)std::min<size_t>((total + per - 1) / per, (size_t)ctx->num_cu * 8);
+    auto launch = [&](auto kern, auto *acc) { hipLaunchKernelGGL(kern, dim3(fgrid), dim3(256), 0, ctx->stream, acc, p.splits, p.fin); };
+    if (p.bits == 32) {
+        const int32_t *acc = reinterpret_cast<const int32_t *>(p.acc);
+        if (share == 1) launch(finish_kernel<int32_t, 1>, acc);
+        else if (share == 4) launch(finish_kernel<int32_t, 4>, acc);
+        else launch(finish_kernel<int32_t, 16>, acc);
+    } else {
+        const long long *acc = reinterpret_cast<const long long *>(p.acc);
+        if (share == 1) launch(finish_kernel<long long, 1>, acc);
+        else if (share == 4) launch(finish_kernel<long long, 4>, acc);
+        else launch(finish_kernel<long long, 16>, acc);
+    }
     note_amax_blocks(ctx, p.fin, fgrid);
     return hipGetLastError();
 }

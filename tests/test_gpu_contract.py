@@ -684,6 +684,44 @@ def test_convolutions_on_patches(case):
         assert np.array_equal(dxq[i:i + 1], orc.requantize(want, sh, wlx, orc.SR, 3, 41, False, start=i * h * w * k)), i
 
 
+# ---- weight gradients of stride-1, three taps wide filters on image rows in LDS: sizes that fill half of the GPU with 12 stages each --
+@pytest.mark.parametrize("case", [
+    # n, h, w, c, k, r, s, pad, wl_dy, wl_x
+    (130, 16, 16, 128, 128, 3, 3, 1, 12, 12),     # whole groups of eight pixels, a last stage and split that are short
+    (130, 16, 16, 128, 128, 3, 3, 1, 16, 16),     # offset split of both operands
+    (1400, 4, 4, 192, 128, 3, 3, 1, 13, 8),       # rows of four pixels: the most lines of a stage
+    (100, 18, 17, 128, 112, 3, 3, 0, 8, 13),      # rows of 15 pixels, no padding, output channels beyond dw
+    (64, 32, 33, 128, 120, 3, 3, 1, 16, 7),       # 29 of a stage's slots unused; copies of dy
+    (8, 16, 16, 512, 512, 3, 3, 1, 15, 9),        # one split: no slabs
+    (8, 16, 16, 500, 512, 3, 3, 1, 8, 16),        # copies of x; slabs with appended channels
+    (100, 16, 16, 256, 256, 1, 3, 1, 9, 12),      # one row of taps
+    (160, 16, 14, 128, 64, 5, 3, 2, 12, 6),       # five rows of taps, output wider than the input
+])
+def test_weight_gradients_on_image_rows(case):
+    n, h, w, c, k, r, s, pad, wldy, wlx = case
+    d = ConvDesc(n, h, w, c, k, r, s, 1, pad)
+    fdy, fx = (wldy, wldy - 3), (wlx, wlx - 3)
+    x, dy = codes((n, h, w, c), wlx, 1, True), codes((n, d.p, d.q, k), wldy, 2, True)
+    want = co.conv_wgrad(dy, x, r, s, 1, pad)
+    dyd, xd = to_dev(dy), to_dev(x)
+    assert np.array_equal(host(ctx().conv_wgrad(d, dyd, fdy, xd, fx, Epilogue.exact())).astype(np.int64), want)
+    got = host(ctx().conv_wgrad(d, dyd, fdy, xd, fx, Epilogue.requant(wlx, 2, pkg.SR, 3, 44))).astype(np.int64)
+    assert np.array_equal(got, orc.requantize(want, wldy - 3 + wlx - 3 - 2, wlx, orc.SR, 3, 44, False))
+
+
+# The slab sum of few outputs: one, four and sixteen threads share an output
+@pytest.mark.parametrize("c,k", [(3, 16), (16, 64), (32, 64)])
+@pytest.mark.parametrize("wl", [8, 12])
+def test_slab_sums_of_few_outputs(c, k, wl):
+    d = ConvDesc(40, 32, 32, c, k, 3, 3, 1, 1)
+    x, dy = codes((40, 32, 32, c), wl, 1), codes((40, 32, 32, k), wl, 2)
+    want = co.conv_wgrad(dy, x, 3, 3, 1, 1)
+    dyd, xd = to_dev(dy), to_dev(x)
+    assert np.array_equal(host(ctx().conv_wgrad(d, dyd, (wl, 4), xd, (wl, 4), Epilogue.exact())).astype(np.int64), want)
+    got = host(ctx().conv_wgrad(d, dyd, (wl, 4), xd, (wl, 4), Epilogue.requant(wl, 0, pkg.SR, 3, 45))).astype(np.int64)
+    assert np.array_equal(got, orc.requantize(want, 8, wl, orc.SR, 3, 45, False))
+
+
 # ---- operands whose rows are not whole 16-byte groups run on padded copies ---------------------------------------------
 @pytest.mark.parametrize("case", [
     # n, h, w, c, k, r, s, stride, pad
