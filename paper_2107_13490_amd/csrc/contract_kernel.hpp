@@ -1251,44 +1251,46 @@ contract_pair_kernel(const ContractArgs a, const ContractArgs b, const unsigned 
 
 // ---- helper: split-K finish ---------------------------------------------------------------------------
 // split-K: sums the `splits` slabs of exact partial sums and converts.  G threads share an output's slabs (where the outputs are few,
-// the chain of loads per output is what takes the time) and add up in LDS.
-template <typename AccT, int G>
+// the chain of loads per output is what takes the time) and add up in LDS.  ROWS: slabs as contract_rows.hpp lays them out.  T: holds
+// the positions (64-bit divisions are 30 instructions each).
+template <typename AccT, int G, bool ROWS, typename T>
 __global__ void __launch_bounds__(256)
 finish_kernel(const AccT *__restrict__ ws, int splits, ContractArgs a)
 {
     constexpr int E = 256 / G;                                      // outputs of a block at a time
     __shared__ long long part[G == 1 ? 1 : 256];
-    const size_t slab = (size_t)a.slab_bytes / sizeof(AccT);        // elements per slab
+    const size_t slab = (size_t)a.slab_bytes / sizeof(AccT);        // elements per slab (more than outputs with appended channels)
     // positions to visit: outputs, or slab elements where rows or columns of them may have no output
-    const size_t total = a.slab_rows ? slab : (size_t)a.M * a.N;
-    const int slab_n = a.pad_c ? a.N / a.pad_c * a.pad_to : a.N;    // columns of a slab
-    const int own = threadIdx.x % E, group = threadIdx.x / E;
+    const T total = ROWS ? (T)slab : (T)a.M * (T)a.N;
+    const T cols = a.pad_c ? (T)a.N / (T)a.pad_c * (T)a.pad_to : (T)a.N;      // of a slab
+    const T own = threadIdx.x % E, group = threadIdx.x / E;
     unsigned long long vmax = 0;
-    for (size_t base = (size_t)blockIdx.x * E; base < total; base += (size_t)gridDim.x * E) {
-        const size_t i = base + own;
-        size_t m, n, j = i;                                         // j: position inside a slab
+    for (T base = (T)blockIdx.x * E; base < total; base += (T)gridDim.x * E) {
+        const T i = base + own;
+        T m, n;
+        size_t j = i;                                               // position inside a slab
         bool out = i < total;
-        if (a.slab_rows) {
-            const size_t q = i / 32;
-            n = q % slab_n;
-            m = q / slab_n * 32 + i % 32;
+        if (ROWS) {
+            const T q = i / 32, rows = q / cols;
+            m = rows * 32 + i % 32;
+            n = q - rows * cols;
             if (a.pad_c) {
-                const size_t tap = n / a.pad_to, c = n - tap * a.pad_to;
-                out = out && c < (size_t)a.pad_c;
-                n = tap * a.pad_c + c;
+                const T tap = n / (T)a.pad_to, c = n - tap * (T)a.pad_to;
+                out = out && c < (T)a.pad_c;
+                n = tap * (T)a.pad_c + c;
             }
-            out = out && m < (size_t)a.M;
+            out = out && m < (T)a.M;
         } else {
-            m = i / a.N;
-            n = i % a.N;
+            m = i / (T)a.N;
+            n = i - m * (T)a.N;
             if (a.pad_c) {
-                const size_t tap = n / a.pad_c, c = n - tap * a.pad_c;
-                j = m * slab_n + tap * a.pad_to + c;
+                const T tap = n / (T)a.pad_c, c = n - tap * (T)a.pad_c;
+                j = (size_t)m * cols + tap * (T)a.pad_to + c;
             }
         }
         long long v = 0;
         if (out) {
-            int y = group;
+            int y = (int)group;
             for (; y + 7 * G < splits; y += 8 * G) {                // eight independent loads in flight
                 AccT t[8];
 #pragma unroll
@@ -1309,7 +1311,7 @@ finish_kernel(const AccT *__restrict__ ws, int splits, ContractArgs a)
             if (group != 0) continue;                               // (the loop's bounds are the block's)
         }
         if (!out) continue;
-        const size_t o = m * (size_t)a.ldc + n;
+        const size_t o = (size_t)m * (size_t)a.ldc + n;
         if (a.out_mode == OUT_RAW32 || a.out_mode == OUT_RAW64) {
             const unsigned long long mag = v < 0 ? 0ull - (unsigned long long)v : (unsigned long long)v;
             vmax = mag > vmax ? mag : vmax;
@@ -1918,18 +1920,15 @@ static hipError_t finish_planned(adapt_ctx *ctx, const ContractPlan &p)
     // 57.9; 589,824, 5 slabs 51.4, 55.4, 77.4)
     const int share = p.splits < 32 || total > 24000 ? 1 : total > 9216 ? 4 : 16;
     const unsigned per = 256 / share, fgrid = (unsigned)std::min<size_t>((total + per - 1) / per, (size_t)ctx->num_cu * 8);
-    auto launch = [&](auto kern, auto *acc) { hipLaunchKernelGGL(kern, dim3(fgrid), dim3(256), 0, ctx->stream, acc, p.splits, p.fin); };
-    if (p.bits == 32) {
-        const int32_t *acc = reinterpret_cast<const int32_t *>(p.acc);
-        if (share == 1) launch(finish_kernel<int32_t, 1>, acc);
-        else if (share == 4) launch(finish_kernel<int32_t, 4>, acc);
-        else launch(finish_kernel<int32_t, 16>, acc);
-    } else {
-        const long long *acc = reinterpret_cast<const long long *>(p.acc);
-        if (share == 1) launch(finish_kernel<long long, 1>, acc);
-        else if (share == 4) launch(finish_kernel<long long, 4>, acc);
-        else launch(finish_kernel<long long, 16>, acc);
-    }
+    auto launch = [&](auto *acc) {
+        typedef std::remove_const_t<std::remove_pointer_t<decltype(acc)>> AccT;
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(fgrid), dim3(256), 0, ctx->stream, acc, p.splits, p.fin); };
+        if (p.fin.slab_rows) go(share == 1 ? finish_kernel<AccT, 1, true, uint32_t> : share == 4 ? finish_kernel<AccT, 4, true, uint32_t> : finish_kernel<AccT, 16, true, uint32_t>);
+        else if (total >= 1u << 31) go(finish_kernel<AccT, 1, false, uint64_t>);
+        else go(share == 1 ? finish_kernel<AccT, 1, false, uint32_t> : share == 4 ? finish_kernel<AccT, 4, false, uint32_t> : finish_kernel<AccT, 16, false, uint32_t>);
+    };
+    if (p.bits == 32) launch(reinterpret_cast<const int32_t *>(p.acc));
+    else launch(reinterpret_cast<const long long *>(p.acc));
     note_amax_blocks(ctx, p.fin, fgrid);
     return hipGetLastError();
 }
