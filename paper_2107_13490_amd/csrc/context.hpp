@@ -68,6 +68,22 @@ int wide_parts(adapt_fmt f, adapt_fmt fmt[3], int *step);
 int requantize_fit_wide(adapt_ctx *ctx, const void *acc, int acc_bits, size_t n, int wl, adapt_rng rng, void *q, int32_t *shift,
                         uint64_t *sumsq, const long long *e_in, long long e_add, long long *e_out);
 
+// A weight gradient fitted to t.wl bits, as adapt_conv_wgrad with an exact output and the fitting requantization of it (contract_wgrad_fit.hip).
+// ADAPT_EUNSUPPORTED, with nothing launched, where those two are to be called.
+struct FitTarget {
+    int wl;
+    adapt_rng rng;
+    void *q;
+    int32_t *shift;
+    unsigned long long *sumsq;
+    const long long *e_in;         // *e_out = (e_in ? *e_in : 0) + e_add - shift
+    long long e_add;
+    long long *e_out;
+    unsigned long long *part;      // room for `parts` maxima
+    int parts;
+};
+int wgrad_fit(adapt_ctx *ctx, const adapt_conv_desc &d, const void *dy, adapt_fmt fdy, const void *x, adapt_fmt fx, const FitTarget &t);
+
 inline char *scratch(adapt_ctx *c) { return c->ws + kCtlBytes; }
 inline size_t scratch_bytes(const adapt_ctx *c) { return c->ws_bytes - kCtlBytes; }
 inline uint32_t *ticket(adapt_ctx *c, int slot) { return reinterpret_cast<uint32_t *>(c->ws) + slot; }

@@ -973,20 +973,32 @@ extern "C" int adapt_net_backward(adapt_net *net, const void *dlogits, int dlogi
         // squares the fitting pass adds to), so that the fitting passes need no pass of their own to find them.  The
         // composed contractions above 16 bits do not (the sinks stay unarmed for them): their counts stay 0.
         unsigned long long *amax_x = reinterpret_cast<unsigned long long *>(net->ws + net->P.off_amax), *amax_w = amax_x + kAmaxCap;
-        if (fdy.wl <= 16 && y.fmt.wl <= 16 && fin.wl <= 16) {
+        const bool narrow = fdy.wl <= 16 && y.fmt.wl <= 16 && fin.wl <= 16;
+        int s_fit = ADAPT_EUNSUPPORTED;
+        if (narrow) {
+            const FitTarget target = {y.fmt.wl, slot_rng(rng, l, 2), net->ws + y.g_off(), &st->shift_w,
+                                      reinterpret_cast<unsigned long long *>(&st->g_sumsq), e_cur, fin.fl, &ex_l->e_g, amax_w, kAmaxCap};
+            s_fit = wgrad_fit(ctx, c, dyc, fdy, a_prev, fin, target);
+            if (s_fit != ADAPT_OK && s_fit != ADAPT_EUNSUPPORTED) return s_fit;
+        }
+        const bool fitted = s_fit == ADAPT_OK;                    // the weight gradient is there already
+        if (narrow) {
             ctx->amax[0] = adapt_amax_sink{amax_x, nullptr, kAmaxCap, 0};
             ctx->amax[1] = adapt_amax_sink{amax_w, reinterpret_cast<unsigned long long *>(&st->g_sumsq), kAmaxCap, 0};
         }
-        int s_bwd;
-        if (y.src >= 0) s_bwd = adapt_conv_backward(ctx, c, dyc, fdy, net->ws + y.off_qw, y.fmt, a_prev, fin, accx, ex, accw, ex);
+        int s_bwd = ADAPT_OK;
+        if (fitted) {
+            if (y.src >= 0) s_bwd = adapt_conv_dgrad(ctx, c, dyc, fdy, net->ws + y.off_qw, y.fmt, accx, ex);
+        } else if (y.src >= 0) s_bwd = adapt_conv_backward(ctx, c, dyc, fdy, net->ws + y.off_qw, y.fmt, a_prev, fin, accx, ex, accw, ex);
         else s_bwd = adapt_conv_wgrad(ctx, c, dyc, fdy, a_prev, fin, accw, ex);
         const int n_amax_x = ctx->amax[0].count, n_amax_w = ctx->amax[1].count;
         ctx->amax[0] = ctx->amax[1] = adapt_amax_sink{};
         if (s_bwd) return s_bwd;
         const int bits_w = adapt_acc_bits((int64_t)c.n * y.p * y.q, fdy, fin);
-        if (int s = requantize_fit_exp(ctx, accw, bits_w, y.n_w, y.fmt.wl, slot_rng(rng, l, 2), net->ws + y.g_off(), &st->shift_w,
-                                       &st->g_sumsq, e_cur, fin.fl, &ex_l->e_g, amax_w, n_amax_w))
-            return s;
+        if (!fitted)
+            if (int s = requantize_fit_exp(ctx, accw, bits_w, y.n_w, y.fmt.wl, slot_rng(rng, l, 2), net->ws + y.g_off(), &st->shift_w,
+                                           &st->g_sumsq, e_cur, fin.fl, &ex_l->e_g, amax_w, n_amax_w))
+                return s;
         if (y.src >= 0) {
             NetLayer &t = net->L[y.src];
             const bool first = ncontrib[y.src] == 0;

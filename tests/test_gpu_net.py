@@ -864,3 +864,51 @@ def test_resnet18_cifar_chain_reduced_batch():
     fmts = [(int(wl), int(wl) - 4) for wl in g.integers(8, 17, len(nodes))]
     fmts[0] = (12, 8)
     _run_graph(nodes, fmts, n=4, steps=1, seed=43, check_all=False, lr=0.02)
+
+
+# ---- weight gradients with a short reduction, fitted without the exact sums in memory ------------------------------------
+@pytest.mark.parametrize("batch,c,k,wl_x,wl_dy", [
+    (128, 2000, 4080, 12, 13),      # whole stage; columns and rows that end inside a tile
+    (1, 2048, 4096, 16, 16),        # offset split, one slot
+    (127, 2000, 4096, 16, 16),
+    (77, 2048, 4080, 8, 16),        # one int16 operand
+    (77, 2048, 4080, 16, 5),
+    (40, 2048, 4096, 7, 12),
+    (40, 2048, 4096, 9, 8),
+    (129, 1040, 1040, 8, 8),        # one limb: two stages per tile
+    (256, 1024, 1024, 4, 8),
+])
+@pytest.mark.parametrize("kind", ["normal", "saturated", "one code"])
+def test_fitted_weight_gradients_of_short_reductions(batch, c, k, wl_x, wl_dy, kind):
+    g = np.random.default_rng(batch + c + k)
+    ws = [g.standard_normal(16 * c).astype(np.float32), (0.01 * g.standard_normal(c * k)).astype(np.float32)]
+    layers = [LayerDesc(ConvDesc(batch, 1, 1, 16, c, 1, 1, 1, 0), 0, 0), LayerDesc(ConvDesc(batch, 1, 1, c, k, 1, 1, 1, 0), 0, 0)]
+    net = pkg.Net(ctx(), layers, [dev(w) for w in ws])
+    # saturated inputs: sums at and next to powers of two, of either sign
+    net.set_format(0, wl_x, max(0, wl_x - 4) if kind == "normal" else 0)
+    net.set_format(1, wl_dy, 3)
+    net.quantize_weights(seed=1)
+    x = g.standard_normal((batch, 1, 1, 16)).astype(np.float32) * (1.0 if kind == "normal" else 3e4)
+    net.forward(dev(x), seed=7, stream=50)
+    lim = 1 << (wl_dy - 1)
+    dl = g.integers(-lim, lim, (batch, k))
+    if kind == "saturated":
+        dl = g.choice([-lim, lim - 1, 0], (batch, k))
+    elif kind == "one code":
+        dl = np.zeros((batch, k), dtype=np.int64)
+        dl[batch // 2, k - 1] = -1
+    dl = dl.astype(_dt(wl_dy))
+    net.backward(dev(dl), 0, seed=7, stream=50)
+    a = host(net.tensor(0, pkg.NT_A)).reshape(batch, c)
+    want, shift, sumsq = _fit_sums(a, dl, wl_dy, 7, 50 + 8 + 2)
+    st = net.tensor(1, pkg.NT_STATS)
+    assert (st.shift_w, _sumsq(st)) == (shift, sumsq)
+    assert np.array_equal(host(net.tensor(1, pkg.NT_G)).astype(np.int64), want.ravel())
+
+
+def _fit_sums(a, dl, wl, seed, stream):
+    # (float64 products of at most 2^30 each, at most 256 of them: exact)
+    sums = (dl.astype(np.float64).T @ a.astype(np.float64)).astype(np.int64)
+    shift = no.fit_shift(sums, wl)
+    q = orc.requantize(sums, shift, wl, orc.SR, seed, stream, False)
+    return q, shift, int((q * q).sum())
