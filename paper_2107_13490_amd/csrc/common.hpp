@@ -147,6 +147,19 @@ __device__ __forceinline__ void load_codes8<int32_t>(const int32_t *g, uint64_t 
     c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w; c[4] = b.x; c[5] = b.y; c[6] = b.z; c[7] = b.w;
 }
 
+// A store to a tensor that nothing reads before it has left the caches (NT): past them, so that it takes no room there
+template <bool NT, typename V>
+__device__ __forceinline__ void store_vec(V *p, const V &v)
+{
+    if (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+typedef unsigned u32v2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32v4 __attribute__((ext_vector_type(4)));
+typedef float f32v4 __attribute__((ext_vector_type(4)));
+// Where a call's tensors exceed the last-level cache together, its results are gone from it before the next call reads them
+constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
+
 template <typename OutT>
 __device__ __forceinline__ void store_codes8(OutT *q, uint64_t grp, const int (&v)[8]);
 template <>

@@ -16,34 +16,31 @@ namespace adapt {
 
 constexpr int kQThreads = 256;
 
-template <typename OutT>
-__device__ __forceinline__ void store8(OutT *q, const int (&v)[8]);
-
-template <>
-__device__ __forceinline__ void store8<int8_t>(int8_t *q, const int (&v)[8])
+template <bool NT>
+__device__ __forceinline__ void store8(int8_t *q, const int (&v)[8])
 {
-    uint2 o;
+    u32v2 o;
     o.x = (uint32_t)(v[0] & 0xff) | ((uint32_t)(v[1] & 0xff) << 8) | ((uint32_t)(v[2] & 0xff) << 16) |
           ((uint32_t)(v[3] & 0xff) << 24);
     o.y = (uint32_t)(v[4] & 0xff) | ((uint32_t)(v[5] & 0xff) << 8) | ((uint32_t)(v[6] & 0xff) << 16) |
           ((uint32_t)(v[7] & 0xff) << 24);
-    *reinterpret_cast<uint2 *>(q) = o;
+    store_vec<NT>(reinterpret_cast<u32v2 *>(q), o);
 }
-template <>
-__device__ __forceinline__ void store8<int16_t>(int16_t *q, const int (&v)[8])
+template <bool NT>
+__device__ __forceinline__ void store8(int16_t *q, const int (&v)[8])
 {
-    uint4 o;
+    u32v4 o;
     o.x = (uint32_t)(v[0] & 0xffff) | ((uint32_t)v[1] << 16);
     o.y = (uint32_t)(v[2] & 0xffff) | ((uint32_t)v[3] << 16);
     o.z = (uint32_t)(v[4] & 0xffff) | ((uint32_t)v[5] << 16);
     o.w = (uint32_t)(v[6] & 0xffff) | ((uint32_t)v[7] << 16);
-    *reinterpret_cast<uint4 *>(q) = o;
+    store_vec<NT>(reinterpret_cast<u32v4 *>(q), o);
 }
 
 // Converts the elements [0, n) of one tensor; this block handles the groups
 // first_group, first_group + group_stride, ...  Returns the thread's (nnz, sat) counts.
 // With RANGE, lo / hi also track the smallest and largest finite input value.
-template <typename OutT, bool RANGE = false>
+template <typename OutT, bool RANGE, bool NT>
 __device__ __forceinline__ void quantize_span(const float *__restrict__ x, OutT *__restrict__ q, uint64_t n,
                                               const QuantParams p, int mode, uint64_t seed, uint64_t stream,
                                               uint64_t first_group, uint64_t group_stride, uint32_t &nnz,
@@ -70,7 +67,7 @@ __device__ __forceinline__ void quantize_span(const float *__restrict__ x, OutT 
             nsat += s;
             if (RANGE && fabsf(v[e]) < INFINITY) { lo = fminf(lo, v[e]); hi = fmaxf(hi, v[e]); }
         }
-        store8<OutT>(q + 8 * g, c);
+        store8<NT>(q + 8 * g, c);
     };
     // two groups per iteration: four 16-byte loads in flight per thread
     const float4 *x4 = reinterpret_cast<const float4 *>(x);
@@ -151,7 +148,7 @@ __device__ __forceinline__ void sum_columns(const uint32_t *partial, const int n
     }
 }
 
-template <typename OutT, bool FUSED>
+template <typename OutT, bool FUSED, bool NT>
 __global__ void __launch_bounds__(kQThreads)
 quantize_kernel(const float *__restrict__ x, OutT *__restrict__ q, uint64_t n, int wl, int fl, int mode,
                 uint64_t seed, uint64_t stream, uint32_t *partial /* [2][gridDim.x] or null */, uint32_t *ticket, uint64_t *out0,
@@ -161,7 +158,7 @@ quantize_kernel(const float *__restrict__ x, OutT *__restrict__ q, uint64_t n, i
     uint32_t nnz = 0, nsat = 0;
     // n <= 2^40 (checked by the host): per-thread and per-block counts stay below 2^32
     float lo = 0.0f, hi = 0.0f;
-    quantize_span<OutT>(x, q, n, p, mode, seed, stream, (uint64_t)blockIdx.x * kQThreads + threadIdx.x,
+    quantize_span<OutT, false, NT>(x, q, n, p, mode, seed, stream, (uint64_t)blockIdx.x * kQThreads + threadIdx.x,
                         (uint64_t)gridDim.x * kQThreads, nnz, nsat, lo, hi);
     if (partial == nullptr) return;
     uint64_t bn, bs;
@@ -303,7 +300,7 @@ struct QuantBatch {
 
 // nnz / saturated of every tensor: per-block partial counts in `partial[2*count][block]`, summed
 // by sum_partials_kernel (no same-address atomics, no zero-fill launch).
-template <bool FUSED>
+template <bool FUSED, bool NT>
 __global__ void __launch_bounds__(kQThreads)
 quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_t *partial /* or null */,
                         float *range_partial /* [2*count][gridDim.x] or null */, uint64_t range_mask /* bit t: tensor t */,
@@ -329,14 +326,14 @@ quantize_batched_kernel(const QuantBatch batch, int mode, uint64_t seed, uint32_
             const uint64_t stride = (uint64_t)blocks_needed * kQThreads;
             if (range_partial != nullptr && ((range_mask >> t) & 1)) {
                 if (it.wl <= 8)
-                    quantize_span<int8_t, true>(it.x, (int8_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
+                    quantize_span<int8_t, true, NT>(it.x, (int8_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
                 else
-                    quantize_span<int16_t, true>(it.x, (int16_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
+                    quantize_span<int16_t, true, NT>(it.x, (int16_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
             } else {
                 if (it.wl <= 8)
-                    quantize_span<int8_t>(it.x, (int8_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
+                    quantize_span<int8_t, false, NT>(it.x, (int8_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
                 else
-                    quantize_span<int16_t>(it.x, (int16_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
+                    quantize_span<int16_t, false, NT>(it.x, (int16_t *)it.q, it.n, p, mode, seed, it.stream, first, stride, nnz, nsat, lo, hi);
             }
         }
         // one barrier pair per tensor: counters and (for the tensors that asked for it) the range
@@ -429,8 +426,13 @@ static int quantize_on(adapt_ctx *ctx, const float *x, size_t n, adapt_fmt fmt, 
             hipLaunchKernelGGL(kern, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, codes, (uint64_t)n, fmt.wl, fmt.fl, rng.mode, rng.seed,
                                rng.stream, partial, control, nnz, saturated);
         };
-        if (fmt.wl <= 8) fused ? launch(quantize_kernel<int8_t, true>, (int8_t *)q) : launch(quantize_kernel<int8_t, false>, (int8_t *)q);
-        else fused ? launch(quantize_kernel<int16_t, true>, (int16_t *)q) : launch(quantize_kernel<int16_t, false>, (int16_t *)q);
+        // Codes past the caches where they and the input exceed the last one.  67 M elements, us, through them / past them: new tensors
+        // each time 12 bits 87.5 / 82.1, 8 bits 74.9 / 70.2, the same tensors again (whose input then stays) 86.3 / 66.1 and 70.8 / 54.3.
+        // Smaller tensors' codes are still there for the call that reads them (16.8 M, 12 bits: 22.3 / 20.1, the next call's way to them
+        // is longer; 4.2 M 8.4 / 8.5).  Loads past the caches as well: 79.8 and 67.2, the same tensors 77.7 and 66.2.
+        const bool past = (uint64_t)n * (4 + storage_bytes(fmt)) > kLastLevelCache;
+        if (fmt.wl <= 8) launch(fused ? quantize_kernel<int8_t, true, false> : past ? quantize_kernel<int8_t, false, true> : quantize_kernel<int8_t, false, false>, (int8_t *)q);
+        else launch(fused ? quantize_kernel<int16_t, true, false> : past ? quantize_kernel<int16_t, false, true> : quantize_kernel<int16_t, false, false>, (int16_t *)q);
     }
     if (count && !fused) {
         // out1 != null selects the two-destination form; a null destination is redirected to a dummy slot
@@ -495,7 +497,7 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
     for (int base = 0; base < count; base += kMaxItems) {
         QuantBatch batch;
         batch.count = count - base < kMaxItems ? count - base : kMaxItems;
-        uint64_t total_blocks = 0;
+        uint64_t total_blocks = 0, bytes = 0;
         for (int t = 0; t < batch.count; ++t) {
             batch.item[t] = items[base + t];
             if (items[base + t].wl > 16) {             // int32 codes: a launch of its own below; an empty placeholder here
@@ -503,6 +505,7 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
                 batch.item[t].wl = 8;
             }
             total_blocks += (((batch.item[t].n + 7) >> 3) + kQThreads - 1) / kQThreads;
+            bytes += batch.item[t].n * (uint64_t)(batch.item[t].wl <= 8 ? 5 : 6);
         }
         uint64_t grid = total_blocks;
         uint64_t cap = (uint64_t)ctx->num_cu * 4;
@@ -514,12 +517,12 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
         float *range_partial = ranges ? reinterpret_cast<float *>(scratch(ctx) + part_bytes) : nullptr;
         if (counters && !ranges && grid <= kFusedBatchBlocks && batch.count <= kFusedItems) {
             grid = std::min<uint64_t>(grid, kFusedGrid);
-            hipLaunchKernelGGL(quantize_batched_kernel<true>, dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
+            hipLaunchKernelGGL((quantize_batched_kernel<true, false>), dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
                                seed, partial, nullptr, (uint64_t)0, ticket(ctx, 0), counters + 2 * base);
             continue;
         }
-        hipLaunchKernelGGL(quantize_batched_kernel<false>, dim3((unsigned)grid), dim3(kQThreads), 0, ctx->stream, batch, mode,
-                           seed, partial, range_partial, range_mask >> base, nullptr, nullptr);
+        hipLaunchKernelGGL((bytes > kLastLevelCache ? quantize_batched_kernel<false, true> : quantize_batched_kernel<false, false>), dim3((unsigned)grid),
+                           dim3(kQThreads), 0, ctx->stream, batch, mode, seed, partial, range_partial, range_mask >> base, nullptr, nullptr);
         // one wavefront per column: enough blocks for all the columns of the batch to run side by side
         const int sum_cols = (counters ? 2 * batch.count : 0) + (ranges ? 2 * batch.count : 0);
         const int sum_blocks = std::min(std::max((sum_cols + kSumThreads / kWave - 1) / (kSumThreads / kWave), 1), 16);

@@ -171,3 +171,22 @@ def test_batched_ranges_feed_the_precision_search():
     it = (pkg.binding.QuantizeItem * 1)(pkg.binding.QuantizeItem(dev(xs[2]).data_ptr(), outs[2].data_ptr(), xs[2].size, 8, 7, 3))
     assert pkg.load_library().adapt_quantize_batched_ranges(ctx().handle, it, 1, pkg.SR, 3, None, r2.data_ptr(), 1) == 0
     assert host(r2).tolist() == [float(xs[2].min()), float(xs[2].max())]
+
+
+@pytest.mark.parametrize("wl,n", [(8, 54_000_003), (12, 45_000_005)])
+@pytest.mark.parametrize("batched", [False, True])
+def test_tensors_that_exceed_the_last_level_cache(wl, n, batched):
+    # their codes take other stores; slices at both ends and inside against the oracle, the counters against the codes
+    x = torch.randn(n, device="cuda")
+    if batched:
+        (q,), counters = ctx().quantize_batched([x], [(wl, wl - 3)], [9], pkg.SR, 5)[:2]
+        counters = u64(counters).ravel()
+    else:
+        q, counters = ctx().quantize(x, wl, wl - 3, pkg.SR, 5, 9)
+        counters = u64(counters)
+    for a in (0, 8 * 262144 - 50, n // 2 + 3, n - 3000):
+        part = host(x[a:a + 3000])
+        bits = orc.r16(5, 9, np.arange(a, a + part.size, dtype=np.uint64))
+        want = orc.quantize_with_bits(part, wl, wl - 3, bits)[0]
+        assert np.array_equal(host(q[a:a + 3000]).astype(np.int64), want), a
+    assert int(counters[0]) == int(torch.count_nonzero(q))
