@@ -26,6 +26,7 @@ struct HaloArgs {
     int pr, pc;                  // input pixel of output pixel (y, x) and tap (r, s): (y - pr + r, x - pc + s)
     int pw;                      // columns of a patch: ow + s - 1
     int pix;                     // most pixels a block's patch has (its LDS buffer)
+    int patches;                 // LDS buffers for patches: two, one where the channels are one chunk
     FastDiv div_ow, div_oh, div_pw, div_ir;      // output columns, output rows, patch columns, patch rows of a whole image (oh + r - 1)
 };
 
@@ -72,7 +73,7 @@ halo_kernel(const HaloArgs h)
     }
 
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(a.act, a.act_bytes), rb = make_rsrc(a.wgt, a.wgt_bytes);
-    char *const patch = smem, *const bbuf = smem + 2 * h.pix * PS;      // two patches, two filter stages
+    char *const patch = smem, *const bbuf = smem + h.patches * h.pix * PS;      // one or two patches, two filter stages
     const int taps = a.r * a.s, chunks = h.ch / kHaloK, stages = chunks * taps;
 
     // unit u of the patch: 16 channels of one pixel.  Beyond the image (and beyond the patch) it loads zeros.
@@ -276,7 +277,7 @@ static hipError_t launch_halo_as(adapt_ctx *ctx, const HaloArgs &h)
     constexpr int BM = kHaloShape[TILE][0], BN = kHaloShape[TILE][1];
     static_assert(kHaloShape[TILE][2] == 64 * WGM * WGN, "threads of the tile");
     void (*kern)(const HaloArgs) = halo_kernel<OP, AES == 1 && WES == 1 ? 1 : 2, AES, WES, BM, BN, WGM, WGN, AMAX>;
-    const size_t lds = halo_lds<OP>(h.a, TILE);
+    const size_t lds = halo_lds<OP>(h.a, TILE, h.patches);
     // a launch's LDS depends on the layer: the most that any layer takes is requested
     if (hipError_t e = allow_big_lds(ctx, reinterpret_cast<const void *>(kern), kHaloMaxLds[TILE]); e != hipSuccess) return e;
     const unsigned tiles = (unsigned)((h.a.M + BM - 1) / BM) * (unsigned)((h.a.N + BN - 1) / BN);
@@ -306,6 +307,7 @@ static hipError_t launch_halo_modes(adapt_ctx *ctx, const ContractPlan &p)
     }
     h.pw = h.ow + a.s - 1;
     h.pix = halo_pixels(kHaloShape[p.halo][0], h.oh, h.ow, a.r, a.s);
+    h.patches = halo_patches<OP>(a, p.halo);
     h.div_ow = make_fastdiv(h.ow); h.div_oh = make_fastdiv(h.oh); h.div_pw = make_fastdiv(h.pw); h.div_ir = make_fastdiv(h.oh + a.r - 1);
     if constexpr (!(AES == 2 && WES == 2))      // not planned: spills
         if (p.halo == HALO_256x128) return launch_halo_tile<OP, AES, WES, HALO_256x128, 4, 2>(ctx, h);

@@ -1590,12 +1590,22 @@ static int halo_pixels(int bm, int oh, int ow, int r, int s)
     const int images = whole && rows % oh == 0 ? rows / oh : whole && oh % rows == 0 ? 1 : (rows + oh - 2) / oh + 1;
     return (rows + images * (r - 1)) * (ow + s - 1);
 }
+// LDS buffers for patches.  One chunk of channels has no next patch: 128 x 64 tiles run three blocks per CU then (mixed operands four)
+// instead of two.  us: 256 x 32 x 32 x 64 -> 64 <12,9> forward 49.4 -> 44.3, data gradient 49.6 -> 46.5; 16 bits 70.9 -> 62.3, 73.4 -> 64.4; 8 x 12
+// bits 31.3 -> 28.3; 12 x 8 bits data gradient 42.0 -> 32.1.  Several column tiles of two balanced operands lose by it (128 x 16 x 16 x 64 ->
+// 192 20.5 -> 21.1, 100 x 31 x 30 x 64 -> 128 40.2 -> 40.4; 16 bits 31.2 -> 27.4).
 template <int OP>
-static size_t halo_lds(const ContractArgs &a, int tile)
+static int halo_patches(const ContractArgs &a, int tile)
+{
+    if ((OP == OP_FWD ? a.c : a.k) > kHaloK) return 2;
+    return a.act_es == 2 && a.wgt_es == 2 && a.balanced && a.N > kHaloShape[tile][1] ? 2 : 1;
+}
+template <int OP>
+static size_t halo_lds(const ContractArgs &a, int tile, int patches)
 {
     const int la = a.act_es, lb = a.wgt_es;      // limbs: int8 one, int16 two
     const int pix = OP == OP_FWD ? halo_pixels(kHaloShape[tile][0], a.p, a.q, a.r, a.s) : halo_pixels(kHaloShape[tile][0], a.h, a.w, a.r, a.s);
-    return 2 * ((size_t)pix * halo_row_bytes(la) + halo_b_bytes(OP, lb, kHaloShape[tile][1]));
+    return (size_t)patches * pix * halo_row_bytes(la) + 2 * halo_b_bytes(OP, lb, kHaloShape[tile][1]);
 }
 // The tile for a contraction, or HALO_NONE where the kernels above are at least as fast.  Times in us, forward at <12,9> unless
 // said otherwise, kernels above -> 256 x 128 / 128 x 64 tiles:
@@ -1621,7 +1631,7 @@ static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
         const int bm = kHaloShape[t][0];
         const int pix = OP == OP_FWD ? halo_pixels(bm, a.p, a.q, a.r, a.s) : halo_pixels(bm, a.h, a.w, a.r, a.s);
         // a chunk's patch is written in one share of the block's threads per tap but the last
-        return halo_lds<OP>(a, t) <= (size_t)kHaloMaxLds[t] && pix * (kHaloK / 16) <= (taps - 1) * kHaloShape[t][2] && 4 * pix <= 7 * bm;
+        return halo_lds<OP>(a, t, 2) <= (size_t)kHaloMaxLds[t] && pix * (kHaloK / 16) <= (taps - 1) * kHaloShape[t][2] && 4 * pix <= 7 * bm;
     };
     const bool offset16 = a.act_es == 2 && a.wgt_es == 2 && !a.balanced;
     // rounds of resident blocks (256 x 128 tiles: one block per CU, 128 x 64: two); a last, partly filled round takes at least a
