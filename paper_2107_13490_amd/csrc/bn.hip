@@ -1152,8 +1152,9 @@ extern "C" int adapt_gap_bwd(adapt_ctx *ctx, const void *dout, int wl, int n, in
     return hip_status(ctx, hipGetLastError());
 }
 
-extern "C" int adapt_grad_add(adapt_ctx *ctx, const void *a, int wl_a, const int64_t *e_a, const void *b, int wl_b, const int64_t *e_b,
-                              size_t n, int wl_out, adapt_rng rng, void *out, int32_t *shift, int64_t *e_out)
+namespace adapt {
+int grad_add(adapt_ctx *ctx, const void *a, int wl_a, const int64_t *e_a, const void *b, int wl_b, const int64_t *e_b, size_t n, int wl_out,
+             adapt_rng rng, void *out, int32_t *shift, int64_t *e_out, const unsigned long long *part, int nparts)
 {
     if (!ctx || wl_a < 2 || wl_a > 32 || wl_out < 2 || wl_out > 32 || (b && (wl_b < 2 || wl_b > 32)) || !rng_ok(rng)) return ADAPT_EINVAL;
     if (n > ((uint64_t)1 << 40)) return ADAPT_EINVAL;
@@ -1173,10 +1174,15 @@ extern "C" int adapt_grad_add(adapt_ctx *ctx, const void *a, int wl_a, const int
         hipLaunchKernelGGL(merge_wide_kernel<1>, dim3(bn_grid(ctx, (uint64_t)n)), t, 0, ctx->stream, m, ea, eb, eo);
         return hip_status(ctx, hipGetLastError());
     }
+    const bool have = !b && part != nullptr && nparts > 0;
+    if (have) {
+        m.part = reinterpret_cast<uint64_t *>(const_cast<unsigned long long *>(part));      // read only, by the fitting pass
+        m.nparts = nparts;
+    }
     const int sel = (wl_a > 8) * 4 + ((b ? wl_b : 8) > 8) * 2 + (wl_out > 8);
 #define ADAPT_MERGE(TA, TB, TO)                                                                               \
     do {                                                                                                      \
-        hipLaunchKernelGGL((merge_kernel<TA, TB, TO, false>), dim3(grid1), t, 0, ctx->stream, m);             \
+        if (!have) hipLaunchKernelGGL((merge_kernel<TA, TB, TO, false>), dim3(grid1), t, 0, ctx->stream, m);  \
         hipLaunchKernelGGL((merge_kernel<TA, TB, TO, true>), g2, t, 0, ctx->stream, m);                       \
     } while (0)
     switch (sel) {
@@ -1191,4 +1197,11 @@ extern "C" int adapt_grad_add(adapt_ctx *ctx, const void *a, int wl_a, const int
     }
 #undef ADAPT_MERGE
     return hip_status(ctx, hipGetLastError());
+}
+}  // namespace adapt
+
+extern "C" int adapt_grad_add(adapt_ctx *ctx, const void *a, int wl_a, const int64_t *e_a, const void *b, int wl_b, const int64_t *e_b,
+                              size_t n, int wl_out, adapt_rng rng, void *out, int32_t *shift, int64_t *e_out)
+{
+    return grad_add(ctx, a, wl_a, e_a, b, wl_b, e_b, n, wl_out, rng, out, shift, e_out, nullptr, 0);
 }

@@ -84,6 +84,11 @@ struct FitTarget {
 };
 int wgrad_fit(adapt_ctx *ctx, const adapt_conv_desc &d, const void *dy, adapt_fmt fdy, const void *x, adapt_fmt fx, const FitTarget &t);
 
+// adapt_grad_add; part / nparts, optional: maxima of a's codes, whose largest is that of the tensor (with b = null and codes of at most
+// 16 bits the maximum pass is left out)
+int grad_add(adapt_ctx *ctx, const void *a, int wl_a, const int64_t *e_a, const void *b, int wl_b, const int64_t *e_b, size_t n, int wl_out,
+             adapt_rng rng, void *out, int32_t *shift, int64_t *e_out, const unsigned long long *part, int nparts);
+
 inline char *scratch(adapt_ctx *c) { return c->ws + kCtlBytes; }
 inline size_t scratch_bytes(const adapt_ctx *c) { return c->ws_bytes - kCtlBytes; }
 inline uint32_t *ticket(adapt_ctx *c, int slot) { return reinterpret_cast<uint32_t *>(c->ws) + slot; }

@@ -68,10 +68,12 @@ __global__ void __launch_bounds__(kEwThreads) maxpool2_kernel(const T *__restric
 
 // POOL: dy = da at the first maximum (scan order) of each window of the stored output y, zero
 // elsewhere; with relu also zero where that maximum is not positive.  !POOL: dy = da where y > 0.
-template <typename T, int V, bool POOL>
+template <typename T, int V, bool POOL, bool MAXIMA>
 __global__ void __launch_bounds__(kEwThreads)
-relu_pool_bwd_kernel(const T *__restrict__ da, const T *__restrict__ y, T *__restrict__ dy, const PoolGeo g, const int relu)
+relu_pool_bwd_kernel(const T *__restrict__ da, const T *__restrict__ y, T *__restrict__ dy, const PoolGeo g, const int relu,
+                     uint64_t *__restrict__ part /* MAXIMA: the largest magnitude of each block's outputs */)
 {
+    int lo = 0, hi = 0;      // MAXIMA: smallest and largest output of the thread
     typedef CodeVec<T, V> Vec;
     const Vec *yv = reinterpret_cast<const Vec *>(y);
     const Vec *dv = reinterpret_cast<const Vec *>(da);
@@ -91,6 +93,7 @@ relu_pool_bwd_kernel(const T *__restrict__ da, const T *__restrict__ y, T *__res
                 const T m = m0 > m1 ? m0 : m1;
                 const int first = v0.v[e] == m ? 0 : v1.v[e] == m ? 1 : v2.v[e] == m ? 2 : 3;
                 const T val = (!relu || m > 0) ? d.v[e] : (T)0;
+                if (MAXIMA) { lo = min(lo, (int)val); hi = max(hi, (int)val); }
                 o0.v[e] = first == 0 ? val : (T)0;
                 o1.v[e] = first == 1 ? val : (T)0;
                 o2.v[e] = first == 2 ? val : (T)0;
@@ -101,9 +104,17 @@ relu_pool_bwd_kernel(const T *__restrict__ da, const T *__restrict__ y, T *__res
             const Vec v = yv[i], d = dv[i];
             Vec o;
 #pragma unroll
-            for (int e = 0; e < V; ++e) o.v[e] = (!relu || v.v[e] > 0) ? d.v[e] : (T)0;
+            for (int e = 0; e < V; ++e) {
+                o.v[e] = (!relu || v.v[e] > 0) ? d.v[e] : (T)0;
+                if (MAXIMA) { lo = min(lo, (int)o.v[e]); hi = max(hi, (int)o.v[e]); }
+            }
             ov[i] = o;
         }
+    }
+    if constexpr (MAXIMA) {
+        __shared__ uint64_t sm[kEwThreads / kWave];
+        const uint64_t m = block_max_u64((uint64_t)max(-(long long)lo, (long long)hi), sm, kEwThreads / kWave);
+        if (threadIdx.x == 0) part[blockIdx.x] = m;
     }
 }
 
@@ -341,9 +352,12 @@ extern "C" int adapt_maxpool2_fwd(adapt_ctx *ctx, const void *y, adapt_fmt f, in
     return hip_status(ctx, hipGetLastError());
 }
 
-extern "C" int adapt_relu_pool_bwd(adapt_ctx *ctx, const void *da, const void *y, adapt_fmt f, int n, int h, int w, int c,
-                                   int relu, int pool, void *dy)
+// part / count, optional (codes of at most 16 bits): the largest magnitude of each block's outputs, room for one per block of the
+// grid (at most eight per CU), and their number (0: none)
+static int relu_pool_bwd(adapt_ctx *ctx, const void *da, const void *y, adapt_fmt f, int n, int h, int w, int c, int relu, int pool, void *dy,
+                         unsigned long long *part, int *count)
 {
+    if (count) *count = 0;
     if (!ctx || !fmt_ok_wide(f)) return ADAPT_EINVAL;
     const int es = storage_bytes(f);
     PoolGeo g;
@@ -352,24 +366,36 @@ extern "C" int adapt_relu_pool_bwd(adapt_ctx *ctx, const void *da, const void *y
     if (g.items == 0) return ADAPT_OK;
     if (!da || !y || !dy || !aligned16(da) || !aligned16(y) || !aligned16(dy)) return ADAPT_EINVAL;
     const dim3 grid(ew_grid(ctx, g.items)), block(kEwThreads);
-#define ADAPT_BWD(T, V, P) hipLaunchKernelGGL((relu_pool_bwd_kernel<T, V, P>), grid, block, 0, ctx->stream, (const T *)da, (const T *)y, (T *)dy, g, relu)
+    const bool maxima = part != nullptr && es <= 2;
+    auto launch = [&](auto kern, auto zero) {
+        typedef decltype(zero) T;
+        hipLaunchKernelGGL(kern, grid, block, 0, ctx->stream, (const T *)da, (const T *)y, (T *)dy, g, relu, reinterpret_cast<uint64_t *>(part));
+    };
+#define ADAPT_BWD(T, V, P) (maxima ? launch(relu_pool_bwd_kernel<T, V, P, true>, (T)0) : launch(relu_pool_bwd_kernel<T, V, P, false>, (T)0))
     if (pool) {
-        if (es == 4 && vec == 4) ADAPT_BWD(int32_t, 4, true);
-        else if (es == 4) ADAPT_BWD(int32_t, 1, true);
+        if (es == 4 && vec == 4) launch(relu_pool_bwd_kernel<int32_t, 4, true, false>, (int32_t)0);
+        else if (es == 4) launch(relu_pool_bwd_kernel<int32_t, 1, true, false>, (int32_t)0);
         else if (es == 1 && vec == 16) ADAPT_BWD(int8_t, 16, true);
         else if (es == 1) ADAPT_BWD(int8_t, 1, true);
         else if (vec == 8) ADAPT_BWD(int16_t, 8, true);
         else ADAPT_BWD(int16_t, 1, true);
     } else {
-        if (es == 4 && vec == 4) ADAPT_BWD(int32_t, 4, false);
-        else if (es == 4) ADAPT_BWD(int32_t, 1, false);
+        if (es == 4 && vec == 4) launch(relu_pool_bwd_kernel<int32_t, 4, false, false>, (int32_t)0);
+        else if (es == 4) launch(relu_pool_bwd_kernel<int32_t, 1, false, false>, (int32_t)0);
         else if (es == 1 && vec == 16) ADAPT_BWD(int8_t, 16, false);
         else if (es == 1) ADAPT_BWD(int8_t, 1, false);
         else if (vec == 8) ADAPT_BWD(int16_t, 8, false);
         else ADAPT_BWD(int16_t, 1, false);
     }
 #undef ADAPT_BWD
+    if (maxima && count) *count = (int)grid.x;
     return hip_status(ctx, hipGetLastError());
+}
+
+extern "C" int adapt_relu_pool_bwd(adapt_ctx *ctx, const void *da, const void *y, adapt_fmt f, int n, int h, int w, int c,
+                                   int relu, int pool, void *dy)
+{
+    return relu_pool_bwd(ctx, da, y, f, n, h, w, c, relu, pool, dy, nullptr, nullptr);
 }
 
 // ext_part / ext_n: per-block maxima that the kernel which produced `acc` has already stored (and, with sumsq, a cleared
@@ -910,14 +936,15 @@ extern "C" int adapt_net_backward(adapt_net *net, const void *dlogits, int dlogi
     // The gradient of layer j's output is the sum of what its consumers hand back.  The first contribution is stored
     // (refitted to layer j's word length when it comes from a layer of another word length), every later one is added
     // to it exactly and the sum refitted.  Exponents stay in device memory.
-    auto contribute = [&](int j, const void *codes, int wl, const long long *e, bool fitted) -> int {
+    // part / nparts: block maxima of `codes`, where the launch that wrote them left some
+    auto contribute = [&](int j, const void *codes, int wl, const long long *e, bool fitted, const unsigned long long *part = nullptr, int nparts = 0) -> int {
         NetLayer &t = net->L[j];
         const int k = ncontrib[j]++;
         char *dst = net->ws + t.off_da;
         long long *e_dst = &net->exps(j)->e_da;
         if (k == 0 && fitted) return ADAPT_OK;                       // written in place by the fitting pass
-        if (k == 0) return adapt_grad_add(ctx, codes, wl, (const int64_t *)e, nullptr, 8, nullptr, t.n_a, t.fmt.wl,
-                                          slot_rng_x(rng, j, X_MERGE), dst, nullptr, (int64_t *)e_dst);
+        if (k == 0) return grad_add(ctx, codes, wl, (const int64_t *)e, nullptr, 8, nullptr, t.n_a, t.fmt.wl,
+                                    slot_rng_x(rng, j, X_MERGE), dst, nullptr, (int64_t *)e_dst, part, nparts);
         return adapt_grad_add(ctx, dst, t.fmt.wl, (const int64_t *)e_dst, codes, wl, (const int64_t *)e, t.n_a, t.fmt.wl,
                               slot_rng_x(rng, j, X_MERGE + k), dst, nullptr, (int64_t *)e_dst);
     };
@@ -938,13 +965,19 @@ extern "C" int adapt_net_backward(adapt_net *net, const void *dlogits, int dlogi
             e_cur = &ex_l->spare;
         }
         const void *dz = da;
+        unsigned long long *const part_dz = reinterpret_cast<unsigned long long *>(net->ws + net->P.off_amax);
+        int n_part_dz = 0;
         if (y.d.relu || y.d.pool) {
-            if (int s = adapt_relu_pool_bwd(ctx, da, net->ws + y.off_y, y.fmt, c.n, y.p, y.q, c.k, y.d.relu, y.d.pool, net->ws + y.off_dy))
+            // the shortcut's first gradient is fitted to its own word length: its largest magnitude comes from the pass that writes it
+            // (a shortcut that has a gradient already merges two tensors, with a maximum of their sum)
+            const bool first = y.res >= 0 && ncontrib[y.res] == 0 && ctx->num_cu * 8 <= kAmaxCap;
+            if (int s = relu_pool_bwd(ctx, da, net->ws + y.off_y, y.fmt, c.n, y.p, y.q, c.k, y.d.relu, y.d.pool, net->ws + y.off_dy,
+                                      first ? part_dz : nullptr, &n_part_dz))
                 return s;
             dz = net->ws + y.off_dy;
         }
         if (y.res >= 0)
-            if (int s = contribute(y.res, dz, y.fmt.wl, e_cur, false)) return s;
+            if (int s = contribute(y.res, dz, y.fmt.wl, e_cur, false, part_dz, n_part_dz)) return s;
         adapt_net_stats *st = reinterpret_cast<adapt_net_stats *>(net->ws + y.off_stat);
         const void *dyc = dz;
         if (y.bn) {
