@@ -1691,7 +1691,7 @@ constexpr size_t rows_lds(int la, int lb)
 //   256 x 16 x 16 x 128 -> 128  <12,9> 65.2 -> 54.7   8 x 12 bits 51.3 -> 37.2   12 x 8 bits 53.9 -> 34.5   16 bits 72.6 -> 64.3
 //   256 x 32 x 32 x 64 -> 64           68.0 -> 49.5               53.3 -> 37.1               50.2 -> 34.9           84.5 -> 62.2
 //   128 x 8 x 8 x 384 -> 256           60.0 -> 44.4               51.0 -> 35.7               47.6 -> 34.9           75.6 -> 58.8
-//   256 x 11 x 11 x 48 -> 112 at 37 images (7 stages) 18.2 -> 18.8, 12.6 -> 14.9, 12.8 -> 14.6: left to the kernels above
+//   37 x 15 x 11 x 48 -> 112 (one and two stages)  18.2 -> 18.8               12.6 -> 14.9               12.8 -> 14.6: left to the kernels above
 static int rows_splits(const ContractArgs &a, int limbs, int num_cu)
 {
     if (limbs != 2 || a.stride != 1 || a.s != kRowsTaps || a.K == 0 || a.act_load != LOAD_ROWS || a.wgt_load != LOAD_ROWS) return 0;
