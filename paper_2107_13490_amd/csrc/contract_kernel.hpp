@@ -1683,16 +1683,19 @@ constexpr size_t rows_lds(int la, int lb)
     const size_t sums = (size_t)512 * 4 * (kRowsTaps * 8 * (la == 2 && lb == 2 ? 3 : la == 2 || lb == 2 ? 2 : 1) + kRowsTaps + 1);
     return 2 * stage > sums ? 2 * stage : sums;
 }
-// Splits of a weight gradient on image rows, 0 where the kernels above take it.  One block per CU; the kernel pays where the blocks
-// fill at least half of the CUs' products with real channels and slots, and where each walks at least 12 stages (its start, the
-// groups' exchange and the slabs are 8 us).  260 drawn layers at 4..16 bits, both kernels with the slab sum: of those that the rule takes none
-// is slower by more than 0.3 us, the median takes 0.83 of the time; of the others a fifth would gain (most by 5 %) and the rest lose (up
-// to 2.1 times).  us, kernels above -> here:
+// Splits of a weight gradient on image rows, 0 where the kernels above take it (with tile t and `splits` splits).  One block per CU; the
+// kernel pays where the blocks fill enough of the CUs' products with real channels and slots, and where each walks at least 12 stages (its
+// start, the groups' exchange and the slabs are 8 us), 15 where the kernels above have no slabs to sum either.  How much has to be filled
+// depends on what it replaces: the 64 x 64 tiles half; the double-buffered 128 x 128 tiles of two int16 operands 0.65; and two operands of
+// 16 bits, whose row sums stand between the products here, 0.65 and 0.85.  1230 layers at 8..16 bits that fill half and walk 12 stages (1 x 3,
+// 3 x 3 and 5 x 3 filters, ragged channels), both kernels with the slab sum: of the 927 that the rule takes three are slower, by at most 0.9
+// us, and the median takes 0.82 of the time; the others take 0.97, from 0.68 to 1.37.  us, kernels above -> here:
 //   256 x 16 x 16 x 128 -> 128  <12,9> 65.2 -> 54.7   8 x 12 bits 51.3 -> 37.2   12 x 8 bits 53.9 -> 34.5   16 bits 72.6 -> 64.3
 //   256 x 32 x 32 x 64 -> 64           68.0 -> 49.5               53.3 -> 37.1               50.2 -> 34.9           84.5 -> 62.2
 //   128 x 8 x 8 x 384 -> 256           60.0 -> 44.4               51.0 -> 35.7               47.6 -> 34.9           75.6 -> 58.8
 //   37 x 15 x 11 x 48 -> 112 (one and two stages)  18.2 -> 18.8               12.6 -> 14.9               12.8 -> 14.6: left to the kernels above
-static int rows_splits(const ContractArgs &a, int limbs, int num_cu)
+//   414 x 12 x 9 x 72 -> 344 (16 bits, fills 0.52) 96.4 -> 121.2, 24 x 28 x 27 x 176 -> 352 (0.63) 79.9 -> 88.8: left as well
+static int rows_splits(const ContractArgs &a, int limbs, int num_cu, const TileShape &t, int splits_above)
 {
     if (limbs != 2 || a.stride != 1 || a.s != kRowsTaps || a.K == 0 || a.act_load != LOAD_ROWS || a.wgt_load != LOAD_ROWS) return 0;
     const RowsGeometry g = rows_geometry(a);
@@ -1706,7 +1709,9 @@ static int rows_splits(const ContractArgs &a, int limbs, int num_cu)
     const int per = (g.stages + want - 1) / want, splits = (g.stages + per - 1) / per;
     const double real = (double)a.M * a.c * a.r / ((double)tiles * kRowsChannels * kRowsChannels) * g.slots / kRowsSlots;
     const double rounds = (double)tiles * splits / num_cu;
-    return per >= 12 && real * rounds >= 0.5 * std::ceil(rounds) ? splits : 0;
+    const bool both16 = a.act_es == 2 && a.wgt_es == 2;
+    const double fill = !both16 ? 0.5 : a.balanced ? (t.pipe ? 0.65 : 0.5) : (t.pipe ? 0.85 : 0.65);
+    return per >= (splits_above == 1 ? 15 : 12) && real * rounds >= fill * std::ceil(rounds) ? splits : 0;
 }
 
 // A contraction planned on the host: what the kernel gets, and what finish_kernel gets when K is
@@ -1792,27 +1797,6 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
         p.fin.slab_bytes = (long long)slab;
         arm(p.fin);
     };
-    if constexpr (OP == OP_WGRAD) {
-        if (const int want = rows_splits(a, limbs, ctx->num_cu)) {
-            const int stages = rows_geometry(a).stages, per = (stages + want - 1) / want, splits = (stages + per - 1) / per;
-            const bool direct = splits == 1 && !a.force_finish;
-            const size_t rows_slab = (size_t)((a.M + 31) / 32 * 32) * a.N * (bits == 32 ? 4 : 8);
-            if (direct || rows_slab * (size_t)splits <= room) {
-                a.k_per_split = per;             // in stages
-                a.slab_bytes = 0;
-                p.halo = 1;
-                if (!direct) {
-                    a.slab_rows = 1;
-                    to_slabs(splits, rows_slab);
-                } else {
-                    a.out_mode = final_mode;
-                    arm(a);
-                    p.kern = a;
-                }
-                return ADAPT_OK;
-            }
-        }
-    }
     TileShape t = pick_tile<OP>(a, limbs, ctx->num_cu);
     int model_splits = 0;
     if (OP == OP_WGRAD && a.act_load != LOAD_SCALAR && a.wgt_load != LOAD_SCALAR) model_splits = pick_split_tile(a, limbs, bits, ctx->num_cu, t);
@@ -1839,6 +1823,27 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
     int k_per = ((a.K + splits - 1) / splits + t.bkt - 1) / t.bkt * t.bkt;
     if (k_per == 0) k_per = t.bkt;
     splits = a.K == 0 ? 1 : (a.K + k_per - 1) / k_per;
+    if constexpr (OP == OP_WGRAD) {
+        if (const int want = rows_splits(a, limbs, ctx->num_cu, t, splits)) {
+            const int stages = rows_geometry(a).stages, per = (stages + want - 1) / want, row_splits = (stages + per - 1) / per;
+            const bool direct = row_splits == 1 && !a.force_finish;
+            const size_t rows_slab = (size_t)((a.M + 31) / 32 * 32) * a.N * (bits == 32 ? 4 : 8);
+            if (direct || rows_slab * (size_t)row_splits <= room) {
+                a.k_per_split = per;             // in stages
+                a.slab_bytes = 0;
+                p.halo = 1;
+                if (!direct) {
+                    a.slab_rows = 1;
+                    to_slabs(row_splits, rows_slab);
+                } else {
+                    a.out_mode = final_mode;
+                    arm(a);
+                    p.kern = a;
+                }
+                return ADAPT_OK;
+            }
+        }
+    }
     a.k_per_split = k_per;
     a.slab_bytes = 0;
     a.dg_classes = 0;

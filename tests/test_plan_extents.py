@@ -1,18 +1,59 @@
-"""What planned contractions read lies inside their operands (a host program, tests/plan_extents.hip; no GPU)."""
+"""What planned contractions read lies inside their operands, and which kernels calls take (host programs, tests/plan_extents.hip
+and tests/plan_routes.hip; no GPU)."""
 import os
 import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_planned_reads_stay_inside_the_operands(tmp_path):
+def _host_program(name, out):
     from paper_2107_13490_amd import build
     if not os.path.exists(build.LIB):
         build.build()
     lib = os.path.dirname(build.LIB)
-    exe = str(tmp_path / "plan_extents")
+    exe = str(out / name)
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17",
                     "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC,
-                    os.path.join(ROOT, "tests", "plan_extents.hip"), "-o", exe, "-L", lib, "-ladapt_fxp", "-Wl,-rpath," + lib], check=True)
-    r = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
+                    os.path.join(ROOT, "tests", name + ".hip"), "-o", exe, "-L", lib, "-ladapt_fxp", "-Wl,-rpath," + lib], check=True)
+    return exe
+
+
+def test_planned_reads_stay_inside_the_operands(tmp_path):
+    r = subprocess.run([_host_program("plan_extents", tmp_path)], stdout=subprocess.PIPE, text=True)
     assert r.returncode == 0, r.stdout[-2000:]
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    """call -> (rows, splits, slab elements) of its weight gradient alone, and beside the data gradient"""
+    exe = _host_program("plan_routes", tmp_path_factory.mktemp("routes"))
+
+    def plan(calls):
+        out = subprocess.run([exe], input="\n".join(" ".join(map(str, c)) for c in calls), stdout=subprocess.PIPE, text=True, check=True).stdout
+        lines = [[int(v) for v in line.split()] for line in out.splitlines()]
+        assert len(lines) == len(calls)
+        return [(tuple(v[:3]), tuple(v[3:])) for v in lines]
+    return plan
+
+
+def test_weight_gradients_take_image_rows_only_where_they_are_faster(routes):
+    # n, h, w, c, k, r, s, stride, pad, bits of dy, w, x; measured in us on the implicit GEMM and on image rows
+    slower = [
+        (414, 12, 9, 72, 344, 3, 3, 1, 1, 16, 16, 16),       # 96.4, 121.2: row sums, against the double-buffered tiles
+        (100, 20, 19, 144, 224, 3, 3, 1, 1, 16, 16, 16),     # 83.6, 98.8
+        (24, 28, 27, 176, 352, 3, 3, 1, 1, 16, 16, 16),      # 79.9, 88.8
+        (17, 16, 13, 400, 512, 3, 3, 1, 1, 16, 16, 16),      # 60.0, 66.1: no slabs on either side
+        (3, 32, 29, 464, 304, 3, 3, 1, 1, 12, 12, 12),       # 35.1, 36.6: twelve stages against no slabs
+        (14, 12, 9, 448, 432, 3, 3, 1, 1, 16, 12, 8),        # 18.2, 23.9
+    ]
+    faster = [
+        (256, 16, 16, 128, 128, 3, 3, 1, 1, 12, 12, 12),     # 65.2, 54.7
+        (256, 32, 32, 64, 64, 3, 3, 1, 1, 12, 12, 12),       # 68.0, 49.5
+        (256, 32, 32, 64, 64, 3, 3, 1, 1, 16, 16, 16),       # 84.5, 62.2
+        (128, 8, 8, 384, 256, 3, 3, 1, 1, 12, 12, 8),        # 47.6, 34.9
+        (256, 16, 16, 128, 128, 3, 3, 1, 1, 8, 12, 12),      # 51.3, 37.2
+    ]
+    plans = routes(slower + faster)
+    assert [p[0][0] for p in plans] == [0] * len(slower) + [1] * len(faster)
