@@ -6,19 +6,6 @@
 
 using namespace adapt;
 
-static bool pairable(const ContractPlan &p, bool is_dgrad)
-{
-    if (p.empty || p.halo || p.tile.pipe || p.tile.bkt != (p.limbs == 1 ? 192 : 64)) return false;
-    if (p.limbs == 2 && (p.kern.act_es != 2 || p.kern.wgt_es != 2)) return false;      // mixed storage: not paired
-    if (is_dgrad) {
-        if (p.kern.dg_classes) return false;      // stride 2 in class order: its own kernel, worth more than the shared launch
-        if (p.splits != 1 || p.kern.act_load != LOAD_VEC || p.kern.wgt_load != LOAD_ROWS) return false;
-    } else {
-        if (p.kern.act_load != LOAD_ROWS || p.kern.wgt_load != LOAD_ROWS) return false;
-    }
-    return (p.tile.bm == 64 || p.tile.bm == 128) && (p.tile.bn == 64 || p.tile.bn == 128);
-}
-
 extern "C" int adapt_conv_backward(adapt_ctx *ctx, adapt_conv_desc d, const void *dy, adapt_fmt fdy, const void *w,
                                    adapt_fmt fw, const void *x, adapt_fmt fx, void *dx, adapt_epilogue ep_dx, void *dw,
                                    adapt_epilogue ep_dw)
@@ -41,7 +28,7 @@ extern "C" int adapt_conv_backward(adapt_ctx *ctx, adapt_conv_desc d, const void
     if (d.n == 0) return hip_status(ctx, launch_and_finish(ctx, pw, launch_planned_wgrad));
     hipError_t e = launch_pads(ctx, pads);
     bool paired = false;
-    if (e == hipSuccess && pairable(pd, true) && pairable(pw, false) && pd.limbs == pw.limbs) {
+    if (e == hipSuccess && pairs(pd, pw)) {
         if (pd.tile.bm == 64 && pd.tile.bn == 64) e = launch_pair_d64x64(ctx, pd, pw, &paired);
         else if (pd.tile.bm == 128 && pd.tile.bn == 64) e = launch_pair_d128x64(ctx, pd, pw, &paired);
         else if (pd.tile.bm == 64 && pd.tile.bn == 128) e = launch_pair_d64x128(ctx, pd, pw, &paired);

@@ -1731,7 +1731,7 @@ struct ContractPlan {
 template <int OP>
 static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_fmt fb, adapt_epilogue ep,
                             size_t ws_offset /* bytes of scratch already in use */, ContractPlan &p,
-                            size_t ws_limit /* bytes of scratch there are */)
+                            size_t ws_limit /* bytes of scratch there are */, bool image_rows = true /* weight gradients may take them */)
 {
     const int limbs = (fa.wl > 8 || fb.wl > 8) ? 2 : 1;
     const int bits = adapt_acc_bits(a.k_bound ? a.k_bound : a.K, fa, fb);
@@ -1824,7 +1824,7 @@ static int plan_contraction(adapt_ctx *ctx, ContractArgs a, adapt_fmt fa, adapt_
     if (k_per == 0) k_per = t.bkt;
     splits = a.K == 0 ? 1 : (a.K + k_per - 1) / k_per;
     if constexpr (OP == OP_WGRAD) {
-        if (const int want = rows_splits(a, limbs, ctx->num_cu, t, splits)) {
+        if (const int want = image_rows ? rows_splits(a, limbs, ctx->num_cu, t, splits) : 0) {
             const int stages = rows_geometry(a).stages, per = (stages + want - 1) / want, row_splits = (stages + per - 1) / per;
             const bool direct = row_splits == 1 && !a.force_finish;
             const size_t rows_slab = (size_t)((a.M + 31) / 32 * 32) * a.N * (bits == 32 ? 4 : 8);
@@ -2105,6 +2105,39 @@ static int plan_fwd(adapt_ctx *ctx, const adapt_conv_desc &d, const void *x, ada
     return plan_contraction<OP_FWD>(ctx, a, fx, fw, ep, 0, p, ws_limit);
 }
 
+static bool pairable(const ContractPlan &p, bool is_dgrad)
+{
+    if (p.empty || p.halo || p.tile.pipe || p.tile.bkt != (p.limbs == 1 ? 192 : 64)) return false;
+    if (p.limbs == 2 && (p.kern.act_es != 2 || p.kern.wgt_es != 2)) return false;      // mixed storage: not paired
+    if (is_dgrad) {
+        if (p.kern.dg_classes) return false;      // stride 2 in class order: its own kernel, worth more than the shared launch
+        if (p.splits != 1 || p.kern.act_load != LOAD_VEC || p.kern.wgt_load != LOAD_ROWS) return false;
+    } else {
+        if (p.kern.act_load != LOAD_ROWS || p.kern.wgt_load != LOAD_ROWS) return false;
+    }
+    return (p.tile.bm == 64 || p.tile.bm == 128) && (p.tile.bn == 64 || p.tile.bn == 128);
+}
+// Both gradients of a layer in one launch (contract_pair.hpp)
+static bool pairs(const ContractPlan &pd, const ContractPlan &pw)
+{
+    return pairable(pd, true) && pairable(pw, false) && pd.limbs == pw.limbs;
+}
+// A weight gradient that could share the data gradient's launch goes to image rows instead where what it gains exceeds what the two launches
+// lose: the data gradient no longer fills the CUs that the weight gradient leaves idle, most of all with fewer than two of its tiles per CU.
+// Times in us from a fit to measured calls; `rows` is the plan on image rows, pw that on the 64 x 64 tiles of the pair.  746 layers at 9..16 bits whose
+// weight gradient alone goes to rows: of the 213 that the rule takes one is slower (1.1 %) and the median takes 0.86 of the time (154 x 20 x
+// 20 x 304 -> 48 190 -> 132, 386 x 31 x 30 x 64 -> 144 1 x 3 178 -> 134); the others take 1.03, up to 1.50 (16 x 15 x 15 x 384 -> 432 57.9 -> 86.0,
+// 128 x 4 x 4 x 512 -> 512 61.3 -> 87.7, 128 x 8 x 8 x 192 -> 384 74.9 -> 82.3, all <12,9>).
+static bool rows_beat_pair(const ContractPlan &pd, const ContractPlan &pw, const ContractPlan &rows, int num_cu)
+{
+    auto tiles = [](const ContractPlan &p) { return (double)((p.kern.M + p.tile.bm - 1) / p.tile.bm) * ((p.kern.N + p.tile.bn - 1) / p.tile.bn); };
+    const double per_cu = tiles(pd) / num_cu;
+    // stages of 64 reduction indices per CU; stages of image rows on the CU that has most
+    const double d = per_cu * pd.kern.K / 64, w = tiles(pw) / num_cu * pw.kern.K / 64;
+    const double r = (double)((rows_tiles(rows.kern) * rows.splits + num_cu - 1) / num_cu) * rows.kern.k_per_split;
+    return 0.46 * w > (0.15 + 0.3 * std::max(0.0, 2.0 - per_cu)) * d + (rows.kern.balanced ? 0.9 : 1.2) * r + 13.0;
+}
+
 // which of the two gradients a call computes
 enum { GRAD_DX = 1, GRAD_DW = 2 };
 static int plan_gradients(adapt_ctx *ctx, int which, const adapt_conv_desc &d, const void *dy, adapt_fmt fdy, const void *w, adapt_fmt fw,
@@ -2161,6 +2194,12 @@ static int plan_gradients(adapt_ctx *ctx, int which, const adapt_conv_desc &d, c
             a.M = d.k;                                // dw keeps its real rows; the appended ones are never written
             if (use & PAD_X) a.force_finish = 1;      // the kernel fills slabs with the appended columns, finish_kernel picks the real ones
             if (s == ADAPT_OK) s = plan_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep_dw, off, pw, ws_limit);
+            if (s == ADAPT_OK && (which & GRAD_DX) && pw.halo) {
+                ContractPlan shared;
+                if (plan_contraction<OP_WGRAD>(ctx, a, fdy, fx, ep_dw, off, shared, ws_limit, false) == ADAPT_OK && pairs(pd, shared) &&
+                    !rows_beat_pair(pd, shared, pw, ctx->num_cu))
+                    pw = shared;
+            }
             if (s == ADAPT_OK && (use & PAD_X) && !pw.empty) {
                 pw.fin.N = d.r * d.s * d.c;
                 pw.fin.ldc = pw.fin.N;

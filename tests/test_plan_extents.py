@@ -57,3 +57,24 @@ def test_weight_gradients_take_image_rows_only_where_they_are_faster(routes):
     ]
     plans = routes(slower + faster)
     assert [p[0][0] for p in plans] == [0] * len(slower) + [1] * len(faster)
+
+
+def test_backward_calls_give_up_a_shared_launch_only_for_less_time(routes):
+    # the weight gradient alone is faster on image rows in all of them; us of the whole call, one launch and two
+    shared = [
+        (128, 4, 4, 512, 512, 3, 3, 1, 1, 12, 12, 12),       # 61.3, 87.7
+        (192, 4, 4, 512, 512, 3, 3, 1, 1, 16, 16, 16),       # 106.6, 130.6
+        (128, 8, 8, 192, 384, 3, 3, 1, 1, 12, 12, 12),       # 74.9, 82.3
+        (24, 20, 19, 96, 448, 3, 3, 1, 1, 12, 12, 12),       # 62.3, 84.3
+        (198, 6, 6, 192, 272, 3, 3, 1, 1, 12, 12, 12),       # 54.3, 65.6
+    ]
+    apart = [
+        (154, 20, 20, 304, 48, 3, 3, 1, 1, 10, 16, 9),       # 190.1, 131.9
+        (386, 31, 30, 64, 144, 1, 3, 1, 1, 12, 14, 13),      # 178.3, 134.2
+        (303, 7, 7, 304, 144, 3, 3, 1, 1, 15, 16, 9),        # 146.1, 102.1
+        (128, 8, 8, 384, 256, 3, 3, 1, 1, 12, 12, 12),       # 91.4, 87.8
+        (256, 16, 16, 128, 128, 3, 3, 1, 1, 12, 12, 12),     # no shared launch: the data gradient runs on patches
+    ]
+    plans = routes(shared + apart)
+    assert all(alone[0] == 1 for alone, _ in plans)
+    assert [both[0] for _, both in plans] == [0] * len(shared) + [1] * len(apart)
