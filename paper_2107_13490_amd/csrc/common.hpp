@@ -156,8 +156,7 @@ __device__ __forceinline__ void store_vec(V *p, const V &v)
 }
 typedef unsigned u32v2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32v4 __attribute__((ext_vector_type(4)));
-typedef float f32v4 __attribute__((ext_vector_type(4)));
-// Where a call's tensors exceed the last-level cache together, its results are gone from it before the next call reads them
+// Bytes: of what a call has written, the next one finds up to this much without going to memory
 constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
 
 template <typename OutT>

@@ -426,11 +426,12 @@ static int quantize_on(adapt_ctx *ctx, const float *x, size_t n, adapt_fmt fmt, 
             hipLaunchKernelGGL(kern, dim3(grid), dim3(kQThreads), 0, ctx->stream, x, codes, (uint64_t)n, fmt.wl, fmt.fl, rng.mode, rng.seed,
                                rng.stream, partial, control, nnz, saturated);
         };
-        // Codes past the caches where they and the input exceed the last one.  67 M elements, us, through them / past them: new tensors
-        // each time 12 bits 87.5 / 82.1, 8 bits 74.9 / 70.2, the same tensors again (whose input then stays) 86.3 / 66.1 and 70.8 / 54.3.
-        // Smaller tensors' codes are still there for the call that reads them (16.8 M, 12 bits: 22.3 / 20.1, the next call's way to them
-        // is longer; 4.2 M 8.4 / 8.5).  Loads past the caches as well: 79.8 and 67.2, the same tensors 77.7 and 66.2.
-        const bool past = (uint64_t)n * (4 + storage_bytes(fmt)) > kLastLevelCache;
+        // Codes past the caches where they alone exceed the last one: less of them would still be there for the call that reads them.
+        // Together with that call (1 x 1 x 64 -> 16, 3 x 3 x 64 -> 64 convolution, 2 x 2 pooling), us, through the caches / past them: 12 bits,
+        // 50 M elements 100.5 / 104.0, 176.1 / 182.7, 85.1 / 87.5; 67 M 134.7 / 136.4, 237.9 / 238.5, 112.5 / 114.2; 147 M (codes of 295 MB) 293.1 /
+        // 291.8, 509.8 / 508.0, 255.1 / 252.6; 229 M 455.7 / 460.5, 791.3 / 792.2, 403.5 / 399.5; 8 bits, 302 M 481.7 / 477.5, 659.1 / 653.2, 402.4 /
+        // 396.3.  By itself the call gains 4 to 5 % at any of these sizes (67 M, 12 bits 86.4 / 82.9).  Loads past the caches as well gain nothing more.
+        const bool past = (uint64_t)n * storage_bytes(fmt) > kLastLevelCache;
         if (fmt.wl <= 8) launch(fused ? quantize_kernel<int8_t, true, false> : past ? quantize_kernel<int8_t, false, true> : quantize_kernel<int8_t, false, false>, (int8_t *)q);
         else launch(fused ? quantize_kernel<int16_t, true, false> : past ? quantize_kernel<int16_t, false, true> : quantize_kernel<int16_t, false, false>, (int16_t *)q);
     }
@@ -497,7 +498,7 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
     for (int base = 0; base < count; base += kMaxItems) {
         QuantBatch batch;
         batch.count = count - base < kMaxItems ? count - base : kMaxItems;
-        uint64_t total_blocks = 0, bytes = 0;
+        uint64_t total_blocks = 0, code_bytes = 0;
         for (int t = 0; t < batch.count; ++t) {
             batch.item[t] = items[base + t];
             if (items[base + t].wl > 16) {             // int32 codes: a launch of its own below; an empty placeholder here
@@ -505,7 +506,7 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
                 batch.item[t].wl = 8;
             }
             total_blocks += (((batch.item[t].n + 7) >> 3) + kQThreads - 1) / kQThreads;
-            bytes += batch.item[t].n * (uint64_t)(batch.item[t].wl <= 8 ? 5 : 6);
+            code_bytes += batch.item[t].n * (uint64_t)(batch.item[t].wl <= 8 ? 1 : 2);
         }
         uint64_t grid = total_blocks;
         uint64_t cap = (uint64_t)ctx->num_cu * 4;
@@ -521,7 +522,9 @@ extern "C" int adapt_quantize_batched_ranges(adapt_ctx *ctx, const adapt_quantiz
                                seed, partial, nullptr, (uint64_t)0, ticket(ctx, 0), counters + 2 * base);
             continue;
         }
-        hipLaunchKernelGGL((bytes > kLastLevelCache ? quantize_batched_kernel<false, true> : quantize_batched_kernel<false, false>), dim3((unsigned)grid),
+        // as in quantize_on; with a pooling of every tensor behind the call, us: two of 69 M to 12 bits 231.8 / 225.2, 33 of 4.2 M 297.3 / 286.0, four
+        // of 67 M to 8 bits 337.4 / 323.4
+        hipLaunchKernelGGL((code_bytes > kLastLevelCache ? quantize_batched_kernel<false, true> : quantize_batched_kernel<false, false>), dim3((unsigned)grid),
                            dim3(kQThreads), 0, ctx->stream, batch, mode, seed, partial, range_partial, range_mask >> base, nullptr, nullptr);
         // one wavefront per column: enough blocks for all the columns of the batch to run side by side
         const int sum_cols = (counters ? 2 * batch.count : 0) + (ranges ? 2 * batch.count : 0);

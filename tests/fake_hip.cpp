@@ -1,11 +1,19 @@
 // Stand-in for the HIP runtime calls that the library makes, for tests without a GPU: nothing is allocated on a device or
-// launched; every launch's dynamic LDS is checked against what was asked for the kernel with hipFuncSetAttribute last.
+// launched; every launch's dynamic LDS is checked against what was asked for the kernel with hipFuncSetAttribute last, and the names
+// of the kernels launched can be asked for.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
 
 #include <map>
+#include <string>
 
+static std::map<const void *, std::string> &names()      // (the library registers its kernels while it is loaded)
+{
+    static std::map<const void *, std::string> m;
+    return m;
+}
+static std::string launched;
 static std::map<const void *, int> limits;
 static int launches, big_launches, over_limit;
 static struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
@@ -15,6 +23,15 @@ extern "C" {
 int fake_launches() { return launches; }              // since the library was loaded
 int fake_big_launches() { return big_launches; }      // with more than the 64 KiB that need no request
 int fake_over_limit() { return over_limit; }          // with more than was requested
+
+const char *fake_launched()                           // names since the last call, a blank behind each
+{
+    static std::string last;
+    last.swap(launched);
+    launched.clear();
+    return last.c_str();
+}
+void __hipRegisterFunction(void **, const void *f, char *, const char *name, unsigned, void *, void *, dim3 *, dim3 *, int *) { names()[f] = name; }
 
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int)
@@ -42,6 +59,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **, size_t lds, hipStream_t)
 {
     ++launches;
+    launched += names()[f] + ' ';
     if (lds <= 64 * 1024) return hipSuccess;
     ++big_launches;
     const auto it = limits.find(f);

@@ -173,10 +173,10 @@ def test_batched_ranges_feed_the_precision_search():
     assert host(r2).tolist() == [float(xs[2].min()), float(xs[2].max())]
 
 
-@pytest.mark.parametrize("wl,n", [(8, 54_000_003), (12, 45_000_005)])
+@pytest.mark.parametrize("wl,n", [(8, 270_000_003), (12, 135_000_005)])
 @pytest.mark.parametrize("batched", [False, True])
-def test_tensors_that_exceed_the_last_level_cache(wl, n, batched):
-    # their codes take other stores; slices at both ends and inside against the oracle, the counters against the codes
+def test_codes_that_exceed_the_last_level_cache(wl, n, batched):
+    # codes of more than 256 MB take other stores; slices at both ends and inside against the oracle, the counters against the codes
     x = torch.randn(n, device="cuda")
     if batched:
         (q,), counters = ctx().quantize_batched([x], [(wl, wl - 3)], [9], pkg.SR, 5)[:2]
