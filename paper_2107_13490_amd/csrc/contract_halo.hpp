@@ -307,7 +307,7 @@ static hipError_t launch_halo_modes(adapt_ctx *ctx, const ContractPlan &p)
     }
     h.pw = h.ow + a.s - 1;
     h.pix = halo_pixels(kHaloShape[p.halo][0], h.oh, h.ow, a.r, a.s);
-    h.patches = halo_patches<OP>(a, p.halo);
+    h.patches = halo_patches<OP>(a);
     h.div_ow = make_fastdiv(h.ow); h.div_oh = make_fastdiv(h.oh); h.div_pw = make_fastdiv(h.pw); h.div_ir = make_fastdiv(h.oh + a.r - 1);
     if constexpr (!(AES == 2 && WES == 2))      // not planned: spills
         if (p.halo == HALO_256x128) return launch_halo_tile<OP, AES, WES, HALO_256x128, 4, 2>(ctx, h);

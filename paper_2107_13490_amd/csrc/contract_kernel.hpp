@@ -1591,14 +1591,14 @@ static int halo_pixels(int bm, int oh, int ow, int r, int s)
     return (rows + images * (r - 1)) * (ow + s - 1);
 }
 // LDS buffers for patches.  One chunk of channels has no next patch: 128 x 64 tiles run three blocks per CU then (mixed operands four)
-// instead of two.  us: 256 x 32 x 32 x 64 -> 64 <12,9> forward 49.4 -> 44.3, data gradient 49.6 -> 46.5; 16 bits 70.9 -> 62.3, 73.4 -> 64.4; 8 x 12
-// bits 31.3 -> 28.3; 12 x 8 bits data gradient 42.0 -> 32.1.  Several column tiles of two balanced operands lose by it (128 x 16 x 16 x 64 ->
-// 192 20.5 -> 21.1, 100 x 31 x 30 x 64 -> 128 40.2 -> 40.4; 16 bits 31.2 -> 27.4).
+// instead of two.  us, two buffers -> one: 256 x 32 x 32 x 64 -> 64 <12,9> forward 49.4 -> 44.3, data gradient 49.6 -> 46.5; 16 bits 70.9 -> 62.3, 73.4 ->
+// 64.4; 8 x 12 bits 31.3 -> 28.3; 12 x 8 bits data gradient 42.0 -> 32.1.  Several column tiles, <12,9>: 192 x 16 x 16 x 64 -> 128 21.0 -> 18.1,
+// 60 x 32 x 32 x 64 -> 288 53.0 -> 49.8; of 45 drawn layers, both directions, none is slower by more than 0.2 %.  256 x 128 tiles have one block per
+// CU either way and take the same time (45 layers, 0.98 to 1.01).
 template <int OP>
-static int halo_patches(const ContractArgs &a, int tile)
+static int halo_patches(const ContractArgs &a)
 {
-    if ((OP == OP_FWD ? a.c : a.k) > kHaloK) return 2;
-    return a.act_es == 2 && a.wgt_es == 2 && a.balanced && a.N > kHaloShape[tile][1] ? 2 : 1;
+    return (OP == OP_FWD ? a.c : a.k) > kHaloK ? 2 : 1;
 }
 template <int OP>
 static size_t halo_lds(const ContractArgs &a, int tile, int patches)
@@ -1615,6 +1615,7 @@ static size_t halo_lds(const ContractArgs &a, int tile, int patches)
 //   128 x 16 x 16 x 64 -> 192   24.9 -> 23.4 / 23.4    8 x 12 bits  18.4 -> 19.0 / 14.9
 //   128 x 8 x 8 x 256 -> 256    29.3 -> 53.0 / 28.9    8 x 12 bits  20.9 -> 38.0 / 22.5   (128 x 64 tiles: one block per CU)
 //   256 x 4 x 4 x 512 -> 512    55.1 ->    - / 61.5    (2.25 patch pixels per output)
+// (64 channels: with two patches in LDS, as the lines drawn below still have them; with the one that they have now 256 x 32 x 32 x 64 -> 64 46.4.)
 // One limb gains 5 % at most (19.9 -> 19.0) and two operands of 16 bits, whose offset sums do not fit the large tile's
 // registers, 6 % (71.0 -> 66.9) where there are tiles enough.
 template <int OP>
@@ -1635,7 +1636,8 @@ static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
     };
     const bool offset16 = a.act_es == 2 && a.wgt_es == 2 && !a.balanced;
     // rounds of resident blocks (256 x 128 tiles: one block per CU, 128 x 64: two); a last, partly filled round takes at least a
-    // third of a whole one
+    // third of a whole one.  Layers of one chunk, whose single patch leaves room for three or four, are counted as the others: of those that
+    // this keeps on the kernels above, <12,9> 150 x 16 x 16 x 64 -> 128 would take 17.5 us for its 23.6, 16 bits 26.9 for 31.6.
     auto rounds = [&](int t, int per_cu) {
         const double r = (double)tiles(t) / (per_cu * num_cu), whole = std::floor(r);
         return r > whole ? whole + 0.35 + 0.65 * (r - whole) : whole;
@@ -1644,7 +1646,8 @@ static int halo_tile(const ContractArgs &a, int limbs, int num_cu)
     const double large = rounds(HALO_256x128, 1), small = rounds(HALO_128x64, 2), ideal = (double)tiles(HALO_128x64) / (2 * num_cu);
     if (!offset16 && 2.0 * large <= 1.2 * small && large >= 0.93 && fits(HALO_256x128)) return HALO_256x128;
     // one chunk of int16 activations against int8 filters: the patch's way into LDS is the longer part (256 x 12 x 11 x 64 -> 192,
-    // 16 x 8 bits 24.5 -> 26.2)
+    // 16 x 8 bits 23.2 -> 24.0; with one patch the others would gain: 12 x 8 bits 22.9 -> 20.0, 256 x 32 x 32 x 64 -> 64 47.1 -> 31.5, 16 x 8 bits 47.3 ->
+    // 38.0)
     if (OP == OP_FWD && a.act_es == 2 && a.wgt_es == 1 && ch == kHaloK) return HALO_NONE;
     // (a nearly empty last round: 528 tiles, data gradient of 128 x 12 x 11 x 256 -> 64, 8 x 16 bits 20.4 -> 23.8)
     if (ideal >= (offset16 ? 1.5 : 1.0) && ideal >= 0.85 * small && fits(HALO_128x64)) return HALO_128x64;

@@ -1,6 +1,6 @@
 // Stand-in for the HIP runtime calls that the library makes, for tests without a GPU: nothing is allocated on a device or
-// launched; every launch's dynamic LDS is checked against what was asked for the kernel with hipFuncSetAttribute last, and the names
-// of the kernels launched can be asked for.
+// launched; every launch's dynamic LDS is checked against what was asked for the kernel with hipFuncSetAttribute last, and what was
+// launched can be asked for.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
@@ -24,7 +24,7 @@ int fake_launches() { return launches; }              // since the library was l
 int fake_big_launches() { return big_launches; }      // with more than the 64 KiB that need no request
 int fake_over_limit() { return over_limit; }          // with more than was requested
 
-const char *fake_launched()                           // names since the last call, a blank behind each
+const char *fake_launched()                           // since the last call: name/bytes of dynamic LDS, a blank behind each
 {
     static std::string last;
     last.swap(launched);
@@ -59,7 +59,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **, size_t lds, hipStream_t)
 {
     ++launches;
-    launched += names()[f] + ' ';
+    launched += names()[f] + '/' + std::to_string(lds) + ' ';
     if (lds <= 64 * 1024) return hipSuccess;
     ++big_launches;
     const auto it = limits.find(f);

@@ -10,6 +10,7 @@ PRELUDE = """
 import ctypes as C, sys
 fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)      # ahead of the HIP runtime that the library loads
 from paper_2107_13490_amd import binding as b
+fake.fake_launched.restype = C.c_char_p
 lib = b.load_library()
 at = 1 << 40      # operands are never read
 def context():
@@ -51,7 +52,6 @@ def test_launches_stay_within_the_lds_requested_for_their_kernels(tmp_path):
 
 
 QUANTIZE = """
-fake.fake_launched.restype = C.c_char_p
 h = context()
 for n, wl in ((45 << 20, 12), (1 << 26, 12), (1 << 27, 12), ((1 << 27) + 1, 12), (1 << 28, 8), ((1 << 28) + 1, 8)):
     assert lib.adapt_quantize(h, at, n, b.Fmt(wl, 4), b.Rng(1, 1, 1), 2 * at, 3 * at, 4 * at) == 0
@@ -68,3 +68,23 @@ def test_codes_are_stored_past_the_caches_only_where_they_exceed_the_last_one(tm
     for n, wl, one, batch in rows:
         past = n * (1 if wl <= 8 else 2) > 256 << 20
         assert (one, batch) == (past, past), (n, wl)
+
+
+PATCHES = """
+h = context()
+for n, hh, c, k in ((192, 16, 64, 128), (355, 8, 64, 240), (13, 32, 64, 400), (256, 32, 64, 64)):
+    for wx, ww in ((12, 12), (16, 16), (8, 13), (12, 9)):
+        f = b.Fmt(wx, 4), b.Fmt(ww, 4)
+        fake.fake_launched()
+        assert lib.adapt_conv_fwd(h, b.ConvDesc(n, hh, hh, c, k, 3, 3, 1, 1), at, f[0], 2 * at, f[1], 3 * at, b.Epilogue.exact()) == 0
+        assert lib.adapt_conv_dgrad(h, b.ConvDesc(n, hh, hh, k, c, 3, 3, 1, 1), at, f[0], 2 * at, f[1], 3 * at, b.Epilogue.exact()) == 0
+        for launch in fake.fake_launched().decode().split():
+            name, lds = launch.rsplit("/", 1)
+            if "halo_kernel" in name and "Li128ELi64E" in name:
+                print(c, lds)
+"""
+
+
+def test_patches_of_one_chunk_of_channels_leave_room_for_three_blocks(tmp_path):
+    rows = [[int(v) for v in line.split()] for line in _run(PATCHES, tmp_path).splitlines()]
+    assert len(rows) >= 16 and all(3 * lds <= 160 * 1024 for _, lds in rows), rows
