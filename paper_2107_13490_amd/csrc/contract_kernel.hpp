@@ -199,6 +199,7 @@ constexpr int limbs_of(int limb_mode) { return limb_mode == 1 ? 1 : 2; }
 constexpr bool bal_of(int limb_mode) { return limb_mode == 3; }
 
 typedef short v2s __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // four int16 in (d0 = e1:e0, d1 = e3:e2) -> the limbs of e0..e3 (see the header of this file)
 template <bool BAL>
 __device__ __forceinline__ void split16(uint32_t d0, uint32_t d1, uint32_t &hi, uint32_t &lo)
@@ -214,6 +215,21 @@ __device__ __forceinline__ void split16(uint32_t d0, uint32_t d1, uint32_t &hi, 
         lo = __builtin_amdgcn_perm(d1, d0, 0x06040200u) ^ 0x80808080u;
     }
 }
+// 16 bytes of codes as they lie in memory to an LDS line at p, their low limbs (int16 codes) to_low bytes further on
+template <int LM>
+__device__ __forceinline__ void store_limbs(const v4u &v, char *p, int to_low)
+{
+    if constexpr (LM == 1) {
+        *reinterpret_cast<v4u *>(p) = v;
+    } else {
+        uint32_t hi[2], lo[2];
+        split16<bal_of(LM)>(v[0], v[1], hi[0], lo[0]);
+        split16<bal_of(LM)>(v[2], v[3], hi[1], lo[1]);
+        *reinterpret_cast<uint2 *>(p) = make_uint2(hi[0], hi[1]);
+        *reinterpret_cast<uint2 *>(p + to_low) = make_uint2(lo[0], lo[1]);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // tile staging: global -> registers (prefetch) -> LDS
 //
@@ -237,7 +253,6 @@ __device__ __forceinline__ void split16(uint32_t d0, uint32_t d1, uint32_t &hi, 
 // unit is written to LDS, a stage later: a wavefront never waits on a load it has just issued.  Branch-free: the
 // operand is read through a raw buffer descriptor whose range check returns zeros for out-of-range offsets, so an
 // invalid unit just uses an offset beyond the tensor; zeros split into the limbs of code 0.
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes)
 {
@@ -1703,7 +1718,8 @@ static int rows_splits(const ContractArgs &a, int limbs, int num_cu, const TileS
     if (limbs != 2 || a.stride != 1 || a.s != kRowsTaps || a.K == 0 || a.act_load != LOAD_ROWS || a.wgt_load != LOAD_ROWS) return 0;
     const RowsGeometry g = rows_geometry(a);
     if (g.stages == 0 || g.lines > kRowsLines) return 0;
-    // the chunks' offsets run on for two stages beyond the reduction and must not come round to the operands' starts
+    // The chunks' offsets run on for two stages beyond the reduction and must not come round to the start of dy, where codes are.  (x's
+    // may, under filters of many rows on images of few output rows: what it meets there is zeros of dy.)
     const uint64_t beyond = 4ull * kRowsSlots * (uint64_t)std::max(a.k * a.act_es, 2 * a.c * a.wgt_es) + (1ull << 20);
     if (a.act_bytes + beyond >= 1ull << 32 || a.wgt_bytes + beyond >= 1ull << 32) return 0;
     const long long tiles = rows_tiles(a);
@@ -1929,18 +1945,30 @@ hipError_t launch_planned_dgrad(adapt_ctx *ctx, const ContractPlan &p);
 hipError_t launch_planned_wgrad(adapt_ctx *ctx, const ContractPlan &p);
 
 // the slab sum + epilogue of a split contraction
+// Threads that share an output of the slab sum: 256 x 28 x 28 x 32 -> 48 at 169 images, 85 slabs, both launches 27.1 us with one, 24.7 with four;
+// 92 x 16 -> 32 at 115, 81 slabs 26.5, 24.9, 24.6 with 16; with more outputs there are threads enough (147,456 outputs, 21 slabs 55.2, 54.7,
+// 57.9; 589,824, 5 slabs 51.4, 55.4, 77.4).  Around the lines, one / four / 16 threads: 9,216 outputs 22.9 / 18.7 / 17.8, 10,240 15.8 / 12.9 / 13.4 and 22.6 /
+// 19.1 / 18.0, 23,040 34.2 / 31.8 / 32.1, 24,576 41.4 / 39.0 / 39.1, 27,648 35.3 / 33.3 / 35.6, 36,864 19.8 / 18.6 / 19.4; fewer than 32 slabs of 4,096 to 9,216 outputs
+// 9.9 / 9.5 / 8.2.  Of 52 layers none is slower than with one thread.
+static size_t slab_sum_positions(const ContractPlan &p)      // outputs, or elements of a slab on image rows
+{
+    return p.fin.slab_rows ? (size_t)p.fin.slab_bytes / (p.bits == 32 ? 4 : 8) : (size_t)p.fin.M * p.fin.N;
+}
+static int slab_sum_share(const ContractPlan &p)
+{
+    const size_t total = slab_sum_positions(p);
+    return p.splits < 32 || total > 24000 ? 1 : total > 9216 ? 4 : 16;
+}
 static hipError_t finish_planned(adapt_ctx *ctx, const ContractPlan &p)
 {
     if (p.empty || p.acc == nullptr) return hipSuccess;
-    const size_t total = p.fin.slab_rows ? (size_t)p.fin.slab_bytes / (p.bits == 32 ? 4 : 8) : (size_t)p.fin.M * p.fin.N;
-    // Threads that share an output: 256 x 28 x 28 x 32 -> 48 at 169 images, 85 slabs, both launches 27.1 us with one, 24.7 with four; 92 x
-    // 16 -> 32 at 115, 81 slabs 26.5, 24.9, 24.6 with 16; with more outputs there are threads enough (147,456 outputs, 21 slabs 55.2, 54.7,
-    // 57.9; 589,824, 5 slabs 51.4, 55.4, 77.4)
-    const int share = p.splits < 32 || total > 24000 ? 1 : total > 9216 ? 4 : 16;
+    const size_t total = slab_sum_positions(p);
+    const int share = slab_sum_share(p);
     const unsigned per = 256 / share, fgrid = (unsigned)std::min<size_t>((total + per - 1) / per, (size_t)ctx->num_cu * 8);
     auto launch = [&](auto *acc) {
         typedef std::remove_const_t<std::remove_pointer_t<decltype(acc)>> AccT;
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(fgrid), dim3(256), 0, ctx->stream, acc, p.splits, p.fin); };
+        // image rows: below 4/3 of 2^31, since fill_conv refuses 2^31 weights (of whole 16s of both channels) and rows_splits tiles that are half empty
         if (p.fin.slab_rows) go(share == 1 ? finish_kernel<AccT, 1, true, uint32_t> : share == 4 ? finish_kernel<AccT, 4, true, uint32_t> : finish_kernel<AccT, 16, true, uint32_t>);
         else if (total >= 1u << 31) go(finish_kernel<AccT, 1, false, uint64_t>);
         else go(share == 1 ? finish_kernel<AccT, 1, false, uint32_t> : share == 4 ? finish_kernel<AccT, 4, false, uint32_t> : finish_kernel<AccT, 16, false, uint32_t>);

@@ -105,25 +105,12 @@ rows_kernel(const RowsArgs h)
         x_p[i] = p - (over ? a.p : 0);
         x_off[i] += x_step + (over ? x_wrap : 0u);
     };
-    // a chunk's limbs to their planes
-    auto store_chunk = [](auto mode, const v4u &v, char *p, int to_low) {
-        constexpr int LM = decltype(mode)::value;
-        if constexpr (LM == 1) {
-            *reinterpret_cast<v4u *>(p) = v;
-        } else {
-            uint32_t hi[2], lo[2];
-            split16<bal_of(LM)>(v[0], v[1], hi[0], lo[0]);
-            split16<bal_of(LM)>(v[2], v[3], hi[1], lo[1]);
-            *reinterpret_cast<uint2 *>(p) = make_uint2(hi[0], hi[1]);
-            *reinterpret_cast<uint2 *>(p + to_low) = make_uint2(lo[0], lo[1]);
-        }
-    };
     auto store_a = [&](char *buf, int i) {
-        store_chunk(std::integral_constant<int, AES>{}, av[i], buf + (a_slot + i * (NT / CLA)) * ARB + threadIdx.x % CLA * PA, A_LO);
+        store_limbs<AES>(av[i], buf + (a_slot + i * (NT / CLA)) * ARB + threadIdx.x % CLA * PA, A_LO);
     };
     auto store_x = [&](char *buf, int i) {
         if (wave_line + i * (NT / CLX) < h.g.lines)
-            store_chunk(std::integral_constant<int, WES>{}, xv[i], buf + X_HI + (x_line + i * (NT / CLX)) * XRB + threadIdx.x % CLX * PX, X_LO);
+            store_limbs<WES>(xv[i], buf + X_HI + (x_line + i * (NT / CLX)) * XRB + threadIdx.x % CLX * PX, X_LO);
     };
     auto load = [&](int i) { if (i < UX) load_x(i); else load_a(i - UX); };
     auto store = [&](char *buf, int i) { if (i < UX) store_x(buf, i); else store_a(buf, i - UX); };

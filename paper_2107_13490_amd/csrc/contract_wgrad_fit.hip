@@ -36,23 +36,6 @@ __device__ __forceinline__ void exchange(uint32_t a, uint32_t b, uint32_t &first
     second = r[1];
 }
 
-// fit_one on sums of 32 bits, and on 256 u + low (0 <= low < 256, u in 32 bits): the same values, since the shift is one after which
-// they fit 16 bits
-__device__ __forceinline__ int fit_one32(int v, int shift, uint32_t r16)
-{
-    if (shift == 0) return v;
-    if (shift <= 16) return (v >> shift) + (int)((((uint32_t)v & ((1u << shift) - 1u)) + (r16 >> (16 - shift))) >> shift);
-    const int t = v >> (shift - 16);
-    return (t >> 16) + (int)((((uint32_t)t & 0xffffu) + r16) >> 16);
-}
-__device__ __forceinline__ int fit_pair(int u, int low, int shift, uint32_t r16)
-{
-    if (shift < 8) return (int)((uint32_t)u << (8 - shift)) + ((low + (int)(r16 >> (16 - shift))) >> shift);
-    if (shift <= 16) return (u + ((low + (int)(r16 >> (16 - shift))) >> 8)) >> (shift - 8);
-    const int t = shift >= 24 ? u >> (shift - 24) : (int)((uint32_t)u << (24 - shift)) | (low >> (shift - 16));
-    return (t >> 16) + (int)((((uint32_t)t & 0xffffu) + r16) >> 16);
-}
-
 template <int AES, int WES, bool FIT>
 __global__ void __launch_bounds__(kThreads, 2)
 short_kernel(const ShortArgs h)
@@ -76,18 +59,6 @@ short_kernel(const ShortArgs h)
     uint64_t part_max = 0;             // the thread's share of the maximum
     if (FIT) part_max = max_of_parts<kThreads>(reinterpret_cast<const uint64_t *>(h.t.part), h.nparts);
 
-    auto store_chunk = [](auto mode, const v4u &v, char *p, int to_low) {
-        constexpr int LM = decltype(mode)::value;
-        if constexpr (LM == 1) {
-            *reinterpret_cast<v4u *>(p) = v;
-        } else {
-            uint32_t hi[2], lo[2];
-            split16<bal_of(LM)>(v[0], v[1], hi[0], lo[0]);
-            split16<bal_of(LM)>(v[2], v[3], hi[1], lo[1]);
-            *reinterpret_cast<uint2 *>(p) = make_uint2(hi[0], hi[1]);
-            *reinterpret_cast<uint2 *>(p + to_low) = make_uint2(lo[0], lo[1]);
-        }
-    };
     const int x_slot = threadIdx.x / CLX, x_col = threadIdx.x % CLX * PX;      // chunk i of a stage of x: slot x_slot + i * kThreads / CLX
     v4u xv[UX];
     auto load_x = [&](int st) {
@@ -102,7 +73,7 @@ short_kernel(const ShortArgs h)
     auto store_x = [&](int st) {
         char *const buf = xbuf + (st & 1) * X_STAGE;
 #pragma unroll
-        for (int i = 0; i < UX; ++i) store_chunk(std::integral_constant<int, WES>{}, xv[i], buf + (x_slot + i * (kThreads / CLX)) * LP + x_col, X_LO);
+        for (int i = 0; i < UX; ++i) store_limbs<WES>(xv[i], buf + (x_slot + i * (kThreads / CLX)) * LP + x_col, X_LO);
     };
     load_x(0);
     for (int c = 0; c < h.chunks; ++c) {
@@ -115,7 +86,7 @@ short_kernel(const ShortArgs h)
             av[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, ok ? ((uint32_t)k * (uint32_t)a.k + (uint32_t)(m0 + col)) * EA : NOWHERE, 0, 0);
         }
 #pragma unroll
-        for (int i = 0; i < UA; ++i) store_chunk(std::integral_constant<int, AES>{}, av[i], smem + c * A_STAGE + (slot + i * (kThreads / CLA)) * LP + col, A_LO);
+        for (int i = 0; i < UA; ++i) store_limbs<AES>(av[i], smem + c * A_STAGE + (slot + i * (kThreads / CLA)) * LP + col, A_LO);
     }
     int shift = 0;
     if (FIT) {
@@ -335,9 +306,11 @@ int wgrad_fit(adapt_ctx *ctx, const adapt_conv_desc &d, const void *dy, adapt_fm
     ContractArgs &a = h.a;
     if (fill_wgrad(a, d, dy, fdy, x, fx, t.q) != ADAPT_OK) return ADAPT_EUNSUPPORTED;
     // Where the second contraction costs less than the sums' way through memory: us, backward pass of a c -> k layer and a small one behind
-    // it, before -> here.  One limb: 128 x 4096 -> 4096 68.0 -> 51.9, 256 images 73.0 -> 61.7, 1024 -> 1024 32.5 -> 30.7.  Two: 16 bits 108.8 ->
-    // 82.0, 12 bits 83.8 -> 67.4, 9216 -> 4096 at 16 bits 264 -> 132; 256 images (two stages per tile) 120.5 -> 146.7; 2048 -> 2048 50.7 ->
-    // 50.6 with two tiles per block, 1024 -> 1024 35.0 -> 40.4 with one.
+    // it, before -> here.  One limb: 128 x 4096 -> 4096 68.0 -> 51.9, 256 images 73.0 -> 61.7, 1024 -> 1024 32.5 -> 30.7; below 2^20 weights 768 -> 768
+    // 29.3 -> 29.4 for 8 images and 30.4 -> 29.5 for 128, an int8 layer on int16 inputs 31.1 -> 31.7 and 33.1 -> 33.0, 512 -> 512 29.6 -> 30.7.  Two: 16 bits
+    // 108.8 -> 82.0, 12 bits 83.8 -> 67.4, 9216 -> 4096 at 16 bits 264 -> 132; 256 images (two stages per tile) 120.5 -> 146.7; 2048 -> 2048 50.7 ->
+    // 50.6 with two tiles per block (8 images, 12 bits 44.5 -> 45.1, 16 x 8 bits 52.7 -> 46.7), 1024 -> 1024 35.0 -> 40.4 with one.  90 layers and word lengths at
+    // 8 to 256 images: none slower where the rule takes it.
     const bool one_limb = a.act_es == 1 && a.wgt_es == 1;
     if (a.act_load != LOAD_ROWS || a.wgt_load != LOAD_ROWS || a.K < 1 || a.K > (one_limb ? kShortMaxK : kShortSlots)) return ADAPT_EUNSUPPORTED;
     if ((long long)a.M * a.N < 1 << 20) return ADAPT_EUNSUPPORTED;

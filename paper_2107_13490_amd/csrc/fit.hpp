@@ -52,6 +52,23 @@ __device__ __forceinline__ int fit_one(long long acc, int shift, uint32_t r16, i
     return min(max(q, qlo), qhi);
 }
 
+// fit_one on sums of 32 bits, and on 256 u + low (0 <= low < 256, u in 32 bits): the same values, since the shift is one after which
+// they fit 16 bits
+__device__ __forceinline__ int fit_one32(int v, int shift, uint32_t r16)
+{
+    if (shift == 0) return v;
+    if (shift <= 16) return (v >> shift) + (int)((((uint32_t)v & ((1u << shift) - 1u)) + (r16 >> (16 - shift))) >> shift);
+    const int t = v >> (shift - 16);
+    return (t >> 16) + (int)((((uint32_t)t & 0xffffu) + r16) >> 16);
+}
+__device__ __forceinline__ int fit_pair(int u, int low, int shift, uint32_t r16)
+{
+    if (shift < 8) return (int)((uint32_t)u << (8 - shift)) + ((low + (int)(r16 >> (16 - shift))) >> shift);
+    if (shift <= 16) return (u + ((low + (int)(r16 >> (16 - shift))) >> 8)) >> (shift - 8);
+    const int t = shift >= 24 ? u >> (shift - 24) : (int)((uint32_t)u << (24 - shift)) | (low >> (shift - 16));
+    return (t >> 16) + (int)((((uint32_t)t & 0xffffu) + r16) >> 16);
+}
+
 // shift = max(0, bit_length(m) - (wl - 1)) for the largest magnitude m
 __device__ __forceinline__ int fit_shift_of(uint64_t m, int wl)
 {
