@@ -17,7 +17,7 @@ constexpr size_t kFar = (size_t)1 << 40;      // distance of the made-up operand
 char *const kA = reinterpret_cast<char *>(kFar), *const kB = reinterpret_cast<char *>(2 * kFar), *const kC = reinterpret_cast<char *>(3 * kFar),
            *const kWorkspace = reinterpret_cast<char *>(5 * kFar);
 struct Operand { const void *at; uint64_t bytes; };
-int failures = 0, gathers = 0, copies = 0;
+int failures = 0, gathers = 0, copies = 0, rows = 0, rows_slabs = 0;
 
 uint64_t bytes_at(const void *p, const Operand *ops, int count, const PadJobs &pads)
 {
@@ -94,7 +94,7 @@ int main()
     const adapt_epilogue exact = {1, {8, 0}, {ADAPT_RN_HALF_UP, 0, 0}, 0}, requant = {0, {8, 4}, {ADAPT_SR, 1, 2}, 0};
     char what[256];
     for (int t = 0; t < 40000; ++t) {
-        const size_t limit = (size_t)1 << pick(8, 28);
+        const size_t limit = (size_t)1 << pick(8, t % 16 == 2 ? 32 : 28);
         const adapt_fmt f[3] = {{pick(2, 16), 4}, {pick(2, 16), 4}, {pick(2, 16), 4}};
         const adapt_epilogue ep = pick(0, 1) ? exact : requant;
         PadJobs pads;
@@ -115,6 +115,12 @@ int main()
         if (pick(0, 2) == 0) d.c = (d.c + 15) / 16 * 16;
         if (pick(0, 2) == 0) d.k = (d.k + 15) / 16 * 16;
         d.r = pick(1, 7); d.s = pick(1, 7); d.stride = pick(1, 3); d.pad = pick(0, 3);
+        if (t % 16 == 2) {      // weight gradients on image rows: fuller tiles, longer reductions
+            const int wide = pick(0, 2) == 0 ? 350 : 0;      // enough tiles for one split each
+            d.n *= wide ? 1 : pick(1, 60);
+            d.w = pick(4, 40); d.c = d.c % 8 * 16 + pick(32, 80) + wide; d.k = d.k % 8 * 16 + pick(32, 80) + wide;
+            d.r = pick(0, 1) ? 3 : pick(1, 5); d.s = 3; d.stride = 1; d.pad = pick(0, 2);
+        }
         if (!conv_ok(d)) continue;
         const uint64_t dy = (uint64_t)d.n * ((d.h + 2 * d.pad - d.r) / d.stride + 1) * ((d.w + 2 * d.pad - d.s) / d.stride + 1) * d.k;
         const uint64_t x = (uint64_t)d.n * d.h * d.w * d.c, w = (uint64_t)d.k * d.r * d.s * d.c;
@@ -133,7 +139,11 @@ int main()
         check_copies(ops, 3, pads, limit, what);
         if (which & GRAD_DX) check<OP_DGRAD>(p, ops, 3, pads, limit, what);
         if (which & GRAD_DW) check<OP_WGRAD>(pw, ops, 3, pads, limit, what);
+        if (which & GRAD_DW && pw.halo) {
+            ++rows;
+            rows_slabs += pw.acc != nullptr;
+        }
     }
-    printf("%d failures, %d plans with gathered operands, %d copies\n", failures, gathers, copies);
-    return failures != 0 || gathers == 0 || copies == 0;
+    printf("%d failures, %d plans with gathered operands, %d copies, %d on image rows, %d of them with slabs\n", failures, gathers, copies, rows, rows_slabs);
+    return failures != 0 || gathers == 0 || copies == 0 || rows_slabs < 100 || rows == rows_slabs;
 }

@@ -1,6 +1,7 @@
 // Host program (no GPU): reads calls, a line of numbers each (n h w c k r s stride pad, word lengths of dy, w and x), and prints for
 // each which kernels a context with enough workspace would take for its weight gradient, alone and together with the data gradient:
-//   rows splits slab_elements   rows splits slab_elements     (rows: on image rows in LDS; 0 slab elements: no slab sum)
+//   rows splits positions threads   rows splits positions threads
+// rows: on image rows in LDS; positions of the slab sum and the threads that share one, 0 0 where there is none.
 #include <stdio.h>
 
 #include "contract_kernel.hpp"
@@ -20,8 +21,8 @@ int main()
         for (int which : {(int)GRAD_DW, GRAD_DX | GRAD_DW}) {
             PadJobs pads;
             ContractPlan pd = {}, pw = {};
-            if (plan_gradients(&ctx, which, d, base, dy, base, w, base, x, base, ep, base, ep, (size_t)1 << 34, pads, pd, pw) != ADAPT_OK) return 1;
-            printf("%d %d %llu ", pw.halo, pw.splits, (unsigned long long)(pw.acc ? pw.fin.slab_bytes / (pw.bits / 8) : 0));
+            if (plan_gradients(&ctx, which, d, base, dy, base, w, base, x, base, ep, base, ep, (size_t)1 << 36, pads, pd, pw) != ADAPT_OK) return 1;
+            printf("%d %d %llu %d ", pw.halo, pw.splits, (unsigned long long)(pw.acc ? slab_sum_positions(pw) : 0), pw.acc ? slab_sum_share(pw) : 0);
         }
         printf("\n");
     }

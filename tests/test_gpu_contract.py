@@ -684,21 +684,36 @@ def test_convolutions_on_patches(case):
         assert np.array_equal(dxq[i:i + 1], orc.requantize(want, sh, wlx, orc.SR, 3, 41, False, start=i * h * w * k)), i
 
 
-# ---- weight gradients of stride-1, three taps wide filters on image rows in LDS: sizes that fill half of the GPU with 12 stages each --
-@pytest.mark.parametrize("case", [
-    # n, h, w, c, k, r, s, pad, wl_dy, wl_x
-    (130, 16, 16, 128, 128, 3, 3, 1, 12, 12),     # whole groups of eight pixels, a last stage and split that are short
-    (130, 16, 16, 128, 128, 3, 3, 1, 16, 16),     # offset split of both operands
-    (1400, 4, 4, 192, 128, 3, 3, 1, 13, 8),       # rows of four pixels: the most lines of a stage
-    (100, 18, 17, 128, 112, 3, 3, 0, 8, 13),      # rows of 15 pixels, no padding, output channels beyond dw
-    (64, 32, 33, 128, 120, 3, 3, 1, 16, 7),       # 29 of a stage's slots unused; copies of dy
-    (8, 16, 16, 512, 512, 3, 3, 1, 15, 9),        # one split: no slabs
-    (8, 16, 16, 500, 512, 3, 3, 1, 8, 16),        # copies of x; slabs with appended channels
-    (100, 16, 16, 256, 256, 1, 3, 1, 9, 12),      # one row of taps
-    (160, 16, 14, 128, 64, 5, 3, 2, 12, 6),       # five rows of taps, output wider than the input
-])
+# ---- weight gradients of stride-1, three taps wide filters on image rows in LDS: sizes that the plan takes there (checked without a GPU in
+# tests/test_plan_extents.py), with the threads that share a position of their slab sum, 0 where one split writes the output itself --
+ROWS_CASES = [
+    # n, h, w, c, k, r, s, pad, wl_dy, wl_x, threads
+    (130, 16, 16, 128, 128, 3, 3, 1, 12, 12, 1),     # whole groups of eight pixels, a last stage and split that are short
+    (130, 16, 16, 128, 128, 3, 3, 1, 16, 16, 1),     # offset split of both operands
+    (130, 16, 16, 128, 128, 3, 3, 1, 8, 12, 1),      # int8 dy
+    (1400, 4, 4, 192, 128, 3, 3, 1, 13, 8, 1),       # rows of four pixels: the most lines of a stage
+    (130, 18, 17, 128, 112, 3, 3, 0, 8, 13, 1),      # rows of 15 pixels, no padding, output channels beyond dw
+    (64, 32, 33, 128, 120, 3, 3, 1, 16, 7, 1),       # 29 of a stage's slots unused; copies of dy
+    (8, 16, 16, 512, 512, 3, 3, 1, 15, 9, 0),        # one split: no slabs
+    (8, 16, 16, 512, 512, 3, 3, 1, 16, 16, 0),
+    (8, 16, 16, 512, 512, 3, 3, 1, 8, 12, 0),
+    (8, 16, 16, 512, 512, 3, 3, 1, 7, 16, 0),
+    (8, 16, 16, 512, 512, 3, 3, 1, 12, 8, 0),
+    (8, 16, 16, 512, 512, 3, 3, 1, 16, 5, 0),
+    (8, 15, 17, 512, 496, 3, 3, 1, 13, 13, 0),       # rows of 17 pixels
+    (8, 16, 16, 500, 512, 3, 3, 1, 8, 16, 1),        # copies of x; slabs with appended channels
+    (100, 16, 16, 256, 256, 1, 3, 1, 9, 12, 1),      # one row of taps
+    (160, 16, 14, 128, 64, 5, 3, 2, 12, 6, 1),       # five rows of taps, output wider than the input
+    (400, 32, 32, 64, 64, 1, 3, 1, 16, 8, 4),        # few outputs
+    (400, 32, 32, 60, 64, 1, 3, 1, 12, 12, 4),       # with appended channels
+    (400, 32, 32, 48, 48, 1, 3, 1, 8, 13, 16),
+    (400, 32, 30, 45, 48, 1, 3, 1, 12, 8, 16),
+]
+
+
+@pytest.mark.parametrize("case", ROWS_CASES)
 def test_weight_gradients_on_image_rows(case):
-    n, h, w, c, k, r, s, pad, wldy, wlx = case
+    n, h, w, c, k, r, s, pad, wldy, wlx, _ = case
     d = ConvDesc(n, h, w, c, k, r, s, 1, pad)
     fdy, fx = (wldy, wldy - 3), (wlx, wlx - 3)
     x, dy = codes((n, h, w, c), wlx, 1, True), codes((n, d.p, d.q, k), wldy, 2, True)
@@ -709,8 +724,11 @@ def test_weight_gradients_on_image_rows(case):
     assert np.array_equal(got, orc.requantize(want, wldy - 3 + wlx - 3 - 2, wlx, orc.SR, 3, 44, False))
 
 
-# The slab sum of few outputs: one, four and sixteen threads share an output
-@pytest.mark.parametrize("c,k", [(3, 16), (16, 64), (32, 64)])
+# The slab sum of few outputs: sixteen, four and one threads share an output (checked without a GPU in tests/test_plan_extents.py)
+SLAB_SUM_CASES = [(3, 16, 16), (16, 64, 16), (32, 64, 4), (48, 64, 1)]
+
+
+@pytest.mark.parametrize("c,k", [case[:2] for case in SLAB_SUM_CASES])
 @pytest.mark.parametrize("wl", [8, 12])
 def test_slab_sums_of_few_outputs(c, k, wl):
     d = ConvDesc(40, 32, 32, c, k, 3, 3, 1, 1)

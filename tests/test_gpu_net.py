@@ -7,6 +7,7 @@ import torch
 
 import paper_2107_13490_amd as pkg
 import workloads as wk
+from oracle import conv_oracle as co
 from oracle import fxp_oracle as orc
 from oracle import net_oracle as no
 from paper_2107_13490_amd import ConvDesc, LayerDesc
@@ -904,6 +905,50 @@ def test_fitted_weight_gradients_of_short_reductions(batch, c, k, wl_x, wl_dy, k
     st = net.tensor(1, pkg.NT_STATS)
     assert (st.shift_w, _sumsq(st)) == (shift, sumsq)
     assert np.array_equal(host(net.tensor(1, pkg.NT_G)).astype(np.int64), want.ravel())
+
+
+# ---- weight gradients on image rows whose launch, or whose slab sum, leaves the largest magnitude for the fit ----------------
+ROWS_NETS = [
+    # n, h, w, c, k, r, bits of the layer's inputs and of the layer, threads of the slab sum (0: none)
+    (8, 16, 16, 512, 512, 3, 16, 16, 0),
+    (8, 15, 17, 512, 496, 3, 12, 12, 0),
+    (256, 4, 4, 512, 512, 3, 13, 12, 0),        # beside the data gradient
+    (8, 16, 16, 512, 512, 3, 13, 8, 0),
+    (8, 15, 17, 512, 496, 3, 16, 7, 0),
+    (8, 16, 16, 512, 512, 3, 7, 16, 0),
+    (8, 15, 17, 512, 496, 3, 8, 12, 0),
+    (130, 16, 16, 128, 128, 3, 12, 12, 1),
+    (130, 16, 16, 128, 128, 3, 8, 16, 1),
+    (400, 32, 32, 64, 64, 1, 8, 12, 4),
+    (400, 32, 32, 48, 48, 1, 12, 12, 16),
+]
+
+
+@pytest.mark.parametrize("case", ROWS_NETS)
+def test_fitted_weight_gradients_on_image_rows(case):
+    n, h, w, c, k, r, wl_x, wl_dy, _ = case
+    g = np.random.default_rng(n + h + wl_x)
+    conv = ConvDesc(n, h, w, c, k, r, 3, 1, 1)
+    layers, ws = [LayerDesc(conv, 0, 0)], [(0.01 * g.standard_normal(c * k * r * 3)).astype(np.float32)]
+    last = 0 if wl_x == wl_dy else 1
+    if last:                                    # codes of another word length come from a layer in front
+        layers.insert(0, LayerDesc(ConvDesc(n, h, w, 16, c, 1, 1, 1, 0), 0, 0))
+        ws.insert(0, g.standard_normal(16 * c).astype(np.float32))
+    net = pkg.Net(ctx(), layers, [dev(v) for v in ws])
+    net.set_format(0, wl_x, max(0, wl_x - 4))
+    if last:
+        net.set_format(1, wl_dy, 3)
+    net.quantize_weights(seed=1)
+    net.forward(dev(g.standard_normal((n, h, w, 16 if last else c)).astype(np.float32)), seed=7, stream=50)
+    lim = 1 << (wl_dy - 1)
+    dl = g.choice([-lim, lim - 1, 0, 1, -1], (n, conv.p, conv.q, k)).astype(_dt(wl_dy))
+    net.backward(dev(dl), 0, seed=7, stream=50)
+    a = host(net.tensor(0, pkg.NT_A if last else pkg.NT_INPUT)).reshape(n, h, w, c)
+    sums = co.conv_wgrad(dl, a, r, 3, 1, conv.pad)
+    want, shift, sumsq = no.requantize_fit(sums.ravel(), wl_dy, orc.SR, 7, 50 + 8 * last + 2)
+    st = net.tensor(last, pkg.NT_STATS)
+    assert (st.shift_w, _sumsq(st)) == (shift, sumsq)
+    assert np.array_equal(host(net.tensor(last, pkg.NT_G)).astype(np.int64), np.asarray(want).ravel())
 
 
 def _fit_sums(a, dl, wl, seed, stream):

@@ -27,14 +27,14 @@ def test_planned_reads_stay_inside_the_operands(tmp_path):
 
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
-    """call -> (rows, splits, slab elements) of its weight gradient alone, and beside the data gradient"""
+    """call -> (rows, splits, positions and threads of the slab sum) of its weight gradient alone, and beside the data gradient"""
     exe = _host_program("plan_routes", tmp_path_factory.mktemp("routes"))
 
     def plan(calls):
         out = subprocess.run([exe], input="\n".join(" ".join(map(str, c)) for c in calls), stdout=subprocess.PIPE, text=True, check=True).stdout
         lines = [[int(v) for v in line.split()] for line in out.splitlines()]
         assert len(lines) == len(calls)
-        return [(tuple(v[:3]), tuple(v[3:])) for v in lines]
+        return [(tuple(v[:4]), tuple(v[4:])) for v in lines]
     return plan
 
 
@@ -78,3 +78,25 @@ def test_backward_calls_give_up_a_shared_launch_only_for_less_time(routes):
     plans = routes(shared + apart)
     assert all(alone[0] == 1 for alone, _ in plans)
     assert [both[0] for _, both in plans] == [0] * len(shared) + [1] * len(apart)
+
+
+def test_the_gpu_tests_of_image_rows_and_of_the_slab_sum_reach_them(routes):
+    from test_gpu_contract import ROWS_CASES, SLAB_SUM_CASES
+    from test_gpu_net import ROWS_NETS
+    calls = [(n, h, w, c, k, r, s, 1, pad, dy, dy, x) for n, h, w, c, k, r, s, pad, dy, x, _ in ROWS_CASES]
+    for call, case, (alone, _) in zip(calls, ROWS_CASES, routes(calls)):
+        assert (alone[0], alone[3]) == (1, case[-1]), (case, alone)
+        assert (alone[1] == 1 and alone[2] == 0) == (case[-1] == 0), (case, alone)
+    calls = [(n, h, w, c, k, r, 3, 1, 1, dy, dy, x) for n, h, w, c, k, r, x, dy, _ in ROWS_NETS]
+    for case, (alone, both) in zip(ROWS_NETS, routes(calls)):
+        route = alone if case[6] == case[7] else both        # a layer in front: both gradients in one call
+        assert (route[0], route[3]) == (1, case[-1]), (case, route)
+    calls = [(40, 32, 32, c, k, 3, 3, 1, 1, wl, wl, wl) for c, k, _ in SLAB_SUM_CASES for wl in (8, 12)]
+    threads = [t for *_, t in SLAB_SUM_CASES for _ in range(2)]
+    assert [(alone[0], alone[3]) for alone, _ in routes(calls)] == [(0, t) for t in threads]
+
+
+def test_slab_positions_on_image_rows_fit_32_bits(routes):
+    # the widest slabs: half of the output channels' tiles empty, weights just below the 2^31 that calls may have
+    plans = routes([(1, p + r - 1, 130, c, 33, r, 3, 1, 0, 12, 12, 8) for p, r, c in ((16, 33, 343999), (16, 51, 249999), (16, 71, 191991))])
+    assert all(alone[0] == 1 and 1 << 31 < alone[2] < (1 << 32) - (1 << 20) for alone, _ in plans), plans
