@@ -427,10 +427,12 @@ static int quantize_on(adapt_ctx *ctx, const float *x, size_t n, adapt_fmt fmt, 
                                rng.stream, partial, control, nnz, saturated);
         };
         // Codes past the caches where they alone exceed the last one: less of them would still be there for the call that reads them.
-        // Together with that call (1 x 1 x 64 -> 16, 3 x 3 x 64 -> 64 convolution, 2 x 2 pooling), us, through the caches / past them: 12 bits,
-        // 50 M elements 100.5 / 104.0, 176.1 / 182.7, 85.1 / 87.5; 67 M 134.7 / 136.4, 237.9 / 238.5, 112.5 / 114.2; 147 M (codes of 295 MB) 293.1 /
-        // 291.8, 509.8 / 508.0, 255.1 / 252.6; 229 M 455.7 / 460.5, 791.3 / 792.2, 403.5 / 399.5; 8 bits, 67 M
-        // 108.5 / 110.2, 152.6 / 156.6, 89.3 / 88.0, 134 M 216.4 / 213.3, 304.6 / 298.8, 176.1 / 173.6, 302 M 481.7 / 477.5, 659.1 / 653.2, 402.4 / 396.3.  By itself the call gains 4 to 5 % at any of these sizes (67 M, 12 bits 86.4 / 82.9).  Loads past the caches as well gain nothing more.
+        // Together with that call (1 x 1 x 64 -> 16, 3 x 3 x 64 -> 64 convolution, 2 x 2 pooling), us, through the caches / past them:
+        //   12 bits   50 M elements   100.5 / 104.0   176.1 / 182.7    85.1 / 87.5        8 bits   67 M   108.5 / 110.2   152.6 / 156.6    89.3 / 88.0
+        //             67 M            134.7 / 136.4   237.9 / 238.5   112.5 / 114.2               134 M   216.4 / 213.3   304.6 / 298.8   176.1 / 173.6
+        //            147 M            293.1 / 291.8   509.8 / 508.0   255.1 / 252.6               302 M   481.7 / 477.5   659.1 / 653.2   402.4 / 396.3
+        //            229 M            455.7 / 460.5   791.3 / 792.2   403.5 / 399.5
+        // By itself the call gains 4 to 5 % at any of these sizes (67 M, 12 bits 86.4 / 82.9).  Loads past the caches as well gain nothing more.
         const bool past = (uint64_t)n * storage_bytes(fmt) > kLastLevelCache;
         if (fmt.wl <= 8) launch(fused ? quantize_kernel<int8_t, true, false> : past ? quantize_kernel<int8_t, false, true> : quantize_kernel<int8_t, false, false>, (int8_t *)q);
         else launch(fused ? quantize_kernel<int16_t, true, false> : past ? quantize_kernel<int16_t, false, true> : quantize_kernel<int16_t, false, false>, (int16_t *)q);
